@@ -170,56 +170,98 @@ __global__ void lane_table_kernel(const float *__restrict__ gamma, const float *
     }
 }
 
-// Stand-alone Temporal Syntax Cache: one thread per (channel, run of NS tokens).
-template <int KC>
+// Stand-alone Temporal Syntax Cache: one thread per (V adjacent channels, run of NS tokens).
+// Bound by HBM: 4 bytes in, 4 out per element.  V = 4 (16-byte accesses) wherever shapes, strides and pointers allow
+// it, single channels otherwise.  The HALO rows before a run are those of the run before it: runs that follow each other
+// in time go to the same XCD (workgroup i runs on XCD i mod 8), whose L2 then serves them.  The carried history is
+// written by the threads that read it (the first run of each channel), so one launch does everything, also where
+// hist_in and hist_out are the same buffer.  B4 L2048 C768: one channel a thread and a second launch for the history
+// took 12.4 - 13.3 us; now 10.9 with default-policy stores, 10.1 with streamed ones (5.0 TB/s; runs of 4 and 16 tokens:
+// 11.5 and 10.0 us, and 8 leave a short call twice the threads of 16).
+constexpr int CONV_NS = 8;      // tokens per thread
+template <int V> struct ConvVec;
+template <> struct ConvVec<1> { typedef float type; };
+template <> struct ConvVec<4> { typedef float type __attribute__((ext_vector_type(4))); };
+template <int KC, int V>
 __global__ __launch_bounds__(256) void syntax_conv_kernel(const float *__restrict__ x, const float *__restrict__ w,
                                                           const float *__restrict__ bias,
                                                           const float *hist_in, float *__restrict__ y,
-                                                          float *hist_out, int B, int L, int C,
-                                                          long long xsb, long long xst, long long ysb,
-                                                          long long yst, float cc, int write_hist_only)
+                                                          float *hist_out, int L, int C, long long xsb, long long xst,
+                                                          long long ysb, long long yst, float cc, unsigned runs, unsigned runs_z)
 {
-    constexpr int NS = 8, HALO = KC - 1;
-    const int cblocks = (C + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int c = (blockIdx.x % cblocks) * blockDim.x + threadIdx.x;
-    const int t0 = (blockIdx.x / cblocks) * NS;
+    constexpr int NS = CONV_NS, HALO = KC - 1;
+    typedef typename ConvVec<V>::type vec;
+    auto at = [](const vec &v, int q) -> float { if constexpr (V == 1) return v; else return v[q]; };
+    auto ld = [](const float *p) { return *reinterpret_cast<const vec *>(p); };
+    // thread -> (run of tokens, channels), channels fastest; each XCD takes a contiguous eighth of the workgroups
+    const unsigned n = gridDim.x, xcd = blockIdx.x % 8u, k8 = blockIdx.x / 8u;
+    const unsigned per = n / 8u, rem = n % 8u;
+    const unsigned id = xcd * per + (xcd < rem ? xcd : rem) + k8;
+    const unsigned e = id * 256u + threadIdx.x, cq = (unsigned)(C / V);
+    const unsigned in_z = e / cq, run = blockIdx.z * runs_z + in_z;
+    if (in_z >= runs_z || run >= runs) return;
+    const int c = (int)(e - in_z * cq) * V, t0 = (int)run * NS;
     const int b = blockIdx.y;
-    if (c >= C) return;
-    if (write_hist_only) {
-        // history rows are copied by a second, tiny launch so that hist_in may alias hist_out
-        if (t0 != 0) return;
-        float rows[HALO > 0 ? HALO : 1];
-        for (int q = 0; q < HALO; ++q) {
-            const int t = L - HALO + q;
-            rows[q] = t >= 0 ? x[(size_t)b * xsb + (size_t)t * xst + c]
-                             : (hist_in ? hist_in[((size_t)b * HALO + (t + HALO)) * C + c] : 0.0f);
-        }
-        for (int q = 0; q < HALO; ++q) hist_out[((size_t)b * HALO + q) * C + c] = rows[q];
-        return;
-    }
-    float wk[KC];
-#pragma unroll
-    for (int i = 0; i < KC; ++i) wk[i] = w[(size_t)c * KC + i];
-    const float bs = bias ? bias[c] : 0.0f;
-    float u[NS + HALO];
+    const float *xb = x + (size_t)b * xsb + c;
+    float *yb = y + (size_t)b * ysb + c;
+    vec u[NS + HALO];
 #pragma unroll
     for (int r = 0; r < NS + HALO; ++r) {
         const int t = t0 - HALO + r;
-        float v = 0.0f;
-        if (t >= 0 && t < L) v = x[(size_t)b * xsb + (size_t)t * xst + c];
-        else if (t < 0 && hist_in && t + HALO >= 0) v = hist_in[((size_t)b * HALO + (t + HALO)) * C + c];
+        vec v = {};
+        if (t >= 0 && t < L) v = ld(xb + (size_t)t * xst);
+        else if (t < 0 && hist_in && t + HALO >= 0) v = ld(hist_in + ((size_t)b * HALO + (t + HALO)) * C + c);
         u[r] = v;
+    }
+    float wk[V][KC], bs[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+        bs[q] = bias ? bias[c + q] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < KC; ++i) wk[q][i] = w[(size_t)(c + q) * KC + i];
     }
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
         const int t = t0 + i;
         if (t >= L) break;
-        float z = bs;
+        vec o;
 #pragma unroll
-        for (int k = 0; k < KC; ++k) z = __builtin_fmaf(wk[k], u[i + k], z);
-        const float zc = clampf(z, cc);
-        y[(size_t)b * ysb + (size_t)t * yst + c] = zc * sigmoid_fast(zc);
+        for (int q = 0; q < V; ++q) {
+            float z = bs[q];
+#pragma unroll
+            for (int k = 0; k < KC; ++k) z = __builtin_fmaf(wk[q][k], at(u[i + k], q), z);
+            const float zc = clampf(z, cc), r = zc * sigmoid_fast(zc);
+            if constexpr (V == 1) o = r; else o[q] = r;
+        }
+        __builtin_nontemporal_store(o, reinterpret_cast<vec *>(yb + (size_t)t * yst));
     }
+    // the last HALO pre-conv rows; what is older than this call comes from hist_in, of which every row my channels
+    // have is in u[0 .. HALO-1] already (in place is fine)
+    if (HALO > 0 && hist_out && t0 == 0) {
+        vec rows[HALO > 0 ? HALO : 1];
+#pragma unroll
+        for (int q = 0; q < HALO; ++q) {
+            const int t = L - HALO + q;
+            rows[q] = vec{};
+            if (t >= 0) rows[q] = ld(xb + (size_t)t * xst);
+            else {
+#pragma unroll
+                for (int r = 0; r < HALO; ++r)
+                    if (r == t + HALO) rows[q] = u[r];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < HALO; ++q) *reinterpret_cast<vec *>(hist_out + ((size_t)b * HALO + q) * C + c) = rows[q];
+    }
+}
+
+template <int KC>
+static void launch_conv(bool vec4, dim3 grid, hipStream_t s, const float *x, const float *w, const float *bias,
+                        const float *hist_in, float *y, float *hist_out, int L, int C, long long xsb, long long xst,
+                        long long ysb, long long yst, float cc, unsigned runs, unsigned runs_z)
+{
+    if (vec4) hipLaunchKernelGGL((syntax_conv_kernel<KC, 4>), grid, dim3(256), 0, s, x, w, bias, hist_in, y, hist_out, L, C, xsb, xst, ysb, yst, cc, runs, runs_z);
+    else hipLaunchKernelGGL((syntax_conv_kernel<KC, 1>), grid, dim3(256), 0, s, x, w, bias, hist_in, y, hist_out, L, C, xsb, xst, ysb, yst, cc, runs, runs_z);
 }
 
 // Sum the backward tiles' parameter partials in a fixed order.  One partial is [tile][row][JB] with
@@ -464,27 +506,25 @@ int cawn_syntax_conv(const cawn_desc *d, int32_t C, const float *x, const float 
     const long long xst = d->in_stride_t ? d->in_stride_t : C, xsb = d->in_stride_b ? d->in_stride_b : (long long)d->L * C;
     const long long yst = d->out_stride_t ? d->out_stride_t : C, ysb = d->out_stride_b ? d->out_stride_b : (long long)d->L * C;
     if (xst < C || yst < C) return CAWN_EINVAL;
+    if (d->conv_k == 1) conv_state_out = nullptr;      // no history
+    if (d->L == 0 && !conv_state_out) return CAWN_OK;
+    // 16-byte accesses: every row of x, y and the histories starts on 16 bytes
+    const bool vec4 = C % 4 == 0 && xst % 4 == 0 && xsb % 4 == 0 && yst % 4 == 0 && ysb % 4 == 0 && aligned(x, 16) &&
+                      aligned(y, 16) && aligned(conv_state_in, 16) && aligned(conv_state_out, 16);
+    const long long runs = d->L > 0 ? ((long long)d->L + CONV_NS - 1) / CONV_NS : 1;     // (no tokens: the history alone)
+    const long long cq = vec4 ? C / 4 : C;
+    const long long most = 0xffffff00LL / cq;       // threads of one grid row are counted in 32 bits: more runs go to grid.z
+    const long long runs_z = runs < most ? runs : most, nz = (runs + runs_z - 1) / runs_z;
+    if (nz > 65535 || d->B > 65535) return CAWN_EUNSUPPORTED;
+    const dim3 grid((unsigned)((runs_z * cq + 255) / 256), d->B, (unsigned)nz);
     hipStream_t s = (hipStream_t)stream;
-    const int NS = 8;
-    const dim3 block(256);
-    for (int pass = 0; pass < 2; ++pass) {
-        if (pass == 0 && d->L == 0) continue;
-        if (pass == 1 && (!conv_state_out || d->conv_k == 1)) continue;
-        const long long nblk = (long long)((C + 255) / 256) * (pass == 0 ? (d->L + NS - 1) / NS : 1);
-        if (nblk > 0x7fffffffLL || d->B > 65535) return CAWN_EUNSUPPORTED;
-        const dim3 grid((unsigned)nblk, d->B, 1);
-#define CAWN_CONV_CASE(K)                                                                          \
-    case K:                                                                                        \
-        hipLaunchKernelGGL((syntax_conv_kernel<K>), grid, block, 0, s, x, w, bias, conv_state_in, y, \
-                           conv_state_out, d->B, d->L, C, xsb, xst, ysb, yst, d->conv_clamp, pass); \
-        break;
-        switch (d->conv_k) {
-            CAWN_CONV_CASE(1) CAWN_CONV_CASE(2) CAWN_CONV_CASE(3) CAWN_CONV_CASE(4)
-        }
-#undef CAWN_CONV_CASE
-        if (hipGetLastError() != hipSuccess) return CAWN_ELAUNCH;
+    switch (d->conv_k) {
+    case 1: launch_conv<1>(vec4, grid, s, x, w, bias, conv_state_in, y, conv_state_out, d->L, C, xsb, xst, ysb, yst, d->conv_clamp, (unsigned)runs, (unsigned)runs_z); break;
+    case 2: launch_conv<2>(vec4, grid, s, x, w, bias, conv_state_in, y, conv_state_out, d->L, C, xsb, xst, ysb, yst, d->conv_clamp, (unsigned)runs, (unsigned)runs_z); break;
+    case 3: launch_conv<3>(vec4, grid, s, x, w, bias, conv_state_in, y, conv_state_out, d->L, C, xsb, xst, ysb, yst, d->conv_clamp, (unsigned)runs, (unsigned)runs_z); break;
+    default: launch_conv<4>(vec4, grid, s, x, w, bias, conv_state_in, y, conv_state_out, d->L, C, xsb, xst, ysb, yst, d->conv_clamp, (unsigned)runs, (unsigned)runs_z); break;
     }
-    return CAWN_OK;
+    return hipGetLastError() == hipSuccess ? CAWN_OK : CAWN_ELAUNCH;
 }
 
 static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, const float *valve,

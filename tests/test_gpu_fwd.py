@@ -292,6 +292,40 @@ def test_standalone_syntax_conv():
             assert np.array_equal(h.cpu().numpy(), h_o)
 
 
+@pytest.mark.parametrize("Kc", [1, 2, 3, 4])
+@pytest.mark.parametrize("L,Cc,off", [(1, 4, 0), (2, 260, 0), (9, 1028, 0), (64, 256, 0), (9, 1028, 1), (0, 8, 0)])
+def test_standalone_syntax_conv_wide_and_narrow_accesses(Kc, L, Cc, off):
+    """16-byte and single-channel accesses (off: rows that start one float beyond 16 bytes), calls shorter than the
+    history, ragged runs, strided rows, history in place and into a second buffer, against the oracle."""
+    import torch
+    G = _gpu()
+    from paper_2604_04250_amd import binding as K
+    r = np.random.Generator(np.random.PCG64(1250 + 10 * Kc + L))
+    B, rs = 3, Cc + 4
+    x = (10 * r.standard_normal((B, max(L, 1), Cc))).astype(np.float32)[:, :L]
+    w = r.standard_normal((Cc, Kc)).astype(np.float32)
+    bias = r.standard_normal(Cc).astype(np.float32)
+    hist = r.standard_normal((B, max(Kc - 1, 0), Cc)).astype(np.float32)
+    if L:
+        y_o, h_o = O.syntax_conv(x, w, bias, hist if Kc > 1 else None)
+    else:
+        y_o, h_o = x, hist
+    buf = torch.zeros(B * max(L, 1) * rs + 4, device=G.DEV)
+    xd = buf[off:off + B * max(L, 1) * rs].view(B, max(L, 1), rs)
+    xd[:, :L, :Cc] = G.dev(x)
+    for in_place in (True, False):
+        d = K.make_desc(B, L, 1, 1, conv_k=Kc, in_stride_t=rs, in_stride_b=max(L, 1) * rs)
+        y = torch.full((B, max(L, 1), Cc), float("nan"), device=G.DEV)
+        h = G.dev(hist) if Kc > 1 else None
+        ho = h if in_place or h is None else torch.full_like(h, float("nan"))
+        K.check(K.cawn_syntax_conv(d, Cc, xd, G.dev(w), G.dev(bias), h, y, ho))
+        torch.cuda.synchronize()
+        assert G.rel_err(y[:, :L].cpu().numpy(), y_o) <= TOL
+        assert L > 0 or bool(torch.isnan(y).all())
+        if Kc > 1:
+            assert np.array_equal(ho.cpu().numpy(), h_o)
+
+
 def test_spin_limit_timeout_is_reported_and_every_wave_exits():
     # a tiny spin limit forces tiles to give up; the kernel must still drain and flag the workspace
     G = _gpu()
