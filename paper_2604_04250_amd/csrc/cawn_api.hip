@@ -565,7 +565,7 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     if (d->gate_mode == 1 && !valve) return CAWN_EINVAL;
     if (d->conv_k > 0 && !conv_w) return CAWN_EINVAL;
     // tile indices and tickets are bounded: B x (tiles per sequence) x (32-lane blocks) <= 2^18 per call
-    if ((unsigned long long)d->B * ((d->L + FwdGeom::TILE_T - 1) / FwdGeom::TILE_T) * ((J + FwdLPR - 1) / FwdLPR) > MAX_TILES)
+    if ((unsigned long long)d->B * ((d->L + FwdGeom::TILE_T - 1) / FwdGeom::TILE_T) * ((J + FwdGeom::JB - 1) / FwdGeom::JB) > MAX_TILES)
         return CAWN_EUNSUPPORTED;
     if (workspace_bytes < w.total || !aligned(workspace, 256)) return CAWN_EWORKSPACE;
     const long long ist = d->in_stride_t ? d->in_stride_t : J, isb = d->in_stride_b ? d->in_stride_b : (long long)d->L * J;
@@ -578,7 +578,6 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     FwdArgs a{};
     a.bf16 = bf16 ? 1 : 0;
     a.hconv = d->hconv_k != 0 ? 1 : 0;
-    a.hcG = d->hconv_k != 0 && d->F > 32 ? d->F / 32 : 1;
     if (d->gate_mode == 1) {
         const float INF = std::numeric_limits<float>::infinity();
         a.gs = GateSet{-INF, INF, INF, -INF};        // no per-lane threshold in this mode
@@ -587,21 +586,18 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     } else if (!make_gate_set(d->conv_k > 0, d->amp_mode, (double)d->conv_clamp, d->gate_tau, &a.gs)) {
         return CAWN_EUNSUPPORTED;
     }
+    // the tile: 32-lane rows, with the harmonic convolution 64-lane rows (the same number of token-lanes)
+    const int JB = hconv_w ? FwdHead::JB : FwdGeom::JB, TT = hconv_w ? FwdHead::TILE_T : FwdGeom::TILE_T;
     a.H = d->H; a.F = d->F;
-    a.gpb = d->F >= 32 ? 1 : 32 / d->F;
+    a.gpb = d->F >= JB ? 1 : JB / d->F;
+    a.hcG = hconv_w && d->F > JB ? d->F / JB : 1;
     if (d->ret_mode == 1) {
         a.ret = ret;
         a.aggp = reinterpret_cast<tagged_t *>(reinterpret_cast<char *>(workspace) + w.off_aggp);
     }
-    const bool vec = (J % FwdV == 0) && (ist % FwdV == 0) && (isb % FwdV == 0) && (ost % FwdV == 0) &&
-                     (osb % FwdV == 0) && aligned(mag, 16) && aligned(ang, 16) && aligned(z_re, 16) &&
-                     aligned(z_im, 16) && (!state_in || aligned(state_in, 16)) &&
-                     (!state_out || aligned(state_out, 16)) && (!ckpt || aligned(ckpt, 16));
-    const int JB = (vec ? FwdV : 1) * FwdLPR;
     const int nLB = (int)((J + JB - 1) / JB);
-    const int nTf = (d->L + FwdGeom::TILE_T - 1) / FwdGeom::TILE_T;
+    const int nTf = (d->L + TT - 1) / TT;
     const size_t tiles = (size_t)d->B * nTf * nLB;
-    if (tiles > MAX_TILES) return CAWN_EUNSUPPORTED;
 
     char *ws = reinterpret_cast<char *>(workspace);
     if (!d->lane_consts_cached) {
@@ -630,7 +626,7 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     a.spin_limit = g_spin_limit.load();
     a.total_tiles = (uint32_t)tiles;
     a.dbg = reinterpret_cast<unsigned long long *>(ws + w.off_dbg);
-    if (launch_fwd(a, d->conv_k, vec, s) != hipSuccess) return CAWN_ELAUNCH;
+    if (launch_fwd(a, d->conv_k, s) != hipSuccess) return CAWN_ELAUNCH;
     return CAWN_OK;
 }
 

@@ -43,17 +43,6 @@ __device__ __forceinline__ float dpp_add_bcast15(float x)
     return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x142, 0xA, 0xF, false));
 }
 
-// Whole-wave shifts by one lane (DPP wave_shr:1 / wave_shl:1): lane i takes lane i-1's (i+1's) value, the
-// first (last) lane keeps its own.
-__device__ __forceinline__ float wave_shift_up(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_shift_down(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x130, 0xF, 0xF, false));
-}
-
 template <int V> struct BVec;
 template <> struct BVec<1> {
     static __device__ __forceinline__ void ld(float (&d)[1], const float *p) { d[0] = *p; }

@@ -171,11 +171,11 @@ static hipError_t launch_step(const FwdArgs &a, int conv_k, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fwd(const FwdArgs &a, int conv_k, bool vec, hipStream_t s)
+hipError_t launch_fwd(const FwdArgs &a, int conv_k, hipStream_t s)
 {
     if (a.L <= CAWN_STEP_MAX_L) return launch_step(a, conv_k, s);
-    if (a.ret) return a.valve ? launch_fwd_valve_ret(a, conv_k, vec, s) : launch_fwd_ret(a, conv_k, vec, s);
-    return a.valve ? launch_fwd_valve(a, conv_k, vec, s) : launch_fwd_plain(a, conv_k, vec, s);
+    if (a.ret) return a.valve ? launch_fwd_valve_ret(a, conv_k, s) : launch_fwd_ret(a, conv_k, s);
+    return a.valve ? launch_fwd_valve(a, conv_k, s) : launch_fwd_plain(a, conv_k, s);
 }
 
 }  // namespace cawn

@@ -85,20 +85,31 @@ __device__ __forceinline__ TileId decode_tile(uint32_t ticket, int nLB, int B, i
     return t;
 }
 
-// Stage the lane constants a forward tile keeps in registers (table rows R_LR .. R_LR + NCR - 1 of
-// lane block lb) in LDS, 16 bytes per lane per load: 8 lanes cover a 32-lane row, a wave 8 rows.
-// Called by one wave.  Table rows are 256-byte aligned and padded, so every address is valid.
-template <int NCR, int JB>
+// The lane constants a forward tile keeps in registers, staged in LDS: lambda, lambda^(NSTEP s) for s = 1 .. NSEG - 1
+// (segment 0 starts at the tile's first token: its power is 1), biases, retention bias, taps (HC: and the harmonic
+// convolution's).  C_* are rows of the staged copy; the table's rows are in the same order with other powers between.
+template <class G> struct FwdConsts {
+    static constexpr int C_LR = 0, C_LI = 1, C_P = 2, C_BIAS_M = C_P + 2 * (G::NSEG - 1), C_BIAS_A = C_BIAS_M + 1,
+                         C_RBIAS = C_BIAS_M + 2, C_W0 = C_BIAS_M + 3;
+    static __device__ __forceinline__ int table_row(int r)
+    {
+        return r < C_P ? R_LR + r : (r < C_BIAS_M ? R_PSEG + 2 + (r - C_P) : R_BIAS_M + (r - C_BIAS_M));
+    }
+};
+// 16 bytes per lane per load: JB / 4 lanes cover a row.  Called by one wave.  Table rows are 256-byte aligned and
+// padded, so every address is valid.
+template <class G, int NCR>
 __device__ __forceinline__ void stage_consts(float *sC, const float *table, int Jp, int lb, int lane)
 {
-    static_assert(JB == 32, "8 lanes x 16 bytes per row");
-    const int r_in = lane >> 3, c_in = (lane & 7) * 4;
-    const float *src = table + ((size_t)(R_LR + r_in) * Jp + (size_t)lb * JB + c_in);
+    constexpr int JB = G::JB, LR = JB / 4, RPI = 64 / LR;      // lanes per row, rows per instruction
+    const int r_in = lane / LR, c_in = (lane % LR) * 4;
 #pragma unroll
-    for (int i = 0; i < (NCR + 7) / 8; ++i) {
-        if (i * 8 + r_in < NCR) {
+    for (int i = 0; i < (NCR + RPI - 1) / RPI; ++i) {
+        const int r = i * RPI + r_in;
+        if (r < NCR) {
+            const float *src = table + ((size_t)FwdConsts<G>::table_row(r) * Jp + (size_t)lb * JB + c_in);
 #if defined(__HIP_DEVICE_COMPILE__)
-            __builtin_amdgcn_global_load_lds(src + (size_t)(i * 8) * Jp, sC + (size_t)(i * 8) * JB, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(src, sC + (size_t)(i * RPI) * JB, 16, 0, 0);
 #else
             (void)src;
             (void)sC;
@@ -120,22 +131,23 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // without the per-token retentions also fit its registers)
 // HC: the depth-wise harmonic convolution of Sec. 3.6 applied to the clamped output before it is
 // stored: channel = (plane, head), three taps along the harmonics of the head, zeros beyond its ends.
-// Neighbouring harmonics are neighbouring lanes of a row.  A head wider than a lane block (F = 32 G,
-// G > 1) is handled by one workgroup drawing the G tickets of the head's blocks together and taking
+// Neighbouring harmonics are neighbouring lanes of a row (rows of 64 lanes here: one wave each).  A head
+// wider than a lane block (F = 64 n, n = 2, 4) is handled by one workgroup drawing the n tickets of the head's blocks together and taking
 // them in order (every other group from the top block down): the lane of a block that borders the
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
-template <int V, int KC, bool VALVE, bool RET, bool BF, bool HC>
-__global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
+__global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
-    static_assert(!BF || V == 1, "bf16 activations: one lane per thread");
-    static_assert(!HC || V == 1, "harmonic convolution: one lane per thread");
-    static_assert(V == 1 && FwdLPR == 32 && FwdGeom::NSTEP <= 32, "the gate mask: a word per token and segment, kept by the segment's lane of that number");
-    constexpr int TILE_T = FwdGeom::TILE_T, NSTEP = FwdGeom::NSTEP, NSEG = FwdGeom::NSEG, LPR = FwdLPR;
-    constexpr int JB = V * LPR;
+    constexpr int V = 1;                           // lanes per thread
+    constexpr int TILE_T = G::TILE_T, NSTEP = G::NSTEP, NSEG = G::NSEG, LPR = G::JB;
+    constexpr int JB = G::JB;
+    constexpr int MW = JB / 32;                    // gate-mask words of a row
+    static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
+    static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
-    constexpr int NT = NSEG * LPR;                 // threads
+    constexpr int NT = G::NT;                      // threads
     constexpr int NW = NT / 64;                    // waves
     constexpr int JBS = BF ? JB / 2 : JB;          // four-byte words per staged row
     constexpr int NRTP = staged_rows<TILE_T, JBS, HALO>();   // staged rows per stream: time tile_t0-HALO+rr
@@ -148,19 +160,22 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
         if constexpr (BF) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(&sU[r][0])[l] << 16);
         else return sU[r][l];
     };
-    __shared__ float sE[NSEG][2][JB];
+    __shared__ float sE[NSEG - 1][2][JB];          // (the last segment's is nobody's predecessor inside the tile)
     __shared__ float sCarry[2][JB];
-    constexpr int NCR = R_W0 - R_LR + 2 * KC + (HC ? HC_ROWS : 0);     // staged lane-constant rows
-    // (only rows below NCR are ever staged; HC needs the room of the padding)
-    __shared__ __attribute__((aligned(16))) float sC[HC ? NCR : (NCR + 7) / 8 * 8][JB];
+    typedef FwdConsts<G> CR;
+    constexpr int NCR = CR::C_W0 + 2 * KC + (HC ? HC_ROWS : 0);     // staged lane-constant rows
+    __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
+    constexpr int R_PT = TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR;     // lambda^TILE_T: hi re, im, lo re, im
+    static_assert(TILE_T == FwdGeom::TILE_T || TILE_T == BwdGeom::TILE_T, "a power the lane table holds");
+    static_assert(NSTEP == FwdGeom::NSTEP, "the segments' powers the lane table holds");
     // valve / retention groups per lane block: F >= 8, or F >= 16 with both (LDS: two workgroups per CU)
-    // (HC: one group, F >= 32 -- the two rows of unfinished outputs take the room)
-    constexpr int GPB_MAX = HC ? 1 : ((VALVE && RET) ? 2 : 4);
-    __shared__ float sV[VALVE ? FwdGeom::TILE_T * GPB_MAX : 1];
-    __shared__ float sR[RET ? FwdGeom::TILE_T * GPB_MAX : 1];     // retention logits, laid out like sV
-    __shared__ float sP[RET ? NSEG : 1][JB];                      // product of each segment's retentions
+    // (HC: F >= 32, i.e. two groups of a 64-lane block)
+    constexpr int GPB_MAX = (HC || (VALVE && RET)) ? 2 : 4;
+    __shared__ float sV[VALVE ? TILE_T * GPB_MAX : 1];
+    __shared__ float sR[RET ? TILE_T * GPB_MAX : 1];     // retention logits, laid out like sV
+    __shared__ float sP[RET ? NSEG - 1 : 1][JB];                  // product of each segment's retentions
     // HC: value and unfinished output of the block's last lane, per token and plane, for the next block
-    __shared__ float sHZ[2][HC ? FwdGeom::TILE_T : 1], sHP[2][HC ? FwdGeom::TILE_T : 1];
+    __shared__ float sHZ[2][HC ? TILE_T : 1], sHP[2][HC ? TILE_T : 1];
     __shared__ uint32_t sTicket[2], sLast, sEpoch;
 
     const int tid = threadIdx.x;
@@ -199,7 +214,7 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
     const int ist32 = (int)a.ist;
     auto stage_tile = [&](const TileId &T) {
         if (owner_wave) return;
-        if (wave == 0) stage_consts<NCR, JB>(&sC[0][0], a.table, a.Jp, T.lb, lane);
+        if (wave == 0) stage_consts<G, NCR>(&sC[0][0], a.table, a.Jp, T.lb, lane);
         if (VALVE && wave == 0) stage_valve<TILE_T, JB>(&sV[0], a.valve, T.b, T.tt * TILE_T, T.lb, a.L, a.H, a.F, a.gpb, lane);
         if (RET && wave == 0) stage_valve<TILE_T, JB>(&sR[0], a.ret, T.b, T.tt * TILE_T, T.lb, a.L, a.H, a.F, a.gpb, lane);
         // (bf16: rows of J/2 words at half the strides; the fp32 conv history is read at its point of use)
@@ -211,14 +226,14 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
                                      BF ? a.J / 2 : a.J, a.L, BF ? a.isb / 2 : a.isb, BF ? ist32 / 2 : ist32, wave, NW - 1, lane);
     };
 
-    // HC, heads of G > 1 lane blocks: a group of G tickets is one head's blocks; groups with an odd index
+    // HC, heads of hcG > 1 lane blocks: a group of hcG tickets is one head's blocks; groups with an odd index
     // take them from the last block down, so that at any time the workgroups of the grid are spread over
     // all positions in a head (in step on one position they would all read and write one 128-byte
     // address class of the rows at a time, i.e. a part of the memory channels)
     auto tile_of = [&](uint32_t tk) {
         if (HC) {
-            const uint32_t G = (uint32_t)a.hcG, g = tk / G, p_ = tk - g * G;
-            tk = g * G + ((g & 1u) ? G - 1u - p_ : p_);
+            const uint32_t n = (uint32_t)a.hcG, g = tk / n, p_ = tk - g * n;
+            tk = g * n + ((g & 1u) ? n - 1u - p_ : p_);
         }
         return decode_tile(tk, a.nLB, a.B, a.nT);
     };
@@ -266,36 +281,38 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
         {
             auto cst = [&](float(&d)[V], int r) {
 #pragma unroll
-                for (int v = 0; v < V; ++v) d[v] = sC[r - R_LR][lv * V + v];
+                for (int v = 0; v < V; ++v) d[v] = sC[r][lv * V + v];
             };
-            cst(lr, R_LR);
-            cst(li, R_LI);
-            cst(pfr, R_PSEG + 2);                 // lambda^NSTEP
-            cst(pfi, R_PSEG + 3);
-            cst(psr, R_PSEG + 2 * seg);           // lambda^(NSTEP*seg)
-            cst(psi, R_PSEG + 2 * seg + 1);
+            cst(lr, CR::C_LR);
+            cst(li, CR::C_LI);
+            cst(pfr, CR::C_P);                    // lambda^NSTEP
+            cst(pfi, CR::C_P + 1);
+            cst(psr, CR::C_P + 2 * (seg > 0 ? seg - 1 : 0));           // lambda^(NSTEP*seg)
+            cst(psi, CR::C_P + 2 * (seg > 0 ? seg - 1 : 0) + 1);
 #pragma unroll
             for (int v = 0; v < V; ++v) {
+                psr[v] = seg > 0 ? psr[v] : 1.f;
+                psi[v] = seg > 0 ? psi[v] : 0.f;
                 bm[v] = ba[v] = 0.f;
 #pragma unroll
                 for (int k = 0; k < KC1; ++k) wm[k][v] = wa[k][v] = 0.f;
             }
-            if (RET) cst(rb, R_RBIAS);
+            if (RET) cst(rb, CR::C_RBIAS);
             if (HC) {
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    hb[p] = sC[R_W0 + 2 * KC + 6 + p - R_LR][lv];
+                    hb[p] = sC[CR::C_W0 + 2 * KC + 6 + p][lv];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) hw[p][k] = sC[R_W0 + 2 * KC + 3 * p + k - R_LR][lv];
+                    for (int k = 0; k < 3; ++k) hw[p][k] = sC[CR::C_W0 + 2 * KC + 3 * p + k][lv];
                 }
             }
             if (KC > 0) {
-                cst(bm, R_BIAS_M);
-                cst(ba, R_BIAS_A);
+                cst(bm, CR::C_BIAS_M);
+                cst(ba, CR::C_BIAS_A);
 #pragma unroll
                 for (int k = 0; k < KC; ++k) {
-                    cst(wm[k], R_W0 + k);
-                    cst(wa[k], R_W0 + KC + k);
+                    cst(wm[k], CR::C_W0 + k);
+                    cst(wa[k], CR::C_W0 + KC + k);
                 }
             }
         }
@@ -304,7 +321,7 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
         float pr[NSTEP][V], pi[NSTEP][V];
         float Er[V], Ei[V];
         float gm[RET ? NSTEP : 1][V], Pth[V];     // RET: retention of each token, product over my tokens
-        uint32_t mword = 0;                       // gate mask: the word of my segment's token lv (lanes lv < NSTEP)
+        uint32_t mword = 0;                       // gate mask: my 32 lanes' word of my segment's token lv % 32
         const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;   // rows before a sequence start
         // bf16: the carried conv history is fp32 and is not staged; the one segment that needs it reads it
         // here (and waits for it here, so that no wait for it lands in the common path)
@@ -386,12 +403,12 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
                     pi[i][v] = ag * s;
                     if (MASK) {
                         // The comparison's result is already a 64-bit lane mask: its two halves are the words of
-                        // this token in the wave's two segments, and lane i of a segment keeps token i's.  (Packed
+                        // this token (32-lane rows: in the wave's two segments), and lane i of 32 keeps token i's.  (Packed
                         // by five lane exchanges per token, the mask took 7 of a tile's 15 us: B4 L2048 J768 with
                         // a mask 46.2 -> 35.4 us.)
                         const unsigned long long bal = __ballot((int)g & (int)active);
                         const uint32_t half = (tid & 32) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
-                        mword = lv == i ? half : mword;
+                        mword = lv % 32 == i ? half : mword;
                     }
                     float nr, ni;
                     if (RET) {
@@ -429,11 +446,13 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
 
         ARGS_AGAIN();
         // ---- segments meet in LDS; after this barrier nobody reads the staged rows any more
+        if (!is_tail_seg) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            sE[seg][0][lv * V + v] = Er[v];
-            sE[seg][1][lv * V + v] = Ei[v];
-            if (RET) sP[seg][lv * V + v] = Pth[v];
+            for (int v = 0; v < V; ++v) {
+                sE[seg][0][lv * V + v] = Er[v];
+                sE[seg][1][lv * V + v] = Ei[v];
+                if (RET) sP[seg][lv * V + v] = Pth[v];
+            }
         }
         if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
         lds_barrier();
@@ -497,10 +516,10 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
             }
             if (active) {   // lambda^TILE_T as a double-float
                 const float *tb = a.table + j0;
-                Vec<V>::ld(hr, tb + (size_t)R_PT_HR * a.Jp);
-                Vec<V>::ld(hi, tb + (size_t)R_PT_HI * a.Jp);
-                Vec<V>::ld(qr, tb + (size_t)R_PT_LR * a.Jp);
-                Vec<V>::ld(qi, tb + (size_t)R_PT_LI * a.Jp);
+                Vec<V>::ld(hr, tb + (size_t)R_PT * a.Jp);
+                Vec<V>::ld(hi, tb + (size_t)(R_PT + 1) * a.Jp);
+                Vec<V>::ld(qr, tb + (size_t)(R_PT + 2) * a.Jp);
+                Vec<V>::ld(qi, tb + (size_t)(R_PT + 3) * a.Jp);
             }
             float cr[V], ci[V];
 #pragma unroll
@@ -571,8 +590,10 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
 
         // ---- optional gate mask: bit j%32 of word j/32, one word per thread (behind the look-back, whose polls
         //      would queue behind these stores; ahead of the output stores, which may stay in flight)
-        if (a.mask && lv < NSTEP && t0 + lv < a.L)
-            a.mask[((size_t)b * a.L + t0 + lv) * ((a.J + 31) >> 5) + T.lb] = mword;
+        if (a.mask && lv % 32 < NSTEP && t0 + lv % 32 < a.L) {
+            const int W = (a.J + 31) >> 5, wd = T.lb * MW + lv / 32;
+            if (MW == 1 || wd < W) a.mask[((size_t)b * a.L + t0 + lv % 32) * W + wd] = mword;
+        }
 
         // ---- checkpoints for the backward pass: the state before every CKPT_T-th token.  The one at
         //      the start of my segment goes out here, the others from inside the replay.
@@ -611,15 +632,17 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
             auto replay = [&](auto plain_c, auto multi_c, auto ck_c) {
                 constexpr bool PLAIN = decltype(plain_c)::value;
                 constexpr bool CK = decltype(ck_c)::value;       // checkpoints wanted (uniform over the launch)
-                // heads of several lane blocks (1, 2); this tile completes outputs of the previous one (2)
-                constexpr bool MULTI = HC && decltype(multi_c)::value > 0, RECV = HC && decltype(multi_c)::value == 2;
+                // heads of several lane blocks (1, 2); this tile completes outputs of the previous one (2); heads
+                // narrower than a block (0), of exactly a block (3)
+                constexpr bool MULTI = HC && (decltype(multi_c)::value == 1 || decltype(multi_c)::value == 2);
+                constexpr bool RECV = HC && decltype(multi_c)::value == 2, WHOLE = HC && decltype(multi_c)::value == 3;
                 if constexpr (HC) {
                     // The harmonic convolution, four tokens at a time: the recurrence of the four, then all
                     // their lane exchanges and LDS reads (one wait instead of one per token), then outputs.
                     // No branch in here, so the steps stay one block of code.  MULTI (a head spans several
                     // blocks): every lane reads the slot of its row (a broadcast) and selects; every lane
-                    // writes -- the deferring lane into the slot, the others into words of sE that only they
-                    // write and nobody reads before the next tile rewrites them; the deferring lane's global
+                    // writes -- the deferring lane into the slot, the others into words of sE that nobody
+                    // reads before the next tile rewrites them; the deferring lane's global
                     // stores are masked off and the receiving lane of the next tile stores the completed
                     // element: a second store that only the receiving lane executes (streamed stores are not merged
                     // in a cache: a second store from every lane, repeating its first, doubled the tile's writes).
@@ -658,10 +681,10 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
                             const int ix = seg * NSTEP + c0 + k;
-                            lzr[k] = __shfl_up(z_r[k], 1, 64);
-                            lzi[k] = __shfl_up(z_i[k], 1, 64);
-                            rzr[k] = __shfl_down(z_r[k], 1, 64);
-                            rzi[k] = __shfl_down(z_i[k], 1, 64);
+                            lzr[k] = wave_shift_up0(z_r[k]);       // (statements of their own: every lane executes them)
+                            lzi[k] = wave_shift_up0(z_i[k]);
+                            rzr[k] = wave_shift_down0(z_r[k]);
+                            rzi[k] = wave_shift_down0(z_i[k]);
                             dpr[k] = dpi[k] = 0.f;     // the neighbouring block's unfinished output, completed
                             if constexpr (RECV) {
                                 const float nzr = sHZ[0][ix], nzi = sHZ[1][ix];
@@ -676,14 +699,15 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
                             const int ix = seg * NSTEP + c0 + k;
-                            const float l_r = h_zl ? 0.f : lzr[k], l_i = h_zl ? 0.f : lzi[k];
-                            const float r_r = h_zr ? 0.f : rzr[k], r_i = h_zr ? 0.f : rzi[k];
+                            // (WHOLE: a row is one head, and the shift itself brings the zeros beyond its ends)
+                            const float l_r = !WHOLE && h_zl ? 0.f : lzr[k], l_i = !WHOLE && h_zl ? 0.f : lzi[k];
+                            const float r_r = !WHOLE && h_zr ? 0.f : rzr[k], r_i = !WHOLE && h_zr ? 0.f : rzi[k];
                             const float cr_ = __builtin_fmaf(hw[0][2], r_r, __builtin_fmaf(hw[0][1], z_r[k], __builtin_fmaf(hw[0][0], l_r, hb[0])));
                             const float ci_ = __builtin_fmaf(hw[1][2], r_i, __builtin_fmaf(hw[1][1], z_i[k], __builtin_fmaf(hw[1][0], l_i, hb[1])));
                             if constexpr (MULTI) {      // (the reads of these slots, above, come first in this wave)
-                                float *wz = h_defer ? &sHZ[0][ix] : &sE[seg][0][lv];
-                                float *wp = h_defer ? &sHP[0][ix] : &sE[seg][1][lv];
-                                constexpr int PL = FwdGeom::TILE_T;      // from plane 0 to plane 1 of a slot
+                                float *wz = h_defer ? &sHZ[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][0][lv];
+                                float *wp = h_defer ? &sHP[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][1][lv];
+                                constexpr int PL = TILE_T;      // from plane 0 to plane 1 of a slot
                                 wz[0] = z_r[k];
                                 wz[h_defer ? PL : 0] = z_i[k];
                                 wp[0] = cr_;
@@ -774,6 +798,7 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
             using M0 = std::integral_constant<int, 0>;
             using M1 = std::integral_constant<int, 1>;
             using M2 = std::integral_constant<int, 2>;
+            using M3 = std::integral_constant<int, 3>;
             using T_ = std::true_type;
             using F_ = std::false_type;
             auto replay_ck = [&](auto plain_c, auto multi_c) {
@@ -783,11 +808,13 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
             if (plain) {
                 if (recv_tile) replay_ck(T_{}, M2{});
                 else if (HC && hcG > 1) replay_ck(T_{}, M1{});
+                else if (HC && a.F == JB) replay_ck(T_{}, M3{});
                 else replay_ck(T_{}, M0{});
                 wait_vm<(2 * NSTEP < 63 ? 2 * NSTEP : 63)>();
             } else {
                 if (recv_tile) replay_ck(F_{}, M2{});
                 else if (HC && hcG > 1) replay_ck(F_{}, M1{});
+                else if (HC && a.F == JB) replay_ck(F_{}, M3{});
                 else replay_ck(F_{}, M0{});
                 wait_vm<0>();
             }
@@ -839,8 +866,8 @@ __global__ __launch_bounds__(FwdGeom::NSEG *FwdLPR, (BF && !RET && !HC) ? CAWN_F
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
 }
 
-template <int V, int KC, bool VALVE, bool RET, bool BF, bool HC>
-static hipError_t launch_fwd_vkh(const FwdArgs &a0, hipStream_t s)
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
+static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 {
     // persistent grid: what fits on the chip (asked once per kernel)
     static int per_cu = 0, cus = 0;
@@ -848,69 +875,62 @@ static hipError_t launch_fwd_vkh(const FwdArgs &a0, hipStream_t s)
         int dev = 0, n = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<V, KC, VALVE, RET, BF, HC>, FwdGeom::NSEG * FwdLPR, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<G, KC, VALVE, RET, BF, HC>, G::NT, 0) != hipSuccess)
             return hipErrorUnknown;
         cus = prop.multiProcessorCount;
         per_cu = n > 0 ? n : 1;
     }
-    FwdArgs a = a0;
     const long long resident = (long long)per_cu * cus;
     const long long tiles = (long long)a.nLB * a.B * a.nT;
     const long long wgs = tiles < resident ? (tiles > 0 ? tiles : 1) : resident;
-    dim3 grid((unsigned)wgs), block(FwdGeom::NSEG * FwdLPR);
-    hipLaunchKernelGGL((fwd_kernel<V, KC, VALVE, RET, BF, HC>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC>), dim3((unsigned)wgs), dim3(G::NT), 0, s, a);
     return hipGetLastError();
 }
 
-template <int V, int KC, bool VALVE, bool RET, bool BF>
-static hipError_t launch_fwd_vk(const FwdArgs &a, hipStream_t s)
+// The tile shape of a call (the host computed nT and nLB from the same rule): 64-lane rows with the harmonic
+// convolution, 32-lane rows without.
+template <int KC, bool VALVE, bool RET, bool BF>
+static hipError_t launch_fwd_k(const FwdArgs &a, hipStream_t s)
 {
 #ifndef CAWN_DEV_PLAIN
-    if constexpr (V == 1) {
-        if (a.hconv) return launch_fwd_vkh<1, KC, VALVE, RET, BF, true>(a, s);
-    }
+    if (a.hconv) return launch_fwd_tile<FwdHead, KC, VALVE, RET, BF, true>(a, s);
 #endif
-    return launch_fwd_vkh<V, KC, VALVE, RET, BF, false>(a, s);
+    return launch_fwd_tile<FwdGeom, KC, VALVE, RET, BF, false>(a, s);
 }
 
 // Tuning aid: -DCAWN_DEV_KC=<k> compiles only the conv_k = k kernels and -DCAWN_DEV_PLAIN only the
 // threshold-mode fp32 ones without the harmonic convolution (a build for timing one variant in
 // seconds; every other variant then fails to launch with hipErrorInvalidValue).  The library is
 // always built without them.
-template <int V, bool VALVE, bool RET, bool BF>
-static hipError_t launch_fwd_vmb(const FwdArgs &a, int conv_k, hipStream_t s)
+template <bool VALVE, bool RET, bool BF>
+static hipError_t launch_fwd_act(const FwdArgs &a, int conv_k, hipStream_t s)
 {
 #ifdef CAWN_DEV_PLAIN
     if constexpr (VALVE || RET || BF) return hipErrorInvalidValue; else
 #endif
     switch (conv_k) {
 #ifdef CAWN_DEV_KC
-    case CAWN_DEV_KC: return launch_fwd_vk<V, CAWN_DEV_KC, VALVE, RET, BF>(a, s);
+    case CAWN_DEV_KC: return launch_fwd_k<CAWN_DEV_KC, VALVE, RET, BF>(a, s);
 #else
-    case 0: return launch_fwd_vk<V, 0, VALVE, RET, BF>(a, s);
-    case 1: return launch_fwd_vk<V, 1, VALVE, RET, BF>(a, s);
-    case 2: return launch_fwd_vk<V, 2, VALVE, RET, BF>(a, s);
-    case 3: return launch_fwd_vk<V, 3, VALVE, RET, BF>(a, s);
-    case 4: return launch_fwd_vk<V, 4, VALVE, RET, BF>(a, s);
+    case 0: return launch_fwd_k<0, VALVE, RET, BF>(a, s);
+    case 1: return launch_fwd_k<1, VALVE, RET, BF>(a, s);
+    case 2: return launch_fwd_k<2, VALVE, RET, BF>(a, s);
+    case 3: return launch_fwd_k<3, VALVE, RET, BF>(a, s);
+    case 4: return launch_fwd_k<4, VALVE, RET, BF>(a, s);
 #endif
     default: return hipErrorInvalidValue;
     }
 }
-template <int V, bool VALVE, bool RET>
-static hipError_t launch_fwd_vm(const FwdArgs &a, int conv_k, hipStream_t s)
-{
-    return a.bf16 ? launch_fwd_vmb<V, VALVE, RET, true>(a, conv_k, s) : launch_fwd_vmb<V, VALVE, RET, false>(a, conv_k, s);
-}
 
 // One translation unit per family of forward kernels (gate mode x retention mode): they compile side by side.
 template <bool VALVE, bool RET>
-static hipError_t launch_fwd_family(const FwdArgs &a, int conv_k, bool vec, hipStream_t s)
+static hipError_t launch_fwd_family(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return vec ? launch_fwd_vm<FwdV, VALVE, RET>(a, conv_k, s) : launch_fwd_vm<1, VALVE, RET>(a, conv_k, s);
+    return a.bf16 ? launch_fwd_act<VALVE, RET, true>(a, conv_k, s) : launch_fwd_act<VALVE, RET, false>(a, conv_k, s);
 }
-hipError_t launch_fwd_plain(const FwdArgs &a, int conv_k, bool vec, hipStream_t s);        // threshold gate, constant retention
-hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, bool vec, hipStream_t s);        // per-head valve, constant retention
-hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, bool vec, hipStream_t s);          // threshold gate, data-dependent retention
-hipError_t launch_fwd_valve_ret(const FwdArgs &a, int conv_k, bool vec, hipStream_t s);    // valve and data-dependent retention
+hipError_t launch_fwd_plain(const FwdArgs &a, int conv_k, hipStream_t s);        // threshold gate, constant retention
+hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, hipStream_t s);        // per-head valve, constant retention
+hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, hipStream_t s);          // threshold gate, data-dependent retention
+hipError_t launch_fwd_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);    // valve and data-dependent retention
 
 }  // namespace cawn

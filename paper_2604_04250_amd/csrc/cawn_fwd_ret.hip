@@ -3,9 +3,9 @@
 
 namespace cawn {
 
-hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, bool vec, hipStream_t s)
+hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return launch_fwd_family<false, true>(a, conv_k, vec, s);
+    return launch_fwd_family<false, true>(a, conv_k, s);
 }
 
 }  // namespace cawn

@@ -3,9 +3,9 @@
 
 namespace cawn {
 
-hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, bool vec, hipStream_t s)
+hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return launch_fwd_family<true, false>(a, conv_k, vec, s);
+    return launch_fwd_family<true, false>(a, conv_k, s);
 }
 
 }  // namespace cawn

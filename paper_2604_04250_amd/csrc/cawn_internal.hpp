@@ -14,24 +14,18 @@ namespace cawn {
 // tile.  The two kernels pick their own shape:
 //   forward : long tiles.  Its tiles of one chain are joined by memory round trips, so the fewer
 //             tiles a chain has the better; it keeps only 2 values per token-lane in registers,
-//             which allows 32 tokens per thread.
+//             which allows 32 tokens per thread.  With the harmonic convolution a tile is 64 lanes
+//             wide: heads of up to 64 harmonics lie inside one wave's lanes, neighbours are a DPP
+//             shift away and only heads of 128 and 256 pass values from block to block.  (32-lane
+//             rows: a head of 64 was two tiles of one workgroup, one after the other, with four LDS
+//             exchanges per token.  Against that: B1 L333 J256 35.8 -> 17.5 us, the training step of
+//             B8 L8192 H4 F64 329 -> 299 us, of B8 L8192 H12 F64 623 -> 544 us, F = 256 156 -> 100 us;
+//             heads of up to 32 on J = 96 and 160, whose last block is half empty: 1.7 % slower.)
 //   backward: keeps ~10 values per token-lane, hence 8 tokens per thread and one lane per thread
 //             (4 waves per SIMD).
 // Checkpoints of the scan state are kept every CKPT_T tokens = one backward segment: a backward
 // thread starts the forward state of its tokens from the checkpoint of its own segment (one more
 // byte per token-lane each way; without it every tile had to join its segments' states in LDS).
-#ifndef CAWN_FWD_TILE_T
-#define CAWN_FWD_TILE_T 256
-#endif
-#ifndef CAWN_FWD_NSTEP
-#define CAWN_FWD_NSTEP 32
-#endif
-#ifndef CAWN_FWD_V
-#define CAWN_FWD_V 1
-#endif
-#ifndef CAWN_FWD_LPR
-#define CAWN_FWD_LPR 32
-#endif
 #ifndef CAWN_BWD_TILE_T
 #define CAWN_BWD_TILE_T 128
 #endif
@@ -50,16 +44,18 @@ namespace cawn {
 #ifndef CAWN_BWD_WAVES
 #define CAWN_BWD_WAVES 4
 #endif
-struct FwdGeom {
-    static constexpr int TILE_T = CAWN_FWD_TILE_T, NSTEP = CAWN_FWD_NSTEP, NSEG = TILE_T / NSTEP;
+// NSTEP tokens per thread, JB lanes (= threads) per row, NT threads
+template <int NSTEP_, int JB_, int NT_> struct FwdTile {
+    static constexpr int NSTEP = NSTEP_, JB = JB_, NT = NT_, NSEG = NT / JB, TILE_T = NSEG * NSTEP;
 };
+using FwdGeom = FwdTile<32, 32, 256>;      // 256 tokens x 32 lanes
+using FwdHead = FwdTile<32, 64, 256>;      // 128 tokens x 64 lanes: harmonic convolution
 struct BwdGeom {
     static constexpr int TILE_T = CAWN_BWD_TILE_T, NSTEP = CAWN_BWD_NSTEP, NSEG = TILE_T / NSTEP;
 };
 constexpr int CKPT_T = BwdGeom::NSTEP;
 static_assert(FwdGeom::NSTEP % CKPT_T == 0, "a forward segment spans whole checkpoint intervals");
 static_assert(BwdGeom::TILE_T % CKPT_T == 0, "backward tiles start on checkpoints");
-constexpr int FwdV = CAWN_FWD_V, FwdLPR = CAWN_FWD_LPR;  // lanes per thread, threads per row
 constexpr int BwdV = CAWN_BWD_V, BwdLPR = CAWN_BWD_LPR;
 constexpr int MAX_KC = 4;
 constexpr uint32_t MAX_TILES = 1u << 18;   // most tiles one call may have (tile indices, tickets)
@@ -69,7 +65,7 @@ constexpr uint32_t MAX_TILES = 1u << 18;   // most tiles one call may have (tile
 // fp64 by a small kernel from gamma, theta, conv_w, conv_b.
 enum LaneRow : int {
     R_COS = 0, R_SIN, R_GAMMA, // e^{i theta}, gamma
-    R_PT_HR, R_PT_HI,          // lambda^(forward TILE_T), leading fp32 part
+    R_PT_HR, R_PT_HI,          // lambda^256 (FwdGeom::TILE_T), leading fp32 part
     R_PT_LR, R_PT_LI,          //                          remainder (double-float)
     R_PTB_HR, R_PTB_HI,        // the same for the backward tile length
     R_PTB_LR, R_PTB_LI,
@@ -145,8 +141,8 @@ struct FwdArgs {
     size_t clear_from;           // byte offset of the first published word (cleared when the epoch wraps)
     unsigned long long *dbg;     // -DCAWN_TIMING builds only
     // (kept behind everything else: the kernels that do not use them fetch none of this)
-    // gate_mode 1 (per-head input valve, Sec. 3.3): logits [B][L][H]; a lane block of 32 lanes
-    // holds gpb = max(1, 32 / F) heads (groups); the valve is open when the logit >= valve_thr
+    // gate_mode 1 (per-head input valve, Sec. 3.3): logits [B][L][H]; a lane block of JB lanes
+    // holds gpb = max(1, JB / F) heads (groups); the valve is open when the logit >= valve_thr
     const float *valve;          // null: gate_mode 0
     int H, F, gpb;
     float valve_thr;
@@ -158,7 +154,7 @@ struct FwdArgs {
     // activations are bfloat16 in memory (mag, ang, z_re, z_im then point to 2-byte elements; strides
     // are in elements); J and the strides are even
     int bf16;
-    // harmonic convolution of the output before it is stored (Sec. 3.6, three taps); hcG: 32-lane blocks
+    // harmonic convolution of the output before it is stored (Sec. 3.6, three taps); hcG: 64-lane blocks
     // per head (1 when a head fits a block), whose tickets one workgroup draws together
     int hconv, hcG;
 };
@@ -212,7 +208,7 @@ struct BwdArgs {
 constexpr int HC_PART_ROWS = 8;
 inline __host__ __device__ int part_rows(int conv_k, bool hconv = false) { return 4 + 2 * conv_k + (hconv ? HC_PART_ROWS : 0); }
 
-hipError_t launch_fwd(const FwdArgs &a, int conv_k, bool vec4, hipStream_t s);
+hipError_t launch_fwd(const FwdArgs &a, int conv_k, hipStream_t s);
 hipError_t launch_bwd(const BwdArgs &a, int conv_k, bool vec, hipStream_t s);
 
 #if defined(__HIP_DEVICE_COMPILE__) || defined(__HIPCC__)
@@ -288,6 +284,25 @@ __device__ __forceinline__ bool in_gate(const GateSet &g, float x)
 {
     // bitwise on purpose: short-circuit forms compile to divergent branches
     return (bool)(((int)(x >= g.a1) & (int)(x <= g.b1)) | ((int)(x >= g.a2) & (int)(x <= g.b2)));
+}
+
+// Whole-wave shifts by one lane (DPP wave_shr:1 / wave_shl:1): lane i takes lane i-1's (i+1's) value, the
+// first (last) lane keeps its own; the *0 forms give it zero.
+__device__ __forceinline__ float wave_shift_up(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_shift_down(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x130, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_shift_up0(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_shift_down0(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, false));
 }
 
 // Cross-tile publication.  Tiles of one chain may run on different XCDs, whose L2 caches are not
