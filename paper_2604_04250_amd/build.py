@@ -12,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcawn.so")
 # (the scan kernels' families are translation units of their own: they compile side by side)
 SOURCES = ["cawn_fwd_plain.hip", "cawn_fwd_valve.hip", "cawn_fwd_ret.hip", "cawn_fwd_valve_ret.hip",
+           "cawn_fwd_short_plain.hip", "cawn_fwd_short_valve.hip", "cawn_fwd_short_ret.hip", "cawn_fwd_short_valve_ret.hip",
            "cawn_api.hip", "cawn_fwd.hip", "cawn_bwd.hip", "cawn_bwd_plain.hip", "cawn_bwd_valve.hip",
            "cawn_bwd_ret.hip", "cawn_bwd_hconv.hip", "cawn_bwd_hconv_valve.hip", "cawn_bwd_hconv_ret.hip"]
 # The backward kernel is a persistent loop whose body fills its register budget (4 waves per SIMD).

@@ -142,7 +142,13 @@ __global__ void lane_table_kernel(const float *__restrict__ gamma, const float *
         const bool fwd = slot - 3 < FwdGeom::NSEG;
         const int sgi = fwd ? slot - 3 : slot - 3 - FwdGeom::NSEG;
         double re, im;
-        power(sgi * (fwd ? FwdGeom::NSTEP : BwdGeom::NSTEP), re, im);
+        const bool rem64 = fwd && sgi == 0;     // (lambda^0 needs no rows: they hold what fp32 drops of lambda^64)
+        power(rem64 ? FwdShort::TILE_T : sgi * (fwd ? FwdGeom::NSTEP : BwdGeom::NSTEP), re, im);
+        if (rem64) {
+            put(R_PT64_LR, re - (double)(float)re);
+            put(R_PT64_LI, im - (double)(float)im);
+            return;
+        }
         put((fwd ? R_PSEG : R_PSEGB) + 2 * sgi, re);
         put((fwd ? R_PSEG : R_PSEGB) + 2 * sgi + 1, im);
         return;
@@ -527,6 +533,22 @@ int cawn_syntax_conv(const cawn_desc *d, int32_t C, const float *x, const float 
     return hipGetLastError() == hipSuccess ? CAWN_OK : CAWN_ELAUNCH;
 }
 
+// Short tiles (64 tokens, 8 per thread) for calls whose 256-token tiles would leave most of the chip idle: as long as
+// every short tile has a compute unit to itself (256 of them) and the chain's last tile reads at most 31 aggregates.
+// Long against short tiles, us a call: J768 conv 4, L32 12.4 / 10.7, L512 (192 short tiles) 14.6 / 10.7, L1024 (384)
+// 15.3 / 16.2; paper's layer J256, L333 16.6 / 10.6, L2048 (256 tiles, 32 in a chain) 19.3 / 17.1; J120 L4096 (256, 64 in a
+// chain) 16.8 / 17.4; with the harmonic convolution L1024 19.9 / 15.3, 7 x L512 19.5 / 15.3, 7 x L1024 (448) 21.8 / 24.5.
+// The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
+// behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
+// small for them the long tiles stay.
+static bool use_short_tiles(const cawn_desc *d, const WsLayout &w, int JB, size_t workspace_bytes)
+{
+    const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
+    const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
+    if (nT > 32 || tiles > 256) return false;
+    return w.off_agg + tiles * JB * (d->ret_mode == 1 ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
+}
+
 static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, const float *valve,
                     const float *ret, const float *ret_bias, const float *gamma, const float *theta, const float *conv_w, const float *conv_b,
                     const void *state_in, float *z_re, float *z_im, void *state_out, void *ckpt,
@@ -587,7 +609,10 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
         return CAWN_EUNSUPPORTED;
     }
     // the tile: 32-lane rows, with the harmonic convolution 64-lane rows (the same number of token-lanes)
-    const int JB = hconv_w ? FwdHead::JB : FwdGeom::JB, TT = hconv_w ? FwdHead::TILE_T : FwdGeom::TILE_T;
+    const int JB = hconv_w ? FwdHead::JB : FwdGeom::JB;
+    const bool short_tiles = use_short_tiles(d, w, JB, workspace_bytes);
+    const int TT = short_tiles ? FwdShort::TILE_T : (hconv_w ? FwdHead::TILE_T : FwdGeom::TILE_T);
+    a.short_tiles = short_tiles ? 1 : 0;
     a.H = d->H; a.F = d->F;
     a.gpb = d->F >= JB ? 1 : JB / d->F;
     a.hcG = hconv_w && d->F > JB ? d->F / JB : 1;
@@ -614,6 +639,10 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     a.hdr = reinterpret_cast<WsHeader *>(ws);
     a.agg = reinterpret_cast<tagged_t *>(ws + w.off_agg);
     a.pre = reinterpret_cast<tagged_t *>(ws + w.off_pre);
+    if (short_tiles) {      // aggregates only, the products behind them: the layout's later regions are the backward's
+        a.pre = nullptr;
+        a.aggp = a.agg + tiles * 2 * JB;
+    }
     a.clear_from = w.off_agg;
     a.B = d->B; a.L = d->L; a.J = (int)J; a.Jp = w.Jp; a.nT = nTf; a.nTc = w.nTc; a.nLB = nLB;
     a.amp_mode = d->amp_mode;

@@ -174,6 +174,10 @@ static hipError_t launch_step(const FwdArgs &a, int conv_k, hipStream_t s)
 hipError_t launch_fwd(const FwdArgs &a, int conv_k, hipStream_t s)
 {
     if (a.L <= CAWN_STEP_MAX_L) return launch_step(a, conv_k, s);
+    if (a.short_tiles) {
+        if (a.ret) return a.valve ? launch_fwd_short_valve_ret(a, conv_k, s) : launch_fwd_short_ret(a, conv_k, s);
+        return a.valve ? launch_fwd_short_valve(a, conv_k, s) : launch_fwd_short_plain(a, conv_k, s);
+    }
     if (a.ret) return a.valve ? launch_fwd_valve_ret(a, conv_k, s) : launch_fwd_ret(a, conv_k, s);
     return a.valve ? launch_fwd_valve(a, conv_k, s) : launch_fwd_plain(a, conv_k, s);
 }

@@ -93,7 +93,7 @@ template <class G> struct FwdConsts {
                          C_RBIAS = C_BIAS_M + 2, C_W0 = C_BIAS_M + 3;
     static __device__ __forceinline__ int table_row(int r)
     {
-        return r < C_P ? R_LR + r : (r < C_BIAS_M ? R_PSEG + 2 + (r - C_P) : R_BIAS_M + (r - C_BIAS_M));
+        return r < C_P ? R_LR + r : (r < C_BIAS_M ? (G::SHORT ? R_PSEGB : R_PSEG) + 2 + (r - C_P) : R_BIAS_M + (r - C_BIAS_M));
     }
 };
 // 16 bytes per lane per load: JB / 4 lanes cover a row.  Called by one wave.  Table rows are 256-byte aligned and
@@ -137,7 +137,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
-__global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
+__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
     constexpr int V = 1;                           // lanes per thread
     constexpr int TILE_T = G::TILE_T, NSTEP = G::NSTEP, NSEG = G::NSEG, LPR = G::JB;
@@ -165,9 +165,12 @@ __global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : C
     typedef FwdConsts<G> CR;
     constexpr int NCR = CR::C_W0 + 2 * KC + (HC ? HC_ROWS : 0);     // staged lane-constant rows
     __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
-    constexpr int R_PT = TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR;     // lambda^TILE_T: hi re, im, lo re, im
-    static_assert(TILE_T == FwdGeom::TILE_T || TILE_T == BwdGeom::TILE_T, "a power the lane table holds");
-    static_assert(NSTEP == FwdGeom::NSTEP, "the segments' powers the lane table holds");
+    // lambda^TILE_T as a double-float: leading part re, im, remainder re, im
+    constexpr int PT = G::SHORT ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
+    constexpr int PTL = G::SHORT ? R_PT64_LR : PT + 2;
+    static_assert(G::SHORT ? TILE_T == 64 && NSTEP == BwdGeom::NSTEP && NSEG <= BwdGeom::NSEG
+                           : (TILE_T == FwdGeom::TILE_T || TILE_T == BwdGeom::TILE_T) && NSTEP == FwdGeom::NSTEP,
+                  "powers the lane table holds");
     // valve / retention groups per lane block: F >= 8, or F >= 16 with both (LDS: two workgroups per CU)
     // (HC: F >= 32, i.e. two groups of a 64-lane block)
     constexpr int GPB_MAX = (HC || (VALVE && RET)) ? 2 : 4;
@@ -516,10 +519,10 @@ __global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : C
             }
             if (active) {   // lambda^TILE_T as a double-float
                 const float *tb = a.table + j0;
-                Vec<V>::ld(hr, tb + (size_t)R_PT * a.Jp);
-                Vec<V>::ld(hi, tb + (size_t)(R_PT + 1) * a.Jp);
-                Vec<V>::ld(qr, tb + (size_t)(R_PT + 2) * a.Jp);
-                Vec<V>::ld(qi, tb + (size_t)(R_PT + 3) * a.Jp);
+                Vec<V>::ld(hr, tb + (size_t)PT * a.Jp);
+                Vec<V>::ld(hi, tb + (size_t)(PT + 1) * a.Jp);
+                Vec<V>::ld(qr, tb + (size_t)PTL * a.Jp);
+                Vec<V>::ld(qi, tb + (size_t)(PTL + 1) * a.Jp);
             }
             float cr[V], ci[V];
 #pragma unroll
@@ -538,8 +541,14 @@ __global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : C
                         if (RET) tagged_store(a.aggp + (size_t)id * JB + lv * V + v, Pt[v], tag);
                     }
                 }
-                if (!look_back<V, false, LPR, CAWN_FWD_NB, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv,
-                                                 hr, hi, qr, qi, a.spin_limit, tag, cr, ci, a.aggp)) {
+                bool got;
+                if constexpr (G::SHORT)
+                    got = walk_chain<JB, RET ? 6 : 8, RET>(a.agg, a.aggp, id - (uint32_t)tt * (uint32_t)a.B, (uint32_t)a.B, tt, lv, hr[0], hi[0],
+                                                 qr[0], qi[0], a.spin_limit, tag, cr[0], ci[0]);
+                else
+                    got = look_back<V, false, LPR, CAWN_FWD_NB, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv,
+                                                 hr, hi, qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
+                if (!got) {
                     // gave up: flag the workspace, keep going so that every wave exits
                     if (lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
@@ -555,7 +564,8 @@ __global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : C
                 sCarry[0][lv * V + v] = cr[v];
                 sCarry[1][lv * V + v] = ci[v];
             }
-            if (tt + 1 < a.nT) {   // the tile's inclusive prefix for the chain
+            if (tt + 1 < a.nT && (!G::SHORT || tt == 0)) {   // the tile's inclusive prefix for the chain
+                tagged_t *pre = G::SHORT ? a.agg : a.pre;     // (short chains: the first tile's stands where its aggregate would)
                 float P_r[V], P_i[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v)
@@ -563,8 +573,8 @@ __global__ __launch_bounds__(G::NT, (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : C
                                       RET ? Pt[v] * ci[v] : ci[v], P_r[v], P_i[v]);
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    tagged_store(a.pre + slot + v, P_r[v], tag);
-                    tagged_store(a.pre + slot + JB + v, P_i[v], tag);
+                    tagged_store(pre + slot + v, P_r[v], tag);
+                    tagged_store(pre + slot + JB + v, P_i[v], tag);
                 }
             }
         }
@@ -889,20 +899,21 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 
 // The tile shape of a call (the host computed nT and nLB from the same rule): 64-lane rows with the harmonic
 // convolution, 32-lane rows without.
-template <int KC, bool VALVE, bool RET, bool BF>
+template <bool SHORT, int KC, bool VALVE, bool RET, bool BF>
 static hipError_t launch_fwd_k(const FwdArgs &a, hipStream_t s)
 {
+    using std::conditional_t;
 #ifndef CAWN_DEV_PLAIN
-    if (a.hconv) return launch_fwd_tile<FwdHead, KC, VALVE, RET, BF, true>(a, s);
+    if (a.hconv) return launch_fwd_tile<conditional_t<SHORT, FwdShortHead, FwdHead>, KC, VALVE, RET, BF, true>(a, s);
 #endif
-    return launch_fwd_tile<FwdGeom, KC, VALVE, RET, BF, false>(a, s);
+    return launch_fwd_tile<conditional_t<SHORT, FwdShort, FwdGeom>, KC, VALVE, RET, BF, false>(a, s);
 }
 
 // Tuning aid: -DCAWN_DEV_KC=<k> compiles only the conv_k = k kernels and -DCAWN_DEV_PLAIN only the
 // threshold-mode fp32 ones without the harmonic convolution (a build for timing one variant in
 // seconds; every other variant then fails to launch with hipErrorInvalidValue).  The library is
 // always built without them.
-template <bool VALVE, bool RET, bool BF>
+template <bool SHORT, bool VALVE, bool RET, bool BF>
 static hipError_t launch_fwd_act(const FwdArgs &a, int conv_k, hipStream_t s)
 {
 #ifdef CAWN_DEV_PLAIN
@@ -910,27 +921,32 @@ static hipError_t launch_fwd_act(const FwdArgs &a, int conv_k, hipStream_t s)
 #endif
     switch (conv_k) {
 #ifdef CAWN_DEV_KC
-    case CAWN_DEV_KC: return launch_fwd_k<CAWN_DEV_KC, VALVE, RET, BF>(a, s);
+    case CAWN_DEV_KC: return launch_fwd_k<SHORT, CAWN_DEV_KC, VALVE, RET, BF>(a, s);
 #else
-    case 0: return launch_fwd_k<0, VALVE, RET, BF>(a, s);
-    case 1: return launch_fwd_k<1, VALVE, RET, BF>(a, s);
-    case 2: return launch_fwd_k<2, VALVE, RET, BF>(a, s);
-    case 3: return launch_fwd_k<3, VALVE, RET, BF>(a, s);
-    case 4: return launch_fwd_k<4, VALVE, RET, BF>(a, s);
+    case 0: return launch_fwd_k<SHORT, 0, VALVE, RET, BF>(a, s);
+    case 1: return launch_fwd_k<SHORT, 1, VALVE, RET, BF>(a, s);
+    case 2: return launch_fwd_k<SHORT, 2, VALVE, RET, BF>(a, s);
+    case 3: return launch_fwd_k<SHORT, 3, VALVE, RET, BF>(a, s);
+    case 4: return launch_fwd_k<SHORT, 4, VALVE, RET, BF>(a, s);
 #endif
     default: return hipErrorInvalidValue;
     }
 }
 
-// One translation unit per family of forward kernels (gate mode x retention mode): they compile side by side.
-template <bool VALVE, bool RET>
+// One translation unit per family of forward kernels (tile length x gate mode x retention mode): they compile side by
+// side.
+template <bool SHORT, bool VALVE, bool RET>
 static hipError_t launch_fwd_family(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return a.bf16 ? launch_fwd_act<VALVE, RET, true>(a, conv_k, s) : launch_fwd_act<VALVE, RET, false>(a, conv_k, s);
+    return a.bf16 ? launch_fwd_act<SHORT, VALVE, RET, true>(a, conv_k, s) : launch_fwd_act<SHORT, VALVE, RET, false>(a, conv_k, s);
 }
 hipError_t launch_fwd_plain(const FwdArgs &a, int conv_k, hipStream_t s);        // threshold gate, constant retention
 hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, hipStream_t s);        // per-head valve, constant retention
 hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, hipStream_t s);          // threshold gate, data-dependent retention
 hipError_t launch_fwd_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);    // valve and data-dependent retention
+hipError_t launch_fwd_short_plain(const FwdArgs &a, int conv_k, hipStream_t s);  // the same four on short tiles
+hipError_t launch_fwd_short_valve(const FwdArgs &a, int conv_k, hipStream_t s);
+hipError_t launch_fwd_short_ret(const FwdArgs &a, int conv_k, hipStream_t s);
+hipError_t launch_fwd_short_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);
 
 }  // namespace cawn

@@ -47,9 +47,13 @@ namespace cawn {
 // NSTEP tokens per thread, JB lanes (= threads) per row, NT threads
 template <int NSTEP_, int JB_, int NT_> struct FwdTile {
     static constexpr int NSTEP = NSTEP_, JB = JB_, NT = NT_, NSEG = NT / JB, TILE_T = NSEG * NSTEP;
+    static constexpr bool SHORT = NSTEP < 32;
 };
 using FwdGeom = FwdTile<32, 32, 256>;      // 256 tokens x 32 lanes
 using FwdHead = FwdTile<32, 64, 256>;      // 128 tokens x 64 lanes: harmonic convolution
+using FwdShort = FwdTile<8, 32, 256>;      // 64 tokens x 32 lanes: calls that leave the chip idle otherwise
+using FwdShortHead = FwdTile<8, 64, 512>;  // 64 tokens x 64 lanes: the same with the harmonic convolution
+static_assert(FwdShort::TILE_T == FwdShortHead::TILE_T, "one table row for both");
 struct BwdGeom {
     static constexpr int TILE_T = CAWN_BWD_TILE_T, NSTEP = CAWN_BWD_NSTEP, NSEG = TILE_T / NSTEP;
 };
@@ -73,7 +77,9 @@ enum LaneRow : int {
     // The rows below are what a forward tile's threads keep in registers; they are contiguous so
     // that a tile stages them in LDS with a few wide loads (R_LR .. R_W0 + 2*conv_k - 1).
     R_LR = R_PSEGB + 2 * BwdGeom::NSEG, R_LI,   // lambda = gamma e^{i theta}
-    R_PSEG,                    // R_PSEG + 2*s (+1): the same powers for the forward segments
+    R_PSEG,                    // R_PSEG + 2*s (+1): lambda^(32 s), the long forward tiles' segments, s >= 1
+    // (s = 0 would be 1: its rows hold the remainder of lambda^64, the short tiles' length, whose leading part is s = 2)
+    R_PT64_LR = R_PSEG, R_PT64_LI, R_PT64_HR = R_PSEG + 4, R_PT64_HI,
     R_BIAS_M = R_PSEG + 2 * FwdGeom::NSEG, R_BIAS_A,
     R_RBIAS,                   // ret_mode 1: the lane's static retention bias b_k (k = j mod F)
     R_W0                       // R_W0 + s*conv_k + i : tap i of stream s
@@ -157,6 +163,7 @@ struct FwdArgs {
     // harmonic convolution of the output before it is stored (Sec. 3.6, three taps); hcG: 64-lane blocks
     // per head (1 when a head fits a block), whose tickets one workgroup draws together
     int hconv, hcG;
+    int short_tiles;             // FwdShort / FwdShortHead instead of FwdGeom / FwdHead
 };
 
 struct BwdArgs {
@@ -501,6 +508,60 @@ __device__ __forceinline__ void chain_step(float Tr, float Ti, float hr, float h
         Pr = __builtin_fmaf(hr, cr, __builtin_fmaf(hi, ci, Tr + lo_r));
         Pi = __builtin_fmaf(hr, ci, __builtin_fmaf(-hi, cr, Ti + lo_i));
     }
+}
+
+// The carry of a tile of a short chain: every tile before it has published its aggregate (the chain's first its
+// prefix, in the same place), and this tile reads them all, NB per round trip, and walks them in order with
+// chain_step().  No tile waits for another tile's prefix: the last aggregate published is the only thing the chain's end
+// depends on, where passing prefixes on costs a round trip per link (0.2 - 0.4 us).  Run by one group of JB
+// consecutive threads of a wave; `first` is the index of the chain's first tile, n >= 1 the tiles before this one.
+// Returns false if a wait gave up (the carry is then meaningless).
+template <int JB, int NB, bool RET>
+__device__ __forceinline__ bool walk_chain(const tagged_t *agg, const tagged_t *aggp, uint32_t first, uint32_t stride, int n,
+                                           int lv, float hr, float hi, float qr, float qi, uint32_t spin_limit,
+                                           uint32_t tag, float &cr, float &ci)
+{
+    const int gshift = (int)(threadIdx.x & 63) - lv;
+    const unsigned long long gmask = JB >= 64 ? ~0ull : ((1ull << JB) - 1ull);
+    uint32_t spins = 0;
+    for (int base = 0; base < n; base += NB) {
+        tagged_t wr[NB], wi[NB], wp[RET ? NB : 1];
+        while (true) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const size_t id = first + (uint32_t)(base + k < n ? base + k : n - 1) * stride;   // (past the end: the last again)
+                wr[k] = tagged_load(agg + id * 2 * JB + lv);
+                wi[k] = tagged_load(agg + id * 2 * JB + JB + lv);
+                if constexpr (RET) wp[k] = tagged_load(aggp + id * JB + lv);
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                ok = ok && tagged_ok(wr[k], tag) && tagged_ok(wi[k], tag);
+                if constexpr (RET) ok = ok && (tagged_ok(wp[k], tag) || (base + k < n ? base + k : n - 1) == 0);
+            }
+            if (((__ballot(ok) >> gshift) & gmask) == gmask) break;
+            if (++spins > spin_limit) return false;
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (base + k < n) {
+                const float tr = tagged_value(wr[k]), ti = tagged_value(wi[k]);
+                if (base + k == 0) {
+                    cr = tr;
+                    ci = ti;
+                } else {
+                    float nr, ni;
+                    if constexpr (RET) { const float p = tagged_value(wp[k]); cr *= p; ci *= p; }
+                    chain_step<false>(tr, ti, hr, hi, qr, qi, cr, ci, nr, ni);
+                    cr = nr;
+                    ci = ni;
+                }
+            }
+        }
+    }
+    return true;
 }
 
 // Decoupled look-back, run by one group of LPR consecutive threads of a wave (thread lv of the

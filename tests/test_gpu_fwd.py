@@ -292,6 +292,32 @@ def test_standalone_syntax_conv():
             assert np.array_equal(h.cpu().numpy(), h_o)
 
 
+@pytest.mark.parametrize("B,L,H,F,Kc", [(1, 17, 1, 8, 4), (1, 64, 3, 24, 0), (2, 65, 2, 16, 3), (1, 2048, 4, 64, 4), (1, 2049, 4, 64, 4),
+                                        (4, 2048, 1, 64, 1), (4, 2048, 1, 65, 1), (32, 500, 1, 32, 2), (33, 500, 1, 32, 2)])
+def test_short_tiles_at_their_edges(B, L, H, F, Kc):
+    """Calls on 64-token tiles: one tile, whole tiles, one token more, the longest chain (32 tiles), the most tiles (256),
+    and the next size of each, which the long tiles take; state in place, checkpoints and the gate mask, against the oracle."""
+    G = _gpu()
+    J, tau = H * F, 0.1
+    d = _inputs(B, L, H, F, Kc, 1700 + L + B)
+    r = np.random.Generator(np.random.PCG64(1701))
+    scan = r.standard_normal((B, 2, J)).astype(np.float32)
+    tail = r.standard_normal((B, max(Kc - 1, 0), 2, J)).astype(np.float32)
+    cfg = O.Cfg(B, L, H, F, conv_k=Kc, gate_tau=tau)
+    kw = dict(conv_w=d["conv_w"], conv_b=d["conv_b"]) if Kc else {}
+    ora = O.phase_fwd(cfg, d["mag"], d["ang"], d["gamma"], d["theta"], scan_in=scan,
+                      tail_in=tail if Kc > 1 else None, **kw)
+    out = G.run_fwd(d, B, L, H, F, conv_k=Kc, gate_tau=tau, state_in=G.pack_state(scan, tail), in_place_state=True, want_ckpt=True)
+    assert G.rel_err(out["z_re"], ora["z_re"]) <= TOL and G.rel_err(out["z_im"], ora["z_im"]) <= TOL
+    assert np.array_equal(out["mask"], G.mask_from_gate(ora["gate"]))
+    s_o, t_o = G.unpack_state(out["state_out"], B, J, Kc)
+    assert np.all(np.isfinite(out["ckpt"]))
+    assert G.rel_err(s_o, ora["scan_out"]) <= TOL
+    if Kc > 1:
+        u = np.stack([d["mag"], d["ang"]], 2)
+        assert np.array_equal(t_o, np.concatenate([tail, u], 1)[:, -(Kc - 1):])
+
+
 @pytest.mark.parametrize("Kc", [1, 2, 3, 4])
 @pytest.mark.parametrize("L,Cc,off", [(1, 4, 0), (2, 260, 0), (9, 1028, 0), (64, 256, 0), (9, 1028, 1), (0, 8, 0)])
 def test_standalone_syntax_conv_wide_and_narrow_accesses(Kc, L, Cc, off):
