@@ -201,10 +201,10 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     const float *dtail_out = a.dstate_out ? a.dstate_out + (size_t)a.B * 2 * a.J : nullptr;
     const uint32_t chain_stride = (uint32_t)a.B * a.nLB;
     const uint32_t ost32 = (uint32_t)a.ost, ist32 = (uint32_t)a.ist;
-    uint32_t ticket_ahead = 0;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
+    uint32_t ticket_ahead = NO_TICKET;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
     if (tid_ == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // all three round trips at once
-        const uint32_t t = __hip_atomic_fetch_add(&a.hdr->ticket[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x, 1u);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -602,8 +602,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     BWD_STAMP(2);
     // (PF: the next tile must be known by the time its gradients are staged; asked for here, the answer
     // arrives with this wave's staged rows, which it waits for below anyway)
-    if (PF && tid == 0)
-        ticket_ahead = __hip_atomic_fetch_add(&a.hdr->ticket[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (PF && tid == 0 && !a.tq.one_each)
+        ticket_ahead = next_ticket_of(a.hdr, 1u);
     float Xr[V], Xi[V];     // adjoint entering my segment (from later segments), zero tile input
     float Cb[V];            // RET: product of the retentions of the segments after mine
     {
@@ -1047,8 +1047,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // the ticket of the next tile: asked for as late as its answer can still arrive unwaited-for, i.e.
     // ahead of this tile's output stores (a ticket held in reserve is a tile that has not started:
     // its successors in other workgroups wait for it)
-    if (!PF && tid == 0)
-        ticket_ahead = __hip_atomic_fetch_add(&a.hdr->ticket[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!PF && tid == 0 && !a.tq.one_each)
+        ticket_ahead = next_ticket_of(a.hdr, 1u);
     const size_t dbase = ((size_t)b * a.isb + (size_t)(tt * TILE_T) * a.ist + (size_t)lb * JB) * ES;
     float *omag = reinterpret_cast<float *>(reinterpret_cast<char *>(a.dmag) + dbase);
     float *oang = reinterpret_cast<float *>(reinterpret_cast<char *>(a.dang) + dbase);
@@ -1377,8 +1377,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // ---- the workgroup that leaves last resets the ticket and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
     if (tid_ == 0) {
-        const uint32_t old = __hip_atomic_fetch_add(&a.hdr->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sLast = (old + 1 == gridDim.x) ? 1u : 0u;
+        sLast = leave_call(a.hdr, blockIdx.x, gridDim.x) ? 1u : 0u;
     }
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x);
@@ -1400,7 +1399,9 @@ static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
     }
     long long g = (long long)per_cu * cus;
     if (g > (long long)a.total_tiles) g = a.total_tiles;
-    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, a);
+    BwdArgs b = a;
+    b.tq = make_queues((uint32_t)a.B * a.nLB, (uint32_t)a.nT, g);
+    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, b);
     return hipGetLastError();
 }
 

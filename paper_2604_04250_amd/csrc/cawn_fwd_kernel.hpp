@@ -13,8 +13,8 @@
 // clamps and stores.  Per token-lane HBM traffic: 8 bytes in, 8 bytes out.
 //
 // Scheduling.  The kernel is persistent: about as many workgroups as fit on the chip are launched
-// and each loops over tiles, handed out by one atomic ticket in the order (time tile, batch row,
-// lane block).  Tickets go out in time order, so a tile only ever waits for tiles that a running
+// and each loops over tiles, handed out by atomic tickets in the order (time tile, batch row,
+// lane block) (see TileQueues).  Tickets go out in time order, so a tile only ever waits for tiles that a running
 // workgroup already holds; all chains advance together, so tiles that happen to be slow (some
 // address classes of the 128-byte lane-block rows are, by a quarter) are spread over every
 // workgroup instead of leaving a few chains to finish alone; and the lane blocks of one row are
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
 
     if (tid == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // both round trips at once
-        const uint32_t t = __hip_atomic_fetch_add(&a.hdr->ticket[0], HC ? (uint32_t)a.hcG : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x, HC ? (uint32_t)a.hcG : 1u);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -269,10 +269,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
         // (HC: the tickets of a head's lane blocks are drawn together, a multiple of hcG first)
         const uint32_t hcG = HC ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
-            if (HC && (ticket + 1) % hcG != 0)
-                ticket_ahead = ticket + 1;
-            else
-                ticket_ahead = __hip_atomic_fetch_add(&a.hdr->ticket[0], hcG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
+            else if (a.tq.one_each) ticket_ahead = NO_TICKET;
+            else ticket_ahead = next_ticket_of(a.hdr, hcG);
         }
 
         // ---- the staged rows have landed (each wave waited for its own loads: before the loop, or
@@ -869,8 +868,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
     // ---- the workgroup that leaves last resets the tickets and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
     if (tid == 0) {
-        const uint32_t old = __hip_atomic_fetch_add(&a.hdr->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sLast = (old + 1 == gridDim.x) ? 1u : 0u;
+        sLast = leave_call(a.hdr, blockIdx.x, gridDim.x) ? 1u : 0u;
     }
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
@@ -891,9 +889,12 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
         per_cu = n > 0 ? n : 1;
     }
     const long long resident = (long long)per_cu * cus;
-    const long long tiles = (long long)a.nLB * a.B * a.nT;
-    const long long wgs = tiles < resident ? (tiles > 0 ? tiles : 1) : resident;
-    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC>), dim3((unsigned)wgs), dim3(G::NT), 0, s, a);
+    const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
+    const long long jobs = (long long)units * a.nT;
+    const long long wgs = jobs < resident ? jobs : resident;
+    FwdArgs b = a;
+    b.tq = make_queues(units, (uint32_t)a.nT, wgs);
+    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
     return hipGetLastError();
 }
 

@@ -102,16 +102,40 @@ inline __host__ __device__ int lane_rows(int conv_k, bool hconv = false) { retur
 // infinity or hardware-made NaN (0x7FC00000) an fp32 computation leaves behind equals one.
 // Nothing is cleared per tile or per call: the workgroup that leaves last resets the tickets and
 // advances the epoch.
-constexpr int MAX_QUEUES = 64;
+constexpr int MAX_QUEUES = 8;
 struct WsHeader {
-    uint32_t ticket[MAX_QUEUES];   // ticket[0]: next tile to hand out (the other words are spare)
-    uint32_t done;                 // tiles finished
+    uint32_t q01[64];              // ticket and finished counters (ticket_word, done_word)
+    uint32_t done;                 // workgroups, or groups of them, finished
     uint32_t error;                // sticky: a tile gave up waiting
     uint32_t epoch;                // calls completed on this workspace (mod EPOCH_MOD): make_tag() of it marks published words
     uint32_t bytes_lo, bytes_hi;   // size given to cawn_workspace_init (what an epoch wrap has to clear)
-    uint32_t pad[256 - MAX_QUEUES - 5];
+    uint32_t q27[256 - 64 - 5];
 };
 static_assert(sizeof(WsHeader) == 1024, "header size");
+// Counters of queue q, as word indices into the header: one 128-byte line each (queue 2 shares its line with `done`)
+inline __host__ __device__ uint32_t ticket_word(uint32_t q) { return q == 2 ? 80u : q * 32u; }
+inline __host__ __device__ uint32_t done_word(uint32_t q) { return ticket_word(q) + 8u; }
+
+// How a call's tiles are handed out.  Atomics on one address complete one after the other, 11.4 ns each here (on
+// addresses 128 bytes apart side by side): the 384 workgroups of a 4096-token call on 768 lanes had their first tickets
+// after 4.4 us, their second ones (which only tell them that there is nothing left) 4.4 us later, and their last
+// count took as long again.  So:
+//   * a call whose workgroups take one tile each (a head's G tiles) draws no second ticket, and its U chains (or
+//     groups of G) are dealt to 2^lq counters; 2^lq divides U, so tile numbers stay what they are,
+//         tile = (number drawn from counter q << lq) + q G,
+//     a chain belongs to one counter, and a tile still only waits for tiles with a lower ticket of its own counter, which
+//     a running workgroup holds.  A workgroup draws from counter (index mod 2^lq): as many draws as the counter has tiles.
+//   * a call with more tiles than workgroups keeps one counter: its draws are spread over the call and cost nothing
+//     (eight counters with a second choice where one ran dry were slower: training step 431 -> 454 us, bf16 B2 L4096
+//     J4096 284 -> 298; the first tickets' delay keeps the workgroups out of step, and loads beside arithmetic);
+//   * workgroups that leave are counted in two levels when there are many.
+struct TileQueues { uint32_t lq, one_each; };
+inline TileQueues make_queues(uint32_t U, uint32_t nT, long long workgroups)
+{
+    TileQueues t{0, workgroups >= (long long)U * nT ? 1u : 0u};
+    while (t.one_each && (2u << t.lq) <= (uint32_t)MAX_QUEUES && U % (2u << t.lq) == 0) ++t.lq;
+    return t;
+}
 
 struct WsLayout {
     int J, Jp, Jp128, nT, nTc;     // nT: backward tiles per sequence, nTc: checkpoint intervals
@@ -134,6 +158,7 @@ struct FwdArgs {
     uint32_t *mask;              // may be null
     WsHeader *hdr;
     tagged_t *agg, *pre;
+    TileQueues tq;
     int B, L, J, Jp, nT, nLB;    // nT: forward tiles per sequence
     int nTc;                     // checkpoint intervals per sequence
     int stage16;                 // input rows may be staged with 16-byte loads (alignment, J % 4 == 0)
@@ -176,6 +201,7 @@ struct BwdArgs {
     float *dstate_in;            // may be null
     WsHeader *hdr;
     tagged_t *agg, *pre, *halo;
+    TileQueues tq;
     float *part;
     int B, L, J, Jp, nT, nLB;
     int nTc;                     // checkpoint intervals per sequence
@@ -467,6 +493,30 @@ __device__ __forceinline__ tagged_t tagged_load(const tagged_t *p)
 __device__ __forceinline__ bool tagged_ok(tagged_t w, uint32_t tag) { return (uint32_t)(w >> 32) == tag; }
 __device__ __forceinline__ float tagged_value(tagged_t w) { return __uint_as_float((uint32_t)w); }
 
+__device__ __forceinline__ uint32_t *hdr_word(WsHeader *h, uint32_t w) { return reinterpret_cast<uint32_t *>(h) + w; }
+constexpr uint32_t NO_TICKET = 0x7fffffffu;     // beyond every call's tiles
+// the first tile (of G) of workgroup `wg`: see TileQueues
+__device__ __forceinline__ uint32_t first_ticket(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t G)
+{
+    const uint32_t q = wg & ((1u << t.lq) - 1u);
+    return (__hip_atomic_fetch_add(hdr_word(h, ticket_word(q)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << t.lq) + q * G;
+}
+// ... and the next ones (calls with one counter)
+__device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h, uint32_t G)
+{
+    return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// A workgroup leaves: true for the last one.  Two levels from 96 workgroups on (a second round trip, 0.4 us, for the last
+// of them; 96 counts on one address take 1.1 us).
+__device__ __forceinline__ bool leave_call(WsHeader *h, uint32_t wg, uint32_t grid)
+{
+    auto add = [&](uint32_t *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u; };
+    if (grid < 96) return add(&h->done) == grid;
+    const uint32_t s = wg % MAX_QUEUES;
+    if (add(hdr_word(h, done_word(s))) != (grid - s + MAX_QUEUES - 1) / MAX_QUEUES) return false;
+    return add(&h->done) == (uint32_t)MAX_QUEUES;
+}
+
 // End of a call, run by thread `tid` of the `nthreads` of the workgroup that left last: tickets and
 // the finished-workgroup count return to zero and the epoch advances.  When the epoch wraps, words of
 // EPOCH_MOD calls ago would become valid again: everything behind the lane table is cleared then
@@ -482,7 +532,10 @@ __device__ __forceinline__ void finish_call(WsHeader *hdr, size_t clear_from, ui
         for (size_t i = tid; i < n; i += nthreads)
             __hip_atomic_store(base + i, (tagged_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid < (uint32_t)MAX_QUEUES) flag_store(&hdr->ticket[tid], 0u);
+    if (tid < (uint32_t)MAX_QUEUES) {
+        flag_store(hdr_word(hdr, ticket_word(tid)), 0u);
+        flag_store(hdr_word(hdr, done_word(tid)), 0u);
+    }
     if (tid == 0) {
         flag_store(&hdr->done, 0u);
         flag_store(&hdr->epoch, next);
