@@ -533,11 +533,15 @@ int cawn_syntax_conv(const cawn_desc *d, int32_t C, const float *x, const float 
     return hipGetLastError() == hipSuccess ? CAWN_OK : CAWN_ELAUNCH;
 }
 
-// Short tiles (64 tokens, 8 per thread) for calls whose 256-token tiles would leave most of the chip idle: as long as
-// every short tile has a compute unit to itself (256 of them) and the chain's last tile reads at most 31 aggregates.
-// Long against short tiles, us a call: J768 conv 4, L32 12.4 / 10.7, L512 (192 short tiles) 14.6 / 10.7, L1024 (384)
-// 15.3 / 16.2; paper's layer J256, L333 16.6 / 10.6, L2048 (256 tiles, 32 in a chain) 19.3 / 17.1; J120 L4096 (256, 64 in a
-// chain) 16.8 / 17.4; with the harmonic convolution L1024 19.9 / 15.3, 7 x L512 19.5 / 15.3, 7 x L1024 (448) 21.8 / 24.5.
+// Short tiles (64 tokens, 8 per thread) for calls whose 256-token tiles would leave much of the chip idle: as long as
+// every short tile has a workgroup of its own on the chip (4 per compute unit; 3 with the per-token retentions, 1 of
+// twice the threads with the harmonic convolution), and while reading all of a chain's aggregates costs less than
+// passing prefixes on.  Beyond the first limit they lose at once (a workgroup's second tile, and all draws on one
+// counter), beyond the second slowly.  Long against short tiles, us a call: J768 conv 4, L512 14.6 / 10.2, L2048 (768 short
+// tiles) 16.4 / 14.8, 8 x L300 (960) 17.1 / 13.7, L4096 (1536) 19.5 / 44.6; J120 L4096 (64 in a chain) 16.8 / 16.3; bf16
+// J256 L4096 17.5 / 17.0; paper's layer J256, L333 16.9 / 10.2, 7 x L512 (448) 18.1 / 12.8, L4096 (64 in a chain) 20.4 /
+// 20.7, 7 x L1024 (896) 18.9 / 29.8; with the harmonic convolution L1024 19.6 / 13.6, L4096 (256) 23.4 / 22.3, 7 x L1024
+// (448) 20.7 / 21.9.
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
@@ -545,8 +549,9 @@ static bool use_short_tiles(const cawn_desc *d, const WsLayout &w, int JB, size_
 {
     const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
     const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
-    if (nT > 32 || tiles > 256) return false;
-    return w.off_agg + tiles * JB * (d->ret_mode == 1 ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
+    const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
+    if (nT > (ret && !hc ? 48 : 64) || tiles > 256u * (hc ? 1 : ret ? 3 : 4)) return false;
+    return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
 
 static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, const float *valve,

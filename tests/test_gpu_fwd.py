@@ -293,10 +293,11 @@ def test_standalone_syntax_conv():
 
 
 @pytest.mark.parametrize("B,L,H,F,Kc", [(1, 17, 1, 8, 4), (1, 64, 3, 24, 0), (2, 65, 2, 16, 3), (1, 2048, 4, 64, 4), (1, 2049, 4, 64, 4),
-                                        (4, 2048, 1, 64, 1), (4, 2048, 1, 65, 1), (32, 500, 1, 32, 2), (33, 500, 1, 32, 2)])
+                                        (4, 2048, 1, 65, 1), (33, 500, 1, 32, 2), (1, 4096, 1, 64, 3), (1, 4097, 1, 64, 3),
+                                        (32, 2048, 1, 32, 2), (33, 2048, 1, 32, 2)])
 def test_short_tiles_at_their_edges(B, L, H, F, Kc):
-    """Calls on 64-token tiles: one tile, whole tiles, one token more, the longest chain (32 tiles), the most tiles (256),
-    and the next size of each, which the long tiles take; state in place, checkpoints and the gate mask, against the oracle."""
+    """Calls on 64-token tiles: one tile, whole tiles, one token more, the longest chain (64 tiles), the most tiles
+    (1024), and the next size of each, which the long tiles take; state in place, checkpoints and the gate mask, against the oracle."""
     G = _gpu()
     J, tau = H * F, 0.1
     d = _inputs(B, L, H, F, Kc, 1700 + L + B)
