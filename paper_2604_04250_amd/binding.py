@@ -1,8 +1,9 @@
-"""Thin ctypes binding of libcawn's C ABI (include/cawn.h): argument marshalling only.
+"""Thin binding of libcawn's C ABI (include/cawn.h): argument marshalling only.
 
 Every step of the hot path runs in the HIP kernels of libcawn.so.  PyTorch tensors are used as
-device-memory handles (``data_ptr()``) and for the current stream; nothing here computes.  If the
-shared library has not been built the import of a function fails loudly -- there is no fallback.
+device-memory handles (``data_ptr()``) and for the current stream; nothing here computes.  The forward and
+backward entry points are called through a small C module (csrc/cawn_call.c), the rest through ctypes.  If the
+shared libraries have not been built the first call fails loudly -- there is no fallback.
 """
 from __future__ import annotations
 
@@ -50,11 +51,13 @@ def make_desc(B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, conv_clamp=50.0, o
 
 
 _lib = None
+_call = None        # csrc/cawn_call.c
+_entry = {}         # entry point -> address, for _call
 
 
 def lib() -> C.CDLL:
     """Load libcawn.so; raise if it was not built (python -m paper_2604_04250_amd.build)."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
@@ -94,15 +97,37 @@ def lib() -> C.CDLL:
                                                       [C.c_size_t, C.c_int32, C.c_void_p])
         L.cawn_stream_copy.argtypes = [C.c_void_p] * 4 + [C.c_size_t, C.c_void_p]
         L.cawn_phase_accumulate_fwd_static.argtypes = [C.POINTER(cawn_desc)] + [C.c_void_p] * 13
+        try:
+            from . import _cawn_call
+        except ImportError as e:
+            raise RuntimeError("the marshalling module _cawn_call is missing: build it with __graft_entry__.build(); "
+                               "there is no fallback path") from e
+        _cawn_call.set_stream(getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device), _raw_stream())
+        for n in EXPORTS:
+            if n.startswith("cawn_phase_accumulate"):
+                _entry[n] = C.cast(getattr(L, n), C.c_void_p).value
+        _call = _cawn_call.call
         _lib = L
     return _lib
+
+
+def _raw_stream():
+    """device index -> handle of its current stream (torch's own accessor where this build of it has one)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw if raw is not None else (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+
+
+def _enter(name, form, *args) -> int:
+    if _call is None:
+        lib()
+    return _call(_entry[name], form, *args)
 
 
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda, "libcawn takes device pointers"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
@@ -164,84 +189,64 @@ def cawn_syntax_conv(d, Cch, x, w, bias, conv_state_in, y, conv_state_out, strea
 
 def cawn_phase_accumulate_fwd(d, mag, ang, gamma, theta, conv_w, conv_b, state_in, z_re, z_im,
                               state_out, ckpt, gate_mask, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_fwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(gamma), _ptr(theta), _ptr(conv_w), _ptr(conv_b),
-        _ptr(state_in), _ptr(z_re), _ptr(z_im), _ptr(state_out), _ptr(ckpt), _ptr(gate_mask),
-        _ptr(workspace), workspace.numel() * workspace.element_size() if workspace is not None else 0,
-        _stream(stream))
+    return _enter("cawn_phase_accumulate_fwd", 1,
+                  d, mag, ang, gamma, theta, conv_w, conv_b, state_in, z_re, z_im, state_out, ckpt, gate_mask,
+                  workspace, stream)
 
 
 def cawn_phase_accumulate_bwd(d, mag, ang, gamma, theta, conv_w, conv_b, state_in, ckpt, dz_re,
                               dz_im, dstate_out, dmag, dang, dgamma, dtheta, dconv_w, dconv_b,
                               dstate_in, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_bwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(gamma), _ptr(theta), _ptr(conv_w), _ptr(conv_b),
-        _ptr(state_in), _ptr(ckpt), _ptr(dz_re), _ptr(dz_im), _ptr(dstate_out), _ptr(dmag),
-        _ptr(dang), _ptr(dgamma), _ptr(dtheta), _ptr(dconv_w), _ptr(dconv_b), _ptr(dstate_in),
-        _ptr(workspace), workspace.numel() * workspace.element_size() if workspace is not None else 0,
-        _stream(stream))
+    return _enter("cawn_phase_accumulate_bwd", 1,
+                  d, mag, ang, gamma, theta, conv_w, conv_b, state_in, ckpt, dz_re, dz_im, dstate_out, dmag, dang,
+                  dgamma, dtheta, dconv_w, dconv_b, dstate_in, workspace, stream)
 
 
 def cawn_phase_accumulate_valve_fwd(d, mag, ang, valve, gamma, theta, conv_w, conv_b, state_in, z_re,
                                     z_im, state_out, ckpt, gate_mask, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_valve_fwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(gamma), _ptr(theta), _ptr(conv_w),
-        _ptr(conv_b), _ptr(state_in), _ptr(z_re), _ptr(z_im), _ptr(state_out), _ptr(ckpt),
-        _ptr(gate_mask), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_valve_fwd", 1,
+                  d, mag, ang, valve, gamma, theta, conv_w, conv_b, state_in, z_re, z_im, state_out, ckpt, gate_mask,
+                  workspace, stream)
 
 
 def cawn_phase_accumulate_valve_bwd(d, mag, ang, valve, gamma, theta, conv_w, conv_b, state_in, ckpt,
                                     dz_re, dz_im, dstate_out, dmag, dang, dvalve, dgamma, dtheta,
                                     dconv_w, dconv_b, dstate_in, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_valve_bwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(gamma), _ptr(theta), _ptr(conv_w),
-        _ptr(conv_b), _ptr(state_in), _ptr(ckpt), _ptr(dz_re), _ptr(dz_im), _ptr(dstate_out),
-        _ptr(dmag), _ptr(dang), _ptr(dvalve), _ptr(dgamma), _ptr(dtheta), _ptr(dconv_w),
-        _ptr(dconv_b), _ptr(dstate_in), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_valve_bwd", 1,
+                  d, mag, ang, valve, gamma, theta, conv_w, conv_b, state_in, ckpt, dz_re, dz_im, dstate_out, dmag,
+                  dang, dvalve, dgamma, dtheta, dconv_w, dconv_b, dstate_in, workspace, stream)
 
 
 def cawn_phase_accumulate_ret_fwd(d, mag, ang, valve, ret, ret_bias, theta, conv_w, conv_b, state_in, z_re,
                                   z_im, state_out, ckpt, gate_mask, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_ret_fwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(theta), _ptr(conv_w),
-        _ptr(conv_b), _ptr(state_in), _ptr(z_re), _ptr(z_im), _ptr(state_out), _ptr(ckpt),
-        _ptr(gate_mask), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_ret_fwd", 1,
+                  d, mag, ang, valve, ret, ret_bias, theta, conv_w, conv_b, state_in, z_re, z_im, state_out, ckpt,
+                  gate_mask, workspace, stream)
 
 
 def cawn_phase_accumulate_ret_bwd(d, mag, ang, valve, ret, ret_bias, theta, conv_w, conv_b, state_in, ckpt,
                                   dz_re, dz_im, dstate_out, dmag, dang, dvalve, dret, dtheta, dconv_w,
                                   dconv_b, dstate_in, workspace, stream=None) -> int:
-    return lib().cawn_phase_accumulate_ret_bwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(theta), _ptr(conv_w),
-        _ptr(conv_b), _ptr(state_in), _ptr(ckpt), _ptr(dz_re), _ptr(dz_im), _ptr(dstate_out),
-        _ptr(dmag), _ptr(dang), _ptr(dvalve), _ptr(dret), _ptr(dtheta), _ptr(dconv_w),
-        _ptr(dconv_b), _ptr(dstate_in), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_ret_bwd", 1,
+                  d, mag, ang, valve, ret, ret_bias, theta, conv_w, conv_b, state_in, ckpt, dz_re, dz_im, dstate_out,
+                  dmag, dang, dvalve, dret, dtheta, dconv_w, dconv_b, dstate_in, workspace, stream)
 
 
 def cawn_phase_accumulate_bf16_fwd(d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, state_in,
                                    z_re, z_im, state_out, ckpt, gate_mask, workspace, stream=None) -> int:
     """mag, ang, z_re, z_im: torch.bfloat16 tensors."""
-    return lib().cawn_phase_accumulate_bf16_fwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(gamma), _ptr(theta),
-        _ptr(conv_w), _ptr(conv_b), _ptr(state_in), _ptr(z_re), _ptr(z_im), _ptr(state_out), _ptr(ckpt),
-        _ptr(gate_mask), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_bf16_fwd", 1,
+                  d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, state_in, z_re, z_im, state_out,
+                  ckpt, gate_mask, workspace, stream)
 
 
 def cawn_phase_accumulate_hconv_fwd(d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, hconv_w,
                                     hconv_b, state_in, zc_re, zc_im, state_out, ckpt, gate_mask, workspace,
                                     activations_bf16=0, stream=None) -> int:
     """mag, ang, zc_re, zc_im: fp32 tensors, or torch.bfloat16 with activations_bf16=1."""
-    return lib().cawn_phase_accumulate_hconv_fwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(gamma), _ptr(theta),
-        _ptr(conv_w), _ptr(conv_b), _ptr(hconv_w), _ptr(hconv_b), _ptr(state_in), _ptr(zc_re), _ptr(zc_im),
-        _ptr(state_out), _ptr(ckpt), _ptr(gate_mask), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0,
-        C.c_int32(activations_bf16), _stream(stream))
+    return _enter("cawn_phase_accumulate_hconv_fwd", 2,
+                  d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, hconv_w, hconv_b, state_in, zc_re,
+                  zc_im, state_out, ckpt, gate_mask, workspace, activations_bf16, stream)
 
 
 def cawn_phase_accumulate_hconv_bwd(d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, hconv_w, hconv_b,
@@ -250,33 +255,26 @@ def cawn_phase_accumulate_hconv_bwd(d, mag, ang, valve, ret, ret_bias, gamma, th
                                     stream=None) -> int:
     """dc_re, dc_im: gradients of the convolved output; dhconv_w [2,H,3], dhconv_b [2,H] beside the usual gradients.
     mag, ang, dc_re, dc_im, dmag, dang: fp32 tensors, or torch.bfloat16 with activations_bf16=1."""
-    return lib().cawn_phase_accumulate_hconv_bwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(gamma), _ptr(theta), _ptr(conv_w),
-        _ptr(conv_b), _ptr(hconv_w), _ptr(hconv_b), _ptr(state_in), _ptr(ckpt), _ptr(dc_re), _ptr(dc_im), _ptr(dstate_out),
-        _ptr(dmag), _ptr(dang), _ptr(dvalve), _ptr(dret), _ptr(dgamma), _ptr(dtheta), _ptr(dconv_w), _ptr(dconv_b),
-        _ptr(dhconv_w), _ptr(dhconv_b), _ptr(dstate_in),
-        _ptr(workspace), workspace.numel() * workspace.element_size() if workspace is not None else 0,
-        C.c_int32(activations_bf16), _stream(stream))
+    return _enter("cawn_phase_accumulate_hconv_bwd", 2,
+                  d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, hconv_w, hconv_b, state_in, ckpt,
+                  dc_re, dc_im, dstate_out, dmag, dang, dvalve, dret, dgamma, dtheta, dconv_w, dconv_b, dhconv_w,
+                  dhconv_b, dstate_in, workspace, activations_bf16, stream)
 
 
 def cawn_phase_accumulate_bf16_bwd(d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, state_in, ckpt,
                                    dz_re, dz_im, dstate_out, dmag, dang, dvalve, dret, dgamma, dtheta, dconv_w,
                                    dconv_b, dstate_in, workspace, stream=None) -> int:
     """mag, ang, dz_re, dz_im, dmag, dang: torch.bfloat16 tensors."""
-    return lib().cawn_phase_accumulate_bf16_bwd(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(valve), _ptr(ret), _ptr(ret_bias), _ptr(gamma), _ptr(theta),
-        _ptr(conv_w), _ptr(conv_b), _ptr(state_in), _ptr(ckpt), _ptr(dz_re), _ptr(dz_im), _ptr(dstate_out),
-        _ptr(dmag), _ptr(dang), _ptr(dvalve), _ptr(dret), _ptr(dgamma), _ptr(dtheta), _ptr(dconv_w),
-        _ptr(dconv_b), _ptr(dstate_in), _ptr(workspace),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(stream))
+    return _enter("cawn_phase_accumulate_bf16_bwd", 1,
+                  d, mag, ang, valve, ret, ret_bias, gamma, theta, conv_w, conv_b, state_in, ckpt, dz_re, dz_im,
+                  dstate_out, dmag, dang, dvalve, dret, dgamma, dtheta, dconv_w, dconv_b, dstate_in, workspace, stream)
 
 
 def cawn_phase_accumulate_fwd_static(d, mag, ang, gamma, theta, conv_w, conv_b, state_in, z_re, z_im,
                                      state_out, ckpt, gate_mask, stream=None) -> int:
     """cawn_phase_accumulate_fwd on the library's static scratch array: allocates nothing."""
-    return lib().cawn_phase_accumulate_fwd_static(
-        C.byref(d), _ptr(mag), _ptr(ang), _ptr(gamma), _ptr(theta), _ptr(conv_w), _ptr(conv_b),
-        _ptr(state_in), _ptr(z_re), _ptr(z_im), _ptr(state_out), _ptr(ckpt), _ptr(gate_mask), _stream(stream))
+    return _enter("cawn_phase_accumulate_fwd_static", 0,
+                  d, mag, ang, gamma, theta, conv_w, conv_b, state_in, z_re, z_im, state_out, ckpt, gate_mask, stream)
 
 
 def cawn_stream_copy(in0, in1, out0, out1, stream=None) -> int:

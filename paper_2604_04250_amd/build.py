@@ -1,15 +1,17 @@
-"""Build libcawn.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libcawn.so (HIP, gfx950 only) in-tree with hipcc, and the binding's marshalling module (C, gcc)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcawn.so")
+CALL_OUT = os.path.join(HERE, "_cawn_call.so")
 # (the scan kernels' families are translation units of their own: they compile side by side)
 SOURCES = ["cawn_fwd_plain.hip", "cawn_fwd_valve.hip", "cawn_fwd_ret.hip", "cawn_fwd_valve_ret.hip",
            "cawn_fwd_short_plain.hip", "cawn_fwd_short_valve.hip", "cawn_fwd_short_ret.hip", "cawn_fwd_short_valve_ret.hip",
@@ -27,6 +29,15 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          # read-back of the result right behind the atomic, i.e. a wait for its round trip
          "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
+def build_call() -> str:
+    """The CPython module that passes tensors on to libcawn's entry points."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-Wextra",
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "cawn_call.c"), "-o", CALL_OUT]
+    subprocess.check_call(cmd)
+    return CALL_OUT
 
 
 def build(verbose: bool = False, defines=(), out: str = OUT, objdir: str = CSRC) -> str:
@@ -79,6 +90,7 @@ def build(verbose: bool = False, defines=(), out: str = OUT, objdir: str = CSRC)
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    build_call()
     return out
 
 

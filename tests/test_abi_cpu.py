@@ -123,6 +123,27 @@ def test_host_side_argument_checks_reject_before_any_launch():
     assert K.cawn_workspace_bytes(hc) > K.cawn_workspace_bytes(K.make_desc(2, 128, 2, 64))
 
 
+def test_marshalling_module_passes_calls_on_and_refuses_what_it_cannot_pass():
+    """The C module behind the forward and backward wrappers: the library's own refusals come back as status codes for
+    every wrapper (so the argument counts agree), host tensors and foreign descriptors raise."""
+    import inspect
+    import torch
+
+    d = K.make_desc(2, 128, 2, 64, conv_k=4)
+    for name in K.EXPORTS:
+        if not name.startswith("cawn_phase_accumulate"):
+            continue
+        f = getattr(K, name)
+        par = inspect.signature(f).parameters
+        n = len([p for p in par if p not in ("d", "stream", "activations_bf16")])
+        assert f(d, *([None] * n), stream=0) == K.CAWN_EINVAL, name       # null pointers, or another entry point's mode
+        assert f(K.make_desc(-1, 1, 1, 1), *([None] * n), stream=0) == K.CAWN_EINVAL, name
+        with pytest.raises(AssertionError, match="device pointers"):
+            f(d, *([torch.zeros(4)] * n), stream=0)
+        with pytest.raises((TypeError, BufferError)):
+            f(b"not a descriptor", *([None] * n), stream=0)
+
+
 def test_header_is_plain_c_and_links(tmp_path):
     """A C99 translation unit that includes the header, fills a descriptor and calls the size
     helpers compiles without warnings and links against the shared library (no compute call)."""
