@@ -585,7 +585,7 @@ static bool use_short_tiles(const cawn_desc *d, const WsLayout &w, int JB, size_
     const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
     const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
-    if (nT > (ret && !hc ? 48 : 64) || tiles > 256u * (hc ? 1 : ret ? 3 : 4)) return false;
+    if (nT > (ret && !hc ? 48 : 64) || tiles > 256u * (hc ? 1 : 4)) return false;
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
 
@@ -649,9 +649,10 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
         return CAWN_EUNSUPPORTED;
     }
     // the tile: 32-lane rows, with the harmonic convolution 64-lane rows (the same number of token-lanes)
-    const int JB = hconv_w ? FwdHead::JB : FwdGeom::JB;
-    const bool short_tiles = use_short_tiles(d, w, JB, workspace_bytes);
-    const int TT = short_tiles ? FwdShort::TILE_T : (hconv_w ? FwdHead::TILE_T : FwdGeom::TILE_T);
+    const bool short_tiles = use_short_tiles(d, w, hconv_w ? FwdHead::JB : FwdGeom::JB, workspace_bytes);
+    const bool head = hconv_w || (bf16 && !short_tiles);
+    const int JB = head ? FwdHead::JB : FwdGeom::JB;
+    const int TT = short_tiles ? FwdShort::TILE_T : (head ? FwdHead::TILE_T : FwdGeom::TILE_T);
     a.short_tiles = short_tiles ? 1 : 0;
     a.H = d->H; a.F = d->F;
     a.gpb = d->F >= JB ? 1 : JB / d->F;

@@ -1377,7 +1377,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // ---- the workgroup that leaves last resets the ticket and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
     if (tid_ == 0) {
-        sLast = leave_call(a.hdr, blockIdx.x, gridDim.x) ? 1u : 0u;
+        sLast = leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x) ? 1u : 0u;
     }
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x);

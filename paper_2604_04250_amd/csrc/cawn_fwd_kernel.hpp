@@ -28,10 +28,6 @@
 
 namespace cawn {
 
-#ifndef CAWN_FWD_NB
-#define CAWN_FWD_NB 2       // predecessors read per look-back round trip
-#endif
-
 // Tuning aid, compiled only with -DCAWN_TIMING: per-tile time stamps (100 MHz counter) of the
 // chain-owning thread, written behind the parameter partials in the workspace.
 #ifdef CAWN_TIMING
@@ -137,7 +133,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
-__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
+__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
     constexpr int V = 1;                           // lanes per thread
     constexpr int TILE_T = G::TILE_T, NSTEP = G::NSTEP, NSEG = G::NSEG, LPR = G::JB;
@@ -145,6 +141,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
     constexpr int MW = JB / 32;                    // gate-mask words of a row
     static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
+    constexpr bool EACH = JB == 32 && !G::SHORT;   // may pass a prefix on per tile (see make_queues)
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -173,7 +170,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
                   "powers the lane table holds");
     // valve / retention groups per lane block: F >= 8, or F >= 16 with both (LDS: two workgroups per CU)
     // (HC: F >= 32, i.e. two groups of a 64-lane block)
-    constexpr int GPB_MAX = (HC || (VALVE && RET)) ? 2 : 4;
+    constexpr int GPB_MAX = HC ? 2 : ((VALVE && RET) ? 2 : 4) * (JB / 32);
     __shared__ float sV[VALVE ? TILE_T * GPB_MAX : 1];
     __shared__ float sR[RET ? TILE_T * GPB_MAX : 1];     // retention logits, laid out like sV
     __shared__ float sP[RET ? NSEG - 1 : 1][JB];                  // product of each segment's retentions
@@ -526,13 +523,18 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
             float cr[V], ci[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) cr[v] = ci[v] = 0.f;
+            // (what this tile publishes: its aggregate, the chain's first tile its prefix instead; the last of a
+            // group also its prefix; the chain's last tile nothing)
+            const int group = (int)a.tq.group;
+            const bool feeds = tt + 1 < a.nT, ends_group = (tt & (group - 1)) == group - 1;
+            const bool each = EACH && group == 1;       // a prefix per tile: the first tile's stands with the others
             if (tt == 0) {
                 if (a.state_in && active) {
                     Vec<V>::ld(cr, a.state_in + ((size_t)b * 2 + 0) * a.J + j0);
                     Vec<V>::ld(ci, a.state_in + ((size_t)b * 2 + 1) * a.J + j0);
                 }
             } else {
-                if (tt + 1 < a.nT) {
+                if (feeds && (!ends_group || each)) {
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         tagged_store(a.agg + slot + v, Tr[v], tag);
@@ -540,13 +542,15 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
                         if (RET) tagged_store(a.aggp + (size_t)id * JB + lv * V + v, Pt[v], tag);
                     }
                 }
+                // aggregates read per round trip: what the register budget leaves
+                constexpr int NB = G::SHORT ? (RET ? (HC ? 6 : 4) : (HC ? 8 : 6)) : (HC && RET ? 2 : (BF && !RET && !HC ? 4 : 7));
                 bool got;
-                if constexpr (G::SHORT)
-                    got = walk_chain<JB, RET ? 6 : 8, RET>(a.agg, a.aggp, id - (uint32_t)tt * (uint32_t)a.B, (uint32_t)a.B, tt, lv, hr[0], hi[0],
-                                                 qr[0], qi[0], a.spin_limit, tag, cr[0], ci[0]);
+                if (each)
+                    got = look_back<V, false, LPR, 2, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv, hr, hi,
+                                                           qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
                 else
-                    got = look_back<V, false, LPR, CAWN_FWD_NB, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv,
-                                                 hr, hi, qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
+                    got = chain_carry<JB, NB, false, RET, !G::SHORT && !(HC && RET)>(a.agg, a.aggp, a.pre, id, (uint32_t)a.B, tt, group, lv, hr[0], hi[0], qr[0],
+                                                     qi[0], a.spin_limit, tag, cr[0], ci[0]);
                 if (!got) {
                     // gave up: flag the workspace, keep going so that every wave exits
                     if (lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -563,8 +567,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
                 sCarry[0][lv * V + v] = cr[v];
                 sCarry[1][lv * V + v] = ci[v];
             }
-            if (tt + 1 < a.nT && (!G::SHORT || tt == 0)) {   // the tile's inclusive prefix for the chain
-                tagged_t *pre = G::SHORT ? a.agg : a.pre;     // (short chains: the first tile's stands where its aggregate would)
+            if (feeds && (tt == 0 || ends_group)) {   // the tile's inclusive prefix for the chain
+                tagged_t *pre = tt == 0 && !each ? a.agg : a.pre;
                 float P_r[V], P_i[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v)
@@ -868,7 +872,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : RET ? 3 : 4) : (BF && !
     // ---- the workgroup that leaves last resets the tickets and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
     if (tid == 0) {
-        sLast = leave_call(a.hdr, blockIdx.x, gridDim.x) ? 1u : 0u;
+        sLast = leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x) ? 1u : 0u;
     }
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
@@ -894,6 +898,8 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
     const long long wgs = jobs < resident ? jobs : resident;
     FwdArgs b = a;
     b.tq = make_queues(units, (uint32_t)a.nT, wgs);
+    if (G::SHORT) b.tq.group = 64;      // (one group: no prefixes)
+    else if (G::JB == 32 && !b.tq.one_each) b.tq.group = 1;
     hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
     return hipGetLastError();
 }
@@ -907,7 +913,7 @@ static hipError_t launch_fwd_k(const FwdArgs &a, hipStream_t s)
 #ifndef CAWN_DEV_PLAIN
     if (a.hconv) return launch_fwd_tile<conditional_t<SHORT, FwdShortHead, FwdHead>, KC, VALVE, RET, BF, true>(a, s);
 #endif
-    return launch_fwd_tile<conditional_t<SHORT, FwdShort, FwdGeom>, KC, VALVE, RET, BF, false>(a, s);
+    return launch_fwd_tile<conditional_t<SHORT, FwdShort, conditional_t<BF, FwdHead, FwdGeom>>, KC, VALVE, RET, BF, false>(a, s);
 }
 
 // Tuning aid: -DCAWN_DEV_KC=<k> compiles only the conv_k = k kernels and -DCAWN_DEV_PLAIN only the

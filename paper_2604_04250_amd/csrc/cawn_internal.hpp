@@ -128,11 +128,17 @@ inline __host__ __device__ uint32_t done_word(uint32_t q) { return ticket_word(q
 //   * a call with more tiles than workgroups keeps one counter: its draws are spread over the call and cost nothing
 //     (eight counters with a second choice where one ran dry were slower: training step 431 -> 454 us, bf16 B2 L4096
 //     J4096 284 -> 298; the first tickets' delay keeps the workgroups out of step, and loads beside arithmetic);
-//   * workgroups that leave are counted in two levels when there are many.
-struct TileQueues { uint32_t lq, one_each; };
+//   * the many workgroups of such a one-tile-each call are counted out in two levels.
+struct TileQueues { uint32_t lq, one_each, group; };     // group: tiles of a chain between two prefixes (see chain_carry)
+// Tiles between two prefixes in the forward: 8; 16 where there are so few chains that passing prefixes on bounds the call.
+// us a call with 2 / 4 / 8 / 16: B1 L4096 J768 20.5 / 18.8 / 18.1 / 19.2; B1 L32768 J256 of the paper's layer in bf16 109 /
+// 71 / 52 / 49, with the harmonic convolution 111 / 73 / 58 / 56; B2 L4096 J4096 bf16 84.5 / 83.6 / 84.8 / 86.9.
+// 1 (a prefix per tile, look_back) for 32-lane rows with more tiles than workgroups: there the nearest prefix has nearly
+// always arrived, and one pair of words is cheaper than a fold: B16 L1000 J768 55.0 against 56.2, paper's layer B8 L8192
+// J256 74.4 against 77.4 (with bf16 or the harmonic convolution, on 64-lane rows, the fold is ahead there too).
 inline TileQueues make_queues(uint32_t U, uint32_t nT, long long workgroups)
 {
-    TileQueues t{0, workgroups >= (long long)U * nT ? 1u : 0u};
+    TileQueues t{0, workgroups >= (long long)U * nT ? 1u : 0u, U <= 8 ? 16u : 8u};
     while (t.one_each && (2u << t.lq) <= (uint32_t)MAX_QUEUES && U % (2u << t.lq) == 0) ++t.lq;
     return t;
 }
@@ -506,12 +512,13 @@ __device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h, uint32_t G)
 {
     return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A workgroup leaves: true for the last one.  Two levels from 96 workgroups on (a second round trip, 0.4 us, for the last
-// of them; 96 counts on one address take 1.1 us).
-__device__ __forceinline__ bool leave_call(WsHeader *h, uint32_t wg, uint32_t grid)
+// A workgroup leaves: true for the last one.  Two levels for 96 and more workgroups that all leave at about the same time
+// (a second round trip, 0.4 us, for the last of them; 96 counts on one address take 1.1 us); those of larger calls are
+// spread by their draws.
+__device__ __forceinline__ bool leave_call(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t grid)
 {
     auto add = [&](uint32_t *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u; };
-    if (grid < 96) return add(&h->done) == grid;
+    if (grid < 96 || !t.one_each) return add(&h->done) == grid;
     const uint32_t s = wg % MAX_QUEUES;
     if (add(hdr_word(h, done_word(s))) != (grid - s + MAX_QUEUES - 1) / MAX_QUEUES) return false;
     return add(&h->done) == (uint32_t)MAX_QUEUES;
@@ -543,9 +550,7 @@ __device__ __forceinline__ void finish_call(WsHeader *hdr, size_t clear_from, ui
 }
 
 // One link of a tile chain: P = T + M c, with M = lambda^TILE_T held as a double-float (h + q) and
-// conjugated for the adjoint chain.  Publication of a prefix and the look-back both go through
-// this one function, so every tile's prefix has the value a strictly sequential chain would give,
-// wherever the look-back happened to find its starting prefix: results do not depend on timing.
+// conjugated for the adjoint chain.
 template <bool CONJ>
 __device__ __forceinline__ void chain_step(float Tr, float Ti, float hr, float hi, float qr, float qi,
                                            float cr, float ci, float &Pr, float &Pi)
@@ -563,56 +568,106 @@ __device__ __forceinline__ void chain_step(float Tr, float Ti, float hr, float h
     }
 }
 
-// The carry of a tile of a short chain: every tile before it has published its aggregate (the chain's first its
-// prefix, in the same place), and this tile reads them all, NB per round trip, and walks them in order with
-// chain_step().  No tile waits for another tile's prefix: the last aggregate published is the only thing the chain's end
-// depends on, where passing prefixes on costs a round trip per link (0.2 - 0.4 us).  Run by one group of JB
-// consecutive threads of a wave; `first` is the index of the chain's first tile, n >= 1 the tiles before this one.
-// Returns false if a wait gave up (the carry is then meaningless).
-template <int JB, int NB, bool RET>
-__device__ __forceinline__ bool walk_chain(const tagged_t *agg, const tagged_t *aggp, uint32_t first, uint32_t stride, int n,
-                                           int lv, float hr, float hi, float qr, float qi, uint32_t spin_limit,
-                                           uint32_t tag, float &cr, float &ci)
+// The carry of a tile: what the tiles before it in its chain leave behind.  Run by one group of JB consecutive threads of
+// a wave.  A chain's tiles form groups of G (a power of two).  Every tile publishes its aggregate as soon as it has it
+// (the chain's first tile its prefix, in the same place), the last tile of a group also its prefix.  A tile reads the
+// aggregates of the r tiles before it in its group, NB per round trip, and folds them, in order, into one link
+//   carry = E + P M^r c      (P: RET, the product of the r tiles' retentions)
+// while the prefix c of the previous group is on its way; the first group needs none (its E is the carry).  So a
+// prefix is passed on once per G tiles, and only that is a chain of round trips: with a prefix per tile, long chains of
+// few rows advanced by 0.22 us a tile, and walking back over aggregates instead read every one of them in every tile.
+// The association is fixed by G and the tile's position alone: results do not depend on timing.
+// `id` is the tile's index, `stride` the distance to its predecessor's, tt >= 1 its position in the chain.  M is
+// lambda^TILE_T as a double-float; its power is formed in fp64.  Every wait is bounded: false if one gave up (the carry
+// is then meaningless).
+template <int JB, int NB, bool CONJ, bool RET, bool PRE>
+__device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t *aggp, const tagged_t *pre, uint32_t id,
+                                            uint32_t stride, int tt, int G, int lv, float hr, float hi, float qr, float qi,
+                                            uint32_t spin_limit, uint32_t tag, float &cr, float &ci)
 {
     const int gshift = (int)(threadIdx.x & 63) - lv;
     const unsigned long long gmask = JB >= 64 ? ~0ull : ((1ull << JB) - 1ull);
+    auto group_all = [&](bool ok) { return ((__ballot(ok) >> gshift) & gmask) == gmask; };
+    const int r = tt & (G - 1);
+    const bool first_group = tt == r;
+    const uint32_t first = id - (uint32_t)r * stride;
     uint32_t spins = 0;
-    for (int base = 0; base < n; base += NB) {
+    float Er = 0.f, Ei = 0.f, P = 1.f;
+    const double Mr = (double)hr + (double)qr, Mi = (double)hi + (double)qi;
+    double mr = 1.0, mi = 0.0;
+    // (PRE: the prefix is asked for with the first aggregates: where it is already there, one round trip brings both)
+    const tagged_t *src = pre + (size_t)(first - stride) * 2 * JB + lv;
+    tagged_t w0 = 0, w1 = 0;
+    if (PRE && !first_group) {
+        w0 = tagged_load(src);
+        w1 = tagged_load(src + JB);
+    }
+    for (int base = 0; base < r; base += NB) {
         tagged_t wr[NB], wi[NB], wp[RET ? NB : 1];
         while (true) {
             bool ok = true;
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
-                const size_t id = first + (uint32_t)(base + k < n ? base + k : n - 1) * stride;   // (past the end: the last again)
-                wr[k] = tagged_load(agg + id * 2 * JB + lv);
-                wi[k] = tagged_load(agg + id * 2 * JB + JB + lv);
-                if constexpr (RET) wp[k] = tagged_load(aggp + id * JB + lv);
+                const size_t t = first + (uint32_t)(base + k < r ? base + k : r - 1) * stride;   // (past the end: the last again)
+                wr[k] = tagged_load(agg + t * 2 * JB + lv);
+                wi[k] = tagged_load(agg + t * 2 * JB + JB + lv);
+                if constexpr (RET) wp[k] = tagged_load(aggp + t * JB + lv);
             }
 #pragma unroll
             for (int k = 0; k < NB; ++k) {
                 ok = ok && tagged_ok(wr[k], tag) && tagged_ok(wi[k], tag);
-                if constexpr (RET) ok = ok && (tagged_ok(wp[k], tag) || (base + k < n ? base + k : n - 1) == 0);
+                // (the chain's first tile publishes no product: nothing comes before it)
+                if constexpr (RET) ok = ok && (tagged_ok(wp[k], tag) || (first_group && (base + k < r ? base + k : r - 1) == 0));
             }
-            if (((__ballot(ok) >> gshift) & gmask) == gmask) break;
+            if (group_all(ok)) break;
             if (++spins > spin_limit) return false;
             __builtin_amdgcn_s_sleep(1);
         }
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-            if (base + k < n) {
+            if (base + k < r) {
                 const float tr = tagged_value(wr[k]), ti = tagged_value(wi[k]);
+                if constexpr (RET) {
+                    const float p = tagged_value(wp[k]);
+                    Er *= p;
+                    Ei *= p;
+                    P *= p;
+                }
                 if (base + k == 0) {
-                    cr = tr;
-                    ci = ti;
+                    Er = tr;
+                    Ei = ti;
                 } else {
                     float nr, ni;
-                    if constexpr (RET) { const float p = tagged_value(wp[k]); cr *= p; ci *= p; }
-                    chain_step<false>(tr, ti, hr, hi, qr, qi, cr, ci, nr, ni);
-                    cr = nr;
-                    ci = ni;
+                    chain_step<CONJ>(tr, ti, hr, hi, qr, qi, Er, Ei, nr, ni);
+                    Er = nr;
+                    Ei = ni;
+                }
+                if (!first_group) {
+                    const double t = mr * Mr - mi * Mi;
+                    mi = mr * Mi + mi * Mr;
+                    mr = t;
                 }
             }
         }
+    }
+    cr = Er;
+    ci = Ei;
+    if (first_group) return true;
+    while (!group_all(tagged_ok(w0, tag) && tagged_ok(w1, tag))) {
+        if (++spins > spin_limit) return false;
+        __builtin_amdgcn_s_sleep(1);
+        w0 = tagged_load(src);
+        w1 = tagged_load(src + JB);
+    }
+    cr = tagged_value(w0);
+    ci = tagged_value(w1);
+    if (r > 0) {
+        const float ar = (float)mr, ai = (float)mi;
+        float nr, ni;
+        if constexpr (RET) { cr *= P; ci *= P; }
+        chain_step<CONJ>(Er, Ei, ar, ai, (float)(mr - (double)ar), (float)(mi - (double)ai), cr, ci, nr, ni);
+        cr = nr;
+        ci = ni;
     }
     return true;
 }
