@@ -58,8 +58,6 @@ static WsLayout make_layout(const cawn_desc *d, bool fwd_only = false)
     w.off_rpart = o;    // ret_mode 1: per-group sums of the retention logits' gradient terms, [B][groups][L]
     if (d->ret_mode == 1 && !fwd_only)
         o = align_up(o + (size_t)d->B * (size_t)(d->H * (d->F >= 32 ? d->F / 32 : 1)) * (size_t)(d->L > 0 ? d->L : 1) * sizeof(float), 256);
-    w.off_hpart = o;    // harmonic convolution: per-lane sums of its taps' and biases' gradient terms, [8][Jp]
-    if (d->hconv_k != 0 && !fwd_only) o = align_up(o + (size_t)HC_PART_ROWS * w.Jp * sizeof(float), 256);
     w.off_dbg = o;
 #ifdef CAWN_TIMING
     o += (size_t)MAX_TILES * 16 * sizeof(unsigned long long);
@@ -274,46 +272,43 @@ static void launch_conv(bool vec4, dim3 grid, hipStream_t s, const float *x, con
 // tile = chain * nLB + lb (chain = position-in-time * B + b).  Block = 32 lanes x 32 groups: group g
 // sums chains g, g+32, ... of its lane's block in increasing order, then the 32 sub-sums meet in LDS
 // and are added in index order -- the association is fixed, so results are bitwise repeatable.
+constexpr int RG = 32;       // groups of a reduction block
+// the sum of group g's chains of one (lane block, row, lane): `acc` continues
+__device__ __forceinline__ float sum_chains(const float *__restrict__ src, size_t step, int chains, int g, float acc)
+{
+    // (eight independent reads in flight per thread; the sum keeps its order)
+    int c = g;
+    for (; c + 7 * RG < chains; c += 8 * RG) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(c + u * RG) * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; c < chains; c += RG) acc += src[(size_t)c * step];
+    return acc;
+}
 __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, float *__restrict__ out0,
                                                 float *__restrict__ out1, float *__restrict__ out2,
-                                                float *__restrict__ out3, float *__restrict__ out4, int rows, int conv_k,
-                                                int hc_row0, int J, int JB, int nLB, int chains, int accumulate, int bx,
-                                                int row)
+                                                float *__restrict__ out3, int rows, int conv_k,
+                                                int J, int JB, int nLB, int chains, int accumulate, int bx,
+                                                int row, float (*sm)[33])
 {
     // one block per (32 lanes, row): bx, row
-    constexpr int G = 32;
-    __shared__ float sm[G][33];
+    constexpr int G = RG;
     const int lane = threadIdx.x % 32, g = threadIdx.x / 32;
     const int j = bx * 32 + lane;
     float acc = 0.0f;
-    if (j < J) {
-        const int lb = j / JB, jj = j % JB;
-        // (eight independent reads in flight per thread; the sum keeps its order)
-        const float *src = part + ((size_t)lb * rows + row) * JB + jj;
-        const size_t step = (size_t)nLB * rows * JB;      // floats between the same slot of consecutive chains
-        int c = g;
-        for (; c + 7 * G < chains; c += 8 * G) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(c + u * G) * step];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-        for (; c < chains; c += G) acc += src[(size_t)c * step];
-    }
+    if (j < J)
+        acc = sum_chains(part + ((size_t)(j / JB) * rows + row) * JB + j % JB, (size_t)nLB * rows * JB, chains, g, acc);
     sm[g][lane] = acc;
     __syncthreads();
     if (g == 0 && j < J) {
         float s = 0.0f;
 #pragma unroll
         for (int qq = 0; qq < G; ++qq) s += sm[qq][lane];
-        // rows: 0 dgamma, 1 dtheta, 2 dbias_m, 3 dbias_a, 4 + s*conv_k + i: dw[s][j][i]; from hc_row0 on (when
-        // >= 0): the harmonic convolution's per-lane terms, kept per lane in out4 [8][J] for their own reduction
+        // rows: 0 dgamma, 1 dtheta, 2 dbias_m, 3 dbias_a, 4 + s*conv_k + i: dw[s][j][i]
         float *dst = nullptr;
-        if (hc_row0 >= 0 && row >= hc_row0) {
-            out4[(size_t)(row - hc_row0) * J + j] = s;
-            return;
-        }
         if (row == 0) dst = out0 ? out0 + j : nullptr;
         else if (row == 1) dst = out1 ? out1 + j : nullptr;
         else if (row < 4) dst = out3 ? out3 + (size_t)(row - 2) * J + j : nullptr;
@@ -325,50 +320,66 @@ __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, 
     }
 }
 
-// What follows the backward kernel, in one launch (each small launch costs 4-5 us on this chip whatever it
-// does): blocks [0, nbx * rows) sum the parameter partials, the blocks behind them share the logit gradients of
-// the valve and of the retention (nsets of them, nb blocks each).
-struct EpilogueArgs {
-    const float *part;
-    float *out0, *out1, *out2, *out3, *out4;
-    int rows, conv_k, hc_row0, J, JB, nLB, chains, accumulate, nbx;
-    const float *lpart[2], *logit[2];
-    float *lout[2];
-    int nsets, nb, B, L, H, G;
-};
-__global__ __launch_bounds__(1024) void bwd_epilogue_kernel(const EpilogueArgs p)
+// Harmonic convolution (Sec. 3.6): its taps and biases belong to a (plane, head) channel.  One block per output: q = 0 .. 5
+// taps (plane, tap), 6, 7 biases, and head h.  Thread (group, lane) sums its chains over the head's 32-lane blocks (F <= 32:
+// the head's lanes of its block), the groups meet in LDS in index order and the 32 lane sums in a butterfly of lane
+// exchanges (both partners add the same two values): the association is fixed, the result repeatable.  (As a kernel of
+// its own behind per-lane sums in memory this cost 4.0 - 4.8 us a call.)
+__device__ __forceinline__ void reduce_hconv(const float *__restrict__ part, float *__restrict__ dw, float *__restrict__ db,
+                                             int rows, int hc_row0, int H, int F, int JB, int nLB, int chains,
+                                             int accumulate, int q, int h, float (*sm)[33])
 {
-    const int nA = p.nbx * p.rows;
-    if ((int)blockIdx.x < nA) {
-        reduce_partials(p.part, p.out0, p.out1, p.out2, p.out3, p.out4, p.rows, p.conv_k, p.hc_row0, p.J, p.JB, p.nLB,
-                        p.chains, p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx);
-        return;
-    }
-    const int bid = (int)blockIdx.x - nA, set = bid / p.nb, blk = bid % p.nb;
-    logit_reduce(p.lpart[set], p.logit[set], p.lout[set], p.B, p.L, p.H, p.G, (long long)blk * blockDim.x + threadIdx.x,
-                 (long long)p.nb * blockDim.x);
-}
-
-// Harmonic convolution (Sec. 3.6): its taps and biases belong to a (plane, head) channel, so the per-lane sums
-// hpart [8][J] (rows: plane-0 taps 0..2, plane-1 taps 0..2, plane-0 bias, plane-1 bias) are summed over the F
-// lanes of each head by one wave per output: lane l adds the head's lanes l, l + 64, ... in ascending order, then
-// the 64 sums meet in a butterfly of lane exchanges (both partners of an exchange add the same two values, so
-// every lane ends with the same bits): the association is fixed, the result repeatable.
-__global__ __launch_bounds__(64) void hconv_grad_reduce_kernel(const float *__restrict__ hpart, float *__restrict__ dw,
-                                                               float *__restrict__ db, int H, int F, int J, int accumulate)
-{
-    const int e = blockIdx.x;        // (row, head)
-    const int q = e / H, h = e % H;
-    const float *src = hpart + (size_t)q * J + (size_t)h * F;
+    const int lane = threadIdx.x % 32, g = threadIdx.x / 32;
+    const int l0 = (h * F) % 32;
+    const bool mine = F >= 32 || (lane >= l0 && lane < l0 + F);
+    float acc = 0.0f;
+    if (mine)
+        for (int k = 0; k < (F >= 32 ? F / 32 : 1); ++k)
+            acc = sum_chains(part + ((size_t)((h * F) / 32 + k) * rows + hc_row0 + q) * JB + lane, (size_t)nLB * rows * JB, chains, g, acc);
+    sm[g][lane] = acc;
+    __syncthreads();
+    if (g != 0) return;
     float s = 0.0f;
-    for (int k = threadIdx.x; k < F; k += 64) s += src[k];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) {
+    for (int k = 0; k < RG; ++k) s += sm[k][lane];
+#pragma unroll
+    for (int o = 16; o >= 1; o >>= 1) s += __shfl_xor(s, o, 32);
+    if (lane == 0) {
         float *dst = q < 6 ? (dw ? dw + ((size_t)(q / 3) * H + h) * 3 + q % 3 : nullptr)
                            : (db ? db + (size_t)(q - 6) * H + h : nullptr);
         if (dst) *dst = accumulate ? *dst + s : s;
     }
+}
+
+// What follows the backward kernel, in one launch (each small launch costs 4-5 us on this chip whatever it
+// does): blocks [0, nbx * rows_lane) sum the parameter partials, nhc blocks behind them the harmonic convolution's, the
+// rest share the logit gradients of the valve and of the retention (nsets of them, nb blocks each).
+struct EpilogueArgs {
+    const float *part;
+    float *out0, *out1, *out2, *out3, *dhw, *dhb;
+    int rows, rows_lane, conv_k, J, JB, nLB, chains, accumulate, nbx, nhc;
+    const float *lpart[2], *logit[2];
+    float *lout[2];
+    int nsets, nb, B, L, H, F, G;
+};
+__global__ __launch_bounds__(1024) void bwd_epilogue_kernel(const EpilogueArgs p)
+{
+    static_assert(BwdLPR == 32, "reduction blocks take a lane block's 32 lanes");
+    __shared__ float sm[RG][33];
+    const int nA = p.nbx * p.rows_lane;
+    if ((int)blockIdx.x < nA) {
+        reduce_partials(p.part, p.out0, p.out1, p.out2, p.out3, p.rows, p.conv_k, p.J, p.JB, p.nLB,
+                        p.chains, p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx, sm);
+        return;
+    }
+    if ((int)blockIdx.x < nA + p.nhc) {
+        const int e = (int)blockIdx.x - nA;
+        reduce_hconv(p.part, p.dhw, p.dhb, p.rows, p.rows - HC_PART_ROWS, p.H, p.F, p.JB, p.nLB, p.chains, p.accumulate, e / p.H, e % p.H, sm);
+        return;
+    }
+    const int bid = (int)blockIdx.x - nA - p.nhc, set = bid / p.nb, blk = bid % p.nb;
+    logit_reduce(p.lpart[set], p.logit[set], p.lout[set], p.B, p.L, p.H, p.G, (long long)blk * blockDim.x + threadIdx.x,
+                 (long long)p.nb * blockDim.x);
 }
 
 // Plain streaming copy with the forward's traffic shape: two fp32 streams in, two out, 8 bytes read and
@@ -862,31 +873,26 @@ static int bwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     if (launch_bwd(a, kc, vec, s) != hipSuccess) return CAWN_ELAUNCH;
     {
         EpilogueArgs p{};
-        float *hpart = reinterpret_cast<float *>(ws + w.off_hpart);
-        if (dgamma || dtheta || want_w || hc) {
-            p.rows = part_rows(kc, hc);
+        p.rows = part_rows(kc, hc);
+        if (dgamma || dtheta || want_w) {
+            p.rows_lane = part_rows(kc);
             p.nbx = (int)((J + 31) / 32);
         }
         p.part = a.part;
-        p.out0 = dgamma; p.out1 = dtheta; p.out2 = dconv_w; p.out3 = dconv_b; p.out4 = hpart;
+        p.out0 = dgamma; p.out1 = dtheta; p.out2 = dconv_w; p.out3 = dconv_b; p.dhw = dhconv_w; p.dhb = dhconv_b;
+        p.nhc = hc && (dhconv_w || dhconv_b) ? HC_PART_ROWS * d->H : 0;
         p.conv_k = kc > 0 ? kc : 1;
-        p.hc_row0 = hc ? 4 + 2 * kc : -1;
         p.J = (int)J; p.JB = JB; p.nLB = nLB; p.chains = d->B * w.nT; p.accumulate = d->accumulate_param_grads;
+        p.F = d->F;
         if (a.vpart) { p.lpart[p.nsets] = a.vpart; p.logit[p.nsets] = valve; p.lout[p.nsets] = dvalve; ++p.nsets; }
         if (a.rpart) { p.lpart[p.nsets] = a.rpart; p.logit[p.nsets] = nullptr; p.lout[p.nsets] = dret; ++p.nsets; }
         const long long n = (long long)d->B * d->H * d->L;
         const long long nb = (n + 1023) / 1024;
         p.nb = p.nsets ? (int)(nb < 1024 ? nb : 1024) : 0;
         p.B = d->B; p.L = d->L; p.H = d->H; p.G = a.G;
-        const unsigned blocks = (unsigned)(p.nbx * p.rows + p.nb * p.nsets);
+        const unsigned blocks = (unsigned)(p.nbx * p.rows_lane + p.nhc + p.nb * p.nsets);
         if (blocks) {
             hipLaunchKernelGGL(bwd_epilogue_kernel, dim3(blocks), dim3(1024), 0, s, p);
-            if (hipGetLastError() != hipSuccess) return CAWN_ELAUNCH;
-        }
-        if (hc && (dhconv_w || dhconv_b)) {
-            const int nh = HC_PART_ROWS * d->H;
-            hipLaunchKernelGGL(hconv_grad_reduce_kernel, dim3((unsigned)nh), dim3(64), 0, s, hpart, dhconv_w,
-                               dhconv_b, d->H, d->F, (int)J, d->accumulate_param_grads);
             if (hipGetLastError() != hipSuccess) return CAWN_ELAUNCH;
         }
     }

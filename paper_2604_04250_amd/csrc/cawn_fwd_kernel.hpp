@@ -89,7 +89,9 @@ template <class G> struct FwdConsts {
                          C_RBIAS = C_BIAS_M + 2, C_W0 = C_BIAS_M + 3;
     static __device__ __forceinline__ int table_row(int r)
     {
-        return r < C_P ? R_LR + r : (r < C_BIAS_M ? (G::SHORT ? R_PSEGB : R_PSEG) + 2 + (r - C_P) : R_BIAS_M + (r - C_BIAS_M));
+        if (!G::SHORT)      // (the table's order with gaps)
+            return R_LR + r + (r < C_P ? 0 : 2) + (r < C_BIAS_M ? 0 : R_BIAS_M - R_PSEG - 2 * G::NSEG);
+        return r < C_P ? R_LR + r : (r < C_BIAS_M ? R_PSEGB + 2 + (r - C_P) : R_BIAS_M + (r - C_BIAS_M));
     }
 };
 // 16 bytes per lane per load: JB / 4 lanes cover a row.  Called by one wave.  Table rows are 256-byte aligned and

@@ -145,7 +145,7 @@ inline TileQueues make_queues(uint32_t U, uint32_t nT, long long workgroups)
 
 struct WsLayout {
     int J, Jp, Jp128, nT, nTc;     // nT: backward tiles per sequence, nTc: checkpoint intervals
-    size_t off_table, off_agg, off_pre, off_halo, off_part, off_vpart, off_aggp, off_rpart, off_hpart, off_dbg, total;
+    size_t off_table, off_agg, off_pre, off_halo, off_part, off_vpart, off_aggp, off_rpart, off_dbg, total;
 };
 
 constexpr uint32_t EPOCH_MOD = (1u << 23) - 1u;     // epochs 0 .. 2^23 - 2
