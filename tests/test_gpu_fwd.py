@@ -319,6 +319,35 @@ def test_short_tiles_at_their_edges(B, L, H, F, Kc):
         assert np.array_equal(t_o, np.concatenate([tail, u], 1)[:, -(Kc - 1):])
 
 
+@pytest.mark.parametrize("mode", ["plain", "ret", "hconv", "hconv_ret"])
+@pytest.mark.parametrize("B,L,H,F", [(1, 4352, 1, 64), (1, 4353, 1, 64), (1, 6145, 1, 64), (3, 4097, 3, 64), (2, 4352, 1, 128)])
+def test_prefixes_per_group_of_tiles(B, L, H, F, mode):
+    """Chains longer than a group (8 tiles, 16 with few chains): ends of groups, one token into the next group, several
+    groups, state in and out, with a product per tile (retention) and without; against the oracle."""
+    G = _gpu()
+    J, Kc, tau = H * F, 3, 0.1
+    d = _inputs(B, L, H, F, Kc, 1800 + L + B)
+    r = np.random.Generator(np.random.PCG64(1801))
+    scan = r.standard_normal((B, 2, J)).astype(np.float32)
+    tail = r.standard_normal((B, Kc - 1, 2, J)).astype(np.float32)
+    ret = rb = hw = hb = None
+    if "ret" in mode:       # retentions near one, so that a prefix reaches across many tiles
+        ret, rb = (6.0 + r.standard_normal((B, L, H))).astype(np.float32), np.linspace(3.0, 0.0, F).astype(np.float32)
+    if "hconv" in mode:
+        hw, hb = r.standard_normal((2, H, 3)).astype(np.float32), r.standard_normal((2, H)).astype(np.float32)
+    cfg = O.Cfg(B, L, H, F, conv_k=Kc, gate_tau=tau, ret_mode=0 if ret is None else 1)
+    kw = {} if ret is None else dict(ret=ret, ret_bias=rb)
+    ora = O.phase_fwd(cfg, d["mag"], d["ang"], None if ret is not None else d["gamma"], d["theta"], conv_w=d["conv_w"],
+                      conv_b=d["conv_b"], scan_in=scan, tail_in=tail, want_gate=False, **kw)
+    z = (ora["z_re"], ora["z_im"])
+    if hw is not None:
+        z = O.harmonic_conv(z[0], z[1], H, F, hw, hb)
+    out = G.run_fwd(d, B, L, H, F, conv_k=Kc, gate_tau=tau, state_in=G.pack_state(scan, tail), want_mask=False, ret=ret,
+                    ret_bias=rb, hconv_w=hw, hconv_b=hb)
+    assert G.rel_err(out["z_re"], z[0]) <= TOL and G.rel_err(out["z_im"], z[1]) <= TOL
+    assert G.rel_err(G.unpack_state(out["state_out"], B, J, Kc)[0], ora["scan_out"]) <= TOL
+
+
 @pytest.mark.parametrize("Kc", [1, 2, 3, 4])
 @pytest.mark.parametrize("L,Cc,off", [(1, 4, 0), (2, 260, 0), (9, 1028, 0), (64, 256, 0), (9, 1028, 1), (0, 8, 0)])
 def test_standalone_syntax_conv_wide_and_narrow_accesses(Kc, L, Cc, off):
