@@ -666,7 +666,7 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     const int TT = short_tiles ? FwdShort::TILE_T : (head ? FwdHead::TILE_T : FwdGeom::TILE_T);
     a.short_tiles = short_tiles ? 1 : 0;
     a.H = d->H; a.F = d->F;
-    a.gpb = d->F >= JB ? 1 : JB / d->F;
+    a.gpb = d->F >= JB ? (d->F % JB ? 2 : 1) : JB / d->F;
     a.hcG = hconv_w && d->F > JB ? d->F / JB : 1;
     if (d->ret_mode == 1) {
         a.ret = ret;

@@ -341,8 +341,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
             }
             wait_vm<0>();
         }
-        // (my lane's valve group in the block is lane / F when heads are narrower than the block)
-        const int vbase = (VALVE || RET) ? (a.F >= JB ? 0 : (lv * V) / a.F) * TILE_T + seg * NSTEP : 0;
+        // (my lane's logits: a block holds whole heads, a part of one, or, where a head ends inside it, the end of one and
+        // the start of the next)
+        const int vgroup = a.F < JB ? (lv * V) / a.F : (JB > 32 && !HC && lv >= a.F - (T.lb * JB) % a.F ? 1 : 0);
+        const int vbase = (VALVE || RET) ? vgroup * TILE_T + seg * NSTEP : 0;
         // The mode switches are uniform over the launch; each combination gets its own straight-line
         // copy of the loop, so that the tokens' dependent chains (exp -> rcp -> sin/cos) interleave.
         auto front_end = [&](auto amp_c, auto small_c, auto mask_c) {

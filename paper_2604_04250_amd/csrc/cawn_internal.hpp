@@ -179,7 +179,8 @@ struct FwdArgs {
     unsigned long long *dbg;     // -DCAWN_TIMING builds only
     // (kept behind everything else: the kernels that do not use them fetch none of this)
     // gate_mode 1 (per-head input valve, Sec. 3.3): logits [B][L][H]; a lane block of JB lanes
-    // holds gpb = max(1, JB / F) heads (groups); the valve is open when the logit >= valve_thr
+    // touches at most gpb heads (groups): JB / F whole ones, a part of one, or two where heads of more than JB lanes
+    // end inside a block (F an odd multiple of 32, 64-lane blocks); the valve is open when the logit >= valve_thr
     const float *valve;          // null: gate_mode 0
     int H, F, gpb;
     float valve_thr;
@@ -455,8 +456,8 @@ __device__ __forceinline__ void stage_rows(float *sU, const float *mag, const fl
     }
 }
 // Stage the valve logits of one tile (gate_mode 1): entry (group, token) of the tile lands at
-// sV[group * TT + token]; the lane block's groups are the heads (gpb = 32 / F of them) or the
-// one head its 32 lanes lie in.  4 bytes per lane per load; called by one wave.
+// sV[group * TT + token]; the lane block's groups are the gpb heads from the one its first lane lies in on.
+// 4 bytes per lane per load; called by one wave.
 template <int TT, int JB>
 __device__ __forceinline__ void stage_valve(float *sV, const float *valve, int b, int tile_t0, int lb, int L, int H,
                                             int F, int gpb, int lane)

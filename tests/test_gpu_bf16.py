@@ -120,6 +120,27 @@ def test_bf16_forward_chunked_state_and_concat_layout():
     assert G.rel_err(G.unpack_state(blob, B, J, Kc)[0], ora["scan_out"]) <= TOL
 
 
+# chains of 66 short tiles, more than short tiles are taken for: 64-lane rows.  Heads of a quarter, half, all and two of a
+# row; of 96, 160 and 224, which end in the middle of one; a last row that is half empty
+@pytest.mark.parametrize("H,F", [(8, 8), (5, 16), (3, 32), (3, 64), (3, 96), (4, 96), (2, 128), (2, 160), (2, 224)])
+@pytest.mark.parametrize("valve,ret", [(False, False), (True, False), (False, True), (True, True)])
+def test_bf16_forward_long_tiles(H, F, valve, ret):
+    if valve and ret and F < 16:
+        pytest.skip("heads of 8 with both logits are refused")
+    B, L, Kc = 1, 4200, 3
+    J = H * F
+    d = _inputs(B, L, H, F, Kc, 8300 + H * 131 + F + 2 * valve + ret)
+    r = np.random.Generator(np.random.PCG64(83))
+    state = (r.standard_normal((B, 2, J)).astype(np.float32), r.standard_normal((B, Kc - 1, 2, J)).astype(np.float32))
+    out, ora = _check_fwd(B, L, H, F, Kc, d, amp_mode=1 if valve else 0, valve=valve, ret=ret, tau=0.25, state=state,
+                          want_ckpt=True)
+    # a checkpoint is the unclamped state before every eighth token, and no state here reaches the clamp
+    z = np.stack([ora["z_re"], ora["z_im"]], 2)
+    assert np.abs(z).max() < 100.0
+    before = np.concatenate([state[0][:, None].astype(np.float64), z[:, 7:L - 1:8]], 1)
+    assert _gpu().rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
+
+
 def test_bf16_odd_lane_count_is_refused():
     import torch
     from paper_2604_04250_amd import binding as K
