@@ -274,7 +274,8 @@ static void launch_conv(bool vec4, dim3 grid, hipStream_t s, const float *x, con
 // and are added in index order -- the association is fixed, so results are bitwise repeatable.
 constexpr int RG = 32;       // groups of a reduction block
 // the sum of group g's chains of one (lane block, row, lane): `acc` continues
-__device__ __forceinline__ float sum_chains(const float *__restrict__ src, size_t step, int chains, int g, float acc)
+template <class A>
+__device__ __forceinline__ A sum_chains(const float *__restrict__ src, size_t step, int chains, int g, A acc)
 {
     // (eight independent reads in flight per thread; the sum keeps its order)
     int c = g;
@@ -283,9 +284,9 @@ __device__ __forceinline__ float sum_chains(const float *__restrict__ src, size_
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(c + u * RG) * step];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
+        for (int u = 0; u < 8; ++u) acc += (A)v[u];
     }
-    for (; c < chains; c += RG) acc += src[(size_t)c * step];
+    for (; c < chains; c += RG) acc += (A)src[(size_t)c * step];
     return acc;
 }
 __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, float *__restrict__ out0,
@@ -325,21 +326,24 @@ __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, 
 // the head's lanes of its block), the groups meet in LDS in index order and the 32 lane sums in a butterfly of lane
 // exchanges (both partners add the same two values): the association is fixed, the result repeatable.  (As a kernel of
 // its own behind per-lane sums in memory this cost 4.0 - 4.8 us a call.)
+// One output sums up to 8 times the terms of a lane's, and one thread those of all of a head's blocks: in fp32 that added
+// to the error (F = 64, L = 8192: 3.7e-7 -> 4.7e-7 of the taps' gradients).  The sums are taken in fp64 and rounded once;
+// the reads bound the loop either way.
 __device__ __forceinline__ void reduce_hconv(const float *__restrict__ part, float *__restrict__ dw, float *__restrict__ db,
                                              int rows, int hc_row0, int H, int F, int JB, int nLB, int chains,
-                                             int accumulate, int q, int h, float (*sm)[33])
+                                             int accumulate, int q, int h, double (*sm)[33])
 {
     const int lane = threadIdx.x % 32, g = threadIdx.x / 32;
     const int l0 = (h * F) % 32;
     const bool mine = F >= 32 || (lane >= l0 && lane < l0 + F);
-    float acc = 0.0f;
+    double acc = 0.0;
     if (mine)
         for (int k = 0; k < (F >= 32 ? F / 32 : 1); ++k)
             acc = sum_chains(part + ((size_t)((h * F) / 32 + k) * rows + hc_row0 + q) * JB + lane, (size_t)nLB * rows * JB, chains, g, acc);
     sm[g][lane] = acc;
     __syncthreads();
     if (g != 0) return;
-    float s = 0.0f;
+    double s = 0.0;
 #pragma unroll
     for (int k = 0; k < RG; ++k) s += sm[k][lane];
 #pragma unroll
@@ -347,7 +351,7 @@ __device__ __forceinline__ void reduce_hconv(const float *__restrict__ part, flo
     if (lane == 0) {
         float *dst = q < 6 ? (dw ? dw + ((size_t)(q / 3) * H + h) * 3 + q % 3 : nullptr)
                            : (db ? db + (size_t)(q - 6) * H + h : nullptr);
-        if (dst) *dst = accumulate ? *dst + s : s;
+        if (dst) *dst = accumulate ? (float)((double)*dst + s) : (float)s;
     }
 }
 
@@ -365,16 +369,16 @@ struct EpilogueArgs {
 __global__ __launch_bounds__(1024) void bwd_epilogue_kernel(const EpilogueArgs p)
 {
     static_assert(BwdLPR == 32, "reduction blocks take a lane block's 32 lanes");
-    __shared__ float sm[RG][33];
+    __shared__ union { float f[RG][33]; double d[RG][33]; } sm;
     const int nA = p.nbx * p.rows_lane;
     if ((int)blockIdx.x < nA) {
         reduce_partials(p.part, p.out0, p.out1, p.out2, p.out3, p.rows, p.conv_k, p.J, p.JB, p.nLB,
-                        p.chains, p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx, sm);
+                        p.chains, p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx, sm.f);
         return;
     }
     if ((int)blockIdx.x < nA + p.nhc) {
         const int e = (int)blockIdx.x - nA;
-        reduce_hconv(p.part, p.dhw, p.dhb, p.rows, p.rows - HC_PART_ROWS, p.H, p.F, p.JB, p.nLB, p.chains, p.accumulate, e / p.H, e % p.H, sm);
+        reduce_hconv(p.part, p.dhw, p.dhb, p.rows, p.rows - HC_PART_ROWS, p.H, p.F, p.JB, p.nLB, p.chains, p.accumulate, e / p.H, e % p.H, sm.d);
         return;
     }
     const int bid = (int)blockIdx.x - nA - p.nhc, set = bid / p.nb, blk = bid % p.nb;

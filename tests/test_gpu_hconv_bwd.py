@@ -269,3 +269,19 @@ def test_hconv_backward_with_valve_and_retention_bf16(valve, ret, H, F, Kc):
     for k in ("c_re", "c_im", "dmag", "dang"):
         assert G.bf16_err(out[k], ora[k]) <= 1.0, k
     _compare(out, ora, Kc, names=[n for n in _names_modes(Kc, valve, ret) if n not in ("c_re", "c_im", "dmag", "dang")])
+
+
+@pytest.mark.parametrize("H,F", [(3, 16), (2, 32), (2, 64), (1, 256)])
+def test_hconv_bias_gradients_are_the_rounded_sum(H, F):
+    """The bias gradient is a plain sum of the upstream gradients.  With whole numbers of up to ten bits a tile's own
+    sums (128 tokens) are exact, so only their reduction over tiles and lanes can round: it must round once."""
+    B, L = 4, 4000
+    d = _inputs(B, L, H, F, 0, 7200 + F)
+    r = np.random.Generator(np.random.PCG64(7201))
+    for k in ("dc_re", "dc_im"):
+        d[k] = r.integers(1, 1024, (B, L, H * F)).astype(np.float32)
+    out = _gpu().run_hconv_fwd_bwd(d, B, L, H, F)
+    for p, k in enumerate(("dc_re", "dc_im")):
+        want = d[k].astype(np.int64).reshape(B, L, H, F).sum((0, 1, 3))
+        assert want.min() > 1 << 24
+        assert np.array_equal(out["dhconv_b"].reshape(2, H)[p], want.astype(np.float32))
