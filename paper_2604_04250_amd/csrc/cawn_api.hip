@@ -366,7 +366,7 @@ struct EpilogueArgs {
     float *lout[2];
     int nsets, nb, B, L, H, F, G;
 };
-__global__ __launch_bounds__(1024) void bwd_epilogue_kernel(const EpilogueArgs p)
+__global__ __launch_bounds__(1024, 8) void bwd_epilogue_kernel(const EpilogueArgs p)
 {
     static_assert(BwdLPR == 32, "reduction blocks take a lane block's 32 lanes");
     __shared__ union { float f[RG][33]; double d[RG][33]; } sm;

@@ -225,6 +225,8 @@ def test_kernels_do_not_spill_and_keep_their_occupancy():
                 elif key.startswith("Occupancy"):
                     want = 4 if "bwd_kernel" in name else 2
                     assert int(val) >= want, (name, line)
+            elif name and "bwd_epilogue_kernel" in name and key.startswith("Occupancy"):
+                assert int(val) >= 8, (name, line)       # two blocks of 1024 threads per compute unit
     assert seen >= 35       # 5 tap counts x (forward, backward with/without parameters) x gate modes, short-call forward
 
 
