@@ -22,6 +22,7 @@
 // constants of the NEXT tile are fetched while the current tile is in its communication phase,
 // whose memory round trips would otherwise leave the SIMDs idle.
 #pragma once
+#include <atomic>
 #include <type_traits>
 
 #include "cawn_internal.hpp"
@@ -134,7 +135,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // them in order (every other group from the top block down): the lane of a block that borders the
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
-template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
 __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
     constexpr int V = 1;                           // lanes per thread
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     constexpr int MW = JB / 32;                    // gate-mask words of a row
     static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
-    constexpr bool EACH = JB == 32 && !G::SHORT;   // may pass a prefix on per tile (see make_queues)
+    static_assert(!EACH || (JB == 32 && !G::SHORT), "a prefix per tile: long 32-lane tiles (see make_queues)");
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
 
     if (tid == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // both round trips at once
-        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x, HC ? (uint32_t)a.hcG : 1u);
+        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, HC ? (uint32_t)a.hcG : 1u);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
         const uint32_t hcG = HC ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
             if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
-            else if (a.tq.one_each) ticket_ahead = NO_TICKET;
+            else if (!EACH && a.tq.one_each) ticket_ahead = NO_TICKET;
             else ticket_ahead = next_ticket_of(a.hdr, hcG);
         }
 
@@ -529,16 +530,16 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
             for (int v = 0; v < V; ++v) cr[v] = ci[v] = 0.f;
             // (what this tile publishes: its aggregate, the chain's first tile its prefix instead; the last of a
             // group also its prefix; the chain's last tile nothing)
-            const int group = (int)a.tq.group;
-            const bool feeds = tt + 1 < a.nT, ends_group = (tt & (group - 1)) == group - 1;
-            const bool each = EACH && group == 1;       // a prefix per tile: the first tile's stands with the others
+            // (EACH: a prefix per tile, the first tile's with the others)
+            const int group = EACH ? 1 : (int)a.tq.group;
+            const bool feeds = tt + 1 < a.nT, ends_group = EACH || (tt & (group - 1)) == group - 1;
             if (tt == 0) {
                 if (a.state_in && active) {
                     Vec<V>::ld(cr, a.state_in + ((size_t)b * 2 + 0) * a.J + j0);
                     Vec<V>::ld(ci, a.state_in + ((size_t)b * 2 + 1) * a.J + j0);
                 }
             } else {
-                if (feeds && (!ends_group || each)) {
+                if (feeds && (EACH || !ends_group)) {
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
                         tagged_store(a.agg + slot + v, Tr[v], tag);
@@ -549,7 +550,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                 // aggregates read per round trip: what the register budget leaves
                 constexpr int NB = G::SHORT ? (RET ? (HC ? 6 : 4) : (HC ? 8 : 6)) : (HC && RET ? 2 : (BF && !RET && !HC ? 4 : 7));
                 bool got;
-                if (each)
+                if constexpr (EACH)
                     got = look_back<V, false, LPR, 2, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv, hr, hi,
                                                            qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
                 else
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                 sCarry[1][lv * V + v] = ci[v];
             }
             if (feeds && (tt == 0 || ends_group)) {   // the tile's inclusive prefix for the chain
-                tagged_t *pre = tt == 0 && !each ? a.agg : a.pre;
+                tagged_t *pre = tt == 0 && !EACH ? a.agg : a.pre;
                 float P_r[V], P_i[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v)
@@ -876,36 +877,54 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     // ---- the workgroup that leaves last resets the tickets and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
     if (tid == 0) {
-        sLast = leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x) ? 1u : 0u;
+        sLast = (EACH ? leave_grid(a.hdr, gridDim.x) : leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     }
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
 }
 
-template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
-static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
+// Workgroups of a kernel that fit on the chip (asked once per kernel); 0: the runtime would not say
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
+static long long fwd_resident()
 {
-    // persistent grid: what fits on the chip (asked once per kernel)
-    static int per_cu = 0, cus = 0;
-    if (per_cu == 0) {
+    static std::atomic<long long> known{0};
+    if (known.load(std::memory_order_relaxed) == 0) {
         int dev = 0, n = 0;
         hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<G, KC, VALVE, RET, BF, HC>, G::NT, 0) != hipSuccess)
-            return hipErrorUnknown;
-        cus = prop.multiProcessorCount;
-        per_cu = n > 0 ? n : 1;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<G, KC, VALVE, RET, BF, HC, EACH>, G::NT, 0) != hipSuccess)
+            return 0;
+        known.store((long long)(n > 0 ? n : 1) * prop.multiProcessorCount, std::memory_order_relaxed);
     }
-    const long long resident = (long long)per_cu * cus;
-    const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
-    const long long jobs = (long long)units * a.nT;
-    const long long wgs = jobs < resident ? jobs : resident;
+    return known.load(std::memory_order_relaxed);
+}
+
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
+static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long jobs, hipStream_t s)
+{
+    const long long resident = fwd_resident<G, KC, VALVE, RET, BF, HC, EACH>();
+    if (resident <= 0) return hipErrorUnknown;
+    const long long wgs = jobs < resident ? jobs : resident;       // persistent grid: what fits on the chip
     FwdArgs b = a;
     b.tq = make_queues(units, (uint32_t)a.nT, wgs);
     if (G::SHORT) b.tq.group = 64;      // (one group: no prefixes)
-    else if (G::JB == 32 && !b.tq.one_each) b.tq.group = 1;
-    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
+    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC, EACH>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
     return hipGetLastError();
+}
+
+// The carry scheme of a call: a prefix per tile for 32-lane rows with more tiles than workgroups (EACH), a prefix per
+// group of tiles otherwise (see make_queues).  A kernel each, and EACH knows that its workgroups take several tiles from
+// one counter: with both schemes in one kernel, and every tile asking whether there is a next one to draw, such calls
+// were 1 - 2.5 % slower (B16 L1000 J768 53.9 us against 52.4, B6 L3001 J768 57.7 against 57.0).
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
+static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
+{
+    const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
+    const long long jobs = (long long)units * a.nT;
+    if constexpr (G::JB == 32 && !G::SHORT) {
+        if (jobs > fwd_resident<G, KC, VALVE, RET, BF, HC, true>()) return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs, s);
+    }
+    return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
 }
 
 // The tile shape of a call (the host computed nT and nLB from the same rule): 64-lane rows with the harmonic

@@ -513,16 +513,20 @@ __device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h, uint32_t G)
 {
     return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A workgroup leaves: true for the last one.  Two levels for 96 and more workgroups that all leave at about the same time
-// (a second round trip, 0.4 us, for the last of them; 96 counts on one address take 1.1 us); those of larger calls are
-// spread by their draws.
+// A workgroup leaves: true for the last one of the grid
+__device__ __forceinline__ bool leave_grid(WsHeader *h, uint32_t grid)
+{
+    return __hip_atomic_fetch_add(&h->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == grid;
+}
+// ... in two levels for 96 and more workgroups that all leave at about the same time (a second round trip, 0.4 us, for the
+// last of them; 96 counts on one address take 1.1 us); those of larger calls are spread by their draws.
 __device__ __forceinline__ bool leave_call(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t grid)
 {
-    auto add = [&](uint32_t *p) { return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u; };
-    if (grid < 96 || !t.one_each) return add(&h->done) == grid;
+    if (grid < 96 || !t.one_each) return leave_grid(h, grid);
     const uint32_t s = wg % MAX_QUEUES;
-    if (add(hdr_word(h, done_word(s))) != (grid - s + MAX_QUEUES - 1) / MAX_QUEUES) return false;
-    return add(&h->done) == (uint32_t)MAX_QUEUES;
+    const uint32_t n = __hip_atomic_fetch_add(hdr_word(h, done_word(s)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    if (n != (grid - s + MAX_QUEUES - 1) / MAX_QUEUES) return false;
+    return leave_grid(h, (uint32_t)MAX_QUEUES);
 }
 
 // End of a call, run by thread `tid` of the `nthreads` of the workgroup that left last: tickets and
