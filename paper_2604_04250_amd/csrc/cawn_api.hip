@@ -584,23 +584,35 @@ static float valve_threshold_of(float eps)
 }
 
 // Short tiles (64 tokens, 8 per thread) for calls whose 256-token tiles would leave much of the chip idle: as long as
-// every short tile has a workgroup of its own on the chip (4 per compute unit; 3 with the per-token retentions, 1 of
-// twice the threads with the harmonic convolution), and while reading all of a chain's aggregates costs less than
-// passing prefixes on.  Beyond the first limit they lose at once (a workgroup's second tile, and all draws on one
-// counter), beyond the second slowly.  Long against short tiles, us a call: J768 conv 4, L512 14.6 / 10.2, L2048 (768 short
-// tiles) 16.4 / 14.8, 8 x L300 (960) 17.1 / 13.7, L4096 (1536) 19.5 / 44.6; J120 L4096 (64 in a chain) 16.8 / 16.3; bf16
-// J256 L4096 17.5 / 17.0; paper's layer J256, L333 16.9 / 10.2, 7 x L512 (448) 18.1 / 12.8, L4096 (64 in a chain) 20.4 /
-// 20.7, 7 x L1024 (896) 18.9 / 29.8; with the harmonic convolution L1024 19.6 / 13.6, L4096 (256) 23.4 / 22.3, 7 x L1024
-// (448) 20.7 / 21.9.
+// every short tile has a workgroup of its own on the chip (4 per compute unit, 1 of twice the threads with the harmonic
+// convolution; beyond that a workgroup's second tile, and all draws on one counter, double a call's time), and while a tile's
+// way to its carry is not too long.  A short tile reads the aggregates of all tiles before it in its chain, which costs
+// with the chain's length (0.15 us a tile, 0.24 with the product of the retentions), and the tiles of a call cost 5 ns each
+// where they start and leave; long tiles cost nearly the same whatever the call.  So the line between them is where
+//     (tiles in a chain) x per + (tiles)  =  most,
+// set from 742 calls without the harmonic convolution (J = 64, 256 and 768, 5 - 64 tiles a chain, 32 - 1024 tiles).  With
+// retentions it lies where the two are equally fast.  With a constant retention it lies further on, where short tiles would
+// be slower than long tiles that pass a prefix on per tile: up to there they cost up to 20 % more than long tiles with a prefix
+// per group, and their error is half as large (runs of 8 instead of 32 tokens between exact powers of lambda: 1.8e-7 against
+// 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
+// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 13.3 / 8.9 (64), J256
+// L4096 15.3 / 17.9 (512), J256 4 x L2048 14.9 / 18.4 (1024), J768 L2048 14.8 / 15.9 (768), J768 3 x L768 14.5 / 14.5 (864); paper's
+// layer, J256: 7 x L1024 17.1 / 16.8 (896), L3072 17.9 / 19.7 (384), in bf16 16.1 / 16.7 and 18.2 / 19.3; J256 L2048 with the
+// valve in bf16 15.8 / 12.8 (256).  With the harmonic convolution, J256: L1024 15.5 / 11.2 (64), L4096 18.1 / 17.8 (256), paper's
+// layer L4096 21.7 / 22.3.
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
-static bool use_short_tiles(const cawn_desc *d, const WsLayout &w, int JB, size_t workspace_bytes)
+static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, int JB, size_t workspace_bytes)
 {
     const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
     const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
-    if (nT > (ret && !hc ? 48 : 64) || tiles > 256u * (hc ? 1 : 4)) return false;
+    if (nT > (hc && ret ? 60 : 64) || tiles > 256u * (hc ? 1 : 4)) return false;
+    if (!hc) {
+        const size_t per = ret ? (bf16 ? 16 : 32) : 24, most = ret ? (bf16 ? 1056 : 1536) : 1608;
+        if (nT * per + tiles > most) return false;
+    }
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
 
@@ -664,7 +676,7 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
         return CAWN_EUNSUPPORTED;
     }
     // the tile: 32-lane rows, with the harmonic convolution 64-lane rows (the same number of token-lanes)
-    const bool short_tiles = use_short_tiles(d, w, hconv_w ? FwdHead::JB : FwdGeom::JB, workspace_bytes);
+    const bool short_tiles = use_short_tiles(d, bf16, w, hconv_w ? FwdHead::JB : FwdGeom::JB, workspace_bytes);
     const bool head = hconv_w || (bf16 && !short_tiles);
     const int JB = head ? FwdHead::JB : FwdGeom::JB;
     const int TT = short_tiles ? FwdShort::TILE_T : (head ? FwdHead::TILE_T : FwdGeom::TILE_T);

@@ -141,6 +141,12 @@ def test_bf16_forward_long_tiles(H, F, valve, ret):
     assert _gpu().rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
 
 
+# the longest chains of a single lane block that go on 64-token tiles, and one token more
+@pytest.mark.parametrize("ret,L", [(False, 4096), (False, 4097), (True, 3968), (True, 3969)])
+def test_bf16_last_short_and_first_long_tiles(ret, L):
+    _check_fwd(1, L, 1, 32, 3, _inputs(1, L, 1, 32, 3, 8400 + L), ret=ret, tau=0.25)
+
+
 def test_bf16_odd_lane_count_is_refused():
     import torch
     from paper_2604_04250_amd import binding as K

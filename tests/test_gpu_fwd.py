@@ -296,8 +296,8 @@ def test_standalone_syntax_conv():
                                         (4, 2048, 1, 65, 1), (33, 500, 1, 32, 2), (1, 4096, 1, 64, 3), (1, 4097, 1, 64, 3),
                                         (32, 2048, 1, 32, 2), (33, 2048, 1, 32, 2)])
 def test_short_tiles_at_their_edges(B, L, H, F, Kc):
-    """Calls on 64-token tiles: one tile, whole tiles, one token more, the longest chain (64 tiles), the most tiles
-    (1024), and the next size of each, which the long tiles take; state in place, checkpoints and the gate mask, against the oracle."""
+    """Calls on 64-token tiles: one tile, whole tiles, one token more, and calls of many tiles and of long chains (64 tiles), on
+    64-token or on long tiles; state in place, checkpoints and the gate mask, against the oracle."""
     G = _gpu()
     J, tau = H * F, 0.1
     d = _inputs(B, L, H, F, Kc, 1700 + L + B)
@@ -319,14 +319,11 @@ def test_short_tiles_at_their_edges(B, L, H, F, Kc):
         assert np.array_equal(t_o, np.concatenate([tail, u], 1)[:, -(Kc - 1):])
 
 
-@pytest.mark.parametrize("mode", ["plain", "ret", "hconv", "hconv_ret"])
-@pytest.mark.parametrize("B,L,H,F", [(1, 4352, 1, 64), (1, 4353, 1, 64), (1, 6145, 1, 64), (3, 4097, 3, 64), (2, 4352, 1, 128)])
-def test_prefixes_per_group_of_tiles(B, L, H, F, mode):
-    """Chains longer than a group (8 tiles, 16 with few chains): ends of groups, one token into the next group, several
-    groups, state in and out, with a product per tile (retention) and without; against the oracle."""
+def _check_modes(mode, B, L, H, F, seed):
+    """A call that continues a sequence, in one of four modes, against the oracle: outputs and carried state."""
     G = _gpu()
     J, Kc, tau = H * F, 3, 0.1
-    d = _inputs(B, L, H, F, Kc, 1800 + L + B)
+    d = _inputs(B, L, H, F, Kc, seed)
     r = np.random.Generator(np.random.PCG64(1801))
     scan = r.standard_normal((B, 2, J)).astype(np.float32)
     tail = r.standard_normal((B, Kc - 1, 2, J)).astype(np.float32)
@@ -346,6 +343,22 @@ def test_prefixes_per_group_of_tiles(B, L, H, F, mode):
                     ret_bias=rb, hconv_w=hw, hconv_b=hb)
     assert G.rel_err(out["z_re"], z[0]) <= TOL and G.rel_err(out["z_im"], z[1]) <= TOL
     assert G.rel_err(G.unpack_state(out["state_out"], B, J, Kc)[0], ora["scan_out"]) <= TOL
+
+
+# the last calls on 64-token tiles (most tiles, longest chain of a single lane block) and the first on long ones
+@pytest.mark.parametrize("mode,B,L", [("plain", 128, 512), ("plain", 129, 512), ("plain", 1, 4096), ("plain", 1, 4097), ("plain", 2, 3904), ("plain", 2, 3905),
+                                      ("ret", 1, 2944), ("ret", 1, 2945), ("hconv", 1, 4096), ("hconv", 1, 4097),
+                                      ("hconv_ret", 1, 3840), ("hconv_ret", 1, 3841)])
+def test_last_short_and_first_long_tiles(mode, B, L):
+    _check_modes(mode, B, L, 1, 32, 1900 + L)
+
+
+@pytest.mark.parametrize("mode", ["plain", "ret", "hconv", "hconv_ret"])
+@pytest.mark.parametrize("B,L,H,F", [(1, 4352, 1, 64), (1, 4353, 1, 64), (1, 6145, 1, 64), (3, 4097, 3, 64), (2, 4352, 1, 128)])
+def test_prefixes_per_group_of_tiles(B, L, H, F, mode):
+    """Chains longer than a group (8 tiles, 16 with few chains): ends of groups, one token into the next group, several
+    groups, state in and out, with a product per tile (retention) and without; against the oracle."""
+    _check_modes(mode, B, L, H, F, 1800 + L + B)
 
 
 @pytest.mark.parametrize("Kc", [1, 2, 3, 4])
