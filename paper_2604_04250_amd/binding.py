@@ -75,6 +75,7 @@ def lib() -> C.CDLL:
         L.cawn_set_spin_limit.restype = None
         L.cawn_theta_init.argtypes = [C.c_int32, C.c_int32, C.c_void_p]
         L.cawn_syntax_conv.argtypes = [C.POINTER(cawn_desc), C.c_int32] + [C.c_void_p] * 7
+        # (the wrappers below pass these calls to _cawn_call; programs that call lib() themselves need the types)
         L.cawn_phase_accumulate_fwd.argtypes = ([C.POINTER(cawn_desc)] + [C.c_void_p] * 13 +
                                                 [C.c_size_t, C.c_void_p])
         L.cawn_phase_accumulate_bwd.argtypes = ([C.POINTER(cawn_desc)] + [C.c_void_p] * 19 +
@@ -102,7 +103,7 @@ def lib() -> C.CDLL:
         except ImportError as e:
             raise RuntimeError("the marshalling module _cawn_call is missing: build it with __graft_entry__.build(); "
                                "there is no fallback path") from e
-        _cawn_call.set_stream(getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device), _raw_stream())
+        _cawn_call.setup(cawn_desc, getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device), _raw_stream())
         for n in EXPORTS:
             if n.startswith("cawn_phase_accumulate"):
                 _entry[n] = C.cast(getattr(L, n), C.c_void_p).value

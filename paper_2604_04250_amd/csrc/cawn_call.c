@@ -14,6 +14,7 @@
 
 static PyObject *s_data_ptr, *s_is_cuda, *s_nbytes, *s_cuda_stream;
 static PyObject *get_stream, *get_device;      /* raw handle of a device's current stream; the current device */
+static PyObject *desc_type;                    /* the binding's cawn_desc */
 
 /* device pointer of a tensor, or NULL for None; -1 with an exception set when it is neither */
 static int pointer(PyObject *t, void **out)
@@ -114,11 +115,14 @@ static PyObject *call(PyObject *self, PyObject *const *args, Py_ssize_t n)
         if (bf16 == -1 && PyErr_Occurred()) return NULL;
     }
     if (stream_of(args[n - 1], &st) < 0) return NULL;
+    const int is_desc = desc_type ? PyObject_IsInstance(args[2], desc_type) : 0;
+    if (is_desc < 0) return NULL;
+    if (!is_desc) return PyErr_Format(PyExc_TypeError, "call: not a cawn_desc");
     Py_buffer view;
     if (PyObject_GetBuffer(args[2], &view, PyBUF_SIMPLE) < 0) return NULL;
-    if (view.len != (Py_ssize_t)sizeof(cawn_desc)) {
+    if (view.len < (Py_ssize_t)sizeof(cawn_desc)) {      /* (a subclass may be longer) */
         PyBuffer_Release(&view);
-        return PyErr_Format(PyExc_TypeError, "call: not a cawn_desc");
+        return PyErr_Format(PyExc_TypeError, "call: cawn_desc has another layout than include/cawn.h");
     }
     const cawn_desc *d = (const cawn_desc *)view.buf;
     int r = 0, known = 1;
@@ -147,20 +151,22 @@ static PyObject *call(PyObject *self, PyObject *const *args, Py_ssize_t n)
     return PyLong_FromLong(r);
 }
 
-static PyObject *set_stream(PyObject *self, PyObject *args)
+static PyObject *setup(PyObject *self, PyObject *args)
 {
     (void)self;
-    PyObject *a, *b;
-    if (!PyArg_ParseTuple(args, "OO", &a, &b)) return NULL;
+    PyObject *d, *a, *b;
+    if (!PyArg_ParseTuple(args, "OOO", &d, &a, &b)) return NULL;
+    Py_INCREF(d);
     Py_INCREF(a);
     Py_INCREF(b);
+    Py_XSETREF(desc_type, d);
     Py_XSETREF(get_device, a);
     Py_XSETREF(get_stream, b);
     Py_RETURN_NONE;
 }
 
 static PyMethodDef methods[] = {{"call", (PyCFunction)(void (*)(void))call, METH_FASTCALL, "call an entry point of libcawn"},
-                                {"set_stream", set_stream, METH_VARARGS, "current device, current raw stream of a device"},
+                                {"setup", setup, METH_VARARGS, "descriptor type, current device, current raw stream of a device"},
                                 {NULL, NULL, 0, NULL}};
 static struct PyModuleDef module = {PyModuleDef_HEAD_INIT, "_cawn_call", NULL, -1, methods, NULL, NULL, NULL, NULL};
 

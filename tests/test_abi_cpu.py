@@ -123,6 +123,14 @@ def test_host_side_argument_checks_reject_before_any_launch():
     assert K.cawn_workspace_bytes(hc) > K.cawn_workspace_bytes(K.make_desc(2, 128, 2, 64))
 
 
+class _Foreign(C.Structure):
+    _fields_ = [("words", C.c_int32 * (C.sizeof(K.cawn_desc) // 4))]
+
+
+class _Longer(K.cawn_desc):
+    _fields_ = [("note", C.c_int64)]
+
+
 def test_marshalling_module_passes_calls_on_and_refuses_what_it_cannot_pass():
     """The C module behind the forward and backward wrappers: the library's own refusals come back as status codes for
     every wrapper (so the argument counts agree), host tensors and foreign descriptors raise."""
@@ -144,6 +152,10 @@ def test_marshalling_module_passes_calls_on_and_refuses_what_it_cannot_pass():
             f(d, *([torch.zeros(4)] * n), stream=0)
         with pytest.raises((TypeError, BufferError)):
             f(b"not a descriptor", *([None] * n), stream=0)
+        for foreign in (bytes(C.sizeof(K.cawn_desc)), _Foreign(), None):       # (as long as a descriptor)
+            with pytest.raises(TypeError, match="cawn_desc"):
+                f(foreign, *([None] * n), stream=0)
+        assert f(_Longer(-1, 1, 1, 1), *([None] * n), stream=0) == K.CAWN_EINVAL, name
 
 
 def test_header_is_plain_c_and_links(tmp_path):
