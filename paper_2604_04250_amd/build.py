@@ -90,7 +90,8 @@ def build(verbose: bool = False, defines=(), out: str = OUT, objdir: str = CSRC)
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
-    build_call()
+    if out == OUT:              # (a variant beside the library leaves the binding's module alone)
+        build_call()
     return out
 
 

@@ -158,6 +158,26 @@ def test_marshalling_module_passes_calls_on_and_refuses_what_it_cannot_pass():
         assert f(_Longer(-1, 1, 1, 1), *([None] * n), stream=0) == K.CAWN_EINVAL, name
 
 
+def test_building_a_variant_leaves_the_library_in_the_tree_alone(tmp_path, monkeypatch):
+    """build() with another output (a geometry sweep) writes no file of the package: neither the library nor the
+    marshalling module.  (Commands are recorded, not run.)"""
+    import subprocess
+    from types import SimpleNamespace
+    from paper_2604_04250_amd import build as BLD
+
+    def record(cmd, *a, **k):
+        outs.append(cmd[cmd.index("-o") + 1])
+        return SimpleNamespace(returncode=0, stderr="")
+
+    for out, objdir, mine in ((str(tmp_path / "v.so"), str(tmp_path), 0), (BLD.OUT, str(tmp_path), 2)):
+        outs = []
+        monkeypatch.setattr(subprocess, "run", record)
+        monkeypatch.setattr(subprocess, "check_call", record)
+        BLD.build(out=out, objdir=objdir)
+        assert len([o for o in outs if o.startswith(BLD.HERE)]) == mine, outs
+        assert out in outs
+
+
 def test_header_is_plain_c_and_links(tmp_path):
     """A C99 translation unit that includes the header, fills a descriptor and calls the size
     helpers compiles without warnings and links against the shared library (no compute call)."""
