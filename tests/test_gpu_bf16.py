@@ -76,7 +76,7 @@ def test_bf16_helpers_round_to_nearest_even():
 @pytest.mark.parametrize("H,F", [(3, 64), (2, 32), (4, 16), (1, 128), (5, 32)])
 @pytest.mark.parametrize("Kc", [0, 4])
 def test_bf16_forward_head_widths(H, F, Kc):
-    B, L = 2, 700                      # three forward tiles, ragged tail
+    B, L = 2, 700                      # eleven 64-token tiles, ragged tail
     d = _inputs(B, L, H, F, Kc, 7700 + H * 131 + F + Kc)
     out, ora = _check_fwd(B, L, H, F, Kc, d, tau=0.25)
     # the outputs really are bf16 values
@@ -139,6 +139,13 @@ def test_bf16_forward_long_tiles(H, F, valve, ret):
     assert np.abs(z).max() < 100.0
     before = np.concatenate([state[0][:, None].astype(np.float64), z[:, 7:L - 1:8]], 1)
     assert _gpu().rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
+
+
+@pytest.mark.parametrize("valve,ret", [(False, False), (True, True)])
+def test_bf16_forward_long_tiles_several_a_workgroup(valve, ret):
+    """825 tiles of 128 tokens x 64 lanes: more than the chip holds workgroups (three a compute unit, two with retentions)."""
+    B, L, H, F, Kc = 5, 4200, 3, 96, 3
+    _check_fwd(B, L, H, F, Kc, _inputs(B, L, H, F, Kc, 8350 + valve), amp_mode=1 if valve else 0, valve=valve, ret=ret, tau=0.25)
 
 
 # the longest chains of a single lane block that go on 64-token tiles, and one token more

@@ -83,7 +83,7 @@ def _check(B, L, H, F, Kc, d, amp_mode=0, valve=False, ret=False, tau=0.0, state
                                  (3, 128), (1, 256), (12, 4)])
 @pytest.mark.parametrize("Kc", [0, 3, 4])
 def test_hconv_forward_head_widths(H, F, Kc):
-    B, L = 2, 700                      # three forward tiles, ragged tail
+    B, L = 2, 700                      # eleven 64-token tiles, ragged tail
     d = _inputs(B, L, H, F, Kc, 5100 + H * 131 + F + Kc)
     _check(B, L, H, F, Kc, d, tau=0.25)
 

@@ -1,0 +1,120 @@
+"""GPU parity of the forward on its long tiles, at sizes where these can go wrong, against the fp64 oracle through the C ABI:
+256 tokens x 32 lanes in fp32, 128 x 64 with the harmonic convolution (bf16 without it: test_gpu_bf16).  4200 tokens are
+more than the 64-token tiles are taken for.  "few" calls have a workgroup for every tile and pass prefixes on per group
+of tiles; "many" have more tiles than the chip holds workgroups (two per compute unit, 512) and, in fp32 on 32-lane rows,
+a kernel of their own that passes a prefix on per tile.  Bar as in the other parity tests; gate masks bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import cawn_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4
+L = 4200
+
+
+def _gpu():
+    import gpu_util
+    return gpu_util
+
+
+def _check(B, H, F, Kc, valve=False, ret=False, hconv=False, bf16=False, concat=False, seed=0, L=L, ws=None):
+    """A call that continues a sequence: outputs, gate mask, carried state and checkpoints."""
+    G = _gpu()
+    r = np.random.Generator(np.random.PCG64(9000 + seed + 131 * H + F + Kc))
+    J, kk = H * F, max(Kc, 1)
+    n = lambda *s: r.standard_normal(s, dtype=np.float32)
+    ex = G.bf16_exact if bf16 else (lambda x: x)
+    d = dict(mag=ex(n(B, L, J)), ang=ex(n(B, L, J)), gamma=r.uniform(0.9, 0.9999, J).astype(np.float32),
+             theta=r.uniform(0, np.pi, J).astype(np.float32), conv_w=n(2, J, kk) / np.float32(np.sqrt(kk)),
+             conv_b=0.1 * n(2, J))
+    scan, tail = n(B, 2, J), n(B, max(Kc - 1, 0), 2, J)
+    mode = dict(valve=-3.9 + 3.0 * n(B, L, H) if valve else None,
+                ret=1.0 + 1.5 * n(B, L, H) if ret else None, ret_bias=np.linspace(3.0, 0.0, F, dtype=np.float32) if ret else None)
+    hc = dict(hconv_w=n(2, H, 3), hconv_b=n(2, H)) if hconv else {}
+    tau, amp = (0.0, 1) if valve else (0.25, 0)
+    ora = O.phase_fwd(O.Cfg(B, L, H, F, conv_k=Kc, amp_mode=amp, gate_mode=int(valve), gate_tau=tau, ret_mode=int(ret)),
+                      d["mag"], d["ang"], None if ret else d["gamma"], d["theta"], conv_w=d["conv_w"], conv_b=d["conv_b"],
+                      scan_in=scan.astype(np.float64), tail_in=tail if Kc > 1 else None, **mode)
+    out = G.run_fwd(d, B, L, H, F, conv_k=Kc, amp_mode=amp, gate_tau=tau, want_ckpt=True, concat=concat, bf16=bf16, ws=ws,
+                    state_in=G.pack_state(scan, tail if Kc > 1 else None), **mode, **hc)
+    z = (ora["z_re"], ora["z_im"])
+    # (a checkpoint is the unclamped state before every eighth token; no state here reaches the clamp)
+    planes = np.stack(z, 2)
+    assert np.abs(planes).max() < 100.0
+    before = np.concatenate([scan[:, None].astype(np.float64), planes[:, 7:L - 1:8]], 1)
+    if hconv:
+        z = O.harmonic_conv(z[0], z[1], H, F, hc["hconv_w"], hc["hconv_b"])
+    for k, want in (("z_re", z[0]), ("z_im", z[1])):
+        e = G.bf16_err(out[k], want) if bf16 else G.rel_err(out[k], want) / TOL
+        assert e <= 1.0, (k, e)
+    assert np.array_equal(out["mask"], G.mask_from_gate(ora["gate"])), "gate mask differs"
+    assert G.rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
+    s, t = G.unpack_state(out["state_out"], B, J, Kc)
+    assert G.rel_err(s, ora["scan_out"]) <= TOL
+    if Kc > 1:
+        assert np.array_equal(t, ora["tail_out"])
+
+
+# lanes that are no multiple of 4 (staged word by word) or of 32 (a ragged last block, a last mask word); few and many tiles
+@pytest.mark.parametrize("B,H,F", [(1, 1, 65), (2, 5, 24), (11, 1, 66), (32, 1, 30)])
+@pytest.mark.parametrize("Kc", [0, 2, 4])
+def test_long_tiles_odd_lanes(B, H, F, Kc):
+    _check(B, H, F, Kc, concat=Kc == 2)
+
+
+# heads of a quarter, half, all and three of a 32-lane row; the last: 33 chains of 17 tiles
+@pytest.mark.parametrize("valve,ret", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("B,H,F", [(1, 5, 8), (1, 3, 16), (2, 1, 96), (11, 3, 32)])
+def test_long_tiles_valve_and_retention(B, H, F, valve, ret):
+    if valve and ret and F < 16:
+        pytest.skip("heads of 8 with both logits are refused")
+    _check(B, H, F, 3, valve=valve, ret=ret, seed=1)
+
+
+# heads inside a 64-lane row, of exactly one, of two and of four; the last two: more heads in flight than workgroups
+@pytest.mark.parametrize("B,H,F", [(1, 5, 4), (1, 3, 16), (1, 3, 32), (2, 3, 64), (1, 3, 128), (1, 3, 256), (8, 2, 64), (8, 2, 128)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_long_tiles_harmonic_convolution(B, H, F, bf16):
+    _check(B, H, F, 3, hconv=True, bf16=bf16, concat=F == 16, seed=2)
+
+
+@pytest.mark.parametrize("valve,ret", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("B,H,F", [(1, 3, 32), (1, 2, 64), (1, 2, 128), (1, 1, 256), (8, 2, 64)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_long_tiles_harmonic_convolution_with_logits(B, H, F, valve, ret, bf16):
+    _check(B, H, F, 3, valve=valve, ret=ret, hconv=True, bf16=bf16, seed=3)
+
+
+# 64-token tiles, long tiles with a workgroup each, rows of 64 lanes; every one with more than 96 workgroups, which are counted
+# out in two levels and draw from several counters
+@pytest.mark.parametrize("B,L,H,F,hconv", [(4, 512, 12, 64, False), (1, 4200, 6, 64, False), (1, 4200, 4, 64, True)])
+def test_a_call_that_gave_up_leaves_the_workspace_ready(B, L, H, F, hconv):
+    """With a spin limit of zero, set from the host, every wait that is not already over gives up: the call drains, and the
+    next one on the same workspace is right (tickets, counts and epoch were reset)."""
+    G = _gpu()
+    from paper_2604_04250_amd import binding as K
+    import torch
+    J = H * F
+    d = K.make_desc(B, L, H, F, gate_tau=0.25, hconv_k=3 if hconv else 0)
+    ws = torch.empty((K.cawn_workspace_bytes(K.make_desc(B, L, H, F, conv_k=3, hconv_k=d.hconv_k)) + 3) // 4,
+                     dtype=torch.int32, device=G.DEV)
+    K.check(K.cawn_workspace_init(ws))
+    x, z = torch.randn((2, B, L, J), device=G.DEV), torch.empty((2, B, L, J), device=G.DEV)
+    g, th, hw = torch.full((J,), 0.9, device=G.DEV), torch.ones(J, device=G.DEV), torch.ones((2, H, 3), device=G.DEV)
+    K.cawn_set_spin_limit(0)
+    try:
+        if hconv:
+            st = K.cawn_phase_accumulate_hconv_fwd(d, x[0], x[1], None, None, None, g, th, None, None, hw, None, None, z[0], z[1],
+                                                   None, None, None, ws)
+        else:
+            st = K.cawn_phase_accumulate_fwd(d, x[0], x[1], g, th, None, None, None, z[0], z[1], None, None, None, ws)
+        assert st == K.CAWN_OK
+        status = K.cawn_workspace_status(ws)
+    finally:
+        K.cawn_set_spin_limit(1 << 20)
+    assert status in (K.CAWN_OK, K.CAWN_ETIMEOUT)      # (a tile whose predecessors were all done never waits)
+    assert int(ws[:64].abs().sum()) == 0, "tickets"    # counters of queues 0 and 1
+    for again in range(2):
+        _check(B, H, F, 3, hconv=hconv, seed=4 + again, L=L, ws=ws)

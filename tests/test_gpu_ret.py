@@ -61,7 +61,7 @@ def _check_fwd(B, L, H, F, Kc, d, amp_mode=0, valve=False, tau=0.0, state=None, 
 @pytest.mark.parametrize("H,F", [(3, 64), (2, 32), (4, 16), (8, 8), (1, 128), (5, 32), (3, 16)])
 @pytest.mark.parametrize("Kc", [0, 4])
 def test_retention_forward_head_widths(H, F, Kc):
-    B, L = 2, 700                      # three forward tiles, ragged tail
+    B, L = 2, 700                      # eleven 64-token tiles, ragged tail
     d = _inputs(B, L, H, F, Kc, 3700 + H * 131 + F + Kc)
     _check_fwd(B, L, H, F, Kc, d, tau=0.25)
 
@@ -75,7 +75,7 @@ def test_retention_forward_with_the_valve(H, F, Kc):
 
 
 def test_retention_long_memory_crosses_many_tiles():
-    """Logits near +7 (retention 0.999): a token is still heard 2000 tokens, i.e. eight tiles, later, so
+    """Logits near +7 (retention 0.999): a token is still heard 2000 tokens, i.e. eight long or 31 short tiles, later, so
     the chained products and the look-back carry real weight."""
     B, L, H, F, Kc = 2, 3000, 2, 64, 4
     d = _inputs(B, L, H, F, Kc, 4100, ret_mean=5.0, ret_std=0.7)

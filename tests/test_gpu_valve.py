@@ -56,7 +56,7 @@ def _check_fwd(B, L, H, F, Kc, d, amp_mode=0, eps=0.001, state=None, **kw):
 @pytest.mark.parametrize("H,F", [(3, 64), (2, 32), (4, 16), (8, 8), (1, 128), (5, 32), (3, 16), (5, 8)])
 @pytest.mark.parametrize("Kc", [0, 4])
 def test_valve_forward_head_widths(H, F, Kc):
-    B, L = 2, 700                      # three forward tiles, ragged tail
+    B, L = 2, 700                      # eleven 64-token tiles, ragged tail
     d = _inputs(B, L, H, F, Kc, 700 + H * 131 + F + Kc)
     out, ora = _check_fwd(B, L, H, F, Kc, d)
     closed = 1.0 - ora["gate"].mean()
