@@ -24,6 +24,10 @@
  * enqueues its kernels on `stream` (a hipStream_t passed as void*; NULL = the default stream)
  * and returns.  Calls that share a workspace must be ordered on one stream.
  *
+ * A call repeated on the same inputs gives the same bits.  How its tokens are cut into tiles follows
+ * from its sizes and modes (B, L, H*F and the type among them), so a batch row computed in a call of
+ * another batch, or a sequence passed in other chunks, agrees to rounding and not bit for bit.
+ *
  * Return value: CAWN_OK (0) or a negative cawn_status.  Nothing is written to stdout/stderr.
  */
 #ifndef CAWN_H_

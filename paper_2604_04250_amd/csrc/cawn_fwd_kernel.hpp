@@ -4,11 +4,14 @@
 // Parallel structure.  The recurrence S[t] = p[t] + lambda S[t-1] has a per-lane constant
 // multiplier, so a run of n tokens acts on an incoming state as  S_out = E + lambda^n S_in,
 // with E the run's result from a zero state.  Three levels use that:
-//   thread    : V adjacent lanes x NSTEP consecutive tokens, serial, phasors kept in registers;
+//   thread    : one lane x NSTEP consecutive tokens, serial, phasors kept in registers;
 //   workgroup : NSEG such segments = one tile of TILE_T tokens; segment results meet in LDS;
 //   grid      : tiles of one (batch row, lane block) form a chain in time.  A tile publishes its
-//               aggregate E, then looks back over earlier tiles' aggregates until it meets one that
-//               already knows its inclusive prefix (decoupled look-back), and publishes its own.
+//               aggregate E and finds its carry in one of two ways: it folds the aggregates before it
+//               in its group of tiles into one link on the prefix of the group before (chain_carry; on
+//               short tiles the whole chain is one group, and no prefix is passed on), or, in calls on
+//               32-lane rows with more tiles than workgroups, it looks back over earlier tiles until it
+//               meets one that already knows its inclusive prefix, and publishes its own (look_back).
 // After the carry is known each thread replays its NSTEP tokens from the true incoming state,
 // clamps and stores.  Per token-lane HBM traffic: 8 bytes in, 8 bytes out.
 //
@@ -41,28 +44,6 @@ template <int V> struct Vec;
 template <> struct Vec<1> {
     static __device__ __forceinline__ void ld(float (&d)[1], const float *p) { d[0] = *p; }
     static __device__ __forceinline__ void st(float *p, const float (&s)[1]) { *p = s[0]; }
-};
-template <> struct Vec<2> {
-    static __device__ __forceinline__ void ld(float (&d)[2], const float *p)
-    {
-        float2 t = *reinterpret_cast<const float2 *>(p);
-        d[0] = t.x; d[1] = t.y;
-    }
-    static __device__ __forceinline__ void st(float *p, const float (&s)[2])
-    {
-        *reinterpret_cast<float2 *>(p) = make_float2(s[0], s[1]);
-    }
-};
-template <> struct Vec<4> {
-    static __device__ __forceinline__ void ld(float (&d)[4], const float *p)
-    {
-        float4 t = *reinterpret_cast<const float4 *>(p);
-        d[0] = t.x; d[1] = t.y; d[2] = t.z; d[3] = t.w;
-    }
-    static __device__ __forceinline__ void st(float *p, const float (&s)[4])
-    {
-        *reinterpret_cast<float4 *>(p) = make_float4(s[0], s[1], s[2], s[3]);
-    }
 };
 
 // Position of a ticket in the problem: tickets count (time tile, batch row, lane block), lane block fastest.
@@ -135,6 +116,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // them in order (every other group from the top block down): the lane of a block that borders the
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
+// EACH: a prefix per tile, for calls on 32-lane rows with more tiles than workgroups (launch_fwd_tile).
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
 __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
@@ -554,7 +536,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                     got = look_back<V, false, LPR, 2, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv, hr, hi,
                                                            qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
                 else
-                    got = chain_carry<JB, NB, false, RET, !G::SHORT && !(HC && RET)>(a.agg, a.aggp, a.pre, id, (uint32_t)a.B, tt, group, lv, hr[0], hi[0], qr[0],
+                    got = chain_carry<JB, NB, RET, !G::SHORT && !(HC && RET)>(a.agg, a.aggp, a.pre, id, (uint32_t)a.B, tt, group, lv, hr[0], hi[0], qr[0],
                                                      qi[0], a.spin_limit, tag, cr[0], ci[0]);
                 if (!got) {
                     // gave up: flag the workspace, keep going so that every wave exits
@@ -740,7 +722,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                                 // cache (streamed, they reach memory as two partial writes of one line: 309 against
                                 // 232 us on the training-step shape).  Rows stored by one tile alone are streamed.
                                 auto put = [&](char *q, float v) {
-                                    if constexpr (BF) {     // (half lines: default policy, see the plain replay below)
+                                    if constexpr (BF) {     // (default policy, see the plain replay below)
                                         *reinterpret_cast<uint16_t *>(q) = to_bf16(v);
                                     } else {
                                         if constexpr (MULTI) *reinterpret_cast<float *>(q) = v;
@@ -788,8 +770,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                     }
                     if (PLAIN || (active && t < a.L)) {
                         if constexpr (BF) {
-                            // (a row segment of 32 bf16 lanes is half a 128-byte line: the default policy lets the cache
-                            // join it with its neighbour's half; streamed, the forward took 155 against 136 us)
+                            // (default policy.  A row segment of 32 bf16 lanes, on short tiles, is half a 128-byte line, which
+                            // the cache joins with its neighbour's half: streamed, a forward took 155 against 136 us.  The 64
+                            // lanes of long tiles are whole lines; streaming those has not been measured)
                             *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(zre) + off) = to_bf16(zr[0]);
                             *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(zim) + off) = to_bf16(zi[0]);
                         } else {

@@ -404,8 +404,8 @@ __device__ __forceinline__ void stage_rows(float *sU, const float *mag, const fl
                                            int wave, int nwaves, int lane)
 {
     constexpr int NRT = TT + HALO;
-    // rows whose segment fills a 128-byte line are streamed; half lines (bf16) keep the default policy, so that
-    // the cache can serve the neighbouring lane block's half of the line
+    // rows whose segment fills a 128-byte line are streamed; half lines (bf16 on 32-lane rows) keep the default policy,
+    // so that the cache can serve the neighbouring lane block's half of the line
     [[maybe_unused]] constexpr int POL = JB * 4 >= 128 ? DMA_STREAM : 0;
     constexpr int NRTP = staged_rows<TT, JB, HALO>();
     constexpr int LR = JB * 4 / LB;                // lanes per row
@@ -555,7 +555,7 @@ __device__ __forceinline__ void finish_call(WsHeader *hdr, size_t clear_from, ui
 }
 
 // One link of a tile chain: P = T + M c, with M = lambda^TILE_T held as a double-float (h + q) and
-// conjugated for the adjoint chain.
+// conjugated for the adjoint chain.  Published prefixes, look_back and chain_carry are all made of it.
 template <bool CONJ>
 __device__ __forceinline__ void chain_step(float Tr, float Ti, float hr, float hi, float qr, float qi,
                                            float cr, float ci, float &Pr, float &Pi)
@@ -581,11 +581,12 @@ __device__ __forceinline__ void chain_step(float Tr, float Ti, float hr, float h
 // while the prefix c of the previous group is on its way; the first group needs none (its E is the carry).  So a
 // prefix is passed on once per G tiles, and only that is a chain of round trips: with a prefix per tile, long chains of
 // few rows advanced by 0.22 us a tile, and walking back over aggregates instead read every one of them in every tile.
-// The association is fixed by G and the tile's position alone: results do not depend on timing.
+// The association is fixed by G and the tile's position alone: results do not depend on timing.  (Tile length and G follow
+// from the whole call's sizes: the same row in a call of another batch may be rounded differently.)  For the forward chains.
 // `id` is the tile's index, `stride` the distance to its predecessor's, tt >= 1 its position in the chain.  M is
 // lambda^TILE_T as a double-float; its power is formed in fp64.  Every wait is bounded: false if one gave up (the carry
 // is then meaningless).
-template <int JB, int NB, bool CONJ, bool RET, bool PRE>
+template <int JB, int NB, bool RET, bool PRE>
 __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t *aggp, const tagged_t *pre, uint32_t id,
                                             uint32_t stride, int tt, int G, int lv, float hr, float hi, float qr, float qi,
                                             uint32_t spin_limit, uint32_t tag, float &cr, float &ci)
@@ -643,7 +644,7 @@ __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t 
                     Ei = ti;
                 } else {
                     float nr, ni;
-                    chain_step<CONJ>(tr, ti, hr, hi, qr, qi, Er, Ei, nr, ni);
+                    chain_step<false>(tr, ti, hr, hi, qr, qi, Er, Ei, nr, ni);
                     Er = nr;
                     Ei = ni;
                 }
@@ -670,7 +671,7 @@ __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t 
         const float ar = (float)mr, ai = (float)mi;
         float nr, ni;
         if constexpr (RET) { cr *= P; ci *= P; }
-        chain_step<CONJ>(Er, Ei, ar, ai, (float)(mr - (double)ar), (float)(mi - (double)ai), cr, ci, nr, ni);
+        chain_step<false>(Er, Ei, ar, ai, (float)(mr - (double)ar), (float)(mi - (double)ai), cr, ci, nr, ni);
         cr = nr;
         ci = ni;
     }
