@@ -902,6 +902,8 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long j
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 {
+    // (the host divided the call by the tile it chose: the same one, or nothing is launched)
+    if (a.nLB != (a.J + G::JB - 1) / G::JB || a.nT != (a.L + G::TILE_T - 1) / G::TILE_T) return hipErrorInvalidValue;
     const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
     const long long jobs = (long long)units * a.nT;
     if constexpr (G::JB == 32 && !G::SHORT) {
