@@ -127,6 +127,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
     static_assert(!EACH || (JB == 32 && !G::SHORT), "a prefix per tile: long 32-lane tiles (see make_queues)");
+    constexpr bool ONE = JB == 32 && !G::SHORT && !EACH;     // such a call has a workgroup for every tile (launch_fwd_tile)
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
         const uint32_t hcG = HC ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
             if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
-            else if (!EACH && a.tq.one_each) ticket_ahead = NO_TICKET;
+            else if (ONE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
             else ticket_ahead = next_ticket_of(a.hdr, hcG);
         }
 
@@ -440,14 +441,14 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                 if (RET) sP[seg][lv * V + v] = Pth[v];
             }
         }
-        if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+        if (!ONE && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
         lds_barrier();
         CAWN_STAMP(3);
 
         // ---- start staging the next tile (it lands during this tile's communication phase)
-        const uint32_t next_ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
+        const uint32_t next_ticket = ONE ? NO_TICKET : (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
         TileId Tn{};
-        if (next_ticket < qtiles) {
+        if (!ONE && next_ticket < qtiles) {
             Tn = tile_of(next_ticket);
             stage_tile(Tn);
         }
@@ -851,6 +852,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
             }
         }
 
+        if (ONE) break;
         ticket = next_ticket;
         T = Tn;
     }
@@ -896,9 +898,11 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long j
 }
 
 // The carry scheme of a call: a prefix per tile for 32-lane rows with more tiles than workgroups (EACH), a prefix per
-// group of tiles otherwise (see make_queues).  A kernel each, and EACH knows that its workgroups take several tiles from
-// one counter: with both schemes in one kernel, and every tile asking whether there is a next one to draw, such calls
-// were 1 - 2.5 % slower (B16 L1000 J768 53.9 us against 52.4, B6 L3001 J768 57.7 against 57.0).
+// group of tiles otherwise (see make_queues).  A kernel each: EACH knows that its workgroups take several tiles from one
+// counter, the other one on long 32-lane rows that each of its workgroups takes one tile (ONE) and looks for no next one.
+// With both schemes in one kernel, and every tile asking whether there is a next one to draw, the first kind was 1 - 2.5 %
+// slower (B16 L1000 J768 53.9 us against 52.4, B6 L3001 J768 57.7 against 57.0) and the second 4 % (B1 L4096 J768 16.8
+// against 16.0, B1 L16300 J256 20.9 against 20.3).
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 {
@@ -907,7 +911,7 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
     const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
     const long long jobs = (long long)units * a.nT;
     if constexpr (G::JB == 32 && !G::SHORT) {
-        if (jobs > fwd_resident<G, KC, VALVE, RET, BF, HC, true>()) return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs, s);
+        if (jobs > fwd_resident<G, KC, VALVE, RET, BF, HC, false>()) return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs, s);
     }
     return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
 }
