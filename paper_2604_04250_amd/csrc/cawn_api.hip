@@ -595,11 +595,11 @@ static float valve_threshold_of(float eps)
 // be slower than long tiles that pass a prefix on per tile: up to there they cost up to 20 % more than long tiles with a prefix
 // per group, and their error is half as large (runs of 8 instead of 32 tokens between exact powers of lambda: 1.8e-7 against
 // 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
-// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 13.3 / 8.9 (64), J256
-// L4096 15.3 / 17.9 (512), J256 4 x L2048 14.9 / 18.4 (1024), J768 L2048 14.8 / 15.9 (768), J768 3 x L768 14.5 / 14.5 (864); paper's
-// layer, J256: 7 x L1024 17.1 / 16.8 (896), L3072 17.9 / 19.7 (384), in bf16 16.1 / 16.7 and 18.2 / 19.3; J256 L2048 with the
-// valve in bf16 15.8 / 12.8 (256).  With the harmonic convolution, J256: L1024 15.5 / 11.2 (64), L4096 18.1 / 17.8 (256), paper's
-// layer L4096 21.7 / 22.3.
+// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 12.5 / 8.9 (64), J256
+// L3584 14.5 / 16.9 (448), J256 4 x L2048 14.2 / 18.1 (1024), J768 L2048 14.0 / 15.2 (768), J768 3 x L768 13.8 / 14.7 (864); paper's
+// layer, J256: 7 x L1024 15.8 / 16.8 (896), L1536 15.4 / 14.8 (192), L3072 16.6 / 19.7 (384), in bf16 7 x L1024 16.1 / 18.0, L3072
+// 18.2 / 19.1; J256 L2048 with the valve in bf16 15.8 / 12.8 (256).  With the harmonic convolution, J256: L1024 15.4 / 11.1 (64),
+// L4096 18.3 / 17.8 (256), paper's layer L4096 21.9 / 22.0.
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
@@ -610,7 +610,7 @@ static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, in
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
     if (nT > (hc && ret ? 60 : 64) || tiles > 256u * (hc ? 1 : 4)) return false;
     if (!hc) {
-        const size_t per = ret ? (bf16 ? 16 : 32) : 24, most = ret ? (bf16 ? 1056 : 1536) : 1608;
+        const size_t per = ret ? (bf16 ? 16 : 40) : 24, most = ret ? (bf16 ? 1056 : 1480) : 1608;
         if (nT * per + tiles > most) return false;
     }
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;

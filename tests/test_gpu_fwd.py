@@ -347,7 +347,7 @@ def _check_modes(mode, B, L, H, F, seed):
 
 # the last calls on 64-token tiles (most tiles, longest chain of a single lane block) and the first on long ones
 @pytest.mark.parametrize("mode,B,L", [("plain", 128, 512), ("plain", 129, 512), ("plain", 1, 4096), ("plain", 1, 4097), ("plain", 2, 3904), ("plain", 2, 3905),
-                                      ("ret", 1, 2944), ("ret", 1, 2945), ("hconv", 1, 4096), ("hconv", 1, 4097),
+                                      ("ret", 1, 2304), ("ret", 1, 2305), ("hconv", 1, 4096), ("hconv", 1, 4097),
                                       ("hconv_ret", 1, 3840), ("hconv_ret", 1, 3841)])
 def test_last_short_and_first_long_tiles(mode, B, L):
     _check_modes(mode, B, L, 1, 32, 1900 + L)
