@@ -1049,6 +1049,103 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // its successors in other workgroups wait for it)
     if (!PF && tid == 0 && !a.tq.one_each)
         ticket_ahead = next_ticket_of(a.hdr, 1u);
+    // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order (behind a barrier)
+    auto param_terms = [&]() {
+        if constexpr (PARAM) {
+            float part[ROWS][V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                part[0][v] = acc_g[v];
+                part[1][v] = acc_t[v];
+#pragma unroll
+                for (int r = 2; r < ROWS; ++r) part[r][v] = 0.f;
+            }
+            if (KC > 0) {
+                const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;
+                float hm_[HALO1], ha_[HALO1];       // bf16: the fp32 history rows again (first segment of a call with history)
+#pragma unroll
+                for (int k = 0; k < HALO1; ++k) hm_[k] = ha_[k] = 0.f;
+                if (BF && hist_bf) {
+#pragma unroll
+                    for (int k = 0; k < HALO; ++k) {
+                        hm_[k] = hist_row(k, 0);
+                        ha_[k] = hist_row(k, 1);
+                    }
+                    wait_vm<0>();
+                }
+#pragma unroll
+                for (int i = 0; i < NSTEP; ++i)
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        part[2][v] += dzr[i][v];
+                        part[3][v] += dzi[i][v];
+#pragma unroll
+                        for (int k = 0; k < KC; ++k) {
+                            const bool z = zero_hist && (i + k < HALO);
+                            const bool hrow = BF && hist_bf && (i + k < HALO);
+                            const float um_ = z ? 0.f : (hrow ? hm_[i + k < HALO ? i + k : 0] : su(seg * NSTEP + i + k, lv * V + v));
+                            const float ua_ = z ? 0.f : (hrow ? ha_[i + k < HALO ? i + k : 0] : su(NRTP + seg * NSTEP + i + k, lv * V + v));
+                            part[4 + k][v] = __builtin_fmaf(dzr[i][v], um_, part[4 + k][v]);
+                            part[4 + KC + k][v] = __builtin_fmaf(dzi[i][v], ua_, part[4 + KC + k][v]);
+                        }
+                    }
+            }
+            if constexpr (HC) {
+#pragma unroll
+                for (int q = 0; q < HC_PART_ROWS; ++q) part[4 + 2 * KC + q][0] = hacc[q];
+            }
+            if (PF) lds_barrier_raw();      // the staging below lies over the input rows: everybody has read them
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const float other = __shfl_xor(part[r][v], 32, 64);    // the wave's other segment
+                    const float s = (seg & 1) ? other + part[r][v] : part[r][v] + other;
+                    if (!(seg & 1)) sRed[wave][r][lv * V + v] = s;
+                }
+        }
+    };
+    auto param_sums = [&]() {
+        if constexpr (PARAM) {
+            for (int e = tid; e < ROWS * JB; e += NT) {
+                const int row = e / JB, c = e % JB;
+                float s = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) s += sRed[w][row][c];
+                a.part[((size_t)ticket * ROWS + row) * JB + c] = s;
+            }
+        }
+        // ---- the valve's gradient terms of the tile go out, token-contiguous per group
+        if (VALVE && a.vpart) {
+            for (int e = tid; e < a.gpb * TILE_T; e += NT) {
+                const int g = e / TILE_T, tok = e - g * TILE_T;
+                const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
+                if (t < a.L && grp < a.G) a.vpart[((size_t)b * a.G + grp) * a.L + t] = sVp[e];
+            }
+        }
+        // ---- and the retention logits' in the same layout
+        if (RET && a.rpart) {
+            for (int e = tid; e < a.gpb * TILE_T; e += NT) {
+                const int g = e / TILE_T, tok = e - g * TILE_T;
+                const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
+                if (t < a.L && grp < a.G) a.rpart[((size_t)b * a.G + grp) * a.L + t] = sRp[e];
+            }
+        }
+    };
+    // LEAN: they leave the tile ahead of its output gradients.  A wave's memory operations complete in issue order, and
+    // these kernels spill a few registers: behind the output stores the first value read back (the tap terms, the
+    // ticket) waited for all 16 of them to reach memory, in every wave (8.7 of a tile's 29 us behind the harmonic
+    // convolution).  Their registers are also free earlier: valve and retention together 36 -> 7 values spilled, with the
+    // convolution 61 -> 27.  Training steps of B8 L8192 H4 F64 conv 3: 232 -> 219 us, with the convolution 300 -> 270,
+    // in bf16 243 -> 225; B7 L1024 46.0 -> 44.5.  (The kernels without spills, whose staging lies over the input rows,
+    // would need two more barriers.)
+    // (KC = 0 has no halo rows, hence no barrier of its own here)
+    if (LEAN && KC == 0) {
+        param_terms();
+        lds_barrier();
+        param_sums();
+        if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+    }
     const size_t dbase = ((size_t)b * a.isb + (size_t)(tt * TILE_T) * a.ist + (size_t)lb * JB) * ES;
     float *omag = reinterpret_cast<float *>(reinterpret_cast<char *>(a.dmag) + dbase);
     float *oang = reinterpret_cast<float *>(reinterpret_cast<char *>(a.dang) + dbase);
@@ -1079,16 +1176,6 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         }
     } else {
         // ---- transposed conv: du[t] = sum_k w[k] dz[t + (KC-1) - k]
-        // (the valve kernels are at their register budget: their taps wait in LDS during the reverse
-        // pass instead of in 2*KC registers)
-        float wm[KC1][V], wa[KC1][V];
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                wm[k][v] = LEAN ? sTaps[k][lv * V + v] : wmf[k][v];
-                wa[k][v] = LEAN ? sTaps[KC + k][lv * V + v] : waf[k][v];
-            }
         // The transposed conv needs the conv pre-activation gradients of the HALO tokens after each
         // segment.  Inside the tile the earlier segment of a wave takes them from the later one by a lane
         // exchange, the later one from the next wave through LDS.  The tile's own first rows go to the
@@ -1134,9 +1221,24 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                     xw[r][1][v] = tagged_load(hin + (r * 2 + 1) * JB + v);
                 }
         };
+        if (LEAN) param_terms();
         if (want_rows) ask_rows();
         if (PF) lds_barrier_raw(); else lds_barrier();
     BWD_STAMP(8);
+        if (LEAN) {
+            param_sums();
+            if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+        }
+        // (the valve kernels are at their register budget: their taps wait in LDS during the reverse
+        // pass instead of in 2*KC registers)
+        float wm[KC1][V], wa[KC1][V];
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                wm[k][v] = LEAN ? sTaps[k][lv * V + v] : wmf[k][v];
+                wa[k][v] = LEAN ? sTaps[KC + k][lv * V + v] : waf[k][v];
+            }
         float hm[HALO1][V], ha[HALO1][V];       // dz of the HALO tokens after my segment
 #pragma unroll
         for (int r = 0; r < HALO1; ++r)
@@ -1281,92 +1383,14 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     ARGS_AGAIN();
-    // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order
-    if (PARAM) {
-        float part[ROWS][V];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            part[0][v] = acc_g[v];
-            part[1][v] = acc_t[v];
-#pragma unroll
-            for (int r = 2; r < ROWS; ++r) part[r][v] = 0.f;
-        }
-        if (KC > 0) {
-            const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;
-            float hm_[HALO1], ha_[HALO1];       // bf16: the fp32 history rows again (first segment of a call with history)
-#pragma unroll
-            for (int k = 0; k < HALO1; ++k) hm_[k] = ha_[k] = 0.f;
-            if (BF && hist_bf) {
-#pragma unroll
-                for (int k = 0; k < HALO; ++k) {
-                    hm_[k] = hist_row(k, 0);
-                    ha_[k] = hist_row(k, 1);
-                }
-                wait_vm<0>();
-            }
-#pragma unroll
-            for (int i = 0; i < NSTEP; ++i)
-#pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    part[2][v] += dzr[i][v];
-                    part[3][v] += dzi[i][v];
-#pragma unroll
-                    for (int k = 0; k < KC; ++k) {
-                        const bool z = zero_hist && (i + k < HALO);
-                        const bool hrow = BF && hist_bf && (i + k < HALO);
-                        const float um_ = z ? 0.f : (hrow ? hm_[i + k < HALO ? i + k : 0] : su(seg * NSTEP + i + k, lv * V + v));
-                        const float ua_ = z ? 0.f : (hrow ? ha_[i + k < HALO ? i + k : 0] : su(NRTP + seg * NSTEP + i + k, lv * V + v));
-                        part[4 + k][v] = __builtin_fmaf(dzr[i][v], um_, part[4 + k][v]);
-                        part[4 + KC + k][v] = __builtin_fmaf(dzi[i][v], ua_, part[4 + KC + k][v]);
-                    }
-                }
-        }
-        if constexpr (HC) {
-#pragma unroll
-            for (int q = 0; q < HC_PART_ROWS; ++q) part[4 + 2 * KC + q][0] = hacc[q];
-        }
-        if (PF) lds_barrier_raw();      // the staging below lies over the input rows: everybody has read them
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const float other = __shfl_xor(part[r][v], 32, 64);    // the wave's other segment
-                const float s = (seg & 1) ? other + part[r][v] : part[r][v] + other;
-                if (!(seg & 1)) sRed[wave][r][lv * V + v] = s;
-            }
-        if (PF) lds_barrier_raw(); else lds_barrier();
+    if (!LEAN) {
+        param_terms();
+        if (PARAM) lds_barrier_raw();
     BWD_STAMP(9);
-        for (int e = tid; e < ROWS * JB; e += NT) {
-            const int row = e / JB, c = e % JB;
-            float s = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) s += sRed[w][row][c];
-            a.part[((size_t)ticket * ROWS + row) * JB + c] = s;
-        }
+        param_sums();
     }
 
-    // ---- the valve's gradient terms of the tile go out, token-contiguous per group
-    if (VALVE && a.vpart) {
-        lds_barrier();
-        for (int e = tid; e < a.gpb * TILE_T; e += NT) {
-            const int g = e / TILE_T, tok = e - g * TILE_T;
-            const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
-            if (t < a.L && grp < a.G) a.vpart[((size_t)b * a.G + grp) * a.L + t] = sVp[e];
-        }
-    }
-    // ---- and the retention logits' in the same layout
-    if (RET && a.rpart) {
-        if (!(VALVE && a.vpart)) lds_barrier();
-        for (int e = tid; e < a.gpb * TILE_T; e += NT) {
-            const int g = e / TILE_T, tok = e - g * TILE_T;
-            const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
-            if (t < a.L && grp < a.G) a.rpart[((size_t)b * a.G + grp) * a.L + t] = sRp[e];
-        }
-    }
-
-    // ---- LDS is reused by the next tile.  The ticket asked for above is parked where this tile's was
-    //      (everything older than the output stores has completed: no further wait)
-    if (!PF && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+    // ---- LDS is reused by the next tile
     if (PF) lds_barrier_raw(); else lds_barrier();
     BWD_STAMP(10);
     ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
