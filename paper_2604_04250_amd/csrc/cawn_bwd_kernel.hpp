@@ -143,64 +143,53 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         if constexpr (BF) return from_bf16(reinterpret_cast<const uint16_t *>(&sU[r][0])[l]);
         else return sU[r][l];
     };
-    // PF: the upstream gradients of a tile are staged in LDS a tile ahead (direct-to-LDS loads issued
-    // while the previous tile is in its front-end), so that a tile starts its local adjoint, and
-    // publishes its aggregate, without waiting for memory.  The 32 KB this takes fit beside the rest
+    // The upstream gradients of a tile are staged in LDS a tile ahead (direct-to-LDS loads issued
+    // while the previous tile is in its front-end, behind the harmonic convolution in its reverse pass), so that a
+    // tile starts its local adjoint, and publishes its aggregate, without waiting for memory: loaded at the top of a
+    // tile they return behind the previous tile's output stores.  (Kernels with the valve or retentions, which loaded
+    // them there: training steps of B8 L8192 H4 F64 conv 3 219 -> 214 us, in bf16 225 -> 211, with the harmonic convolution
+    // 270 -> 263, in bf16 278 -> 256, with the valve alone B8 L8192 H12 F64 486 -> 479; and no register spilled without it.)
+    // The 32 KB this takes fit beside the rest
     // only because arrays with disjoint lifetimes share storage: the conv-gradient halo rows (written
     // after the reverse pass) lie over the segment aggregates (dead by then), and the partial-sum
     // staging lies over the input rows (dead after the last weight-gradient read, one more barrier).
-    constexpr bool PF = !VALVE && !RET;
-    // SDZ: the upstream gradients pass through LDS at all.  The valve and retention kernels load them into
-    // registers, except behind the harmonic convolution: its transposed form and its tap gradients read three
-    // neighbouring lanes of every gradient, twice in a tile, so there the tile's gradients are staged too -- at
-    // the top of the tile itself, not a tile ahead (see OVL below for where the 32 KB come from).
-    constexpr bool SDZ = PF || HC;
+    constexpr int RB_ROW = HC ? 4 + HC_ROWS : 4;
     constexpr int NRZ = staged_rows<TILE_T, JBS, 0>();                // staged rows per gradient stream
-    __shared__ __attribute__((aligned(16))) float sDz[SDZ ? 2 * NRZ : 1][JBS];    // [stream*NRZ + token][lane]
+    __shared__ __attribute__((aligned(16))) float sDz[2 * NRZ][JBS];    // [stream*NRZ + token][lane]
     // ... and with them the four lane constants the local adjoint needs (lambda, lambda^NSTEP): a wave's
     // memory operations complete in issue order, so a load issued at the top of a tile returns only after
     // the previous tile's output stores have been acknowledged
     // HC: ... and the lane block's harmonic-convolution taps (table rows R_W0 + 2 KC + 0 .. 7)
-    __shared__ float sLam[SDZ ? (HC ? 4 + HC_ROWS : 4) : 1][JB];
+    // (RET: and the retention bias, row RB_ROW; the tile's logits are staged in sR)
+    __shared__ float sLam[RB_ROW + (RET ? 1 : 0)][JB];
     // HC: the gradients of the two lanes beside the lane block, [plane][side: lane -1, lane JB][token]
     __shared__ float sEdge[HC ? 4 * NRZ : 1];
-    constexpr int N_EB = NSEG * 2 * JB, N_HALO = NW * HALO1 * 2 * JB;
-    // OVL: the valve and retention kernels behind the harmonic convolution (fp32 rows) stage a tile's gradients at
-    // its top and read them for the last time in the tap pass, in the middle of the tile: what is written only
-    // after the barrier that follows that pass -- the conv-gradient halo rows, the valve's and the retention
-    // logits' gradient terms, the partial-sum staging -- lies over them.  With that the kernel fits twice on a
-    // compute unit.
-    constexpr bool OVL = HC && !PF && !BF;
-    constexpr int N_RED = NW * ROWS * JB, N_VT = BwdGeom::TILE_T * 4;
-    static_assert(!OVL || N_RED + N_HALO + 2 * N_VT <= 2 * NRZ * JBS, "what lies over the staged gradients fits there");
-    __shared__ float sPool[PF ? (N_EB > N_HALO ? N_EB : N_HALO) : (OVL ? N_EB : N_EB + N_HALO)];
+    constexpr int N_EB = NW * 2 * JB, N_HALO = NW * HALO1 * 2 * JB;
+    __shared__ float sPool[N_EB > N_HALO ? N_EB : N_HALO];
     float (*sEb)[2][JB] = reinterpret_cast<float (*)[2][JB]>(&sPool[0]);
-    float (*sHalo)[HALO1][2][JB] = reinterpret_cast<float (*)[HALO1][2][JB]>(OVL ? &sDz[0][0] + N_RED : &sPool[PF ? 0 : N_EB]);   // [NW]: first rows of each wave's earlier segment
+    float (*sHalo)[HALO1][2][JB] = reinterpret_cast<float (*)[HALO1][2][JB]>(&sPool[0]);   // [NW]: first rows of each wave's earlier segment
     __shared__ float sCarry[2][JB];
     // (bf16 rows are half as large and the harmonic convolution adds 8 partial rows: that combination has LDS to
     // spare and keeps the staging in an array of its own)
-    constexpr bool RED_OVER_ROWS = PF && !(BF && HC);
-    __shared__ float sRedOwn[(PARAM && !RED_OVER_ROWS && !OVL) ? NW : 1][ROWS][JB];
+    constexpr bool RED_OVER_ROWS = !(BF && HC);
+    __shared__ float sRedOwn[(PARAM && !RED_OVER_ROWS) ? NW : 1][ROWS][JB];
     static_assert(!RED_OVER_ROWS || (size_t)NW * ROWS * JB <= (size_t)2 * NRTP * JBS, "the partial-sum staging fits over the input rows");
-    float (*sRed)[ROWS][JB] = RED_OVER_ROWS ? reinterpret_cast<float (*)[ROWS][JB]>(&sU[0][0])
-                                            : (OVL ? reinterpret_cast<float (*)[ROWS][JB]>(&sDz[0][0]) : sRedOwn);
-    constexpr int GPB_MAX = 4;                    // valve groups per lane block (F >= 8)
-    static_assert(N_VT == BwdGeom::TILE_T * GPB_MAX, "");
+    float (*sRed)[ROWS][JB] = RED_OVER_ROWS ? reinterpret_cast<float (*)[ROWS][JB]>(&sU[0][0]) : sRedOwn;
+    constexpr int GPB_MAX = HC ? 1 : (VALVE && RET ? 2 : 4);   // heads per lane block: F >= 8, with both 16, behind the harmonic convolution 32
     __shared__ float sV[VALVE ? BwdGeom::TILE_T * GPB_MAX : 1];      // valve logits, [group][token]
-    __shared__ float sVpOwn[VALVE && !OVL ? BwdGeom::TILE_T * GPB_MAX : 1];     // valve gradient terms summed over a group's lanes
-    float *sVp = OVL ? &sDz[0][0] + N_RED + N_HALO : sVpOwn;
+    __shared__ float sVp[VALVE ? BwdGeom::TILE_T * GPB_MAX : 1];     // valve gradient terms summed over a group's lanes
     __shared__ float sTaps[LEAN ? 2 * KC1 : 1][JB];                 // conv taps of the lane block (valve kernels)
-    __shared__ float sPb[RET ? NSEG : 1][JB];                        // product of each wave's retentions
-    __shared__ float sPt[RET ? 1 : 1][JB];                           // product of the tile's retentions (head group)
-    __shared__ float sRpOwn[RET && !OVL ? BwdGeom::TILE_T * GPB_MAX : 1];       // retention-logit gradient terms per (group, token)
-    float *sRp = OVL ? &sDz[0][0] + N_RED + N_HALO + N_VT : sRpOwn;
+    __shared__ float sPb[RET ? NW : 1][JB];                        // product of each wave's retentions
+    float (*sPt)[JB] = &sPb[0];                 // product of the tile's retentions (head group; the first wave's own is read by nobody)
+    __shared__ float sRp[RET ? BwdGeom::TILE_T * GPB_MAX : 1];       // retention-logit gradient terms per (group, token)
+    __shared__ float sR[RET ? BwdGeom::TILE_T * GPB_MAX : 1];  // retention logits, staged with the gradients
     __shared__ uint32_t sTicket[2], sLast, sEpoch;     // tickets of this tile and the next one
 
     const int tid_ = threadIdx.x;
     const float *tail_in = a.state_in ? a.state_in + (size_t)a.B * 2 * a.J : nullptr;
     const float *dtail_out = a.dstate_out ? a.dstate_out + (size_t)a.B * 2 * a.J : nullptr;
     const uint32_t chain_stride = (uint32_t)a.B * a.nLB;
-    const uint32_t ost32 = (uint32_t)a.ost, ist32 = (uint32_t)a.ist;
+    const uint32_t ist32 = (uint32_t)a.ist;
     uint32_t ticket_ahead = NO_TICKET;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
     if (tid_ == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // all three round trips at once
@@ -215,10 +204,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     const uint32_t tag = make_tag(epoch);      // of every word this call publishes
 
     // Persistent: each workgroup loops over tiles, handed out in chain order by an atomic ticket.  A
-    // workgroup also holds the ticket of its next tile: it asks for it just before the previous tile's
-    // output stores go out (a wave's memory operations complete in issue order: asked for behind them,
-    // at the top of a tile, the answer would arrive only after they are acknowledged, and the next tile
-    // must be known early, for its staged gradients).  Every workgroup works through its tickets in
+    // workgroup asks for the ticket of its next tile behind the first barrier of a tile (the next tile must be known early,
+    // for its staged gradients).  Every workgroup works through its tickets in
     // increasing order and a tile waits only for lower tickets, so the lowest unfinished ticket is always
     // some workgroup's current tile: no wait can last.  (Holding tickets two tiles ahead was tried: the
     // reserved tiles start later and their successors in other workgroups wait for them, +3 % to +30 %.)
@@ -278,7 +265,10 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                     __builtin_amdgcn_global_load_lds(table + (size_t)(R_W0 + 2 * KC + 2 * q + (lane >> 5)) * Jp + jl,
                                                      &sLam[4 + 2 * q][0], 4, 0, 0);
             }
+            if (RET && lane < JB)
+                __builtin_amdgcn_global_load_lds(table + (size_t)R_RBIAS * Jp + jl, &sLam[RET ? RB_ROW : 0][0], 4, 0, 0);
 #endif
+            if (RET) stage_valve<TILE_T, JB>(&sR[0], a.ret, b_, tt_ * TILE_T, lb_, a.L, a.H, a.F, a.gpb, lane);
         }
         if constexpr (HC) {
             // the two neighbour lanes of the block, 64 tokens per instruction; rows past the end and lanes
@@ -375,8 +365,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             ci[1] = c0i;
         }
     };
-    if (SDZ) {
-        if (!PF || it == 0) {      // a workgroup's first tile: nobody staged its gradients ahead
+    {
+        if (it == 0) {      // a workgroup's first tile: nobody staged its gradients ahead
             stage_dz(b, tt, lb, wave, NW);
             wait_vm<0>();
             lds_barrier();
@@ -425,63 +415,35 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         // (a tile that lies wholly inside the tensors takes the rows as they are: no per-row selects)
         if (full) dz_from_lds(std::true_type{});
         else dz_from_lds(std::false_type{});
-    } else {
-        const size_t gbase = ((size_t)b * a.osb + (size_t)(tt * TILE_T) * a.ost + (size_t)lb * JB) * ES;
-        const float *gre = reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.dz_re) + gbase);
-        const float *gim = reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.dz_im) + gbase);
-        uint32_t off = ((uint32_t)(seg * NSTEP) * ost32 + (uint32_t)(lv * V)) * ES;      // bytes
-        auto ldg = [&](float (&d)[V], const float *ub, uint32_t bo) {
-            // (read once: streamed, like the staged rows; bf16 rows are half lines and keep the default policy)
-            if constexpr (BF) d[0] = from_bf16(*reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(ub) + bo));
-            else d[0] = __builtin_nontemporal_load(reinterpret_cast<const float *>(reinterpret_cast<const char *>(ub) + bo));
-        };
-        if (full) {
-#pragma unroll
-            for (int i = 0; i < NSTEP; ++i) {
-                ldg(dzr[i], gre, off);
-                ldg(dzi[i], gim, off);
-                off += ost32 * ES;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NSTEP; ++i) {
-#pragma unroll
-                for (int v = 0; v < V; ++v) dzr[i][v] = dzi[i][v] = 0.f;
-                if (active && t0 + i < a.L) {
-                    ldg(dzr[i], gre, off);
-                    ldg(dzi[i], gim, off);
-                }
-                off += ost32 * ES;
-            }
-        }
     }
+    // lanes that share a valve: a head, or the part of it inside the 32-lane block (8, 16 or 32).
+    // Where my tokens' entries start in sV / sVp is formed again at each use (from an opaque copy of
+    // the thread index) rather than kept in a register across the tile.
+    const int vwidth = (VALVE || RET) ? (a.F >= JB ? JB : a.F) : 1;
+    auto valve_base = [&]() {
+        int t_ = tid_;
+        asm volatile("" : "+v"(t_));
+        const int lv_ = t_ % LPR, seg_ = t_ / LPR;
+        const int grp = vwidth == 32 ? 0 : (vwidth == 16 ? lv_ >> 4 : lv_ >> 3);
+        return grp * TILE_T + seg_ * NSTEP;
+    };
     // ---- retention logits of my tokens (one per token and head: the lanes of a head read one address)
     float gm[RET ? NSTEP : 1][V];           // logit, then the retention itself
     if (RET) {
-        const float *rp = a.ret + (size_t)b * a.L * a.H + (active ? j0 : 0) / a.F;
+        const int rbase = valve_base();
 #pragma unroll
-        for (int i = 0; i < NSTEP; ++i) {
-            const int t = t0 + i < a.L ? t0 + i : a.L - 1;     // rows past the end: a valid address, the value is harmless
-            gm[i][0] = rp[(size_t)t * a.H];
-        }
+        for (int i = 0; i < NSTEP; ++i) gm[i][0] = sR[rbase + i];
     }
     // ---- lane constants
     float lr[V], li[V], pnr[V], pni[V];
     float wmf[KC1][V], waf[KC1][V], bm[V], ba[V];   // taps for the front-end
-    if (PF) {       // staged with the gradients (lanes beyond J hold table padding: their results are never stored)
-        lr[0] = sLam[0][lv];
-        li[0] = sLam[1][lv];
-        pnr[0] = sLam[2][lv];
-        pni[0] = sLam[3][lv];
-    } else {
-        ldu<V>(lr, row(R_LR), jb);
-        ldu<V>(li, row(R_LI), jb);
-        ldu<V>(pnr, row(R_PSEGB + 2), jb);                       // lambda^NSTEP
-        ldu<V>(pni, row(R_PSEGB + 3), jb);
-    }
-    // the forward state before my first token: the checkpoint of my segment (PF: fetched here, so that it
-    // has arrived with the staged rows; the other kernels fetch it behind that wait, next to the
-    // constants of the reverse pass)
+    // (staged with the gradients; lanes beyond J hold table padding: their results are never stored)
+    lr[0] = sLam[0][lv];
+    li[0] = sLam[1][lv];
+    pnr[0] = sLam[2][lv];
+    pni[0] = sLam[3][lv];
+    // the forward state before my first token: the checkpoint of my segment (fetched here, so that it has arrived with
+    // the staged rows)
     float kr[V], ki[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) kr[v] = ki[v] = 0.f;
@@ -492,11 +454,11 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             BVec<V>::ld(ki, ck + a.J);
         }
     };
-    if (PF) load_ckpt();
+    load_ckpt();
     float rb[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) rb[v] = 0.f;
-    if (RET) ldu<V>(rb, row(R_RBIAS), jb);
+    if (RET) rb[0] = sLam[RET ? RB_ROW : 0][lv];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         bm[v] = ba[v] = 0.f;
@@ -512,18 +474,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             ldu<V>(waf[k], row(R_W0 + KC + k), jb);
         }
     }
-    if (LEAN && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
-#pragma unroll
-        for (int k = 0; k < KC; ++k)
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                sTaps[k][lv * V + v] = wmf[k][v];
-                sTaps[KC + k][lv * V + v] = waf[k][v];
-            }
-    }
-
-    // ---- the tile's input rows go to LDS (needed from the front-end on; issued after the loads the
-    //      local adjoint waits for, so that it does not wait for these as well)
+    // ---- the tile's input rows go to LDS (needed from the front-end on; behind the loads above: in front of them the
+    //      training step of B8 L8192 H12 F64 took 438 us against 431)
     // (bf16: rows of J/2 words at half the strides; the fp32 conv history is read at its points of use)
     if (a.stage16)
         stage_rows<TILE_T, JBS, HALO, 16>(&sU[0][0], a.mag, a.ang, BF ? nullptr : tail_in, b, tt * TILE_T, lb, BF ? a.J / 2 : a.J,
@@ -600,9 +552,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
     lds_barrier_raw();     // the staged rows are still on their way
     BWD_STAMP(2);
-    // (PF: the next tile must be known by the time its gradients are staged; asked for here, the answer
+    // (the next tile must be known by the time its gradients are staged; asked for here, the answer
     // arrives with this wave's staged rows, which it waits for below anyway)
-    if (PF && tid == 0 && !a.tq.one_each)
+    if (tid == 0 && !a.tq.one_each)
         ticket_ahead = next_ticket_of(a.hdr, 1u);
     float Xr[V], Xi[V];     // adjoint entering my segment (from later segments), zero tile input
     float Cb[V];            // RET: product of the retentions of the segments after mine
@@ -679,7 +631,16 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // operations, in flight: their round trip is nobody's business here)
     if (wave == 0 && chained && feeds) wait_vm<(RET ? 3 : 2) * V>();
     else wait_stores_done();
-    if (PF && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+    if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+    if (LEAN && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                sTaps[k][lv * V + v] = wmf[k][v];
+                sTaps[KC + k][lv * V + v] = waf[k][v];
+            }
+    }
     lds_barrier();
     BWD_STAMP(3);
 
@@ -690,7 +651,6 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     float psr[V], psi[V], cth[V], sth[V], gam[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) { sth[v] = gam[v] = 0.f; cth[v] = 1.f; }
-    if (!PF) load_ckpt();
     if (!LEAN) {
         ldu<V>(psr, row(R_PSEGB + 2 * (NSEG - 1 - seg)), jb);    // adjoint: segments after mine
         ldu<V>(psi, row(R_PSEGB + 2 * (NSEG - 1 - seg) + 1), jb);
@@ -703,17 +663,6 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // ---- front-end recompute, rows from LDS as a sliding window
     float cs[NSTEP][V], sn[NSTEP][V], ag[NSTEP][V], dsm[NSTEP][V];   // ag: a*g*SiLU'(z_ang)
     float am[VALVE ? NSTEP : 1][V];                                  // the amplitude itself (valve gradient)
-    // lanes that share a valve: a head, or the part of it inside the 32-lane block (8, 16 or 32).
-    // Where my tokens' entries start in sV / sVp is formed again at each use (from an opaque copy of
-    // the thread index) rather than kept in a register across the tile.
-    const int vwidth = (VALVE || RET) ? (a.F >= JB ? JB : a.F) : 1;
-    auto valve_base = [&]() {
-        int t_ = tid_;
-        asm volatile("" : "+v"(t_));
-        const int lv_ = t_ % LPR, seg_ = t_ / LPR;
-        const int grp = vwidth == 32 ? 0 : (vwidth == 16 ? lv_ >> 4 : lv_ >> 3);
-        return grp * TILE_T + seg_ * NSTEP;
-    };
     float Spr[PARAM ? NSTEP : 1][V], Spi[PARAM ? NSTEP : 1][V];      // forward state before each token
     float Efr[V], Efi[V];
 
@@ -905,7 +854,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             stage_dz(nrest % a.B, a.nT - 1 - nrest / a.B, nlb, wave - 1, NW - 1);
         }
     };
-    if (PF && !HC && wave != 0) stage_next();
+    if (!HC && wave != 0) stage_next();
     // ---- chain, second half: look-back (its round trips were hidden behind the recompute above)
     if (head) {
         float cr[V], ci[V], Tr[V], Ti[V], hr[V], hi[V], qr[V], qi[V];
@@ -946,9 +895,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         }
     }
     if (wave == 0) __builtin_amdgcn_s_setprio(0);
-    if (PF) lds_barrier_raw(); else lds_barrier();
+    lds_barrier_raw();
     BWD_STAMP(6);
-    if (PF && HC && wave != 0) stage_next();
+    if (HC && wave != 0) stage_next();
 
     // ---- true adjoint entering my segment
     float Gr[V], Gi[V];
@@ -1044,11 +993,6 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     ARGS_AGAIN();
-    // the ticket of the next tile: asked for as late as its answer can still arrive unwaited-for, i.e.
-    // ahead of this tile's output stores (a ticket held in reserve is a tile that has not started:
-    // its successors in other workgroups wait for it)
-    if (!PF && tid == 0 && !a.tq.one_each)
-        ticket_ahead = next_ticket_of(a.hdr, 1u);
     // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order (behind a barrier)
     auto param_terms = [&]() {
         if constexpr (PARAM) {
@@ -1094,7 +1038,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 #pragma unroll
                 for (int q = 0; q < HC_PART_ROWS; ++q) part[4 + 2 * KC + q][0] = hacc[q];
             }
-            if (PF) lds_barrier_raw();      // the staging below lies over the input rows: everybody has read them
+            if (RED_OVER_ROWS) lds_barrier_raw();      // the staging below lies over the input rows: everybody has read them
 #pragma unroll
             for (int r = 0; r < ROWS; ++r)
 #pragma unroll
@@ -1142,9 +1086,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // (KC = 0 has no halo rows, hence no barrier of its own here)
     if (LEAN && KC == 0) {
         param_terms();
-        lds_barrier();
+        lds_barrier_raw();
         param_sums();
-        if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
     }
     const size_t dbase = ((size_t)b * a.isb + (size_t)(tt * TILE_T) * a.ist + (size_t)lb * JB) * ES;
     float *omag = reinterpret_cast<float *>(reinterpret_cast<char *>(a.dmag) + dbase);
@@ -1223,12 +1166,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         };
         if (LEAN) param_terms();
         if (want_rows) ask_rows();
-        if (PF) lds_barrier_raw(); else lds_barrier();
+        lds_barrier_raw();
     BWD_STAMP(8);
-        if (LEAN) {
-            param_sums();
-            if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
-        }
+        if (LEAN) param_sums();
         // (the valve kernels are at their register budget: their taps wait in LDS during the reverse
         // pass instead of in 2*KC registers)
         float wm[KC1][V], wa[KC1][V];
@@ -1391,7 +1331,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     // ---- LDS is reused by the next tile
-    if (PF) lds_barrier_raw(); else lds_barrier();
+    lds_barrier_raw();
     BWD_STAMP(10);
     ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
 #undef a
