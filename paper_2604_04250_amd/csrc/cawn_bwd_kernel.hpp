@@ -855,6 +855,11 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         }
     };
     if (!HC && wave != 0) stage_next();
+    // (a workgroup without a next tile: one of the waves that would only wait counts it)
+    const TileQueues tq_ = {a.tq.lq, a.tq.one_each, a.tq.group};
+    if (counts_early(tq_, epoch) && tid == NT - 64 &&
+        leave_last(a.hdr, tq_, blockIdx.x, gridDim.x, leave_ask(a.hdr, tq_, blockIdx.x, gridDim.x)))
+        reset_header(a.hdr, epoch + 1u, 0u, 1u);
     // ---- chain, second half: look-back (its round trips were hidden behind the recompute above)
     if (head) {
         float cr[V], ci[V], Tr[V], Ti[V], hr[V], hi[V], qr[V], qi[V];
@@ -1340,9 +1345,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 
     // ---- the workgroup that leaves last resets the ticket and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
-    if (tid_ == 0) {
-        sLast = leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x) ? 1u : 0u;
-    }
+    if (counts_early(a.tq, epoch)) return;      // (counted in its tile)
+    if (tid_ == 0)
+        sLast = leave_last(a.hdr, a.tq, blockIdx.x, gridDim.x, leave_ask(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x);
 }

@@ -128,6 +128,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
     static_assert(!EACH || (JB == 32 && !G::SHORT), "a prefix per tile: long 32-lane tiles (see make_queues)");
     constexpr bool ONE = JB == 32 && !G::SHORT && !EACH;     // such a call has a workgroup for every tile (launch_fwd_tile)
+    // (64-lane rows with retentions: at the register limit, the count in the middle spilled 6 more values; the paper's layer
+    // in bf16, B1 L32768, 56.1 -> 57.3 us)
+    constexpr bool COUNT_EARLY = !EACH && !(JB == 64 && !G::SHORT && RET);
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -477,6 +480,14 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
                 Xr[v] = nr;
                 Xi[v] = ni;
             }
+        }
+
+        // (the last tile of a workgroup that is counted early: by a wave that waits for the owner's carry)
+        if constexpr (COUNT_EARLY) {
+            const TileQueues tq_ = {a.tq.lq, a.tq.one_each, a.tq.group};
+            if (next_ticket >= qtiles && counts_early(tq_, epoch) && tid == 0 &&
+                leave_last(a.hdr, tq_, blockIdx.x, gridDim.x, leave_ask(a.hdr, tq_, blockIdx.x, gridDim.x)))
+                reset_header(a.hdr, epoch + 1u, 0u, 1u);
         }
 
         // ---- chain.  The threads of the last segment own the tile aggregate: they publish it, do
@@ -861,9 +872,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
 #undef ARGS_AGAIN
     // ---- the workgroup that leaves last resets the tickets and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
-    if (tid == 0) {
-        sLast = (EACH ? leave_grid(a.hdr, gridDim.x) : leave_call(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
-    }
+    if (COUNT_EARLY && counts_early(a.tq, epoch)) return;      // (counted in its last tile)
+    if (tid == 0)
+        sLast = leave_last(a.hdr, a.tq, blockIdx.x, gridDim.x, leave_ask(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     __syncthreads();
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
 }

@@ -128,7 +128,7 @@ inline __host__ __device__ uint32_t done_word(uint32_t q) { return ticket_word(q
 //   * a call with more tiles than workgroups keeps one counter: its draws are spread over the call and cost nothing
 //     (eight counters with a second choice where one ran dry were slower: training step 431 -> 454 us, bf16 B2 L4096
 //     J4096 284 -> 298; the first tickets' delay keeps the workgroups out of step, and loads beside arithmetic);
-//   * the many workgroups of such a one-tile-each call are counted out in two levels.
+//   * the many workgroups of such a one-tile-each call are counted in two levels, in the middle of their tile (counts_early).
 struct TileQueues { uint32_t lq, one_each, group; };     // group: tiles of a chain between two prefixes (see chain_carry)
 // Tiles between two prefixes in the forward: 8; 16 where there are so few chains that passing prefixes on bounds the call.
 // us a call with 2 / 4 / 8 / 16: B1 L4096 J768 20.5 / 18.8 / 18.1 / 19.2; B1 L32768 J256 of the paper's layer in bf16 109 /
@@ -516,22 +516,40 @@ __device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h, uint32_t G)
 {
     return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A workgroup leaves: true for the last one of the grid
-__device__ __forceinline__ bool leave_grid(WsHeader *h, uint32_t grid)
+// A workgroup leaves the call: the count is asked for (leave_ask), and its answer says whether it was the last one of the
+// grid (leave_last).  96 and more workgroups that take one tile each, and so are counted at about the same time, are counted
+// in two levels (a second round trip, 0.4 us, for the last of them; 96 counts on one address take 1.1 us); those of larger
+// calls are spread by their draws.
+__device__ __forceinline__ bool leave_two_levels(const TileQueues &t, uint32_t grid) { return t.one_each && grid >= 96; }
+__device__ __forceinline__ uint32_t leave_ask(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t grid)
 {
-    return __hip_atomic_fetch_add(&h->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == grid;
+    uint32_t *w = leave_two_levels(t, grid) ? hdr_word(h, done_word(wg % MAX_QUEUES)) : &h->done;
+    return __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// ... in two levels for 96 and more workgroups that all leave at about the same time (a second round trip, 0.4 us, for the
-// last of them; 96 counts on one address take 1.1 us); those of larger calls are spread by their draws.
-__device__ __forceinline__ bool leave_call(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t grid)
+__device__ __forceinline__ bool leave_last(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t grid, uint32_t before)
 {
-    if (grid < 96 || !t.one_each) return leave_grid(h, grid);
-    const uint32_t s = wg % MAX_QUEUES;
-    const uint32_t n = __hip_atomic_fetch_add(hdr_word(h, done_word(s)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-    if (n != (grid - s + MAX_QUEUES - 1) / MAX_QUEUES) return false;
-    return leave_grid(h, (uint32_t)MAX_QUEUES);
+    if (!leave_two_levels(t, grid)) return before + 1u == grid;
+    if (before + 1u != (grid - wg % MAX_QUEUES + MAX_QUEUES - 1) / MAX_QUEUES) return false;
+    return __hip_atomic_fetch_add(&h->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)MAX_QUEUES;
 }
+// Workgroups that take one tile each have drawn all they will ever draw, and read the epoch, before they start on it: they
+// are counted in the middle of the tile, by a wave that waits for the carry, and the last one counted resets the counters
+// while tiles are still at work.  Counted behind its output stores, a call ended with these round trips: B1 L333 J256 with the
+// harmonic convolution 11.0 -> 10.5 us, a training step of B7 L1024 J256 43.4 -> 41.9, of B3 L1777 J120 36.1 -> 34.3.
+// Only the call that wraps the epoch is counted at its end: it clears published words.
+__device__ __forceinline__ bool counts_early(const TileQueues &t, uint32_t epoch) { return t.one_each && epoch + 1u != EPOCH_MOD; }
 
+__device__ __forceinline__ void reset_header(WsHeader *hdr, uint32_t next_epoch, uint32_t tid, uint32_t nthreads)
+{
+    for (uint32_t q = tid; q < (uint32_t)MAX_QUEUES; q += nthreads) {
+        flag_store(hdr_word(hdr, ticket_word(q)), 0u);
+        flag_store(hdr_word(hdr, done_word(q)), 0u);
+    }
+    if (tid == 0) {
+        flag_store(&hdr->done, 0u);
+        flag_store(&hdr->epoch, next_epoch);
+    }
+}
 // End of a call, run by thread `tid` of the `nthreads` of the workgroup that left last: tickets and
 // the finished-workgroup count return to zero and the epoch advances.  When the epoch wraps, words of
 // EPOCH_MOD calls ago would become valid again: everything behind the lane table is cleared then
@@ -547,14 +565,7 @@ __device__ __forceinline__ void finish_call(WsHeader *hdr, size_t clear_from, ui
         for (size_t i = tid; i < n; i += nthreads)
             __hip_atomic_store(base + i, (tagged_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid < (uint32_t)MAX_QUEUES) {
-        flag_store(hdr_word(hdr, ticket_word(tid)), 0u);
-        flag_store(hdr_word(hdr, done_word(tid)), 0u);
-    }
-    if (tid == 0) {
-        flag_store(&hdr->done, 0u);
-        flag_store(&hdr->epoch, next);
-    }
+    reset_header(hdr, next, tid, nthreads);
 }
 
 // One link of a tile chain: P = T + M c, with M = lambda^TILE_T held as a double-float (h + q) and
