@@ -40,6 +40,7 @@ namespace cawn {
 #define CAWN_STAMP(k) do { } while (0)
 #endif
 
+typedef float v4f __attribute__((ext_vector_type(4)));
 template <int V> struct Vec;
 template <> struct Vec<1> {
     static __device__ __forceinline__ void ld(float (&d)[1], const float *p) { d[0] = *p; }
@@ -118,7 +119,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // that next block completes the output and stores it next to its own.
 // EACH: a prefix per tile, for calls on 32-lane rows with more tiles than workgroups (launch_fwd_tile).
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
-__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
+__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 32 && !EACH && !VALVE)) && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
     constexpr int V = 1;                           // lanes per thread
     constexpr int TILE_T = G::TILE_T, NSTEP = G::NSTEP, NSEG = G::NSEG, LPR = G::JB;
@@ -140,7 +141,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     static_assert(JB <= 256 && 256 % JB == 0, "a staged row must fit a wave");
     static_assert(NW >= 2, "one wave owns the chain, the others stage the next tile");
 
-    __shared__ __attribute__((aligned(16))) float sU[2 * NRTP][JBS];  // [stream*NRTP + rr][lane]
+    // ONE: a thread reads its rows from memory itself (see the loads below)
+    __shared__ __attribute__((aligned(16))) float sU[ONE ? 1 : 2 * NRTP][JBS];  // [stream*NRTP + rr][lane]
     // element (row, lane) of the staged rows as fp32
     auto su = [&](int r, int l) -> float {
         if constexpr (BF) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(&sU[r][0])[l] << 16);
@@ -229,10 +231,70 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
     TileId T{};
     if (ticket < qtiles) {
         T = tile_of(ticket);
-        stage_tile(T);
+        if constexpr (!ONE) stage_tile(T);
     }
 
-    wait_vm<0>();     // the first tile's staged rows
+    // ONE: the rows of my segment, HALO of the one before it among them, straight into registers.  Nothing has to be
+    // staged ahead in such a call, a thread's rows are its own, and the first of them are worked on while the
+    // last are on their way; without the staged tile in LDS a third workgroup fits a compute unit.  Staged, such a call went
+    // through its loads, its arithmetic and its stores one after the other on the whole chip, and 768 tiles of B4 L2048 J768
+    // took two rounds: 35.2 -> 25.1 us with this; B1 L4096 J768 17.8 -> 16.2.  (The KC - 1 rows that two
+    // segments share are read by both, the second time from a cache.)
+    constexpr int NRD = ONE ? NSTEP + HALO : 1;
+    float dm[NRD], da[NRD];
+    if constexpr (ONE) {
+        static_assert(!BF && !HC, "32-lane rows of long tiles are fp32");
+        // What the tile's threads share -- lane constants, logits -- goes to LDS by way of registers, asked for ahead of the
+        // rows: direct-to-LDS loads in flight would make the compiler wait for everything at the first read of LDS.
+        static_assert(NCR * JB / 4 <= NT && NT == TILE_T, "lane constants: four words a thread; logits: a thread's token");
+        const int cq = tid < NCR * JB / 4 ? tid : 0;
+        const v4f cv = *reinterpret_cast<const v4f *>(a.table + (size_t)CR::table_row(cq / (JB / 4)) * a.Jp + (size_t)T.lb * JB + cq % (JB / 4) * 4);
+        float lgv[VALVE ? GPB_MAX : 1], lgr[RET ? GPB_MAX : 1];
+        auto logit = [&](const float *p, int g) {
+            const int t = T.tt * TILE_T + tid, h = (T.lb * JB) / a.F + g;
+            return p[((size_t)T.b * a.L + (t < a.L ? t : a.L - 1)) * a.H + (h < a.H ? h : a.H - 1)];   // (beyond the end: never used)
+        };
+#pragma unroll
+        for (int g = 0; g < GPB_MAX; ++g) {
+            if constexpr (VALVE) lgv[g] = logit(a.valve, g < a.gpb ? g : 0);
+            if constexpr (RET) lgr[g] = logit(a.ret, g < a.gpb ? g : 0);
+        }
+        // Rows outside the call have the address of one inside it (a row before the first token wraps to the last one's):
+        // their values are not used.  One straight path, no branch between a load and its use: the compiler's waits are
+        // exact only there.
+        const int jl = T.lb * JB + lv;
+        const uint32_t jc4 = (uint32_t)(jl < a.J ? jl : 0) * 4u, ist4 = (uint32_t)ist32 * 4u;
+        const int first = T.tt == 0 ? 0 : T.tt * TILE_T - HALO, end = (T.tt + 1) * TILE_T < a.L ? (T.tt + 1) * TILE_T : a.L;
+        const uint32_t last = (uint32_t)(end - 1 - first) * ist4 + jc4, off0 = (uint32_t)(seg * NSTEP - (T.tt == 0 ? HALO : 0)) * ist4 + jc4;
+        const long long at = (long long)T.b * a.isb + (long long)first * a.ist;
+        const char *um = reinterpret_cast<const char *>(a.mag + at), *ua = reinterpret_cast<const char *>(a.ang + at);
+        // the rows before the first token: the carried history's
+        const bool from_hist = HALO > 0 && tail_in && T.tt == 0 && seg == 0;
+        const char *hm = reinterpret_cast<const char *>(tail_in ? tail_in + (size_t)T.b * HALO * 2 * a.J : a.mag + at);
+        auto ld = [](const char *p) { return __builtin_nontemporal_load(reinterpret_cast<const float *>(p)); };
+#pragma unroll
+        for (int r = 0; r < NRD; ++r) {
+            uint32_t off = off0 + (uint32_t)r * ist4;
+            off = off < last ? off : last;
+            if (r < HALO) {
+                const uint32_t h = (uint32_t)(r * 2) * (uint32_t)a.J * 4u + jc4;
+                dm[r] = ld(from_hist ? hm + h : um + off);
+                da[r] = ld(from_hist ? hm + h + (uint32_t)a.J * 4u : ua + off);
+            } else {
+                dm[r] = ld(um + off);
+                da[r] = ld(ua + off);
+            }
+        }
+        compiler_fence();       // (everything above is on its way before anything is waited for)
+        if (tid < NCR * JB / 4) *reinterpret_cast<v4f *>(&sC[tid / (JB / 4)][tid % (JB / 4) * 4]) = cv;
+#pragma unroll
+        for (int g = 0; g < GPB_MAX; ++g) {
+            if constexpr (VALVE) sV[g * TILE_T + tid] = lgv[g];
+            if constexpr (RET) sR[g * TILE_T + tid] = lgr[g];
+        }
+    } else {
+        wait_vm<0>();     // the first tile's staged rows
+    }
 
     float lr[V], li[V], pfr[V], pfi[V], psr[V], psi[V];
     float wm[KC1][V], wa[KC1][V], bm[V], ba[V];
@@ -332,6 +394,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
         // the start of the next)
         const int vgroup = a.F < JB ? (lv * V) / a.F : (JB > 32 && !HC && lv >= a.F - (T.lb * JB) % a.F ? 1 : 0);
         const int vbase = (VALVE || RET) ? vgroup * TILE_T + seg * NSTEP : 0;
+        // row r of my segment, HALO of the segment before it first
+        auto row_m = [&](int r) -> float { if constexpr (ONE) return dm[r]; else return su(seg * NSTEP + r, lv); };
+        auto row_a = [&](int r) -> float { if constexpr (ONE) return da[r]; else return su(NRTP + seg * NSTEP + r, lv); };
         // The mode switches are uniform over the launch; each combination gets its own straight-line
         // copy of the loop, so that the tokens' dependent chains (exp -> rcp -> sin/cos) interleave.
         auto front_end = [&](auto amp_c, auto small_c, auto mask_c) {
@@ -343,8 +408,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
             for (int k = 0; k < KC1 - 1; ++k) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    wnm[k % KC1][v] = zero_hist ? 0.f : (hist_bf ? hwm[k][v] : su(seg * NSTEP + k, lv * V + v));
-                    wna[k % KC1][v] = zero_hist ? 0.f : (hist_bf ? hwa[k][v] : su(NRTP + seg * NSTEP + k, lv * V + v));
+                    wnm[k % KC1][v] = zero_hist ? 0.f : (hist_bf ? hwm[k][v] : row_m(k));
+                    wna[k % KC1][v] = zero_hist ? 0.f : (hist_bf ? hwa[k][v] : row_a(k));
                 }
             }
 #pragma unroll
@@ -353,8 +418,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : (BF && !RET && !HC
             for (int i = 0; i < NSTEP; ++i) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    wnm[(i + HALO) % KC1][v] = su(seg * NSTEP + i + HALO, lv * V + v);
-                    wna[(i + HALO) % KC1][v] = su(NRTP + seg * NSTEP + i + HALO, lv * V + v);
+                    wnm[(i + HALO) % KC1][v] = row_m(i + HALO);
+                    wna[(i + HALO) % KC1][v] = row_a(i + HALO);
                 }
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
