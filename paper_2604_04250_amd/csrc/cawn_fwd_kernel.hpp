@@ -117,9 +117,10 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // them in order (every other group from the top block down): the lane of a block that borders the
 // next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
 // that next block completes the output and stores it next to its own.
-// EACH: a prefix per tile, for calls on 32-lane rows with more tiles than workgroups (launch_fwd_tile).
-template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
-__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 32 && !EACH && !VALVE)) && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
+// MANY: workgroups take several tiles (launch_fwd_tile); on 32-lane rows these calls pass a prefix on per tile (EACH).
+// Long tiles without it: a workgroup for every tile (ONE).
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool MANY>
+__global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF && !VALVE) && !RET && !HC) ? CAWN_FWD_WAVES + 1 : CAWN_FWD_WAVES) void fwd_kernel(const FwdArgs a)
 {
     constexpr int V = 1;                           // lanes per thread
     constexpr int TILE_T = G::TILE_T, NSTEP = G::NSTEP, NSEG = G::NSEG, LPR = G::JB;
@@ -127,11 +128,11 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
     constexpr int MW = JB / 32;                    // gate-mask words of a row
     static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
-    static_assert(!EACH || (JB == 32 && !G::SHORT), "a prefix per tile: long 32-lane tiles (see make_queues)");
-    constexpr bool ONE = JB == 32 && !G::SHORT && !EACH;     // such a call has a workgroup for every tile (launch_fwd_tile)
-    // (64-lane rows with retentions: at the register limit, the count in the middle spilled 6 more values; the paper's layer
+    static_assert(!MANY || !G::SHORT, "short tiles: one a workgroup (a head's)");
+    constexpr bool EACH = MANY && JB == 32, ONE = !MANY && !G::SHORT;
+    // (64-lane rows with retentions and several tiles a workgroup: at the register limit, the count in the middle spilled 6 more values; the paper's layer
     // in bf16, B1 L32768, 56.1 -> 57.3 us)
-    constexpr bool COUNT_EARLY = !EACH && !(JB == 64 && !G::SHORT && RET);
+    constexpr bool COUNT_EARLY = !EACH && !(JB == 64 && MANY && RET);
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
 
     if (tid == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // both round trips at once
-        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, HC ? (uint32_t)a.hcG : 1u);
+        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, HC && !ONE ? (uint32_t)a.hcG : 1u);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
     // all positions in a head (in step on one position they would all read and write one 128-byte
     // address class of the rows at a time, i.e. a part of the memory channels)
     auto tile_of = [&](uint32_t tk) {
-        if (HC) {
+        if (HC && !ONE) {
             const uint32_t n = (uint32_t)a.hcG, g = tk / n, p_ = tk - g * n;
             tk = g * n + ((g & 1u) ? n - 1u - p_ : p_);
         }
@@ -241,56 +242,69 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
     // took two rounds: 35.2 -> 25.1 us with this; B1 L4096 J768 17.8 -> 16.2.  (The KC - 1 rows that two
     // segments share are read by both, the second time from a cache.)
     constexpr int NRD = ONE ? NSTEP + HALO : 1;
-    float dm[NRD], da[NRD];
+    typedef std::conditional_t<BF, uint16_t, float> elem;
+    elem dm[NRD], da[NRD];
+    uint32_t dmh[KC1], dah[KC1];   // BF: the HALO first rows as the four-byte words that hold them, or the history's fp32 values
+    bool from_hist = false;
     if constexpr (ONE) {
-        static_assert(!BF && !HC, "32-lane rows of long tiles are fp32");
         // What the tile's threads share -- lane constants, logits -- goes to LDS by way of registers, asked for ahead of the
         // rows: direct-to-LDS loads in flight would make the compiler wait for everything at the first read of LDS.
-        static_assert(NCR * JB / 4 <= NT && NT == TILE_T, "lane constants: four words a thread; logits: a thread's token");
-        const int cq = tid < NCR * JB / 4 ? tid : 0;
-        const v4f cv = *reinterpret_cast<const v4f *>(a.table + (size_t)CR::table_row(cq / (JB / 4)) * a.Jp + (size_t)T.lb * JB + cq % (JB / 4) * 4);
-        float lgv[VALVE ? GPB_MAX : 1], lgr[RET ? GPB_MAX : 1];
-        auto logit = [&](const float *p, int g) {
-            const int t = T.tt * TILE_T + tid, h = (T.lb * JB) / a.F + g;
-            return p[((size_t)T.b * a.L + (t < a.L ? t : a.L - 1)) * a.H + (h < a.H ? h : a.H - 1)];   // (beyond the end: never used)
+        constexpr int NCQ = (NCR * JB / 4 + NT - 1) / NT, NLG = (TILE_T * GPB_MAX + NT - 1) / NT;
+        v4f cv[NCQ];
+        float lgv[VALVE ? NLG : 1], lgr[RET ? NLG : 1];
+#pragma unroll
+        for (int q = 0; q < NCQ; ++q) {
+            const int w = q * NT + tid < NCR * JB / 4 ? q * NT + tid : 0;
+            cv[q] = *reinterpret_cast<const v4f *>(a.table + (size_t)CR::table_row(w / (JB / 4)) * a.Jp + (size_t)T.lb * JB + w % (JB / 4) * 4);
+        }
+        auto logit = [&](const float *p, int i) {       // (beyond the end: a valid address, never used)
+            const int t = T.tt * TILE_T + i % TILE_T, g = i / TILE_T, h = (T.lb * JB) / a.F + (g < a.gpb ? g : 0);
+            return p[((size_t)T.b * a.L + (t < a.L ? t : a.L - 1)) * a.H + (h < a.H ? h : a.H - 1)];
         };
 #pragma unroll
-        for (int g = 0; g < GPB_MAX; ++g) {
-            if constexpr (VALVE) lgv[g] = logit(a.valve, g < a.gpb ? g : 0);
-            if constexpr (RET) lgr[g] = logit(a.ret, g < a.gpb ? g : 0);
+        for (int q = 0; q < NLG; ++q) {
+            if constexpr (VALVE) lgv[q] = logit(a.valve, q * NT + tid);
+            if constexpr (RET) lgr[q] = logit(a.ret, q * NT + tid);
         }
+        compiler_fence();       // (the rows in their order behind these, and)
         // Rows outside the call have the address of one inside it (a row before the first token wraps to the last one's):
         // their values are not used.  One straight path, no branch between a load and its use: the compiler's waits are
         // exact only there.
+        constexpr uint32_t ESZ = BF ? 2u : 4u;
         const int jl = T.lb * JB + lv;
-        const uint32_t jc4 = (uint32_t)(jl < a.J ? jl : 0) * 4u, ist4 = (uint32_t)ist32 * 4u;
+        const uint32_t jc = (uint32_t)(jl < a.J ? jl : 0), istb = (uint32_t)ist32 * ESZ;
         const int first = T.tt == 0 ? 0 : T.tt * TILE_T - HALO, end = (T.tt + 1) * TILE_T < a.L ? (T.tt + 1) * TILE_T : a.L;
-        const uint32_t last = (uint32_t)(end - 1 - first) * ist4 + jc4, off0 = (uint32_t)(seg * NSTEP - (T.tt == 0 ? HALO : 0)) * ist4 + jc4;
-        const long long at = (long long)T.b * a.isb + (long long)first * a.ist;
-        const char *um = reinterpret_cast<const char *>(a.mag + at), *ua = reinterpret_cast<const char *>(a.ang + at);
+        const uint32_t last = (uint32_t)(end - 1 - first) * istb + jc * ESZ, off0 = (uint32_t)(seg * NSTEP - (T.tt == 0 ? HALO : 0)) * istb + jc * ESZ;
+        const long long at = ((long long)T.b * a.isb + (long long)first * a.ist) * (long long)ESZ;
+        const char *um = reinterpret_cast<const char *>(a.mag) + at, *ua = reinterpret_cast<const char *>(a.ang) + at;
         // the rows before the first token: the carried history's
-        const bool from_hist = HALO > 0 && tail_in && T.tt == 0 && seg == 0;
-        const char *hm = reinterpret_cast<const char *>(tail_in ? tail_in + (size_t)T.b * HALO * 2 * a.J : a.mag + at);
-        auto ld = [](const char *p) { return __builtin_nontemporal_load(reinterpret_cast<const float *>(p)); };
+        from_hist = HALO > 0 && tail_in && T.tt == 0 && seg == 0;
+        const char *hm = tail_in ? reinterpret_cast<const char *>(tail_in + (size_t)T.b * HALO * 2 * a.J) : um;
+        auto ld = [](const char *p) { return __builtin_nontemporal_load(reinterpret_cast<const elem *>(p)); };
 #pragma unroll
         for (int r = 0; r < NRD; ++r) {
-            uint32_t off = off0 + (uint32_t)r * ist4;
+            uint32_t off = off0 + (uint32_t)r * istb;
             off = off < last ? off : last;
-            if (r < HALO) {
-                const uint32_t h = (uint32_t)(r * 2) * (uint32_t)a.J * 4u + jc4;
-                dm[r] = ld(from_hist ? hm + h : um + off);
-                da[r] = ld(from_hist ? hm + h + (uint32_t)a.J * 4u : ua + off);
+            const uint32_t h = ((uint32_t)(r * 2) * (uint32_t)a.J + jc) * 4u;
+            if (BF && r < HALO) {
+                dmh[r] = *reinterpret_cast<const uint32_t *>(from_hist ? hm + h : um + (off & ~3u));
+                dah[r] = *reinterpret_cast<const uint32_t *>(from_hist ? hm + h + (uint32_t)a.J * 4u : ua + (off & ~3u));
             } else {
-                dm[r] = ld(um + off);
-                da[r] = ld(ua + off);
+                const bool fh = r < HALO && from_hist;
+                dm[r] = ld(fh ? hm + h : um + off);
+                da[r] = ld(fh ? hm + h + (uint32_t)a.J * 4u : ua + off);
             }
         }
-        compiler_fence();       // (everything above is on its way before anything is waited for)
-        if (tid < NCR * JB / 4) *reinterpret_cast<v4f *>(&sC[tid / (JB / 4)][tid % (JB / 4) * 4]) = cv;
+        compiler_fence();       // (all of it on its way before anything is waited for)
 #pragma unroll
-        for (int g = 0; g < GPB_MAX; ++g) {
-            if constexpr (VALVE) sV[g * TILE_T + tid] = lgv[g];
-            if constexpr (RET) sR[g * TILE_T + tid] = lgr[g];
+        for (int q = 0; q < NCQ; ++q) {
+            const int w = q * NT + tid;
+            if (w < NCR * JB / 4) *reinterpret_cast<v4f *>(&sC[w / (JB / 4)][w % (JB / 4) * 4]) = cv[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NLG; ++q) {
+            if (VALVE && q * NT + tid < TILE_T * GPB_MAX) sV[q * NT + tid] = lgv[VALVE ? q : 0];
+            if (RET && q * NT + tid < TILE_T * GPB_MAX) sR[q * NT + tid] = lgr[RET ? q : 0];
         }
     } else {
         wait_vm<0>();     // the first tile's staged rows
@@ -315,7 +329,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
         uint32_t ticket_ahead;   // (only thread 0's copy is ever set or read; no initialiser, so no
                              // merge of values that would wait for the atomic right here)
         // (HC: the tickets of a head's lane blocks are drawn together, a multiple of hcG first)
-        const uint32_t hcG = HC ? (uint32_t)a.hcG : 1u;
+        const uint32_t hcG = HC && !ONE ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
             if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
             else if (ONE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
@@ -380,7 +394,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
         for (int k = 0; k < KC1; ++k)
 #pragma unroll
             for (int v = 0; v < V; ++v) hwm[k][v] = hwa[k][v] = 0.f;
-        const bool hist_bf = BF && HALO > 0 && tail_in && tt == 0 && seg == 0;
+        const bool hist_bf = !ONE && BF && HALO > 0 && tail_in && tt == 0 && seg == 0;
         if (hist_bf) {
 #pragma unroll
             for (int k = 0; k < HALO; ++k) {
@@ -395,8 +409,13 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
         const int vgroup = a.F < JB ? (lv * V) / a.F : (JB > 32 && !HC && lv >= a.F - (T.lb * JB) % a.F ? 1 : 0);
         const int vbase = (VALVE || RET) ? vgroup * TILE_T + seg * NSTEP : 0;
         // row r of my segment, HALO of the segment before it first
-        auto row_m = [&](int r) -> float { if constexpr (ONE) return dm[r]; else return su(seg * NSTEP + r, lv); };
-        auto row_a = [&](int r) -> float { if constexpr (ONE) return da[r]; else return su(NRTP + seg * NSTEP + r, lv); };
+        auto own = [&](int r, const elem(&d)[NRD], const uint32_t(&dh)[KC1]) -> float {
+            if constexpr (!BF) return d[r];
+            else if (r >= HALO) return from_bf16(d[r]);
+            else return __uint_as_float(from_hist ? dh[r] : (lv & 1) ? dh[r] & 0xffff0000u : dh[r] << 16);   // (even strides: odd lanes are the upper halves)
+        };
+        auto row_m = [&](int r) -> float { if constexpr (ONE) return own(r, dm, dmh); else return su(seg * NSTEP + r, lv); };
+        auto row_a = [&](int r) -> float { if constexpr (ONE) return own(r, da, dah); else return su(NRTP + seg * NSTEP + r, lv); };
         // The mode switches are uniform over the launch; each combination gets its own straight-line
         // copy of the loop, so that the tokens' dependent chains (exp -> rcp -> sin/cos) interleave.
         auto front_end = [&](auto amp_c, auto small_c, auto mask_c) {
@@ -944,41 +963,59 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((BF || (G::JB == 
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
 }
 
-// Workgroups of a kernel that fit on the chip (asked once per kernel); 0: the runtime would not say
-template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
+// Compute units of the device, and workgroups of a kernel that fit on it (asked once per kernel); 0: the runtime would not say
+static inline long long fwd_cus()
+{
+    static std::atomic<long long> known{0};
+    if (known.load(std::memory_order_relaxed) == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+        known.store(prop.multiProcessorCount, std::memory_order_relaxed);
+    }
+    return known.load(std::memory_order_relaxed);
+}
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool MANY>
 static long long fwd_resident()
 {
     static std::atomic<long long> known{0};
     if (known.load(std::memory_order_relaxed) == 0) {
-        int dev = 0, n = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<G, KC, VALVE, RET, BF, HC, EACH>, G::NT, 0) != hipSuccess)
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fwd_kernel<G, KC, VALVE, RET, BF, HC, MANY>, G::NT, 0) != hipSuccess)
             return 0;
-        known.store((long long)(n > 0 ? n : 1) * prop.multiProcessorCount, std::memory_order_relaxed);
+        known.store((long long)(n > 0 ? n : 1) * fwd_cus(), std::memory_order_relaxed);
     }
     return known.load(std::memory_order_relaxed);
 }
 
-template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool EACH>
-static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long jobs, hipStream_t s)
+template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool MANY>
+static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long wgs, hipStream_t s)
 {
-    const long long resident = fwd_resident<G, KC, VALVE, RET, BF, HC, EACH>();
-    if (resident <= 0) return hipErrorUnknown;
-    const long long wgs = jobs < resident ? jobs : resident;       // persistent grid: what fits on the chip
     FwdArgs b = a;
     b.tq = make_queues(units, (uint32_t)a.nT, wgs);
     if (G::SHORT) b.tq.group = 64;      // (one group: no prefixes)
-    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC, EACH>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
+    hipLaunchKernelGGL((fwd_kernel<G, KC, VALVE, RET, BF, HC, MANY>), dim3((unsigned)wgs), dim3(G::NT), 0, s, b);
     return hipGetLastError();
 }
 
-// The carry scheme of a call: a prefix per tile for 32-lane rows with more tiles than workgroups (EACH), a prefix per
-// group of tiles otherwise (see make_queues).  A kernel each: EACH knows that its workgroups take several tiles from one
-// counter, the other one on long 32-lane rows that each of its workgroups takes one tile (ONE) and looks for no next one.
-// With both schemes in one kernel, and every tile asking whether there is a next one to draw, the first kind was 1 - 2.5 %
-// slower (B16 L1000 J768 53.9 us against 52.4, B6 L3001 J768 57.7 against 57.0) and the second 4 % (B1 L4096 J768 16.8
-// against 16.0, B1 L16300 J256 20.9 against 20.3).
+// Two kernels of long tiles.  ONE: a workgroup for every tile, rows straight into registers, the carry by groups of tiles.
+// MANY: as many workgroups as fit on the chip, each with the next tile's rows on their way to LDS while it works on one; on
+// 32-lane rows a prefix per tile (see make_queues).  (Both schemes in one kernel: the first kind 1 - 2.5 % slower, B16 L1000 J768
+// 53.9 us against 52.4, the second 4 %.)
+// A call may have more tiles than fit as workgroups of ONE at a time: the others start as these end, and still draw in
+// the chains' order.  They start with nothing on its way, and where there are many of them MANY is ahead.  us MANY / ONE:
+//   32 lanes, constant retention, tau  : B1 L9000 J768 (864 tiles) 37.3 / 35.1, B1 L60000 J128 (940) 56.2 / 42.5; B1 L16384 J768 (1536)
+//     55.4 / 56.6, B1 L32768 J768 (3072) 91 / 114.  768 of them fit at a time; beyond that the chains should be dealt to four and more
+//     counters, with two the first draws take longer: B3 L8192 J320 (960, 30 chains) 38.8 / 40.4
+//   32 lanes, valve or retentions      : B1 L6400 J768 (600) 34.7 / 29.7 valve, 40.4 / 36.3 both; B1 L32768 J256 (1024) 56.4 / 49.1; (1536) 57.8 /
+//     58.9, 66.2 / 63.8, 65.2 / 68.0
+//   64 lanes: bf16 B11 L2500 J256 (880) 39.1 / 31.4, B8 L2048 J768 (1536) 48.5 / 44.1, B8 L8192 J256 (2048) 59.5 / 59.6, B1 L32768
+//     J768 (3072) 83.8 / 95.9; harmonic convolution (1536) 57.8 / 55.0, (2048) 72.6 / 75.4
+//   64 lanes with retentions: bf16 and harmonic convolution B1 L32768 J256 (1024) 56.4 / 48.0, (2048) 78.8 / 74.1, B8 L8192 J768 (6144) 187 / 192
+//   bf16 with the valve alone: B1 L9000 J768 (864) 43.9 / 34.3, B1 L2048 J4096 (1024) 46.5 / 34.8, (1536) 51 / 51 and 57.8 / 62
+// bf16 without retentions needs fewer registers in MANY, of which 768 workgroups fit, than in ONE, of which 512 do: in
+// between every workgroup of MANY has one tile and ONE takes a second round, B1 L8192 J768 (768) 28.8 / 31.1.
+// Heads of several 64-lane blocks take their blocks one after the other in one workgroup: always MANY.
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 {
@@ -986,10 +1023,19 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
     if (a.nLB != (a.J + G::JB - 1) / G::JB || a.nT != (a.L + G::TILE_T - 1) / G::TILE_T) return hipErrorInvalidValue;
     const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
     const long long jobs = (long long)units * a.nT;
-    if constexpr (G::JB == 32 && !G::SHORT) {
-        if (jobs > fwd_resident<G, KC, VALVE, RET, BF, HC, false>()) return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs, s);
+    if constexpr (!G::SHORT) {
+        constexpr bool W64 = G::JB == 64;
+        const int per_cu = W64 && RET ? 8 : W64 && (HC || !VALVE) ? 7 : W64 || VALVE || RET || units % 4 == 0 ? 4 : 3;      // (tiles a compute unit)
+        const long long one = fwd_resident<G, KC, VALVE, RET, BF, HC, false>(), many = fwd_resident<G, KC, VALVE, RET, BF, HC, true>();
+        if (one <= 0 || many <= 0) return hipErrorUnknown;
+        if (a.hcG > 1 || jobs > per_cu * fwd_cus() || (jobs > one && jobs <= many))
+            return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s);   // persistent: what fits on the chip
+        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
+    } else {
+        const long long fit = fwd_resident<G, KC, VALVE, RET, BF, HC, false>();
+        if (fit <= 0) return hipErrorUnknown;
+        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs < fit ? jobs : fit, s);
     }
-    return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
 }
 
 // The tile shape of a call (the host computed nT and nLB from the same rule): 64-lane rows with the harmonic

@@ -1,8 +1,8 @@
 """GPU parity of the forward on its long tiles, at sizes where these can go wrong, against the fp64 oracle through the C ABI:
 256 tokens x 32 lanes in fp32, 128 x 64 with the harmonic convolution (bf16 without it: test_gpu_bf16).  4200 tokens are
-more than the 64-token tiles are taken for.  "few" calls have a workgroup for every tile and pass prefixes on per group
-of tiles; "many" have more tiles than the chip holds workgroups (two per compute unit, 512) and, in fp32 on 32-lane rows,
-a kernel of their own that passes a prefix on per tile.  Bar as in the other parity tests; gate masks bit for bit."""
+more than the 64-token tiles are taken for.  Up to 768 - 2048 tiles a call has a workgroup for every tile, whose threads read
+their rows themselves; beyond that workgroups take several, staged ahead in LDS, and in fp32 on 32-lane rows pass a prefix on
+per tile instead of per group of tiles.  Bar as in the other parity tests; gate masks bit for bit."""
 import numpy as np
 import pytest
 
@@ -85,6 +85,21 @@ def test_long_tiles_harmonic_convolution(B, H, F, bf16):
 @pytest.mark.parametrize("bf16", [False, True])
 def test_long_tiles_harmonic_convolution_with_logits(B, H, F, valve, ret, bf16):
     _check(B, H, F, 3, valve=valve, ret=ret, hconv=True, bf16=bf16, seed=3)
+
+
+# Either side of the lines between a workgroup for every tile and workgroups that take several (17 and 33 tiles a chain, 256
+# compute units): 32-lane rows 768 tiles, 1024 where the chains are a multiple of four or a head has logits; 64-lane rows 1792,
+# 2048 with retentions (bf16 without the harmonic convolution: test_gpu_bf16).  The first of each pair has more tiles than the
+# chip holds workgroups of its kernel at a time.
+@pytest.mark.parametrize("B,F,valve,ret,hconv,bf16", [
+    (45, 24, False, False, False, False), (46, 24, False, False, False, False), (60, 24, False, False, False, False), (61, 24, False, False, False, False),
+    (60, 32, True, False, False, False), (61, 32, True, False, False, False), (60, 32, False, True, False, False), (61, 32, False, True, False, False),
+    (60, 32, True, True, False, False), (61, 32, True, True, False, False),
+    (54, 64, False, False, True, False), (55, 64, False, False, True, False), (62, 64, True, True, True, False), (63, 64, True, True, True, False),
+    (54, 64, True, False, True, True), (55, 64, True, False, True, True),
+    (62, 32, True, True, True, True), (63, 32, True, True, True, True)])
+def test_long_tiles_around_the_line_between_one_and_several_a_workgroup(B, F, valve, ret, hconv, bf16):
+    _check(B, 1, F, 3, valve=valve, ret=ret, hconv=hconv, bf16=bf16, seed=4)
 
 
 # 64-token tiles, long tiles with a workgroup each, rows of 64 lanes; every one with more than 96 workgroups, which are counted
