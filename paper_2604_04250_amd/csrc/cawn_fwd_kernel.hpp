@@ -10,12 +10,13 @@
 //               aggregate E and finds its carry in one of two ways: it folds the aggregates before it
 //               in its group of tiles into one link on the prefix of the group before (chain_carry; on
 //               short tiles the whole chain is one group, and no prefix is passed on), or, in calls on
-//               32-lane rows with more tiles than workgroups, it looks back over earlier tiles until it
+//               32-lane rows whose workgroups take several tiles, it looks back over earlier tiles until it
 //               meets one that already knows its inclusive prefix, and publishes its own (look_back).
 // After the carry is known each thread replays its NSTEP tokens from the true incoming state,
 // clamps and stores.  Per token-lane HBM traffic: 8 bytes in, 8 bytes out.
 //
-// Scheduling.  The kernel is persistent: about as many workgroups as fit on the chip are launched
+// Scheduling.  Small calls have a workgroup for every tile, whose threads read their rows into registers; larger ones run
+// the persistent kernel (MANY, see launch_fwd_tile for the line): about as many workgroups as fit on the chip are launched
 // and each loops over tiles, handed out by atomic tickets in the order (time tile, batch row,
 // lane block) (see TileQueues).  Tickets go out in time order, so a tile only ever waits for tiles that a running
 // workgroup already holds; all chains advance together, so tiles that happen to be slow (some
@@ -130,6 +131,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
     static_assert(!MANY || !G::SHORT, "short tiles: one a workgroup (a head's)");
     constexpr bool EACH = MANY && JB == 32, ONE = !MANY && !G::SHORT;
+    // One tile a workgroup, known at compile time: no loop, nothing kept across it.  (A short tile's head of several blocks: its
+    // workgroup takes them all.)  On short tiles of 32 lanes the loop cost 20 - 30 registers and, with retentions, 2 - 10 spilled
+    // ones: training step B3 L1777 J120 34.5 -> 33.5 us.
+    constexpr bool SINGLE = !MANY && !(G::SHORT && HC);
     // (64-lane rows with retentions and several tiles a workgroup: at the register limit, the count in the middle spilled 6 more values; the paper's layer
     // in bf16, B1 L32768, 56.1 -> 57.3 us)
     constexpr bool COUNT_EARLY = !EACH && !(JB == 64 && MANY && RET);
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         const uint32_t hcG = HC && !ONE ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
             if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
-            else if (ONE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
+            else if (SINGLE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
             else ticket_ahead = next_ticket_of(a.hdr, hcG);
         }
 
@@ -528,14 +533,14 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                 if (RET) sP[seg][lv * V + v] = Pth[v];
             }
         }
-        if (!ONE && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+        if (!SINGLE && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
         lds_barrier();
         CAWN_STAMP(3);
 
         // ---- start staging the next tile (it lands during this tile's communication phase)
-        const uint32_t next_ticket = ONE ? NO_TICKET : (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
+        const uint32_t next_ticket = SINGLE ? NO_TICKET : (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
         TileId Tn{};
-        if (!ONE && next_ticket < qtiles) {
+        if (!SINGLE && next_ticket < qtiles) {
             Tn = tile_of(next_ticket);
             stage_tile(Tn);
         }
@@ -947,7 +952,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             }
         }
 
-        if (ONE) break;
+        if (SINGLE) break;
         ticket = next_ticket;
         T = Tn;
     }
@@ -1030,6 +1035,8 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
         if (one <= 0 || many <= 0) return hipErrorUnknown;
         if (a.hcG > 1 || jobs > per_cu * fwd_cus() || (jobs > one && jobs <= many))
             return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s);   // persistent: what fits on the chip
+        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
+    } else if constexpr (!HC) {
         return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
     } else {
         const long long fit = fwd_resident<G, KC, VALVE, RET, BF, HC, false>();
