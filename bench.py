@@ -475,16 +475,21 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
                       "buffer_sets_rotated": nsets}}
     bflag = lambda x: "true" if x else "false"
     fwd_tile = "FwdTile<32,64,256>" if hconv or bf16 else "FwdTile<32,32,256>"     # (long calls)
-    # (32-lane rows with more tiles than workgroups, two per compute unit: a prefix per tile)
-    each = fwd_tile == "FwdTile<32,32,256>" and B * -(-L // 256) * -(-J // 32) > 512
-    fwd_label = f"fwd_kernel<{fwd_tile},{Kc},{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(each)}>"
+    # (whether a workgroup takes several tiles: the line at launch_fwd_tile, for 256 compute units)
+    w64 = hconv or bf16
+    chains = B * -(-J // (64 if w64 else 32))
+    tiles = chains * -(-L // (128 if w64 else 256))
+    per_cu = (8 if w64 and ret_on else 7 if w64 and (hconv or not valve_on) else
+              4 if w64 or valve_on or ret_on or chains % 4 == 0 else 3)
+    many = tiles > 256 * per_cu or bool(hconv and F > 64) or (bf16 and not hconv and not ret_on and 512 < tiles <= 768)
+    fwd_label = f"fwd_kernel<{fwd_tile},{Kc},{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(many)}>"
     bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)}>"
     extra = valve_on or ret_on or bf16 or unfused or hconv
     if paper:
         out["config"]["layer"] = ("the paper's statement of the layer: H=4, K=64 (Sec. 4.3), conv kernel 3 (Sec. 3.2), "
                                   "softplus amplitude, per-head valve, data-dependent retention (Sec. 3.3)")
     if unfused:
-        fwd_label = f"2 x syntax_conv_kernel<4,4> + fwd_kernel<FwdTile<32,32,256>,0,false,false,false,false,{bflag(each)}> (one event span; the path's own 16 B per token-lane)"
+        fwd_label = f"2 x syntax_conv_kernel<4,4> + fwd_kernel<FwdTile<32,32,256>,0,false,false,false,false,{bflag(many)}> (one event span; the path's own 16 B per token-lane)"
     out["config"]["activations"] = "bfloat16 in memory, fp32 arithmetic and state" if bf16 else "fp32"
     if hconv:
         out["config"]["epilogue"] = "depth-wise harmonic convolution (3 taps per (plane, head) channel) fused behind the clamp"
