@@ -483,7 +483,13 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
               4 if w64 or valve_on or ret_on or chains % 4 == 0 else 3)
     many = tiles > 256 * per_cu or bool(hconv and F > 64) or (bf16 and not hconv and not ret_on and 512 < tiles <= 768)
     fwd_label = f"fwd_kernel<{fwd_tile},{Kc},{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(many)}>"
-    bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)}>"
+    # (whether a backward tile's gradients are staged a tile ahead: the line at launch_bwd_vkp, for 512 workgroups)
+    bchains = B * -(-J // 32)
+    btiles = bchains * -(-L // 128)
+    halves = 4 if hconv else (4 if bf16 else 2) if valve_on and ret_on else 8 if bf16 else 3 if ret_on else 4
+    late = ((bchains <= (16 if ret_on else 32) or 2 * btiles <= halves * 512) if btiles > 512 else
+            valve_on != ret_on and not hconv and 2 * btiles <= 512) if valve_on or ret_on else False
+    bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(not late)}>"
     extra = valve_on or ret_on or bf16 or unfused or hconv
     if paper:
         out["config"]["layer"] = ("the paper's statement of the layer: H=4, K=64 (Sec. 4.3), conv kernel 3 (Sec. 3.2), "

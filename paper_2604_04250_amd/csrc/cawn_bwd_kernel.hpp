@@ -19,6 +19,7 @@
 // Parameter gradients leave each tile as per-lane partial sums (fixed order inside the tile) and
 // are summed over tiles by a second kernel in a fixed order: results are bitwise repeatable.
 #pragma once
+#include <atomic>
 #include <type_traits>
 
 #include "cawn_internal.hpp"
@@ -112,7 +113,7 @@ __device__ __forceinline__ bool head_sum_lane(int lv, int vwidth)
 // the rows.  The tap gradients d w_i = sum dC[k] Z[k+i-1] = sum_k' Z[k'] dC[k'-i+1] pair a thread's own
 // clamped state Z (rebuilt in the front-end) with the same three gradients, read again from LDS there; they
 // leave the tile as 8 more rows of per-lane partial sums.
-template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC = false>
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
 __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_kernel(const BwdArgs a)
 {
     static_assert(!HC || (PARAM && V == 1), "harmonic convolution: with the state rebuild, one lane per thread");
@@ -122,6 +123,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // of its sin and cos between the front-end and the reverse pass, park the conv taps in LDS during
     // the reverse pass and fetch the reverse-pass constants after the front-end.
     constexpr bool LEAN = VALVE || RET;
+    static_assert(AHEAD || LEAN, "the other kernels stage a tile ahead in every call");
     constexpr int TILE_T = BwdGeom::TILE_T, NSTEP = BwdGeom::NSTEP, NSEG = BwdGeom::NSEG, LPR = BwdLPR;
     constexpr int JB = V * LPR;
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
@@ -143,25 +145,32 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         if constexpr (BF) return from_bf16(reinterpret_cast<const uint16_t *>(&sU[r][0])[l]);
         else return sU[r][l];
     };
-    // The upstream gradients of a tile are staged in LDS a tile ahead (direct-to-LDS loads issued
+    // AHEAD: the upstream gradients of a tile are staged in LDS a tile ahead (direct-to-LDS loads issued
     // while the previous tile is in its front-end, behind the harmonic convolution in its reverse pass), so that a
     // tile starts its local adjoint, and publishes its aggregate, without waiting for memory: loaded at the top of a
-    // tile they return behind the previous tile's output stores.  (Kernels with the valve or retentions, which loaded
-    // them there: training steps of B8 L8192 H4 F64 conv 3 219 -> 214 us, in bf16 225 -> 211, with the harmonic convolution
-    // 270 -> 263, in bf16 278 -> 256, with the valve alone B8 L8192 H12 F64 486 -> 479; and no register spilled without it.)
+    // tile they return behind the previous tile's output stores.  (Kernels with the valve or retentions, us with them
+    // loaded there and with AHEAD: B8 L8192 H12 F64 conv 3 with the valve in bf16 312 and 297, with retentions 312 and 305, with
+    // both 349 and 336, in bf16 393 and 349; B8 L8192 H4 F64 with both 131 and 126, in bf16 144 and 132.)
+    // The next tile must be known early for that, so a workgroup draws it before it knows its own tile's carry, and
+    // whoever draws first need not be the one who finishes first.  Where chains are few, a tile that continues a chain waits
+    // so for the workgroup of one far behind; and a workgroup's first tile gains nothing.  Kernels with the valve or
+    // retentions are there without AHEAD (launch_bwd_vkp has the line): the next tile is drawn once the reverse pass is
+    // done, and gradients and logits are loaded at the tile's top straight into registers (REGS) -- behind the harmonic
+    // convolution, which reads three neighbouring lanes of each twice, staged there.
     // The 32 KB this takes fit beside the rest
     // only because arrays with disjoint lifetimes share storage: the conv-gradient halo rows (written
     // after the reverse pass) lie over the segment aggregates (dead by then), and the partial-sum
     // staging lies over the input rows (dead after the last weight-gradient read, one more barrier).
+    constexpr bool REGS = !AHEAD && !HC;
     constexpr int RB_ROW = HC ? 4 + HC_ROWS : 4;
     constexpr int NRZ = staged_rows<TILE_T, JBS, 0>();                // staged rows per gradient stream
-    __shared__ __attribute__((aligned(16))) float sDz[2 * NRZ][JBS];    // [stream*NRZ + token][lane]
+    __shared__ __attribute__((aligned(16))) float sDz[REGS ? 1 : 2 * NRZ][JBS];    // [stream*NRZ + token][lane]
     // ... and with them the four lane constants the local adjoint needs (lambda, lambda^NSTEP): a wave's
     // memory operations complete in issue order, so a load issued at the top of a tile returns only after
     // the previous tile's output stores have been acknowledged
     // HC: ... and the lane block's harmonic-convolution taps (table rows R_W0 + 2 KC + 0 .. 7)
     // (RET: and the retention bias, row RB_ROW; the tile's logits are staged in sR)
-    __shared__ float sLam[RB_ROW + (RET ? 1 : 0)][JB];
+    __shared__ float sLam[REGS ? 1 : RB_ROW + (RET ? 1 : 0)][JB];
     // HC: the gradients of the two lanes beside the lane block, [plane][side: lane -1, lane JB][token]
     __shared__ float sEdge[HC ? 4 * NRZ : 1];
     constexpr int N_EB = NW * 2 * JB, N_HALO = NW * HALO1 * 2 * JB;
@@ -171,7 +180,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     __shared__ float sCarry[2][JB];
     // (bf16 rows are half as large and the harmonic convolution adds 8 partial rows: that combination has LDS to
     // spare and keeps the staging in an array of its own)
-    constexpr bool RED_OVER_ROWS = !(BF && HC);
+    constexpr bool RED_OVER_ROWS = !(BF && HC) && !REGS;
     __shared__ float sRedOwn[(PARAM && !RED_OVER_ROWS) ? NW : 1][ROWS][JB];
     static_assert(!RED_OVER_ROWS || (size_t)NW * ROWS * JB <= (size_t)2 * NRTP * JBS, "the partial-sum staging fits over the input rows");
     float (*sRed)[ROWS][JB] = RED_OVER_ROWS ? reinterpret_cast<float (*)[ROWS][JB]>(&sU[0][0]) : sRedOwn;
@@ -182,14 +191,14 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     __shared__ float sPb[RET ? NW : 1][JB];                        // product of each wave's retentions
     float (*sPt)[JB] = &sPb[0];                 // product of the tile's retentions (head group; the first wave's own is read by nobody)
     __shared__ float sRp[RET ? BwdGeom::TILE_T * GPB_MAX : 1];       // retention-logit gradient terms per (group, token)
-    __shared__ float sR[RET ? BwdGeom::TILE_T * GPB_MAX : 1];  // retention logits, staged with the gradients
+    __shared__ float sR[RET && !REGS ? BwdGeom::TILE_T * GPB_MAX : 1];  // retention logits, staged with the gradients
     __shared__ uint32_t sTicket[2], sLast, sEpoch;     // tickets of this tile and the next one
 
     const int tid_ = threadIdx.x;
     const float *tail_in = a.state_in ? a.state_in + (size_t)a.B * 2 * a.J : nullptr;
     const float *dtail_out = a.dstate_out ? a.dstate_out + (size_t)a.B * 2 * a.J : nullptr;
     const uint32_t chain_stride = (uint32_t)a.B * a.nLB;
-    const uint32_t ist32 = (uint32_t)a.ist;
+    const uint32_t ost32 = (uint32_t)a.ost, ist32 = (uint32_t)a.ist;
     uint32_t ticket_ahead = NO_TICKET;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
     if (tid_ == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // all three round trips at once
@@ -205,7 +214,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 
     // Persistent: each workgroup loops over tiles, handed out in chain order by an atomic ticket.  A
     // workgroup asks for the ticket of its next tile behind the first barrier of a tile (the next tile must be known early,
-    // for its staged gradients).  Every workgroup works through its tickets in
+    // for its staged gradients; without AHEAD behind the reverse pass, ahead of the output stores).  Every workgroup works
+    // through its tickets in
     // increasing order and a tile waits only for lower tickets, so the lowest unfinished ticket is always
     // some workgroup's current tile: no wait can last.  (Holding tickets two tiles ahead was tried: the
     // reserved tiles start later and their successors in other workgroups wait for them, +3 % to +30 %.)
@@ -365,8 +375,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             ci[1] = c0i;
         }
     };
-    {
-        if (it == 0) {      // a workgroup's first tile: nobody staged its gradients ahead
+    if constexpr (!REGS) {
+        if (!AHEAD || it == 0) {      // (a workgroup's first tile: nobody staged its gradients ahead)
             stage_dz(b, tt, lb, wave, NW);
             wait_vm<0>();
             lds_barrier();
@@ -415,6 +425,45 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         // (a tile that lies wholly inside the tensors takes the rows as they are: no per-row selects)
         if (full) dz_from_lds(std::true_type{});
         else dz_from_lds(std::false_type{});
+    } else {
+        const size_t gbase = ((size_t)b * a.osb + (size_t)(tt * TILE_T) * a.ost + (size_t)lb * JB) * ES;
+        const char *gre = reinterpret_cast<const char *>(a.dz_re) + gbase, *gim = reinterpret_cast<const char *>(a.dz_im) + gbase;
+        auto dz_from_rows = [&](auto full_c) {
+            constexpr bool FULL = decltype(full_c)::value;
+            typedef std::conditional_t<BF, uint16_t, float> elem;
+            // (read once: streamed, like the staged rows; bf16 rows are half lines and keep the default policy)
+            auto ldg = [](const char *p_) {
+                if constexpr (BF) return *reinterpret_cast<const elem *>(p_);
+                else return __builtin_nontemporal_load(reinterpret_cast<const elem *>(p_));
+            };
+            auto val = [](elem e_) -> float {
+                if constexpr (BF) return from_bf16(e_);
+                else return e_;
+            };
+            // rows and lanes outside the tensor: the address of one inside it, the value counts as zero
+            const uint32_t ln = (uint32_t)(FULL || active ? lv : 0) * ES, last = (uint32_t)(a.L - 1 - tt * TILE_T) * (ost32 * ES) + ln;
+            uint32_t off = (uint32_t)(seg * NSTEP) * (ost32 * ES) + ln;      // bytes
+            elem er[NSTEP], ei[NSTEP];
+#pragma unroll
+            for (int i = 0; i < NSTEP; ++i) er[i] = ei[i] = 0;
+            if (FULL || tt * TILE_T + wave * 2 * NSTEP < a.L) {      // (the wave has a row inside)
+#pragma unroll
+                for (int i = 0; i < NSTEP; ++i) {
+                    const uint32_t o_ = FULL || off < last ? off : last;
+                    er[i] = ldg(gre + o_);
+                    ei[i] = ldg(gim + o_);
+                    off += ost32 * ES;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NSTEP; ++i) {
+                const bool live = FULL || (active && t0 + i < a.L);
+                dzr[i][0] = live ? val(er[i]) : 0.f;
+                dzi[i][0] = live ? val(ei[i]) : 0.f;
+            }
+        };
+        if (full) dz_from_rows(std::true_type{});
+        else dz_from_rows(std::false_type{});
     }
     // lanes that share a valve: a head, or the part of it inside the 32-lane block (8, 16 or 32).
     // Where my tokens' entries start in sV / sVp is formed again at each use (from an opaque copy of
@@ -429,7 +478,14 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     };
     // ---- retention logits of my tokens (one per token and head: the lanes of a head read one address)
     float gm[RET ? NSTEP : 1][V];           // logit, then the retention itself
-    if (RET) {
+    if constexpr (RET && REGS) {
+        const float *rp = a.ret + (size_t)b * a.L * a.H + (active ? j0 : 0) / a.F;
+#pragma unroll
+        for (int i = 0; i < NSTEP; ++i) {
+            const int t = t0 + i < a.L ? t0 + i : a.L - 1;     // rows past the end: a valid address, the value is harmless
+            gm[i][0] = rp[(size_t)t * a.H];
+        }
+    } else if constexpr (RET) {
         const int rbase = valve_base();
 #pragma unroll
         for (int i = 0; i < NSTEP; ++i) gm[i][0] = sR[rbase + i];
@@ -438,12 +494,19 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     float lr[V], li[V], pnr[V], pni[V];
     float wmf[KC1][V], waf[KC1][V], bm[V], ba[V];   // taps for the front-end
     // (staged with the gradients; lanes beyond J hold table padding: their results are never stored)
-    lr[0] = sLam[0][lv];
-    li[0] = sLam[1][lv];
-    pnr[0] = sLam[2][lv];
-    pni[0] = sLam[3][lv];
+    if constexpr (!REGS) {
+        lr[0] = sLam[0][lv];
+        li[0] = sLam[1][lv];
+        pnr[0] = sLam[2][lv];
+        pni[0] = sLam[3][lv];
+    } else {
+        ldu<V>(lr, row(R_LR), jb);
+        ldu<V>(li, row(R_LI), jb);
+        ldu<V>(pnr, row(R_PSEGB + 2), jb);                       // lambda^NSTEP
+        ldu<V>(pni, row(R_PSEGB + 3), jb);
+    }
     // the forward state before my first token: the checkpoint of my segment (fetched here, so that it has arrived with
-    // the staged rows)
+    // the staged rows; REGS, two registers short until then: behind that wait, next to the constants of the reverse pass)
     float kr[V], ki[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) kr[v] = ki[v] = 0.f;
@@ -454,11 +517,12 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             BVec<V>::ld(ki, ck + a.J);
         }
     };
-    load_ckpt();
+    if (!REGS) load_ckpt();
     float rb[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) rb[v] = 0.f;
-    if (RET) rb[0] = sLam[RET ? RB_ROW : 0][lv];
+    if constexpr (RET && REGS) ldu<V>(rb, row(R_RBIAS), jb);
+    else if constexpr (RET) rb[0] = sLam[RB_ROW][lv];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         bm[v] = ba[v] = 0.f;
@@ -554,7 +618,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     BWD_STAMP(2);
     // (the next tile must be known by the time its gradients are staged; asked for here, the answer
     // arrives with this wave's staged rows, which it waits for below anyway)
-    if (tid == 0 && !a.tq.one_each)
+    if (AHEAD && tid == 0 && !a.tq.one_each)
         ticket_ahead = next_ticket_of(a.hdr, 1u);
     float Xr[V], Xi[V];     // adjoint entering my segment (from later segments), zero tile input
     float Cb[V];            // RET: product of the retentions of the segments after mine
@@ -631,7 +695,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // operations, in flight: their round trip is nobody's business here)
     if (wave == 0 && chained && feeds) wait_vm<(RET ? 3 : 2) * V>();
     else wait_stores_done();
-    if (tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
+    if (AHEAD && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
     if (LEAN && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
 #pragma unroll
         for (int k = 0; k < KC; ++k)
@@ -651,6 +715,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     float psr[V], psi[V], cth[V], sth[V], gam[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) { sth[v] = gam[v] = 0.f; cth[v] = 1.f; }
+    if (REGS) load_ckpt();
     if (!LEAN) {
         ldu<V>(psr, row(R_PSEGB + 2 * (NSEG - 1 - seg)), jb);    // adjoint: segments after mine
         ldu<V>(psi, row(R_PSEGB + 2 * (NSEG - 1 - seg) + 1), jb);
@@ -854,7 +919,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             stage_dz(nrest % a.B, a.nT - 1 - nrest / a.B, nlb, wave - 1, NW - 1);
         }
     };
-    if (!HC && wave != 0) stage_next();
+    if (AHEAD && !HC && wave != 0) stage_next();
     // (a workgroup without a next tile: one of the waves that would only wait counts it)
     const TileQueues tq_ = {a.tq.lq, a.tq.one_each, a.tq.group};
     if (counts_early(tq_, epoch) && tid == NT - 64 &&
@@ -902,7 +967,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     if (wave == 0) __builtin_amdgcn_s_setprio(0);
     lds_barrier_raw();
     BWD_STAMP(6);
-    if (HC && wave != 0) stage_next();
+    if (AHEAD && HC && wave != 0) stage_next();
 
     // ---- true adjoint entering my segment
     float Gr[V], Gi[V];
@@ -998,6 +1063,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     ARGS_AGAIN();
+    if (!AHEAD && tid == 0 && !a.tq.one_each)
+        ticket_ahead = next_ticket_of(a.hdr, 1u);
     // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order (behind a barrier)
     auto param_terms = [&]() {
         if constexpr (PARAM) {
@@ -1088,8 +1155,10 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // convolution 61 -> 27.  Training steps of B8 L8192 H4 F64 conv 3: 232 -> 219 us, with the convolution 300 -> 270,
     // in bf16 243 -> 225; B7 L1024 46.0 -> 44.5.  (The kernels without spills, whose staging lies over the input rows,
     // would need two more barriers.)
-    // (KC = 0 has no halo rows, hence no barrier of its own here)
-    if (LEAN && KC == 0) {
+    // (KC = 0 has no halo rows, hence no barrier of its own here.  Without AHEAD its partials follow the stores: valve alone,
+    // B10 L1139 H2 F96 28.3 us against 29.6, B21 L472 H5 F96 40.3 against 42.3.)
+    constexpr bool PART_FIRST = LEAN && (KC > 0 || AHEAD);
+    if (PART_FIRST && KC == 0) {
         param_terms();
         lds_barrier_raw();
         param_sums();
@@ -1169,11 +1238,11 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                     xw[r][1][v] = tagged_load(hin + (r * 2 + 1) * JB + v);
                 }
         };
-        if (LEAN) param_terms();
+        if (PART_FIRST) param_terms();
         if (want_rows) ask_rows();
         lds_barrier_raw();
     BWD_STAMP(8);
-        if (LEAN) param_sums();
+        if (PART_FIRST) param_sums();
         // (the valve kernels are at their register budget: their taps wait in LDS during the reverse
         // pass instead of in 2*KC registers)
         float wm[KC1][V], wa[KC1][V];
@@ -1328,14 +1397,15 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     ARGS_AGAIN();
-    if (!LEAN) {
+    if (!PART_FIRST) {
         param_terms();
-        if (PARAM) lds_barrier_raw();
+        if (PARAM || LEAN) lds_barrier_raw();
     BWD_STAMP(9);
         param_sums();
     }
 
     // ---- LDS is reused by the next tile
+    if (!AHEAD && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
     lds_barrier_raw();
     BWD_STAMP(10);
     ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
@@ -1352,26 +1422,59 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x);
 }
 
-// Persistent grid: what fits on the chip at once (asked once per kernel), never more than tiles.
-template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC = false>
-static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
+// Workgroups of a kernel that fit on the chip (asked once per kernel); 0: the runtime would not say
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
+static long long bwd_resident()
 {
-    static int per_cu = 0, cus = 0;
-    if (per_cu == 0) {
+    static std::atomic<long long> known{0};
+    if (known.load(std::memory_order_relaxed) == 0) {
         int dev = 0, n = 0;
         hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC>, BwdGeom::NSEG * BwdLPR, 0) != hipSuccess)
-            return hipErrorUnknown;
-        cus = prop.multiProcessorCount;
-        per_cu = n > 0 ? n : 1;
+        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>, BwdGeom::NSEG * BwdLPR, 0) != hipSuccess)
+            return 0;
+        known.store((long long)(n > 0 ? n : 1) * prop.multiProcessorCount, std::memory_order_relaxed);
     }
-    long long g = (long long)per_cu * cus;
+    return known.load(std::memory_order_relaxed);
+}
+
+// Persistent grid: what fits on the chip at once, never more than tiles.
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
+static hipError_t launch_bwd_tiles(const BwdArgs &a, hipStream_t s)
+{
+    long long g = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>();
+    if (g <= 0) return hipErrorUnknown;
     if (g > (long long)a.total_tiles) g = a.total_tiles;
     BwdArgs b = a;
     b.tq = make_queues((uint32_t)a.B * a.nLB, (uint32_t)a.nT, g);
-    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, b);
+    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, b);
     return hipGetLastError();
+}
+// Kernels with the valve or retentions: a tile's gradients staged ahead, or loaded at its top and the next tile drawn late
+// (see AHEAD in the kernel; the others always stage ahead).  Time ahead / time late, mean over 1500 calls of all conv lengths,
+// odd and even sizes, 512 workgroups (valve, retentions, both, fp32 | bf16 | with the harmonic convolution fp32 | bf16):
+//   more tiles than workgroups, up to 32 chains (16 with retentions): 1.05 1.05 1.04 | 1.06 1.05 1.02 | 1.04 1.05 1.08 | 1.05 1.04 1.06
+//     as many chains again                                          : 1.02 1.03 1.00 | 1.03 1.04 1.03 | 0.98 1.01 1.02 | 1.03 1.04 1.02
+//     more chains, 513 - 768 tiles (the one who is free first takes : 1.06 1.02 0.98 | 1.07 1.06 1.06 | 1.03 1.04 1.03 | 1.04 1.07 1.09
+//       - 1024 tiles                                 a second one)  : 1.03 1.01 1.00 | 1.07 1.05 1.02 | 1.01 1.02 1.02 | 1.05 1.03 1.05
+//       - 2048 tiles                                                : 0.99 0.99 0.97 | 1.05 1.02 0.99 | 0.99 1.01 1.01 | 1.03 1.01 1.03
+//       more                                                        : 1.00 0.99 0.97 | 1.01 0.99 0.94 | 0.97 0.97 0.99 | 1.00 1.00 1.00
+//   a workgroup for every tile, up to 256                           : 1.05 1.05 1.01 | 1.03 1.04 1.00 | 1.00 1.01 1.00 | 1.01 1.00 1.00
+//     257 - 512                                                     : 1.01 1.02 0.98 | 1.01 1.01 0.97 | 1.00 1.00 1.00 | 1.00 1.00 1.00
+// (B1 L32768 H4 F64: valve 94 / 86 us, retentions 96 / 90, both with the convolution 122 / 111)
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC>
+static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
+{
+    if constexpr (VALVE || RET) {
+        const long long fit = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, true>(), tiles = a.total_tiles;
+        if (fit <= 0) return hipErrorUnknown;
+        const int few = RET ? 16 : 32;
+        const int halves = HC ? 4 : VALVE && RET ? (BF ? 4 : 2) : BF ? 8 : RET ? 3 : 4;     // tiles for half the workgroups
+        const bool late = tiles > fit ? (long long)a.B * a.nLB <= few || 2 * tiles <= halves * fit
+                                      : VALVE != RET && !HC && 2 * tiles <= fit;
+        if (late) return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, false>(a, s);
+    }
+    return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, true>(a, s);
 }
 
 // The kernels of one family (gate mode x retention mode x harmonic convolution), one per conv_k.  Each family

@@ -170,12 +170,24 @@ def mask_from_gate(gate):
     return bits.view("<u4").reshape(B, L, W)
 
 
+def padded_rows(t, pad):
+    """The same values of [B, L, J] in rows of J + pad elements."""
+    w = torch.full((t.shape[0], t.shape[1], t.shape[2] + pad), float("nan"), device=t.device, dtype=t.dtype)
+    w[:, :, :t.shape[2]] = t
+    return w[:, :, :t.shape[2]]
+
+
+def _pad_desc(d, B, L, J, pad):
+    d.in_stride_t = d.out_stride_t = J + pad
+    d.in_stride_b = d.out_stride_b = max(L, 1) * (J + pad)
+
+
 def run_fwd_bwd(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, conv_clamp=50.0, out_clamp=100.0,
                 grad_clamp=100.0, state_in=None, dstate_out=None, want_param=True, want_dstate=True,
                 accumulate=0, preset=None, ws=None, valve=None, valve_eps=0.001, want_dvalve=True,
-                ret=None, ret_bias=None, want_dret=True, concat=False):
+                ret=None, ret_bias=None, want_dret=True, concat=False, pad=0):
     """Forward (to get the checkpoints) then backward through the C ABI.  inp additionally holds
-    dz_re, dz_im [B,L,J].  Returns dict of numpy arrays: dmag, dang, dgamma, dtheta, dconv_w, dconv_b,
+    dz_re, dz_im [B,L,J].  pad: every activation lies in rows of J + pad elements.  Returns dict of numpy arrays: dmag, dang, dgamma, dtheta, dconv_w, dconv_b,
     dstate_in (flat blob)."""
     J = H * F
     d = K.make_desc(B, L, H, F, conv_k=conv_k, amp_mode=amp_mode, gate_tau=gate_tau, conv_clamp=conv_clamp,
@@ -200,6 +212,9 @@ def run_fwd_bwd(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, conv_clamp=
         z_re, z_im = zc[:, :, :J], zc[:, :, J:]
         d.in_stride_t, d.in_stride_b = 2 * J, Lr * 2 * J
         d.out_stride_t, d.out_stride_b = 2 * J, Lr * 2 * J
+    if pad:
+        mag, ang, z_re, z_im = (padded_rows(t, pad) for t in (mag, ang, z_re, z_im))
+        _pad_desc(d, B, L, J, pad)
     st_in = dev(state_in)
     ckpt = torch.full((max(K.cawn_ckpt_bytes(d) // 4, 1),), float("nan"), device=DEV)
     ws = ws if ws is not None else Workspaces.get(d)
@@ -219,6 +234,8 @@ def run_fwd_bwd(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, conv_clamp=
         dz_re, dz_im = dzc[:, :, :J], dzc[:, :, J:]
         dxc = torch.full((B, max(L, 1), 2 * J), float("nan"), device=DEV)
         dmag, dang = dxc[:, :, :J], dxc[:, :, J:]
+    if pad:
+        dz_re, dz_im, dmag, dang = (padded_rows(t, pad) for t in (dz_re, dz_im, dmag, dang))
     nstate = K.cawn_state_bytes(d) // 4
     fill = float("nan") if preset is None else preset
     dgamma = torch.full((J,), fill, device=DEV) if want_param and ret is None else None
@@ -407,9 +424,9 @@ def run_hconv_fwd_bwd(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, out_c
 
 def run_fwd_bwd_bf16(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, grad_clamp=100.0, state_in=None,
                      dstate_out=None, want_param=True, valve=None, ret=None, ret_bias=None, valve_eps=0.001,
-                     concat=False):
+                     concat=False, pad=0):
     """Forward (for the checkpoints) then backward, bfloat16 activations.  dmag, dang come back as float32
-    (widened from what the kernel stored); the other gradients are fp32."""
+    (widened from what the kernel stored); the other gradients are fp32.  pad: as in run_fwd_bwd."""
     J = H * F
     d = K.make_desc(B, L, H, F, conv_k=conv_k, amp_mode=amp_mode, gate_tau=gate_tau, grad_clamp=grad_clamp,
                     gate_mode=0 if valve is None else 1, valve_eps=valve_eps, ret_mode=0 if ret is None else 1)
@@ -437,6 +454,9 @@ def run_fwd_bwd_bf16(inp, B, L, H, F, conv_k=0, amp_mode=0, gate_tau=0.0, grad_c
         dmag, dang = dxc[:, :, :J], dxc[:, :, J:]
         d.in_stride_t, d.in_stride_b = 2 * J, Lr * 2 * J
         d.out_stride_t, d.out_stride_b = 2 * J, Lr * 2 * J
+    if pad:
+        mag, ang, z_re, z_im, dz_re, dz_im, dmag, dang = (padded_rows(t, pad) for t in (mag, ang, z_re, z_im, dz_re, dz_im, dmag, dang))
+        _pad_desc(d, B, L, J, pad)
     st_in = dev(state_in)
     ckpt = torch.full((max(K.cawn_ckpt_bytes(d) // 4, 1),), float("nan"), device=DEV)
     ws = Workspaces.get(d)

@@ -236,7 +236,7 @@ def test_kernels_do_not_spill_and_keep_their_occupancy():
                 name = val.strip()
             elif name and ("fwd_kernel" in name or "bwd_kernel" in name or "step_kernel" in name):
                 if key.startswith("ScratchSize"):
-                    # boolean template arguments: forward (VALVE, RET, BF, HC, EACH), backward (PARAM, VALVE, RET, BF, HC)
+                    # boolean template arguments: forward (VALVE, RET, BF, HC, MANY), backward (PARAM, VALVE, RET, BF, HC, AHEAD)
                     flags = [f == "1" for f in re.findall(r"Lb([01])E", name)]
                     strict = True
                     allowed = 128     # (the compiler sometimes reserves a frame it never touches)
