@@ -141,9 +141,9 @@ def test_bf16_forward_long_tiles(H, F, valve, ret):
     assert _gpu().rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
 
 
-# Either side of the lines between a workgroup for every tile and workgroups that take several (33 tiles a chain, 256 compute
-# units): 512, 768 and 1792 tiles with a constant retention, of which those from 513 to 768 and from 1793 on share workgroups;
-# 1024 with the valve, 2048 with retentions
+# Either side of the lines between the kernel whose threads read their rows themselves and the one that stages them (33 tiles a
+# chain, 256 compute units): 512, 768 and 1792 tiles with a constant retention, of which those from 513 to 768, a workgroup
+# each, and from 1793 on, several a workgroup, are staged; 1024 with the valve, 2048 with retentions
 @pytest.mark.parametrize("B,valve,ret", [(15, False, False), (16, False, False), (23, False, False), (24, False, False), (54, False, False),
                                          (55, False, False), (31, True, False), (32, True, False), (62, False, True), (63, False, True)])
 def test_bf16_forward_around_the_line_between_one_and_several_a_workgroup(B, valve, ret):
@@ -153,10 +153,12 @@ def test_bf16_forward_around_the_line_between_one_and_several_a_workgroup(B, val
     _check_fwd(B, L, H, F, Kc, _inputs(B, L, H, F, Kc, 8370 + B), amp_mode=1 if valve else 0, valve=valve, ret=ret, tau=0.25, state=state)
 
 
+@pytest.mark.parametrize("B", [5, 13])
 @pytest.mark.parametrize("valve,ret", [(False, False), (True, True)])
-def test_bf16_forward_long_tiles_several_a_workgroup(valve, ret):
-    """825 tiles of 128 tokens x 64 lanes: more than the chip holds workgroups at a time."""
-    B, L, H, F, Kc = 5, 4200, 3, 96, 3
+def test_bf16_forward_long_tiles_more_than_fit(valve, ret, B):
+    """Tiles of 128 tokens x 64 lanes, the last block of a row half full, a head ending inside the second: 825, a workgroup
+    each, more than the chip holds at a time; 2145, several a workgroup."""
+    L, H, F, Kc = 4200, 3, 96, 3
     _check_fwd(B, L, H, F, Kc, _inputs(B, L, H, F, Kc, 8350 + valve), amp_mode=1 if valve else 0, valve=valve, ret=ret, tau=0.25)
 
 

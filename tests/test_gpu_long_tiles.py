@@ -40,48 +40,55 @@ def _check(B, H, F, Kc, valve=False, ret=False, hconv=False, bf16=False, concat=
     out = G.run_fwd(d, B, L, H, F, conv_k=Kc, amp_mode=amp, gate_tau=tau, want_ckpt=True, concat=concat, bf16=bf16, ws=ws,
                     state_in=G.pack_state(scan, tail if Kc > 1 else None), **mode, **hc)
     z = (ora["z_re"], ora["z_im"])
-    # (a checkpoint is the unclamped state before every eighth token; no state here reaches the clamp)
+    # (a checkpoint is the unclamped state before every eighth token, the oracle's output that state unless it was clamped)
     planes = np.stack(z, 2)
-    assert np.abs(planes).max() < 100.0
     before = np.concatenate([scan[:, None].astype(np.float64), planes[:, 7:L - 1:8]], 1)
+    free = np.abs(before) < 100.0
+    assert free.mean() > 0.9999
     if hconv:
         z = O.harmonic_conv(z[0], z[1], H, F, hc["hconv_w"], hc["hconv_b"])
     for k, want in (("z_re", z[0]), ("z_im", z[1])):
         e = G.bf16_err(out[k], want) if bf16 else G.rel_err(out[k], want) / TOL
         assert e <= 1.0, (k, e)
     assert np.array_equal(out["mask"], G.mask_from_gate(ora["gate"])), "gate mask differs"
-    assert G.rel_err(out["ckpt"].reshape(before.shape), before) <= TOL
+    assert G.rel_err(out["ckpt"].reshape(before.shape)[free], before[free]) <= TOL
     s, t = G.unpack_state(out["state_out"], B, J, Kc)
     assert G.rel_err(s, ora["scan_out"]) <= TOL
     if Kc > 1:
         assert np.array_equal(t, ora["tail_out"])
 
 
-# lanes that are no multiple of 4 (staged word by word) or of 32 (a ragged last block, a last mask word); few and many tiles
-@pytest.mark.parametrize("B,H,F", [(1, 1, 65), (2, 5, 24), (11, 1, 66), (32, 1, 30)])
+# lanes that are no multiple of 4 or of 32 (a ragged last block, a last mask word); few tiles, more than the chip holds
+# workgroups at a time (561 and 544), and workgroups that take several (1071 and 1037: staged word by word)
+@pytest.mark.parametrize("B,H,F", [(1, 1, 65), (2, 5, 24), (11, 1, 66), (32, 1, 30), (21, 1, 66), (61, 1, 30)])
 @pytest.mark.parametrize("Kc", [0, 2, 4])
 def test_long_tiles_odd_lanes(B, H, F, Kc):
     _check(B, H, F, Kc, concat=Kc == 2)
 
 
-# heads of a quarter, half, all and three of a 32-lane row; the last: 33 chains of 17 tiles
+# heads of a quarter, half, all and three of a 32-lane row; then a workgroup for each of 33 chains of 17 tiles; the last three:
+# workgroups that take several (1054, 1037 and 1071 tiles), with a last block that is half, three quarters and wholly full
 @pytest.mark.parametrize("valve,ret", [(True, False), (False, True), (True, True)])
-@pytest.mark.parametrize("B,H,F", [(1, 5, 8), (1, 3, 16), (2, 1, 96), (11, 3, 32)])
+@pytest.mark.parametrize("B,H,F", [(1, 5, 8), (1, 3, 16), (2, 1, 96), (11, 3, 32), (31, 3, 16), (61, 3, 8), (21, 3, 32)])
 def test_long_tiles_valve_and_retention(B, H, F, valve, ret):
     if valve and ret and F < 16:
         pytest.skip("heads of 8 with both logits are refused")
     _check(B, H, F, 3, valve=valve, ret=ret, seed=1)
 
 
-# heads inside a 64-lane row, of exactly one, of two and of four; the last two: more heads in flight than workgroups
-@pytest.mark.parametrize("B,H,F", [(1, 5, 4), (1, 3, 16), (1, 3, 32), (2, 3, 64), (1, 3, 128), (1, 3, 256), (8, 2, 64), (8, 2, 128)])
+# heads inside a 64-lane row, of exactly one, of two and of four; then 528 tiles, more than the chip holds workgroups at a time,
+# and heads of two blocks, more than workgroups that take them; the last two: workgroups that take several tiles (1848, 1815),
+# with a last row that is full and one that is three quarters full
+@pytest.mark.parametrize("B,H,F", [(1, 5, 4), (1, 3, 16), (1, 3, 32), (2, 3, 64), (1, 3, 128), (1, 3, 256), (8, 2, 64), (8, 2, 128),
+                                   (28, 2, 64), (55, 3, 16)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_long_tiles_harmonic_convolution(B, H, F, bf16):
     _check(B, H, F, 3, hconv=True, bf16=bf16, concat=F == 16, seed=2)
 
 
+# ... and the last: workgroups that take several of 2112 tiles, a second row of lanes that is half full
 @pytest.mark.parametrize("valve,ret", [(True, False), (False, True), (True, True)])
-@pytest.mark.parametrize("B,H,F", [(1, 3, 32), (1, 2, 64), (1, 2, 128), (1, 1, 256), (8, 2, 64)])
+@pytest.mark.parametrize("B,H,F", [(1, 3, 32), (1, 2, 64), (1, 2, 128), (1, 1, 256), (8, 2, 64), (32, 3, 32)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_long_tiles_harmonic_convolution_with_logits(B, H, F, valve, ret, bf16):
     _check(B, H, F, 3, valve=valve, ret=ret, hconv=True, bf16=bf16, seed=3)
@@ -133,3 +140,74 @@ def test_a_call_that_gave_up_leaves_the_workspace_ready(B, L, H, F, hconv):
     assert int(ws[:64].abs().sum()) == 0, "tickets"    # counters of queues 0 and 1
     for again in range(2):
         _check(B, H, F, 3, hconv=hconv, seed=4 + again, L=L, ws=ws)
+
+
+def _training_calls(B, L, H, F, ret, hconv=False, seed=0):
+    """A forward and a backward through the C ABI, conv 3, plain or with the valve and retentions; the workspace they share and
+    a function that makes one of the calls on a stream and returns what it writes."""
+    G = _gpu()
+    from paper_2604_04250_amd import binding as K
+    import torch
+    J, Kc = H * F, 3
+    g = torch.Generator(device=G.DEV)
+    g.manual_seed(9500 + seed)
+    n = lambda *s: torch.randn(s, device=G.DEV, generator=g)
+    d = K.make_desc(B, L, H, F, conv_k=Kc, gate_tau=0.0 if ret else 0.25, amp_mode=int(ret), gate_mode=int(ret), ret_mode=int(ret),
+                    hconv_k=3 if hconv else 0)
+    ws = torch.empty((K.cawn_workspace_bytes(d) + 3) // 4, dtype=torch.int32, device=G.DEV)
+    K.check(K.cawn_workspace_init(ws))
+    x, dz, cw, cb, ck = n(2, B, L, J), n(2, B, L, J), n(2, J, Kc) / 3 ** 0.5, 0.1 * n(2, J), n(K.cawn_ckpt_bytes(d) // 4)
+    valve, rl, rb = (n(B, L, H) * 3 - 3.9, n(B, L, H) * 1.5 - 2, torch.linspace(3, 0, F, device=G.DEV)) if ret else (None,) * 3
+    gamma = None if ret else 0.9 + 0.0999 * torch.rand(J, device=G.DEV, generator=g)
+    theta, hw, hb = torch.rand(J, device=G.DEV, generator=g) * np.pi, n(2, H, 3), n(2, H)
+
+    def fwd(stream=None):
+        z = torch.full((2, B, L, J), float("nan"), device=G.DEV)
+        tail = (None, z[0], z[1], None, ck, None, ws)
+        if hconv:
+            st = K.cawn_phase_accumulate_hconv_fwd(d, x[0], x[1], valve, rl, rb, gamma, theta, cw, cb, hw, hb, *tail, stream=stream)
+        elif ret:
+            st = K.cawn_phase_accumulate_ret_fwd(d, x[0], x[1], valve, rl, rb, theta, cw, cb, *tail, stream=stream)
+        else:
+            st = K.cawn_phase_accumulate_fwd(d, x[0], x[1], gamma, theta, cw, cb, *tail, stream=stream)
+        K.check(st)
+        return [z, ck]
+
+    def bwd(stream=None):
+        e = lambda *s: torch.full(s, float("nan"), device=G.DEV)
+        dx, dl, par = e(2, B, L, J), [e(B, L, H), e(B, L, H)] if ret else [], [e(J), e(2, J, Kc), e(2, J)]
+        dg, dh = [] if ret else [e(J)], [e(2, H, 3), e(2, H)] if hconv else []
+        up = (None, ck, dz[0], dz[1], None, dx[0], dx[1])
+        if hconv:
+            st = K.cawn_phase_accumulate_hconv_bwd(d, x[0], x[1], valve, rl, rb, gamma, theta, cw, cb, hw, hb, *up, *(dl or (None, None)),
+                                                   *(dg or (None,)), *par, *dh, None, ws, stream=stream)
+        elif ret:
+            st = K.cawn_phase_accumulate_ret_bwd(d, x[0], x[1], valve, rl, rb, theta, cw, cb, *up, *dl, *par, None, ws, stream=stream)
+        else:
+            st = K.cawn_phase_accumulate_bwd(d, x[0], x[1], gamma, theta, cw, cb, *up, *dg, *par, None, ws, stream=stream)
+        K.check(st)
+        return [dx] + dl + dg + par + dh
+    return ws, fwd, bwd
+
+
+# A workgroup for every tile, more than the chip holds at a time even alone: 960 tiles of 32 lanes, 768 with the valve and
+# retentions, 1536 of 64 lanes with the harmonic convolution (256 compute units; 3, 2 and 2 of them a compute unit)
+@pytest.mark.parametrize("B,L,H,F,ret,hconv", [(4, 4096, 15, 32, False, False), (4, 4096, 6, 64, True, False), (4, 4096, 12, 64, True, True)])
+def test_more_tiles_than_fit_on_two_streams(B, L, H, F, ret, hconv):
+    """Two forward + backward calls at the same time, a workspace each, no grid resident as a whole: results equal those of the
+    same calls one after the other, bit for bit, and no wait gave up."""
+    from paper_2604_04250_amd import binding as K
+    import torch
+    jobs = [_training_calls(B, L, H, F, ret, hconv, seed=s) for s in range(2)]
+    ref = [[t.clone() for t in fwd() + bwd()] for _, fwd, bwd in jobs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]    # (default priority)
+    for _ in range(3):
+        got = []
+        for (_, fwd, bwd), s in zip(jobs, streams):
+            with torch.cuda.stream(s):                      # allocations belong to the stream
+                got.append(fwd(s) + bwd(s))
+        torch.cuda.synchronize()
+        for (ws, _, _), r, o in zip(jobs, ref, got):
+            K.check(K.cawn_workspace_status(ws))
+            assert all(torch.equal(a, b) for a, b in zip(r, o))
