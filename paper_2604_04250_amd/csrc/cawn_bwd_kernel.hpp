@@ -1419,7 +1419,13 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     if (tid_ == 0)
         sLast = leave_last(a.hdr, a.tq, blockIdx.x, gridDim.x, leave_ask(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     __syncthreads();
-    if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x);
+    if (sLast) {
+        auto in = [](const uint32_t *p, const float *from, size_t n) { return from && (size_t)(reinterpret_cast<const float *>(p) - from) < n; };
+        const size_t logits = (VALVE || RET) ? (size_t)a.B * a.G * a.L : 0;
+        finish_call(a.hdr, a.clear_from, epoch, tid_, blockDim.x, [&](const uint32_t *p) {
+            return (PARAM && in(p, a.part, (size_t)a.total_tiles * ROWS * JB)) || (VALVE && in(p, a.vpart, logits)) || (RET && in(p, a.rpart, logits));
+        });
+    }
 }
 
 // Workgroups of a kernel that fit on the chip (asked once per kernel); 0: the runtime would not say

@@ -965,7 +965,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     if (tid == 0)
         sLast = leave_last(a.hdr, a.tq, blockIdx.x, gridDim.x, leave_ask(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     __syncthreads();
-    if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x);
+    if (sLast) finish_call(a.hdr, a.clear_from, epoch, tid, blockDim.x, [](const uint32_t *) { return false; });
 }
 
 // Compute units of the device, and workgroups of a kernel that fit on it (asked once per kernel); 0: the runtime would not say

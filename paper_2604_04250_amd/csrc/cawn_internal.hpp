@@ -553,17 +553,19 @@ __device__ __forceinline__ void reset_header(WsHeader *hdr, uint32_t next_epoch,
 // End of a call, run by thread `tid` of the `nthreads` of the workgroup that left last: tickets and
 // the finished-workgroup count return to zero and the epoch advances.  When the epoch wraps, words of
 // EPOCH_MOD calls ago would become valid again: everything behind the lane table is cleared then
-// (`clear_from`: byte offset of this call's first published word).
+// (`clear_from`: byte offset of this call's first published word) but what `keep` says of a word's address: the partial
+// sums that a backward's epilogue has yet to read, every word of which this call wrote.
+template <class Keep>
 __device__ __forceinline__ void finish_call(WsHeader *hdr, size_t clear_from, uint32_t epoch, uint32_t tid,
-                                            uint32_t nthreads)
+                                            uint32_t nthreads, Keep keep)
 {
     const uint32_t next = (epoch + 1) % EPOCH_MOD;
     if (next == 0) {
         const size_t bytes = (size_t)hdr->bytes_lo | ((size_t)hdr->bytes_hi << 32);
-        tagged_t *base = reinterpret_cast<tagged_t *>(reinterpret_cast<char *>(hdr) + clear_from);
-        const size_t n = bytes > clear_from ? (bytes - clear_from) / sizeof(tagged_t) : 0;
+        uint32_t *base = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hdr) + clear_from);
+        const size_t n = bytes > clear_from ? (bytes - clear_from) / sizeof(uint32_t) : 0;
         for (size_t i = tid; i < n; i += nthreads)
-            __hip_atomic_store(base + i, (tagged_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!keep(base + i)) flag_store(base + i, 0u);
     }
     reset_header(hdr, next, tid, nthreads);
 }

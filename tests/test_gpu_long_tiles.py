@@ -211,3 +211,27 @@ def test_more_tiles_than_fit_on_two_streams(B, L, H, F, ret, hconv):
         for (ws, _, _), r, o in zip(jobs, ref, got):
             K.check(K.cawn_workspace_status(ws))
             assert all(torch.equal(a, b) for a, b in zip(r, o))
+
+
+# a workgroup for every tile in both calls, in the forward only (backward tiles are half as long: 594), in neither (1071 forward
+# tiles, 2079 backward)
+@pytest.mark.parametrize("B,L,H,F,hconv", [(1, 4200, 4, 32, False), (1, 4200, 4, 64, True), (6, 4200, 3, 32, False), (21, 4200, 3, 32, False)])
+@pytest.mark.parametrize("ret", [False, True])
+@pytest.mark.parametrize("backward_wraps", [False, True])
+def test_epoch_wraps_in_a_long_forward_or_a_backward(B, L, H, F, hconv, ret, backward_wraps):
+    """The call that wraps a workspace's epoch (every 2^23 - 1 calls) clears what was published: with the counter set from the host so
+    that it is the forward, or the backward, this call and those after it equal those before, bit for bit."""
+    from paper_2604_04250_amd import binding as K
+    import torch
+    ws, fwd, bwd = _training_calls(B, L, H, F, ret, hconv, seed=7)
+    ref = [t.clone() for t in fwd() + bwd()]
+    EPOCH_WORD, EPOCH_MOD = 64 + 2, (1 << 23) - 1     # header: 64 ticket words, finished count, error flag, epoch
+    torch.cuda.synchronize()
+    assert int(ws[EPOCH_WORD]) == 2
+    ws[EPOCH_WORD] = EPOCH_MOD - (2 if backward_wraps else 1)
+    for n in range(3):
+        out = fwd() + bwd()
+        torch.cuda.synchronize()
+        K.check(K.cawn_workspace_status(ws))
+        assert int(ws[EPOCH_WORD]) == 2 * n + (0 if backward_wraps else 1)
+        assert all(torch.equal(a, b) for a, b in zip(ref, out))
