@@ -15,7 +15,8 @@
 // After the carry is known each thread replays its NSTEP tokens from the true incoming state,
 // clamps and stores.  Per token-lane HBM traffic: 8 bytes in, 8 bytes out.
 //
-// Scheduling.  Small calls have a workgroup for every tile, whose threads read their rows into registers; larger ones run
+// Scheduling.  Small calls have a workgroup for every tile, whose threads read their rows into registers (short tiles
+// have theirs staged in LDS); larger ones run
 // the persistent kernel (MANY, see launch_fwd_tile for the line): about as many workgroups as fit on the chip are launched
 // and each loops over tiles, handed out by atomic tickets in the order (time tile, batch row,
 // lane block) (see TileQueues).  Tickets go out in time order, so a tile only ever waits for tiles that a running
@@ -1008,16 +1009,25 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long w
 // 32-lane rows a prefix per tile (see make_queues).  (Both schemes in one kernel: the first kind 1 - 2.5 % slower, B16 L1000 J768
 // 53.9 us against 52.4, the second 4 %.)
 // A call may have more tiles than fit as workgroups of ONE at a time: the others start as these end, and still draw in
-// the chains' order.  They start with nothing on its way, and where there are many of them MANY is ahead.  us MANY / ONE:
-//   32 lanes, constant retention, tau  : B1 L9000 J768 (864 tiles) 37.3 / 35.1, B1 L60000 J128 (940) 56.2 / 42.5; B1 L16384 J768 (1536)
-//     55.4 / 56.6, B1 L32768 J768 (3072) 91 / 114.  768 of them fit at a time; beyond that the chains should be dealt to four and more
-//     counters, with two the first draws take longer: B3 L8192 J320 (960, 30 chains) 38.8 / 40.4
-//   32 lanes, valve or retentions      : B1 L6400 J768 (600) 34.7 / 29.7 valve, 40.4 / 36.3 both; B1 L32768 J256 (1024) 56.4 / 49.1; (1536) 57.8 /
-//     58.9, 66.2 / 63.8, 65.2 / 68.0
-//   64 lanes: bf16 B11 L2500 J256 (880) 39.1 / 31.4, B8 L2048 J768 (1536) 48.5 / 44.1, B8 L8192 J256 (2048) 59.5 / 59.6, B1 L32768
-//     J768 (3072) 83.8 / 95.9; harmonic convolution (1536) 57.8 / 55.0, (2048) 72.6 / 75.4
-//   64 lanes with retentions: bf16 and harmonic convolution B1 L32768 J256 (1024) 56.4 / 48.0, (2048) 78.8 / 74.1, B8 L8192 J768 (6144) 187 / 192
-//   bf16 with the valve alone: B1 L9000 J768 (864) 43.9 / 34.3, B1 L2048 J4096 (1024) 46.5 / 34.8, (1536) 51 / 51 and 57.8 / 62
+// the chains' order.  They start with nothing on its way, and where there are many of them MANY is ahead.  All first draws of
+// ONE come from one counter with an odd number of chains, from two, four or eight with more factors of two (make_queues),
+// 11 ns each: the fewer counters, the later its tiles start, unless the chains are so few that their own length bounds the
+// call.  Time ONE / time MANY, conv 3 if not said, 3100 calls (chains in brackets):
+//   32 lanes, constant retention (768 fit at a time): tau 770 - 830 tiles 0.56 (1), 0.87 (5), 0.95 (7), 1.05 (13 - 63 odd); 0.56 (2), 0.86 (10),
+//     0.89 (14), 0.93 (18 - 66); 0.87 (24).  840 - 1020 tiles 0.55 (1), 0.89 (5), 0.98 - 1.03 (7), 1.03 (9), 1.10 (13 - 63); 0.94 (10), 0.98 (14),
+//     1.01 (18 - 66); 0.95 (24).  1150 tiles 0.90 (22 - 128), 1400 tiles 0.96 - 1.01, 1536 and more 1.02 - 1.25.  Valve the same to 0.03,
+//     at 840 - 1020 tiles 1.03 (18 - 66), 1.12 (21 - 63): B7 L5035 J224 39.1 us MANY, 45.0 ONE
+//   32 lanes, retentions: 560 - 1020 tiles 0.79 - 0.95 (even), 0.94 - 1.00 (odd); 1150 tiles 0.92, 1400 tiles 0.96; 1536 1.04 with the valve
+//   64 lanes, no retentions: bf16 800 - 1750 tiles 0.68 - 0.97, 2000 0.87 - 1.01, 3000 0.92 - 1.18, with the valve at 1280 0.90, at 1500 0.89 -
+//     1.03; harmonic convolution 560 - 2300 tiles 0.77 - 1.00, 3000 0.86 - 1.04, 4500 0.83 - 1.14
+//   64 lanes, retentions: 800 - 2300 tiles 0.80 - 1.01, 3000 0.84 - 1.03, 4500 0.84 - 1.13; B8 L8192 J768 (6144) 187 / 192 us
+//   64 lanes, no conv (less arithmetic to hide the loads of MANY behind), more than 32 chains: at 1300 / 1400 - 1600 / 1700 - 1800 tiles, mean,
+//     bf16 with retentions 0.98 / 1.06 / 1.02, fp32 harmonic convolution 1.00 / 1.03 / 1.06, in bf16 0.92 / 1.01 / 1.05, with retentions 0.96 / 1.00 /
+//     1.05; the other kinds 0.80 - 1.12, mean 0.98 (0.97 with conv 1), with retentions at 2020 tiles 1.02: B4 L3741 J1088 fp32 with retentions and the
+//     harmonic convolution 67 us MANY, 72 - 75 ONE.  Up to 32 chains 0.81 - 1.07, mean 0.95.  Up to conv 2 768 of ONE fit behind the harmonic
+//     convolution without retentions, and 800 - 1010 tiles are 1.00 - 1.10 (15, 49)
+//   a few tiles more than the 512 that fit, an odd number of 7 chains and more: fp32, and bf16 with retentions but without the harmonic
+//     convolution 513 - 560 tiles 0.96 - 1.11, mean 1.03, 575 tiles 1.05 (7 - 15), from 600 on 0.85 - 1.00; other kinds, and even chains, 0.85 - 1.00
 // bf16 without retentions needs fewer registers in MANY, of which 768 workgroups fit, than in ONE, of which 512 do: in
 // between every workgroup of MANY has one tile and ONE takes a second round, B1 L8192 J768 (768) 28.8 / 31.1.
 // Heads of several 64-lane blocks take their blocks one after the other in one workgroup: always MANY.
@@ -1030,10 +1040,15 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
     const long long jobs = (long long)units * a.nT;
     if constexpr (!G::SHORT) {
         constexpr bool W64 = G::JB == 64;
-        const int per_cu = W64 && RET ? 8 : W64 && (HC || !VALVE) ? 7 : W64 || VALVE || RET || units % 4 == 0 ? 4 : 3;      // (tiles a compute unit)
-        const long long one = fwd_resident<G, KC, VALVE, RET, BF, HC, false>(), many = fwd_resident<G, KC, VALVE, RET, BF, HC, true>();
+        const long long one = fwd_resident<G, KC, VALVE, RET, BF, HC, false>(), many = fwd_resident<G, KC, VALVE, RET, BF, HC, true>(), cus = fwd_cus();
         if (one <= 0 || many <= 0) return hipErrorUnknown;
-        if (a.hcG > 1 || jobs > per_cu * fwd_cus() || (jobs > one && jobs <= many))
+        const bool light = KC == 0 && !VALVE && (RET ? BF : HC) && units > 32;
+        const int per_cu = !W64 || (BF && VALVE && !RET && !HC) ? 4 : light ? 5 : RET && KC > 0 ? 8 : 7;      // (tiles a compute unit)
+        const bool dealt = units % 4 == 0 || units <= (units % 2 ? 5u : 14u);      // (four counters or more, or few chains)
+        const bool few_more = jobs > one && !dealt &&
+                              (one >= 3 * cus ? !RET && (!W64 || HC) && 3 * jobs <= 4 * one
+                                              : (RET ? !(BF && HC) : !BF) && units % 2 && jobs - one <= (units < 16 ? 64 : 48));
+        if (a.hcG > 1 || jobs > per_cu * cus || (jobs > one && jobs <= many) || few_more)
             return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s);   // persistent: what fits on the chip
         return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
     } else if constexpr (!HC) {

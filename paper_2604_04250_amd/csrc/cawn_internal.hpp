@@ -136,7 +136,7 @@ struct TileQueues { uint32_t lq, one_each, group; };     // group: tiles of a ch
 // Between them, 8 against 16 at U = 4 / 8 / 10 / 12 / 16 chains: L32700 bf16 50.1 and 45.4 / 64.4 and 62.0 / 73.2 and 72.1 /
 // 78.9 and 78.2 / 98.5 and 99.6, with retentions 48.9 and 46.5 / 71.2 and 74.1 / 83.1 and 87.5 / 95.7 and 101 / 120 and 129;
 // fp32 with a workgroup a tile 28.1 and 24.9 / 22.2 and 21.4 / 24.3 and 23.8 / 28.6 and 28.4 / 20.6 and 20.9.  (conv 3)
-// 1 (a prefix per tile, look_back) for 32-lane rows with more tiles than workgroups: there the nearest prefix has nearly
+// 1 (a prefix per tile, look_back) for 32-lane rows whose workgroups take several tiles (MANY): there the nearest prefix has nearly
 // always arrived, and one pair of words is cheaper than a fold: B16 L1000 J768 55.0 against 56.2, paper's layer B8 L8192
 // J256 74.4 against 77.4 (with bf16 or the harmonic convolution, on 64-lane rows, the fold is ahead there too).
 inline TileQueues make_queues(uint32_t U, uint32_t nT, long long workgroups)
