@@ -1460,7 +1460,8 @@ static hipError_t launch_bwd_tiles(const BwdArgs &a, hipStream_t s)
 // (see AHEAD in the kernel; the others always stage ahead).  Time ahead / time late, mean over 1500 calls of all conv lengths,
 // odd and even sizes, 512 workgroups (valve, retentions, both, fp32 | bf16 | with the harmonic convolution fp32 | bf16):
 //   more tiles than workgroups, up to 32 chains (16 with retentions): 1.05 1.05 1.04 | 1.06 1.05 1.02 | 1.04 1.05 1.08 | 1.05 1.04 1.06
-//     as many chains again                                          : 1.02 1.03 1.00 | 1.03 1.04 1.03 | 0.98 1.01 1.02 | 1.03 1.04 1.02
+//     as many chains again (late too, but with the valve and fp32    : 1.02 1.03 1.00 | 1.03 1.04 1.03 | 0.98 1.01 1.02 | 1.03 1.04 1.02
+//       behind the harmonic convolution; B3 L26796 H22 F16 with the valve, 33 chains: 333 / 340 us the whole step, late / ahead)
 //     more chains, 513 - 768 tiles (the one who is free first takes : 1.06 1.02 0.98 | 1.07 1.06 1.06 | 1.03 1.04 1.03 | 1.04 1.07 1.09
 //       - 1024 tiles                                 a second one)  : 1.03 1.01 1.00 | 1.07 1.05 1.02 | 1.01 1.02 1.02 | 1.05 1.03 1.05
 //       - 2048 tiles                                                : 0.99 0.99 0.97 | 1.05 1.02 0.99 | 0.99 1.01 1.01 | 1.03 1.01 1.03
@@ -1474,7 +1475,7 @@ static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
     if constexpr (VALVE || RET) {
         const long long fit = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, true>(), tiles = a.total_tiles;
         if (fit <= 0) return hipErrorUnknown;
-        const int few = RET ? 16 : 32;
+        const int few = RET || (HC && !BF) ? 32 : 64;
         const int halves = HC ? 4 : VALVE && RET ? (BF ? 4 : 2) : BF ? 8 : RET ? 3 : 4;     // tiles for half the workgroups
         const bool late = tiles > fit ? (long long)a.B * a.nLB <= few || 2 * tiles <= halves * fit
                                       : VALVE != RET && !HC && 2 * tiles <= fit;

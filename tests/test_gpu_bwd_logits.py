@@ -76,22 +76,29 @@ def _check(B, L, H, F, Kc, valve, ret, hconv=False, bf16=False, concat=False, wa
 
 
 # A second tile with its gradients staged ahead: odd numbers of tokens, heads of 8 to 64, blocks of lanes not all full; chains
-# beyond 32 (16 with retentions), tiles beyond the line (1024 with the valve, 768 with retentions, 512 with both, in bf16
-# 2048, 2048 and 1024, behind the harmonic convolution 1024)
+# beyond 64 (32 with retentions and, in fp32, behind the harmonic convolution), tiles beyond the line (1024 with the valve, 768
+# with retentions, 512 with both, in bf16 2048, 2048 and 1024, behind the harmonic convolution 1024)
 @pytest.mark.parametrize("B,L,H,F,Kc,valve,ret,hconv,bf16", [
-    (12, 3717, 9, 8, 3, True, False, False, False), (12, 3717, 9, 8, 0, True, False, False, False),
-    (7, 4750, 9, 8, 4, False, True, False, False), (7, 4750, 9, 8, 0, False, True, False, False),
-    (6, 3900, 5, 16, 3, True, True, False, False), (6, 3900, 5, 16, 0, True, True, False, False),
-    (12, 7400, 9, 8, 3, True, False, False, True), (6, 14710, 3, 32, 2, False, True, False, True),
-    (6, 7500, 5, 16, 3, True, True, False, True), (6, 7500, 5, 16, 0, True, True, False, True),
-    (3, 7400, 3, 64, 3, True, True, True, False), (6, 7400, 3, 32, 0, False, True, True, False), (12, 3700, 3, 32, 3, True, False, True, False),
-    (6, 7400, 3, 32, 3, True, True, True, True), (3, 7400, 3, 64, 0, False, True, True, True)])
+    (24, 1859, 9, 8, 3, True, False, False, False), (24, 1859, 9, 8, 0, True, False, False, False),
+    (11, 3101, 9, 8, 4, False, True, False, False), (11, 3101, 9, 8, 0, False, True, False, False),
+    (11, 1999, 5, 16, 3, True, True, False, False), (11, 1999, 5, 16, 0, True, True, False, False),
+    (24, 3700, 9, 8, 3, True, False, False, True), (11, 8001, 3, 32, 2, False, True, False, True),
+    (11, 4001, 5, 16, 3, True, True, False, True), (11, 4001, 5, 16, 0, True, True, False, True),
+    (6, 3700, 3, 64, 3, True, True, True, False), (11, 4101, 3, 32, 0, False, True, True, False), (12, 3700, 3, 32, 3, True, False, True, False),
+    (11, 4101, 3, 32, 3, True, True, True, True), (6, 3700, 3, 64, 0, False, True, True, True), (24, 1859, 3, 32, 3, True, False, True, True)])
 def test_second_tile_staged_ahead(B, L, H, F, Kc, valve, ret, hconv, bf16):
     _check(B, L, H, F, Kc, valve, ret, hconv, bf16)
 
 
 def test_second_tile_staged_ahead_without_parameter_gradients():
-    _check(12, 3717, 9, 8, 3, True, False, want_param=False)
+    _check(24, 1859, 9, 8, 3, True, False, want_param=False)
+
+
+# More tiles than workgroups and as many chains as the last that draw late
+@pytest.mark.parametrize("B,L,H,F,valve,ret,hconv,bf16", [(16, 2300, 4, 32, True, False, False, False), (8, 5100, 4, 32, False, True, False, True),
+                                                          (8, 4200, 4, 32, True, False, True, False)])
+def test_second_tile_at_the_line_of_few_chains(B, L, H, F, valve, ret, hconv, bf16):
+    _check(B, L, H, F, 3, valve, ret, hconv, bf16)
 
 
 # ... and loaded at the tile's top: few chains of many tiles; many chains of up to two tiles a workgroup, the tail tiles with
