@@ -79,17 +79,21 @@ def parse():
     return ap.parse_args()
 
 
-def read_traffic(workload):
+def read_traffic(workload, kernel):
     """HBM bytes per launch of the dominant kernel from a committed rocprofv3 --pmc summary (profiles/*_pmc.txt
-    holds a line 'TRAFFIC_BYTES_PER_LAUNCH <workload> <bytes>'): (bytes, file) or (None, None).  This is a
-    figure of an earlier profiling run of the same command, not a measurement of this run."""
+    holds a line 'TRAFFIC_BYTES_PER_LAUNCH <workload> <bytes>'): (bytes, file), or (None, None) where the summary's
+    table does not have this very kernel (its counters are of another one then).  This is a figure of an earlier
+    profiling run of the same command, not a measurement of this run."""
     pdir = os.path.join(ROOT, "profiles")
     if not os.path.isdir(pdir):
         return None, None
     for fn in sorted(os.listdir(pdir)):
         if not fn.endswith("_pmc.txt"):
             continue
-        for line in open(os.path.join(pdir, fn)):
+        lines = open(os.path.join(pdir, fn)).read().splitlines()
+        if not any(l.replace(" ", "").startswith(kernel) for l in lines):
+            continue
+        for line in lines:
             p = line.split()
             if len(p) == 3 and p[0] == "TRAFFIC_BYTES_PER_LAUNCH" and p[1] == workload:
                 return float(p[2]), "profiles/" + fn
@@ -479,15 +483,20 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
     w64 = hconv or bf16
     chains = B * -(-J // (64 if w64 else 32))
     tiles = chains * -(-L // (128 if w64 else 256))
-    per_cu = (8 if w64 and ret_on else 7 if w64 and (hconv or not valve_on) else
-              4 if w64 or valve_on or ret_on or chains % 4 == 0 else 3)
-    many = tiles > 256 * per_cu or bool(hconv and F > 64) or (bf16 and not hconv and not ret_on and 512 < tiles <= 768)
+    light = Kc == 0 and not valve_on and (bf16 if ret_on else hconv) and chains > 32
+    per_cu = 4 if not w64 or (bf16 and valve_on and not ret_on and not hconv) else 5 if light else 8 if ret_on and Kc > 0 else 7
+    dealt = chains % 4 == 0 or chains <= (5 if chains % 2 else 14)
+    one = 768 if not ret_on and (Kc <= 2 if hconv else not bf16 and not (valve_on and Kc == 4)) else 512      # (tiles of the kernel with one a workgroup that fit)
+    few_more = tiles > one and not dealt and (3 * tiles <= 4 * one if one == 768 else
+                                              (not (bf16 and hconv) if ret_on else not bf16) and chains % 2 and
+                                              tiles - one <= (64 if chains < 16 else 48))
+    many = bool(tiles > 256 * per_cu or (hconv and F > 64) or (bf16 and not hconv and not ret_on and 512 < tiles <= 768) or few_more)
     fwd_label = f"fwd_kernel<{fwd_tile},{Kc},{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(many)}>"
     # (whether a backward tile's gradients are staged a tile ahead: the line at launch_bwd_vkp, for 512 workgroups)
     bchains = B * -(-J // 32)
     btiles = bchains * -(-L // 128)
     halves = 4 if hconv else (4 if bf16 else 2) if valve_on and ret_on else 8 if bf16 else 3 if ret_on else 4
-    late = ((bchains <= (16 if ret_on else 32) or 2 * btiles <= halves * 512) if btiles > 512 else
+    late = ((bchains <= (32 if ret_on or (hconv and not bf16) else 64) or 2 * btiles <= halves * 512) if btiles > 512 else
             valve_on != ret_on and not hconv and 2 * btiles <= 512) if valve_on or ret_on else False
     bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(not late)}>"
     extra = valve_on or ret_on or bf16 or unfused or hconv
@@ -503,7 +512,7 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
         out["config"]["front_end"] = "conv as separate calls (2 x cawn_syntax_conv + scan): 32 B per token-lane"
     fwd_bpl = FWD_BYTES_PER_TOKEN_LANE // (2 if bf16 else 1)
     bwd_bpl = BWD_BYTES_PER_TOKEN_LANE // (2 if bf16 else 1)
-    traffic, traffic_src = (None, None) if extra or (stream_mode and args.chunk) else read_traffic(name)
+    traffic, traffic_src = (None, None) if extra or (stream_mode and args.chunk) else read_traffic(name, bwd_label if do_bwd else fwd_label)
 
     # ---- roofline of the dominant kernel, from HIP events on the launch stream
     if stream_mode:

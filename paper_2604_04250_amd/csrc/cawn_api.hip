@@ -590,16 +590,16 @@ static float valve_threshold_of(float eps)
 // with the chain's length (0.15 us a tile, 0.24 with the product of the retentions), and the tiles of a call cost 5 ns each
 // where they start and leave; long tiles cost nearly the same whatever the call.  So the line between them is where
 //     (tiles in a chain) x per + (tiles)  =  most,
-// set from 742 calls without the harmonic convolution (J = 64, 256 and 768, 5 - 64 tiles a chain, 32 - 1024 tiles).  With
-// retentions it lies where the two are equally fast.  With a constant retention it lies further on, where short tiles would
-// be slower than long tiles that pass a prefix on per tile: up to there they cost up to 20 % more than long tiles with a prefix
-// per group, and their error is half as large (runs of 8 instead of 32 tokens between exact powers of lambda: 1.8e-7 against
-// 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
-// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 12.5 / 8.9 (64), J256
-// L3584 14.5 / 16.9 (448), J256 4 x L2048 14.2 / 18.1 (1024), J768 L2048 14.0 / 15.2 (768), J768 3 x L768 13.8 / 14.7 (864); paper's
-// layer, J256: 7 x L1024 15.8 / 16.8 (896), L1536 15.4 / 14.8 (192), L3072 16.6 / 19.7 (384), in bf16 7 x L1024 16.1 / 18.0, L3072
-// 18.2 / 19.1; J256 L2048 with the valve in bf16 15.8 / 12.8 (256).  With the harmonic convolution, J256: L1024 15.4 / 11.1 (64),
-// L4096 18.3 / 17.8 (256), paper's layer L4096 21.9 / 22.0.
+// set from 742 calls without the harmonic convolution (J = 64, 256 and 768, 5 - 64 tiles a chain, 32 - 1024 tiles) while long
+// tiles staged their rows; calls just below it are up to a fifth faster on long tiles since those read their rows themselves.
+// With a constant retention a short tile's error is half as large (runs of 8 instead of 32 tokens between exact powers of
+// lambda: 1.8e-7 against 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
+// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 11.1 / 8.7 (64), J256
+// L2048 11.8 / 12.4 (256), L3584 12.5 / 15.9 (448), 4 x L2048 12.7 / 15.9 (1024); J768 L1024 11.6 / 10.6 (384), L2048 12.2 / 14.7
+// (768, short), 3 x L768 12.1 / 12.6 (864, short); paper's layer, J256: L1024 14.5 / 11.6 (128), L1536 14.7 / 13.2 (192), 7 x L1024 15.5 /
+// 16.5 (896), L3072 16.1 / 18.9 (384), in bf16 L1536 15.7 / 13.4, 7 x L1024 15.6 / 16.6, L3072 17.6 / 19.1; J256 L2048 with the valve in bf16
+// 14.9 / 12.8 (256).  With the harmonic convolution, J256: L1024 12.4 / 11.1 (64), L2048 14.3 / 13.7 (128), L4096 15.1 / 18.2 (256,
+// short), paper's layer L2048 18.7 / 16.8 (128), L3700 19.1 / 21.3 (232, short).
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
