@@ -75,22 +75,30 @@ static int valve_groups(const cawn_desc *d) { return d->H * (d->F >= 32 ? d->F /
 // sig = sigmoid(valve - 3): the straight-through gradient of Sec. 3.3.  One thread per (b, h, t),
 // t fastest; the groups of a head are summed in index order.  valve == nullptr: the plain sum (the
 // retention logits' gradient, whose terms already carry their sigmoid factor per lane).  The calling
-// threads share the elements: thread `first` of `stride`.
+// threads share the elements: thread `first` of `stride`.  (A call has at most 2^18 tiles of 128 tokens and 4 heads:
+// 32-bit indices, whose divisions take a fifth of the instructions of 64-bit ones.)
 __device__ __forceinline__ void logit_reduce(const float *__restrict__ vpart, const float *__restrict__ valve,
-                                             float *__restrict__ dvalve, int B, int L, int H, int G, long long first,
-                                             long long stride)
+                                             float *__restrict__ dvalve, uint32_t B, uint32_t L, uint32_t H, uint32_t G,
+                                             uint32_t first, uint32_t stride)
 {
-    const long long n = (long long)B * H * L;
-    const int gph = G / H;       // groups per head
-    for (long long e = first; e < n; e += stride) {
-        const int t = (int)(e % L);
-        const long long r = e / L;
-        const int h = (int)(r % H), b = (int)(r / H);
-        float sum = 0.f;
-        for (int g = 0; g < gph; ++g) sum += vpart[((size_t)b * G + (size_t)h * gph + g) * L + t];
+    const uint32_t n = B * H * L;
+    const uint32_t gph = G / H;       // groups per head
+    for (uint32_t e = first; e < n; e += stride) {
+        const uint32_t r = e / L, t = e - r * L;      // r = b H + h: the head's groups follow each other in vpart
+        const uint32_t b = r / H, h = r - b * H;
         const size_t o = ((size_t)b * L + t) * H + h;
+        const float vl = valve ? valve[o] : 0.f;      // (asked for with the terms)
+        const float *src = vpart + (size_t)r * gph * L + t;
+        float sum = 0.f;
+        for (uint32_t g = 0; g < gph; g += 8) {
+            float x[8];
+#pragma unroll
+            for (uint32_t q = 0; q < 8; ++q) x[q] = g + q < gph ? src[(size_t)(g + q) * L] : 0.f;
+#pragma unroll
+            for (uint32_t q = 0; q < 8; ++q) sum += x[q];
+        }
         if (valve) {
-            const float sg = 1.0f / (1.0f + expf(-(valve[o] - 3.0f)));
+            const float sg = 1.0f / (1.0f + expf(-(vl - 3.0f)));
             sum *= sg * (1.0f - sg);
         }
         dvalve[o] = sum;
@@ -103,13 +111,48 @@ __global__ void fill_zero_kernel(uint32_t *p, size_t n)
         p[i] = 0u;
 }
 
-// Every per-lane constant the scan kernels need, formed in fp64.  One thread per (lane, slot): slot 0 writes the
-// lane's plain constants and taps, every other slot one power of lambda (an fp64 pow, sine and cosine each: one
-// thread per lane, working through all 26 of them in turn, took 24 us).
+// sin and cos in fp64 of an angle of at most 33 significant bits.  Up to 2^20 radians: two-term Cody-Waite reduction by multiples of pi/2 (the
+// fused products round once each, at the size of their result), then the Taylor series to r^17 and r^16, whose next terms
+// are below 1e-17 on [-pi/4, pi/4].  (The library's functions carry the reduction of any argument: far more code, which a
+// table built between two large kernels fetches anew each time.)
+__device__ __forceinline__ void sincos_f64(double x, double &s, double &c)
+{
+    if (!(__builtin_fabs(x) < 1048576.0)) {
+        s = sin(x);
+        c = cos(x);
+        return;
+    }
+    const double k = __builtin_rint(x * 0.63661977236758134308);         // 2 / pi
+    double r = __builtin_fma(-k, 1.57079632679489661923, x);             // fp64(pi / 2)
+    r = __builtin_fma(-k, 6.12323399573676603587e-17, r);                // pi / 2 - fp64(pi / 2)
+    const double q = r * r;
+    double ps = 1.0 / 355687428096000.0, pc = 1.0 / 20922789888000.0;    // 1 / 17!, 1 / 16!
+    const double fs[8] = {1.0, -1.0 / 6, 1.0 / 120, -1.0 / 5040, 1.0 / 362880, -1.0 / 39916800, 1.0 / 6227020800.0, -1.0 / 1307674368000.0};
+    const double fc[8] = {1.0, -1.0 / 2, 1.0 / 24, -1.0 / 720, 1.0 / 40320, -1.0 / 3628800, 1.0 / 479001600, -1.0 / 87178291200.0};
+#pragma unroll
+    for (int i = 7; i >= 0; --i) {
+        ps = __builtin_fma(ps, q, fs[i]);
+        pc = __builtin_fma(pc, q, fc[i]);
+    }
+    ps *= r;
+    const int n = (int)k & 3;
+    s = (n & 1) ? pc : ps;
+    c = (n & 1) ? ps : pc;
+    s = (n & 2) ? -s : s;
+    c = ((n + 1) & 2) ? -c : c;
+}
+
+// Every per-lane constant the scan kernels need, formed in fp64.  One thread per (lane, slot): a slot is one power of
+// lambda, or one of the values that are copied into the table.  A call's cost is its longest chain of dependent reads and
+// arithmetic, all cold behind the kernels of a training step: one thread copying a lane's taps, each read behind the last
+// one's store, and library pow, sin and cos took 4.2 - 4.7 us at 120 and 256 lanes and 5.8 - 6.6 us in large steps (an empty
+// kernel 1.6); a slot for every value, powers by squaring: 3.2 and 4.8 - 4.9.
+// (One thread per lane, working through all powers in turn, took 24 us.)
 // gamma == nullptr (data-dependent retention): the table is built with gamma = 1, i.e. its powers
 // are pure rotations, and row R_RBIAS receives the static retention bias b_k of the lane's harmonic.
-constexpr int LANE_TABLE_SLOTS = 3 + FwdGeom::NSEG + BwdGeom::NSEG;
-__global__ void lane_table_kernel(const float *__restrict__ gamma, const float *__restrict__ theta,
+constexpr int LANE_TABLE_POWERS = 3 + FwdGeom::NSEG + BwdGeom::NSEG;
+inline int lane_table_slots(int conv_k, bool hconv) { return LANE_TABLE_POWERS + 3 + 2 * conv_k + (hconv ? HC_ROWS : 0); }
+__global__ __launch_bounds__(128) void lane_table_kernel(const float *__restrict__ gamma, const float *__restrict__ theta,
                                   const float *__restrict__ conv_w, const float *__restrict__ conv_b,
                                   const float *__restrict__ ret_bias, int F,
                                   const float *__restrict__ hconv_w, const float *__restrict__ hconv_b,
@@ -118,59 +161,68 @@ __global__ void lane_table_kernel(const float *__restrict__ gamma, const float *
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     const int slot = blockIdx.y;
     if (j >= Jp) return;
-    auto put = [&](int row, double v) { table[(size_t)row * Jp + j] = (float)v; };
     const bool live = j < J;
-    const double g = live ? (gamma ? (double)gamma[j] : 1.0) : 0.0, th = live ? (double)theta[j] : 0.0;
-    auto power = [&](int n, double &re, double &im) {
-        const double m = n == 0 ? 1.0 : pow(g, (double)n);
-        re = m * cos(n * th);
-        im = m * sin(n * th);
+    if (slot >= LANE_TABLE_POWERS) {        // copies: retention bias, conv biases, taps, the harmonic convolution's constants
+        const int r = slot - LANE_TABLE_POWERS, w0 = 3, h0 = w0 + 2 * conv_k;
+        const float *src = nullptr;
+        int row = R_RBIAS;
+        if (r == 0) {
+            if (ret_bias) src = ret_bias + j % F;
+        } else if (r < w0) {
+            row = r == 1 ? R_BIAS_M : R_BIAS_A;
+            if (conv_b && conv_k > 0) src = conv_b + (size_t)(r - 1) * J + j;
+        } else if (r < h0) {
+            const int q = r - w0, sidx = q >= conv_k ? 1 : 0;
+            row = R_W0 + q;
+            src = conv_w + ((size_t)sidx * J + j) * conv_k + (q - sidx * conv_k);
+        } else {                            // taps [2][H][3] and biases [2][H] of the lane's head
+            const int q = r - h0, H = J / F, h = j / F;
+            row = R_W0 + 2 * conv_k + q;
+            if (q < 6) src = hconv_w + ((size_t)(q / 3) * H + h) * 3 + q % 3;
+            else if (hconv_b) src = hconv_b + (size_t)(q - 6) * H + h;
+        }
+        table[(size_t)row * Jp + j] = live && src ? *src : 0.0f;
+        return;
+    }
+    auto put = [&](int row, double v) { table[(size_t)row * Jp + j] = (float)v; };
+    const double g = live ? (gamma ? (double)gamma[j] : 1.0) : 0.0;
+    const bool fwd = slot >= 3 && slot - 3 < FwdGeom::NSEG;
+    const int sgi = fwd ? slot - 3 : slot - 3 - FwdGeom::NSEG;
+    const bool rem64 = fwd && sgi == 0;     // (lambda^0 needs no rows: they hold what fp32 drops of lambda^64)
+    const int n = slot == 0 ? 1 : slot == 1 ? FwdGeom::TILE_T : slot == 2 ? BwdGeom::TILE_T : rem64 ? FwdShort::TILE_T
+                                                            : sgi * (fwd ? FwdGeom::NSTEP : BwdGeom::NSTEP);
+    double c, s;
+    sincos_f64(n * (live ? (double)theta[j] : 0.0), s, c);      // (n <= 256: the product is exact)
+    // gamma^n by squaring, highest bit of n first, carried as the sum of two fp64 numbers: exact to the last bit of the result
+    double m = 1.0, ml = 0.0;
+    auto times = [&](double f, double fl) {
+        const double p = m * f, e = __builtin_fma(m, f, -p) + __builtin_fma(m, fl, ml * f);
+        m = p + e;
+        ml = e - (m - p);
     };
-    if (slot == 1 || slot == 2) {       // lambda^(tile length) as a double-float: forward, backward
-        double tr, ti;
-        power(slot == 1 ? FwdGeom::TILE_T : BwdGeom::TILE_T, tr, ti);
-        const float hr = (float)tr, hi = (float)ti;
+    for (int bit = 31 - __builtin_clz(n | 1); bit >= 0; --bit) {     // (n is the same for the whole block)
+        times(m, ml);
+        if (n >> bit & 1) times(g, 0.0);
+    }
+    const double re = m * c, im = m * s;
+    if (slot == 0) {
+        put(R_LR, re);
+        put(R_LI, im);
+        put(R_COS, c);
+        put(R_SIN, s);
+        put(R_GAMMA, g);
+    } else if (slot <= 2) {                 // lambda^(tile length) as a double-float: forward, backward
+        const float hr = (float)re, hi = (float)im;
         put(slot == 1 ? R_PT_HR : R_PTB_HR, hr);
         put(slot == 1 ? R_PT_HI : R_PTB_HI, hi);
-        put(slot == 1 ? R_PT_LR : R_PTB_LR, tr - (double)hr);
-        put(slot == 1 ? R_PT_LI : R_PTB_LI, ti - (double)hi);
-        return;
-    }
-    if (slot >= 3) {                    // lambda^(segment start): forward segments, then backward segments
-        const bool fwd = slot - 3 < FwdGeom::NSEG;
-        const int sgi = fwd ? slot - 3 : slot - 3 - FwdGeom::NSEG;
-        double re, im;
-        const bool rem64 = fwd && sgi == 0;     // (lambda^0 needs no rows: they hold what fp32 drops of lambda^64)
-        power(rem64 ? FwdShort::TILE_T : sgi * (fwd ? FwdGeom::NSTEP : BwdGeom::NSTEP), re, im);
-        if (rem64) {
-            put(R_PT64_LR, re - (double)(float)re);
-            put(R_PT64_LI, im - (double)(float)im);
-            return;
-        }
+        put(slot == 1 ? R_PT_LR : R_PTB_LR, re - (double)hr);
+        put(slot == 1 ? R_PT_LI : R_PTB_LI, im - (double)hi);
+    } else if (rem64) {
+        put(R_PT64_LR, re - (double)(float)re);
+        put(R_PT64_LI, im - (double)(float)im);
+    } else {                                // lambda^(segment start): forward segments, then backward segments
         put((fwd ? R_PSEG : R_PSEGB) + 2 * sgi, re);
         put((fwd ? R_PSEG : R_PSEGB) + 2 * sgi + 1, im);
-        return;
-    }
-    const double c = cos(th), s = sin(th);
-    put(R_LR, g * c);
-    put(R_LI, g * s);
-    put(R_COS, c);
-    put(R_SIN, s);
-    put(R_GAMMA, g);
-    put(R_RBIAS, live && ret_bias ? (double)ret_bias[j % F] : 0.0);
-    put(R_BIAS_M, live && conv_b && conv_k > 0 ? (double)conv_b[j] : 0.0);
-    put(R_BIAS_A, live && conv_b && conv_k > 0 ? (double)conv_b[(size_t)J + j] : 0.0);
-    for (int sidx = 0; sidx < 2; ++sidx)
-        for (int i = 0; i < conv_k; ++i)
-            table[(size_t)(R_W0 + sidx * conv_k + i) * Jp + j] =
-                live ? conv_w[((size_t)sidx * J + j) * conv_k + i] : 0.0f;
-    if (hconv_w) {     // harmonic convolution: the taps [2][H][3] and bias [2][H] of the lane's head, per plane
-        const int H = J / F, h = live ? j / F : 0;
-        for (int p = 0; p < 2; ++p) {
-            for (int i = 0; i < 3; ++i)
-                table[(size_t)(R_W0 + 2 * conv_k + 3 * p + i) * Jp + j] = live ? hconv_w[((size_t)p * H + h) * 3 + i] : 0.0f;
-            table[(size_t)(R_W0 + 2 * conv_k + 6 + p) * Jp + j] = live && hconv_b ? hconv_b[(size_t)p * H + h] : 0.0f;
-        }
     }
 }
 
@@ -268,53 +320,65 @@ static void launch_conv(bool vec4, dim3 grid, hipStream_t s, const float *x, con
     else hipLaunchKernelGGL((syntax_conv_kernel<KC, 1>), grid, dim3(256), 0, s, x, w, bias, hist_in, y, hist_out, L, C, xsb, xst, ysb, yst, cc, runs, runs_z);
 }
 
-// Sum the backward tiles' parameter partials in a fixed order.  One partial is [tile][row][JB] with
-// tile = chain * nLB + lb (chain = position-in-time * B + b).  Block = 32 lanes x 32 groups: group g
-// sums chains g, g+32, ... of its lane's block in increasing order, then the 32 sub-sums meet in LDS
+// Sum the backward tiles' parameter partials in a fixed order.  The partials are [lane block][row][chain][32 lanes]
+// (chain = position-in-time * B + b): what a block reads is one run of memory.  Block = 8 threads of four lanes each x 32
+// groups: group g sums chains g, g+32, ... of its lanes in increasing order, then the 32 sub-sums meet in LDS
 // and are added in index order -- the association is fixed, so results are bitwise repeatable.
-constexpr int RG = 32;       // groups of a reduction block
-// the sum of group g's chains of one (lane block, row, lane): `acc` continues
+// (The partials as [chain][lane block][row][32], which a tile writes in one run and a block of 1024 threads read 128 bytes
+// at a time, and 64-bit divisions for the logits: B2 L4096 J4096 8.7 us, now 5.4; B8 L8192 J768 5.9, now 5.0; B7 L1024 J256 of
+// the paper's layer 4.7, now 4.1.)
+constexpr int RG = 32, EPI_NT = 8 * RG;       // groups and threads of a reduction block
+typedef float v4f __attribute__((ext_vector_type(4)));
+// the sums of group g's chains of four lanes of one (lane block, row): `acc` continues
 template <class A>
-__device__ __forceinline__ A sum_chains(const float *__restrict__ src, size_t step, int chains, int g, A acc)
+__device__ __forceinline__ void sum_chains(const float *__restrict__ src, int chains, int g, A (&acc)[4])
 {
+    auto add = [&](const v4f &v) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += (A)v[q];
+    };
     // (eight independent reads in flight per thread; the sum keeps its order)
     int c = g;
     for (; c + 7 * RG < chains; c += 8 * RG) {
-        float v[8];
+        v4f v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(c + u * RG) * step];
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const v4f *>(src + (size_t)(c + u * RG) * 32);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += (A)v[u];
+        for (int u = 0; u < 8; ++u) add(v[u]);
     }
-    for (; c < chains; c += RG) acc += (A)src[(size_t)c * step];
-    return acc;
+    if (c >= chains) return;
+    v4f v[7];
+#pragma unroll
+    for (int u = 0; u < 7; ++u) v[u] = *reinterpret_cast<const v4f *>(src + (size_t)(c + u * RG < chains ? c + u * RG : c) * 32);
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+        if (c + u * RG < chains) add(v[u]);
 }
 __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, float *__restrict__ out0,
                                                 float *__restrict__ out1, float *__restrict__ out2,
                                                 float *__restrict__ out3, int rows, int conv_k,
-                                                int J, int JB, int nLB, int chains, int accumulate, int bx,
+                                                int J, int chains, int accumulate, int bx,
                                                 int row, float (*sm)[33])
 {
     // one block per (32 lanes, row): bx, row
-    constexpr int G = RG;
-    const int lane = threadIdx.x % 32, g = threadIdx.x / 32;
-    const int j = bx * 32 + lane;
-    float acc = 0.0f;
-    if (j < J)
-        acc = sum_chains(part + ((size_t)(j / JB) * rows + row) * JB + j % JB, (size_t)nLB * rows * JB, chains, g, acc);
-    sm[g][lane] = acc;
+    const int l4 = threadIdx.x % 8 * 4, g = threadIdx.x / 8;
+    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    sum_chains(part + ((size_t)bx * rows + row) * chains * 32 + l4, chains, g, acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sm[g][l4 + q] = acc[q];
     __syncthreads();
-    if (g == 0 && j < J) {
+    const int lane = threadIdx.x, j = bx * 32 + lane;
+    if (lane < 32 && j < J) {
         float s = 0.0f;
 #pragma unroll
-        for (int qq = 0; qq < G; ++qq) s += sm[qq][lane];
+        for (int qq = 0; qq < RG; ++qq) s += sm[qq][lane];
         // rows: 0 dgamma, 1 dtheta, 2 dbias_m, 3 dbias_a, 4 + s*conv_k + i: dw[s][j][i]
         float *dst = nullptr;
         if (row == 0) dst = out0 ? out0 + j : nullptr;
         else if (row == 1) dst = out1 ? out1 + j : nullptr;
         else if (row < 4) dst = out3 ? out3 + (size_t)(row - 2) * J + j : nullptr;
         else {
-            const int sidx = (row - 4) / conv_k, i = (row - 4) % conv_k;
+            const int sidx = row - 4 >= conv_k ? 1 : 0, i = row - 4 - sidx * conv_k;
             dst = out2 ? out2 + ((size_t)sidx * J + j) * conv_k + i : nullptr;
         }
         if (dst) *dst = accumulate ? *dst + s : s;
@@ -322,30 +386,30 @@ __device__ __forceinline__ void reduce_partials(const float *__restrict__ part, 
 }
 
 // Harmonic convolution (Sec. 3.6): its taps and biases belong to a (plane, head) channel.  One block per output: q = 0 .. 5
-// taps (plane, tap), 6, 7 biases, and head h.  Thread (group, lane) sums its chains over the head's 32-lane blocks (F <= 32:
-// the head's lanes of its block), the groups meet in LDS in index order and the 32 lane sums in a butterfly of lane
+// taps (plane, tap), 6, 7 biases, and head h.  The threads of a group sum its chains over the head's 32-lane blocks, four lanes
+// each, the groups meet in LDS in index order and the 32 lane sums (F <= 32: those of the head) in a butterfly of lane
 // exchanges (both partners add the same two values): the association is fixed, the result repeatable.  (As a kernel of
 // its own behind per-lane sums in memory this cost 4.0 - 4.8 us a call.)
 // One output sums up to 8 times the terms of a lane's, and one thread those of all of a head's blocks: in fp32 that added
 // to the error (F = 64, L = 8192: 3.7e-7 -> 4.7e-7 of the taps' gradients).  The sums are taken in fp64 and rounded once;
 // the reads bound the loop either way.
 __device__ __forceinline__ void reduce_hconv(const float *__restrict__ part, float *__restrict__ dw, float *__restrict__ db,
-                                             int rows, int hc_row0, int H, int F, int JB, int nLB, int chains,
+                                             int rows, int hc_row0, int H, int F, int chains,
                                              int accumulate, int q, int h, double (*sm)[33])
 {
-    const int lane = threadIdx.x % 32, g = threadIdx.x / 32;
-    const int l0 = (h * F) % 32;
-    const bool mine = F >= 32 || (lane >= l0 && lane < l0 + F);
-    double acc = 0.0;
-    if (mine)
-        for (int k = 0; k < (F >= 32 ? F / 32 : 1); ++k)
-            acc = sum_chains(part + ((size_t)((h * F) / 32 + k) * rows + hc_row0 + q) * JB + lane, (size_t)nLB * rows * JB, chains, g, acc);
-    sm[g][lane] = acc;
+    const int l4 = threadIdx.x % 8 * 4, g = threadIdx.x / 8;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < (F >= 32 ? F / 32 : 1); ++k)
+        sum_chains(part + ((size_t)((h * F) / 32 + k) * rows + hc_row0 + q) * chains * 32 + l4, chains, g, acc);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sm[g][l4 + k] = acc[k];
     __syncthreads();
-    if (g != 0) return;
+    const int lane = threadIdx.x, l0 = (h * F) % 32;
+    if (lane >= 32) return;
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < RG; ++k) s += sm[k][lane];
+    if (F < 32 && (lane < l0 || lane >= l0 + F)) s = 0.0;
 #pragma unroll
     for (int o = 16; o >= 1; o >>= 1) s += __shfl_xor(s, o, 32);
     if (lane == 0) {
@@ -355,35 +419,34 @@ __device__ __forceinline__ void reduce_hconv(const float *__restrict__ part, flo
     }
 }
 
-// What follows the backward kernel, in one launch (each small launch costs 4-5 us on this chip whatever it
-// does): blocks [0, nbx * rows_lane) sum the parameter partials, nhc blocks behind them the harmonic convolution's, the
+// What follows the backward kernel, in one launch: blocks [0, nbx * rows_lane) sum the parameter partials, nhc blocks behind them the harmonic convolution's, the
 // rest share the logit gradients of the valve and of the retention (nsets of them, nb blocks each).
 struct EpilogueArgs {
     const float *part;
     float *out0, *out1, *out2, *out3, *dhw, *dhb;
-    int rows, rows_lane, conv_k, J, JB, nLB, chains, accumulate, nbx, nhc;
+    int rows, rows_lane, conv_k, J, chains, accumulate, nbx, nhc;
     const float *lpart[2], *logit[2];
     float *lout[2];
     int nsets, nb, B, L, H, F, G;
 };
-__global__ __launch_bounds__(1024, 8) void bwd_epilogue_kernel(const EpilogueArgs p)
+__global__ __launch_bounds__(EPI_NT, 8) void bwd_epilogue_kernel(const EpilogueArgs p)
 {
     static_assert(BwdLPR == 32, "reduction blocks take a lane block's 32 lanes");
     __shared__ union { float f[RG][33]; double d[RG][33]; } sm;
     const int nA = p.nbx * p.rows_lane;
     if ((int)blockIdx.x < nA) {
-        reduce_partials(p.part, p.out0, p.out1, p.out2, p.out3, p.rows, p.conv_k, p.J, p.JB, p.nLB,
-                        p.chains, p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx, sm.f);
+        reduce_partials(p.part, p.out0, p.out1, p.out2, p.out3, p.rows, p.conv_k, p.J, p.chains,
+                        p.accumulate, (int)blockIdx.x % p.nbx, (int)blockIdx.x / p.nbx, sm.f);
         return;
     }
     if ((int)blockIdx.x < nA + p.nhc) {
         const int e = (int)blockIdx.x - nA;
-        reduce_hconv(p.part, p.dhw, p.dhb, p.rows, p.rows - HC_PART_ROWS, p.H, p.F, p.JB, p.nLB, p.chains, p.accumulate, e / p.H, e % p.H, sm.d);
+        reduce_hconv(p.part, p.dhw, p.dhb, p.rows, p.rows - HC_PART_ROWS, p.H, p.F, p.chains, p.accumulate, e / p.H, e % p.H, sm.d);
         return;
     }
     const int bid = (int)blockIdx.x - nA - p.nhc, set = bid / p.nb, blk = bid % p.nb;
-    logit_reduce(p.lpart[set], p.logit[set], p.lout[set], p.B, p.L, p.H, p.G, (long long)blk * blockDim.x + threadIdx.x,
-                 (long long)p.nb * blockDim.x);
+    logit_reduce(p.lpart[set], p.logit[set], p.lout[set], p.B, p.L, p.H, p.G, (uint32_t)blk * blockDim.x + threadIdx.x,
+                 (uint32_t)p.nb * blockDim.x);
 }
 
 // Plain streaming copy with the forward's traffic shape: two fp32 streams in, two out, 8 bytes read and
@@ -391,7 +454,6 @@ __global__ __launch_bounds__(1024, 8) void bwd_epilogue_kernel(const EpilogueArg
 // kernel reaches is the practical ceiling of the HBM roofline on the chip at hand; it computes nothing.
 // (Of the shapes tried at 50 MB .. 1.2 GB -- grid-stride and slab-per-workgroup, 1/2/4 loads in flight,
 // 2 .. 32 workgroups per CU, one element per thread -- this one was at or within 3 % of the best.)
-typedef float v4f __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void stream_copy_kernel(const v4f *__restrict__ a0, const v4f *__restrict__ a1,
                                                           v4f *__restrict__ o0, v4f *__restrict__ o1, size_t n4)
 {
@@ -424,7 +486,7 @@ static hipError_t build_table(const cawn_desc *d, const WsLayout &w, char *ws, c
 {
     float *table = reinterpret_cast<float *>(ws + w.off_table);
     const int threads = 128;
-    hipLaunchKernelGGL(lane_table_kernel, dim3((w.Jp + threads - 1) / threads, LANE_TABLE_SLOTS), dim3(threads), 0, s,
+    hipLaunchKernelGGL(lane_table_kernel, dim3((w.Jp + threads - 1) / threads, lane_table_slots(d->conv_k, hconv_w != nullptr)), dim3(threads), 0, s,
                        gamma, theta, conv_w, conv_b, ret_bias, d->F, hconv_w, hconv_b, table, w.J, w.Jp, d->conv_k);
     return hipGetLastError();
 }
@@ -898,17 +960,17 @@ static int bwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
         p.out0 = dgamma; p.out1 = dtheta; p.out2 = dconv_w; p.out3 = dconv_b; p.dhw = dhconv_w; p.dhb = dhconv_b;
         p.nhc = hc && (dhconv_w || dhconv_b) ? HC_PART_ROWS * d->H : 0;
         p.conv_k = kc > 0 ? kc : 1;
-        p.J = (int)J; p.JB = JB; p.nLB = nLB; p.chains = d->B * w.nT; p.accumulate = d->accumulate_param_grads;
+        p.J = (int)J; p.chains = d->B * w.nT; p.accumulate = d->accumulate_param_grads;
         p.F = d->F;
         if (a.vpart) { p.lpart[p.nsets] = a.vpart; p.logit[p.nsets] = valve; p.lout[p.nsets] = dvalve; ++p.nsets; }
         if (a.rpart) { p.lpart[p.nsets] = a.rpart; p.logit[p.nsets] = nullptr; p.lout[p.nsets] = dret; ++p.nsets; }
         const long long n = (long long)d->B * d->H * d->L;
-        const long long nb = (n + 1023) / 1024;
-        p.nb = p.nsets ? (int)(nb < 1024 ? nb : 1024) : 0;
+        const long long nb = (n + EPI_NT - 1) / EPI_NT;
+        p.nb = p.nsets ? (int)(nb < 4096 ? nb : 4096) : 0;
         p.B = d->B; p.L = d->L; p.H = d->H; p.G = a.G;
         const unsigned blocks = (unsigned)(p.nbx * p.rows_lane + p.nhc + p.nb * p.nsets);
         if (blocks) {
-            hipLaunchKernelGGL(bwd_epilogue_kernel, dim3(blocks), dim3(1024), 0, s, p);
+            hipLaunchKernelGGL(bwd_epilogue_kernel, dim3(blocks), dim3(EPI_NT), 0, s, p);
             if (hipGetLastError() != hipSuccess) return CAWN_ELAUNCH;
         }
     }

@@ -1128,7 +1128,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                 float s = 0.f;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) s += sRed[w][row][c];
-                a.part[((size_t)ticket * ROWS + row) * JB + c] = s;
+                a.part[(((size_t)lb * ROWS + row) * ((uint32_t)a.B * a.nT) + rest) * JB + c] = s;
             }
         }
         // ---- the valve's gradient terms of the tile go out, token-contiguous per group
