@@ -168,6 +168,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                   "powers the lane table holds");
     // valve / retention groups per lane block: F >= 8, or F >= 16 with both (LDS: two workgroups per CU)
     // (HC: F >= 32, i.e. two groups of a 64-lane block)
+    constexpr bool FACTORS = VALVE && !G::SHORT;         // the staged logits become factors in LDS (short tiles: on the way to every call's end)
     constexpr int GPB_MAX = HC ? 2 : ((VALVE && RET) ? 2 : 4) * (JB / 32);
     __shared__ float sV[VALVE ? TILE_T * GPB_MAX : 1];
     __shared__ float sR[RET ? TILE_T * GPB_MAX : 1];     // retention logits, laid out like sV
@@ -309,11 +310,12 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         }
 #pragma unroll
         for (int q = 0; q < NLG; ++q) {
-            if (VALVE && q * NT + tid < TILE_T * GPB_MAX) sV[q * NT + tid] = lgv[VALVE ? q : 0];
+            if (VALVE && q * NT + tid < TILE_T * GPB_MAX) sV[q * NT + tid] = valve_factor(lgv[VALVE ? q : 0], a.valve_thr);
             if (RET && q * NT + tid < TILE_T * GPB_MAX) sR[q * NT + tid] = lgr[RET ? q : 0];
         }
     } else {
         wait_vm<0>();     // the first tile's staged rows
+        if (FACTORS && wave == 0) valve_factors<TILE_T>(&sV[0], a.valve_thr, a.gpb, lane);
     }
 
     float lr[V], li[V], pfr[V], pfi[V], psr[V], psi[V];
@@ -469,9 +471,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                     bool g;
                     float ag;
                     if (VALVE) {      // beta = sigmoid(logit - 3), zero when the valve is closed
-                        const float vl = sV[vbase + i];
-                        g = vl >= a.valve_thr;
-                        ag = g ? amp * sigmoid_fast(vl - 3.0f) : 0.0f;
+                        const float beta = FACTORS ? sV[vbase + i] : valve_factor(sV[vbase + i], a.valve_thr);
+                        g = beta >= 0.0f;
+                        ag = g ? amp * beta : 0.0f;
                     } else {
                         g = in_gate(gs_, zm);
                         ag = g ? amp : 0.0f;
@@ -780,6 +782,18 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                                 a.state_out[((size_t)b * 2 + 1) * a.J + j0] = ni;
                             }
                         }
+                        float c_r[CH], c_i[CH];                    // the outputs
+                        if constexpr (WHOLE) {      // a row is one head: the shift itself brings the zeros beyond its ends
+#pragma unroll
+                            for (int k = 0; k < CH; ++k) {
+                                dpr[k] = dpi[k] = 0.f;
+                                c_r[k] = __builtin_fmaf(hw[0][1], z_r[k], hb[0]);
+                                c_i[k] = __builtin_fmaf(hw[1][1], z_i[k], hb[1]);
+                            }
+#pragma unroll
+                            for (int k = 0; k < CH; k += 2)
+                                fma_neighbours(c_r[k], c_i[k], c_r[k + 1], c_i[k + 1], z_r[k], z_i[k], z_r[k + 1], z_i[k + 1], hw);
+                        } else {
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
                             const int ix = seg * NSTEP + c0 + k;
@@ -800,12 +814,16 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                         }
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
+                            const float l_r = h_zl ? 0.f : lzr[k], l_i = h_zl ? 0.f : lzi[k];
+                            const float r_r = h_zr ? 0.f : rzr[k], r_i = h_zr ? 0.f : rzi[k];
+                            c_r[k] = __builtin_fmaf(hw[0][2], r_r, __builtin_fmaf(hw[0][1], z_r[k], __builtin_fmaf(hw[0][0], l_r, hb[0])));
+                            c_i[k] = __builtin_fmaf(hw[1][2], r_i, __builtin_fmaf(hw[1][1], z_i[k], __builtin_fmaf(hw[1][0], l_i, hb[1])));
+                        }
+                        }
+#pragma unroll
+                        for (int k = 0; k < CH; ++k) {
                             const int ix = seg * NSTEP + c0 + k;
-                            // (WHOLE: a row is one head, and the shift itself brings the zeros beyond its ends)
-                            const float l_r = !WHOLE && h_zl ? 0.f : lzr[k], l_i = !WHOLE && h_zl ? 0.f : lzi[k];
-                            const float r_r = !WHOLE && h_zr ? 0.f : rzr[k], r_i = !WHOLE && h_zr ? 0.f : rzi[k];
-                            const float cr_ = __builtin_fmaf(hw[0][2], r_r, __builtin_fmaf(hw[0][1], z_r[k], __builtin_fmaf(hw[0][0], l_r, hb[0])));
-                            const float ci_ = __builtin_fmaf(hw[1][2], r_i, __builtin_fmaf(hw[1][1], z_i[k], __builtin_fmaf(hw[1][0], l_i, hb[1])));
+                            const float cr_ = c_r[k], ci_ = c_i[k];
                             if constexpr (MULTI) {      // (the reads of these slots, above, come first in this wave)
                                 float *wz = h_defer ? &sHZ[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][0][lv];
                                 float *wp = h_defer ? &sHP[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][1][lv];
@@ -954,6 +972,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         }
 
         if (SINGLE) break;
+        // (the next tile's logits have landed: waited for above)
+        if (FACTORS && wave == 0 && next_ticket < qtiles) valve_factors<TILE_T>(&sV[0], a.valve_thr, a.gpb, lane);
         ticket = next_ticket;
         T = Tn;
     }

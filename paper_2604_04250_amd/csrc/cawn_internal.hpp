@@ -341,11 +341,33 @@ __device__ __forceinline__ float wave_shift_down(float x)
 }
 __device__ __forceinline__ float wave_shift_up0(float x)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, true));
 }
 __device__ __forceinline__ float wave_shift_down0(float x)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, true));
+}
+
+// Two tokens' outputs of both planes += w[plane][0] * (lane i-1's z) + w[plane][2] * (lane i+1's z), zero beyond the wave's
+// ends: the shift is the multiply-add's own operand modifier, which the compiler does not form for it (it moves first: two
+// instructions a neighbour instead of one; with a cleared destination, as the shifts above were once written, three).  Two
+// wait states stand between a vector write and a shifted read of it.  Every lane of the wave must be active.
+__device__ __forceinline__ void fma_neighbours(float &r0, float &i0, float &r1, float &i1, float zr0, float zi0, float zr1, float zi1,
+                                               const float (&w)[2][3])
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n"
+                 "v_fmac_f32_dpp %0, %4, %8 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %1, %5, %9 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %2, %6, %8 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %3, %7, %9 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %0, %4, %10 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %1, %5, %11 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %2, %6, %10 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+                 "v_fmac_f32_dpp %3, %7, %11 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+                 : "+&v"(r0), "+&v"(i0), "+&v"(r1), "+&v"(i1)
+                 : "v"(zr0), "v"(zi0), "v"(zr1), "v"(zi1), "v"(w[0][0]), "v"(w[1][0]), "v"(w[0][2]), "v"(w[1][2]));
+#endif
 }
 
 // Cross-tile publication.  Tiles of one chain may run on different XCDs, whose L2 caches are not
@@ -458,6 +480,8 @@ __device__ __forceinline__ void stage_rows(float *sU, const float *mag, const fl
         }
     }
 }
+// A valve logit's factor of the amplitude: sigmoid(logit - 3), -1 where the valve is closed.
+__device__ __forceinline__ float valve_factor(float logit, float thr) { return logit >= thr ? sigmoid_fast(logit - 3.0f) : -1.0f; }
 // Stage the valve logits of one tile (gate_mode 1): entry (group, token) of the tile lands at
 // sV[group * TT + token]; the lane block's groups are the gpb heads from the one its first lane lies in on.
 // 4 bytes per lane per load; called by one wave.
@@ -478,6 +502,15 @@ __device__ __forceinline__ void stage_valve(float *sV, const float *valve, int b
         (void)valve;
 #endif
     }
+}
+
+// ... and once they have landed, the same wave turns them into factors.  One element a lane
+// instead of one a lane, token and head: in the front-end, where every lane of a head formed the same factor, this was 8 of
+// its 45 instructions, two of them transcendental.
+template <int TT>
+__device__ __forceinline__ void valve_factors(float *sV, float thr, int gpb, int lane)
+{
+    for (int i = 0; i < TT * gpb / 64; ++i) sV[i * 64 + lane] = valve_factor(sV[i * 64 + lane], thr);
 }
 
 __device__ __forceinline__ void flag_store(uint32_t *p, uint32_t v)
