@@ -13,7 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libcawn.so")
 CALL_OUT = os.path.join(HERE, "_cawn_call.so")
 # (the scan kernels' families are translation units of their own: they compile side by side)
-SOURCES = ["cawn_fwd_plain.hip", "cawn_fwd_valve.hip", "cawn_fwd_ret.hip", "cawn_fwd_valve_ret.hip",
+SOURCES = ["cawn_fwd_hconv_valve_ret.hip", "cawn_fwd_hconv_ret.hip", "cawn_fwd_hconv_valve.hip", "cawn_fwd_hconv_plain.hip",
+           "cawn_fwd_plain.hip", "cawn_fwd_valve.hip", "cawn_fwd_ret.hip", "cawn_fwd_valve_ret.hip",
            "cawn_fwd_short_plain.hip", "cawn_fwd_short_valve.hip", "cawn_fwd_short_ret.hip", "cawn_fwd_short_valve_ret.hip",
            "cawn_api.hip", "cawn_fwd.hip", "cawn_bwd.hip", "cawn_bwd_plain.hip", "cawn_bwd_valve.hip",
            "cawn_bwd_ret.hip", "cawn_bwd_hconv.hip", "cawn_bwd_hconv_valve.hip", "cawn_bwd_hconv_ret.hip"]

@@ -667,6 +667,7 @@ static float valve_threshold_of(float eps)
 // small for them the long tiles stay.
 static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, int JB, size_t workspace_bytes)
 {
+    if (d->hconv_k != 0 && d->F > FwdShortHead::JB) return false;      // (a row is a whole head)
     const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
     const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
@@ -740,12 +741,13 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     // the tile: 32-lane rows, with the harmonic convolution 64-lane rows (the same number of token-lanes)
     const bool short_tiles = use_short_tiles(d, bf16, w, hconv_w ? FwdHead::JB : FwdGeom::JB, workspace_bytes);
     const bool head = hconv_w || (bf16 && !short_tiles);
-    const int JB = head ? FwdHead::JB : FwdGeom::JB;
-    const int TT = short_tiles ? FwdShort::TILE_T : (head ? FwdHead::TILE_T : FwdGeom::TILE_T);
+    const bool wide = hconv_w && d->F > FwdHead::JB;      // 128 or 256: a row is a head
+    static_assert(FwdWide128::TILE_T == 64 && FwdWide256::TILE_T == 64, "");
+    const int JB = wide ? d->F : head ? FwdHead::JB : FwdGeom::JB;
+    const int TT = short_tiles ? FwdShort::TILE_T : wide ? FwdWide128::TILE_T : (head ? FwdHead::TILE_T : FwdGeom::TILE_T);
     a.short_tiles = short_tiles ? 1 : 0;
     a.H = d->H; a.F = d->F;
     a.gpb = d->F >= JB ? (d->F % JB ? 2 : 1) : JB / d->F;
-    a.hcG = hconv_w && d->F > JB ? d->F / JB : 1;
     if (d->ret_mode == 1) {
         a.ret = ret;
         a.aggp = reinterpret_cast<tagged_t *>(reinterpret_cast<char *>(workspace) + w.off_aggp);
@@ -772,6 +774,11 @@ static int fwd_impl(const cawn_desc *d, const float *mag, const float *ang, cons
     if (short_tiles) {      // aggregates only, the products behind them: the layout's later regions are the backward's
         a.pre = nullptr;
         a.aggp = a.agg + tiles * 2 * JB;
+    }
+    if (wide) {             // twice the tiles the layout's regions are for: aggregates, prefixes and products in a row
+        a.pre = a.agg + tiles * 2 * JB;
+        a.aggp = a.pre + tiles * 2 * JB;
+        if (w.off_agg + tiles * JB * (d->ret_mode == 1 ? 5 : 4) * sizeof(tagged_t) > workspace_bytes) return CAWN_EWORKSPACE;
     }
     a.clear_from = w.off_agg;
     a.B = d->B; a.L = d->L; a.J = (int)J; a.Jp = w.Jp; a.nT = nTf; a.nTc = w.nTc; a.nLB = nLB;

@@ -1312,15 +1312,13 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         // loop, and the whole of it inside each of the two paths below: the compiler places its own waits
         // for those loads from what it knows of a path, and where paths meet it knows the least.
         auto take_rows = [&]() {
-            const int gshift = (int)(threadIdx.x & 63) - lv;
-            const unsigned long long gmask = (1ull << LPR) - 1ull;
             auto all_tagged = [&]() {      // valid when every lane of the group found all its tags
                 bool mine = true;
 #pragma unroll
                 for (int r = 0; r < HALO; ++r)
 #pragma unroll
                     for (int v = 0; v < V; ++v) mine = mine && tagged_ok(xw[r][0][v], tag) && tagged_ok(xw[r][1][v], tag);
-                return ((__ballot(mine) >> gshift) & gmask) == gmask;
+                return group_all<LPR>(mine);
             };
             bool ok = all_tagged();
             for (uint32_t spins = 0; !ok && spins < a.spin_limit; ++spins) {

@@ -138,8 +138,10 @@ __global__ __launch_bounds__(256) void step_kernel(const FwdArgs a)
         }
         if (a.mask) {   // bit j%32 of word j/32: one ballot covers two words
             const unsigned long long bal = __ballot(g && active);
+            uint32_t lower = (uint32_t)bal, upper = (uint32_t)(bal >> 32);
+            asm("" : "+s"(lower), "+s"(upper));      // (a choice of two words, no shift by a register: see group_all)
             if ((threadIdx.x & 31) == 0 && active)
-                a.mask[((size_t)b * a.L + t) * W + (j >> 5)] = (uint32_t)(bal >> (threadIdx.x & 32));
+                a.mask[((size_t)b * a.L + t) * W + (j >> 5)] = (threadIdx.x & 32) ? upper : lower;
         }
 #pragma unroll
         for (int r = 0; r + 1 < HALO; ++r) { hm[r] = hm[r + 1]; ha[r] = ha[r + 1]; }
@@ -177,6 +179,10 @@ hipError_t launch_fwd(const FwdArgs &a, int conv_k, hipStream_t s)
     if (a.short_tiles) {
         if (a.ret) return a.valve ? launch_fwd_short_valve_ret(a, conv_k, s) : launch_fwd_short_ret(a, conv_k, s);
         return a.valve ? launch_fwd_short_valve(a, conv_k, s) : launch_fwd_short_plain(a, conv_k, s);
+    }
+    if (a.hconv) {
+        if (a.ret) return a.valve ? launch_fwd_hconv_valve_ret(a, conv_k, s) : launch_fwd_hconv_ret(a, conv_k, s);
+        return a.valve ? launch_fwd_hconv_valve(a, conv_k, s) : launch_fwd_hconv_plain(a, conv_k, s);
     }
     if (a.ret) return a.valve ? launch_fwd_valve_ret(a, conv_k, s) : launch_fwd_ret(a, conv_k, s);
     return a.valve ? launch_fwd_valve(a, conv_k, s) : launch_fwd_plain(a, conv_k, s);

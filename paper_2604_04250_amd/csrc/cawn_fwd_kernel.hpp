@@ -115,10 +115,9 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
 // HC: the depth-wise harmonic convolution of Sec. 3.6 applied to the clamped output before it is
 // stored: channel = (plane, head), three taps along the harmonics of the head, zeros beyond its ends.
 // Neighbouring harmonics are neighbouring lanes of a row (rows of 64 lanes here: one wave each).  A head
-// wider than a lane block (F = 64 n, n = 2, 4) is handled by one workgroup drawing the n tickets of the head's blocks together and taking
-// them in order (every other group from the top block down): the lane of a block that borders the
-// next block to come leaves its value and its unfinished output in LDS, and the bordering lane of
-// that next block completes the output and stores it next to its own.
+// of 128 or 256 lanes is a row of its own width (WIDE): the waves side by side leave the values of their outermost lanes in LDS
+// between the recurrence and the convolution, which therefore run one after the other, the clamped states waiting in the
+// registers of the phasors.  Every row is stored whole, by one workgroup.
 // MANY: workgroups take several tiles (launch_fwd_tile); on 32-lane rows these calls pass a prefix on per tile (EACH).
 // Long tiles without it: a workgroup for every tile (ONE).
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC, bool MANY>
@@ -129,16 +128,18 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     constexpr int JB = G::JB;
     constexpr int MW = JB / 32;                    // gate-mask words of a row
     static_assert(MW * NSTEP <= JB, "the gate mask: every word of a segment has a lane that keeps it");
-    static_assert(!HC || JB == 64, "harmonic convolution: a row is a wave");
-    static_assert(!MANY || !G::SHORT, "short tiles: one a workgroup (a head's)");
+    static_assert(!HC || JB >= 64, "harmonic convolution: a row is a wave, or a head of several");
+    static_assert(!MANY || !G::SHORT, "short tiles: one a workgroup");
+    constexpr bool WIDE = JB > 64;                 // a row is one head of WPS waves
+    constexpr int WPS = WIDE ? JB / 64 : 1;
+    static_assert(!WIDE || (HC && !G::SHORT), "rows of several waves: wide heads behind the harmonic convolution");
     constexpr bool EACH = MANY && JB == 32, ONE = !MANY && !G::SHORT;
-    // One tile a workgroup, known at compile time: no loop, nothing kept across it.  (A short tile's head of several blocks: its
-    // workgroup takes them all.)  On short tiles of 32 lanes the loop cost 20 - 30 registers and, with retentions, 2 - 10 spilled
-    // ones: training step B3 L1777 J120 34.5 -> 33.5 us.
-    constexpr bool SINGLE = !MANY && !(G::SHORT && HC);
+    // One tile a workgroup, known at compile time: no loop, nothing kept across it.  On short tiles of 32 lanes the loop cost
+    // 20 - 30 registers and, with retentions, 2 - 10 spilled ones: training step B3 L1777 J120 34.5 -> 33.5 us.
+    constexpr bool SINGLE = !MANY;
     // (64-lane rows with retentions and several tiles a workgroup: at the register limit, the count in the middle spilled 6 more values; the paper's layer
     // in bf16, B1 L32768, 56.1 -> 57.3 us)
-    constexpr bool COUNT_EARLY = !EACH && !(JB == 64 && MANY && RET);
+    constexpr bool COUNT_EARLY = !EACH && !(JB >= 64 && MANY && RET);
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     constexpr int JBS = BF ? JB / 2 : JB;          // four-byte words per staged row
     constexpr int NRTP = staged_rows<TILE_T, JBS, HALO>();   // staged rows per stream: time tile_t0-HALO+rr
     static_assert(JB <= 256 && 256 % JB == 0, "a staged row must fit a wave");
-    static_assert(NW >= 2, "one wave owns the chain, the others stage the next tile");
+    static_assert(NW > WPS, "the last segment's waves own the chain, the others stage the next tile");
 
     // ONE: a thread reads its rows from memory itself (see the loads below)
     __shared__ __attribute__((aligned(16))) float sU[ONE ? 1 : 2 * NRTP][JBS];  // [stream*NRTP + rr][lane]
@@ -158,23 +159,26 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     __shared__ float sE[NSEG - 1][2][JB];          // (the last segment's is nobody's predecessor inside the tile)
     __shared__ float sCarry[2][JB];
     typedef FwdConsts<G> CR;
-    constexpr int NCR = CR::C_W0 + 2 * KC + (HC ? HC_ROWS : 0);     // staged lane-constant rows
+    constexpr int NCR = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0);     // staged lane-constant rows
     __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
     // lambda^TILE_T as a double-float: leading part re, im, remainder re, im
-    constexpr int PT = G::SHORT ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
-    constexpr int PTL = G::SHORT ? R_PT64_LR : PT + 2;
+    constexpr int PT = TILE_T == 64 ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
+    constexpr int PTL = TILE_T == 64 ? R_PT64_LR : PT + 2;
     static_assert(G::SHORT ? TILE_T == 64 && NSTEP == BwdGeom::NSTEP && NSEG <= BwdGeom::NSEG
-                           : (TILE_T == FwdGeom::TILE_T || TILE_T == BwdGeom::TILE_T) && NSTEP == FwdGeom::NSTEP,
+                           : (TILE_T == FwdGeom::TILE_T || TILE_T == BwdGeom::TILE_T || TILE_T == 64) && NSTEP == FwdGeom::NSTEP,
                   "powers the lane table holds");
     // valve / retention groups per lane block: F >= 8, or F >= 16 with both (LDS: two workgroups per CU)
     // (HC: F >= 32, i.e. two groups of a 64-lane block)
     constexpr bool FACTORS = VALVE && !G::SHORT;         // the staged logits become factors in LDS (short tiles: on the way to every call's end)
-    constexpr int GPB_MAX = HC ? 2 : ((VALVE && RET) ? 2 : 4) * (JB / 32);
+    constexpr int GPB_MAX = WIDE ? 1 : HC ? 2 : ((VALVE && RET) ? 2 : 4) * (JB / 32);
     __shared__ float sV[VALVE ? TILE_T * GPB_MAX : 1];
     __shared__ float sR[RET ? TILE_T * GPB_MAX : 1];     // retention logits, laid out like sV
     __shared__ float sP[RET ? NSEG - 1 : 1][JB];                  // product of each segment's retentions
-    // HC: value and unfinished output of the block's last lane, per token and plane, for the next block
-    __shared__ float sHZ[2][HC ? TILE_T : 1], sHP[2][HC ? TILE_T : 1];
+    // WIDE: the head's taps and biases, and the clamped states of the lanes on either side of a boundary between waves,
+    // [plane][boundary][0: the lane below, 1: the lane above][token]
+    __shared__ float sHW[WIDE ? HC_ROWS : 1];
+    constexpr int NBD = WIDE ? WPS - 1 : 1;
+    __shared__ __attribute__((aligned(16))) float sEdge[2][NBD][2][WIDE ? TILE_T : 1];
     __shared__ uint32_t sTicket[2], sLast, sEpoch;
 
     const int tid = threadIdx.x;
@@ -182,12 +186,12 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // (wave index: scalar)
     const uint32_t qtiles = (uint32_t)a.nLB * a.B * a.nT;     // all tiles of the call
     const bool is_tail_seg = seg == NSEG - 1;
-    const bool owner_wave = wave == NW - 1;        // the wave holding the last segment owns the chain
+    const bool owner_wave = wave >= NW - WPS;      // the waves holding the last segment own the chain
     const float *tail_in = a.state_in ? a.state_in + (size_t)a.B * 2 * a.J : nullptr;
 
     if (tid == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // both round trips at once
-        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, HC && !ONE ? (uint32_t)a.hcG : 1u);
+        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, 1u);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -214,31 +218,24 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     auto stage_tile = [&](const TileId &T) {
         if (owner_wave) return;
         if (wave == 0) stage_consts<G, NCR>(&sC[0][0], a.table, a.Jp, T.lb, lane);
+#if defined(__HIP_DEVICE_COMPILE__)
+        if (WIDE && wave == 0 && lane < HC_ROWS)
+            __builtin_amdgcn_global_load_lds(a.table + ((size_t)(R_W0 + 2 * KC + lane) * a.Jp + (size_t)T.lb * JB), &sHW[0], 4, 0, 0);
+#endif
         if (VALVE && wave == 0) stage_valve<TILE_T, JB>(&sV[0], a.valve, T.b, T.tt * TILE_T, T.lb, a.L, a.H, a.F, a.gpb, lane);
         if (RET && wave == 0) stage_valve<TILE_T, JB>(&sR[0], a.ret, T.b, T.tt * TILE_T, T.lb, a.L, a.H, a.F, a.gpb, lane);
         // (bf16: rows of J/2 words at half the strides; the fp32 conv history is read at its point of use)
         if (a.stage16)
             stage_rows<TILE_T, JBS, HALO, 16>(&sU[0][0], a.mag, a.ang, BF ? nullptr : tail_in, T.b, T.tt * TILE_T, T.lb,
-                                      BF ? a.J / 2 : a.J, a.L, BF ? a.isb / 2 : a.isb, BF ? ist32 / 2 : ist32, wave, NW - 1, lane);
+                                      BF ? a.J / 2 : a.J, a.L, BF ? a.isb / 2 : a.isb, BF ? ist32 / 2 : ist32, wave, NW - WPS, lane);
         else
             stage_rows<TILE_T, JBS, HALO, 4>(&sU[0][0], a.mag, a.ang, BF ? nullptr : tail_in, T.b, T.tt * TILE_T, T.lb,
-                                     BF ? a.J / 2 : a.J, a.L, BF ? a.isb / 2 : a.isb, BF ? ist32 / 2 : ist32, wave, NW - 1, lane);
+                                     BF ? a.J / 2 : a.J, a.L, BF ? a.isb / 2 : a.isb, BF ? ist32 / 2 : ist32, wave, NW - WPS, lane);
     };
 
-    // HC, heads of hcG > 1 lane blocks: a group of hcG tickets is one head's blocks; groups with an odd index
-    // take them from the last block down, so that at any time the workgroups of the grid are spread over
-    // all positions in a head (in step on one position they would all read and write one 128-byte
-    // address class of the rows at a time, i.e. a part of the memory channels)
-    auto tile_of = [&](uint32_t tk) {
-        if (HC && !ONE) {
-            const uint32_t n = (uint32_t)a.hcG, g = tk / n, p_ = tk - g * n;
-            tk = g * n + ((g & 1u) ? n - 1u - p_ : p_);
-        }
-        return decode_tile(tk, a.nLB, a.B, a.nT);
-    };
     TileId T{};
     if (ticket < qtiles) {
-        T = tile_of(ticket);
+        T = decode_tile(ticket, a.nLB, a.B, a.nT);
         if constexpr (!ONE) stage_tile(T);
     }
 
@@ -258,7 +255,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         // rows: direct-to-LDS loads in flight would make the compiler wait for everything at the first read of LDS.
         constexpr int NCQ = (NCR * JB / 4 + NT - 1) / NT, NLG = (TILE_T * GPB_MAX + NT - 1) / NT;
         v4f cv[NCQ];
-        float lgv[VALVE ? NLG : 1], lgr[RET ? NLG : 1];
+        float lgv[VALVE ? NLG : 1], lgr[RET ? NLG : 1], hcv = 0.f;
+        if (WIDE && tid < HC_ROWS) hcv = a.table[(size_t)(R_W0 + 2 * KC + tid) * a.Jp + (size_t)T.lb * JB];
 #pragma unroll
         for (int q = 0; q < NCQ; ++q) {
             const int w = q * NT + tid < NCR * JB / 4 ? q * NT + tid : 0;
@@ -303,6 +301,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             }
         }
         compiler_fence();       // (all of it on its way before anything is waited for)
+        if (WIDE && tid < HC_ROWS) sHW[tid] = hcv;
 #pragma unroll
         for (int q = 0; q < NCQ; ++q) {
             const int w = q * NT + tid;
@@ -336,12 +335,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         // of the atomic stays off the path to the barrier below)
         uint32_t ticket_ahead;   // (only thread 0's copy is ever set or read; no initialiser, so no
                              // merge of values that would wait for the atomic right here)
-        // (HC: the tickets of a head's lane blocks are drawn together, a multiple of hcG first)
-        const uint32_t hcG = HC && !ONE ? (uint32_t)a.hcG : 1u;
         if (tid == 0) {
-            if (HC && (ticket + 1) % hcG != 0) ticket_ahead = ticket + 1;
-            else if (SINGLE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
-            else ticket_ahead = next_ticket_of(a.hdr, hcG);
+            if (SINGLE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
+            else ticket_ahead = next_ticket_of(a.hdr, 1u);
         }
 
         // ---- the staged rows have landed (each wave waited for its own loads: before the loop, or
@@ -373,9 +369,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             if (HC) {
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    hb[p] = sC[CR::C_W0 + 2 * KC + 6 + p][lv];
+                    hb[p] = WIDE ? sHW[WIDE ? 6 + p : 0] : sC[WIDE ? 0 : CR::C_W0 + 2 * KC + 6 + p][lv];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) hw[p][k] = sC[CR::C_W0 + 2 * KC + 3 * p + k][lv];
+                    for (int k = 0; k < 3; ++k) hw[p][k] = WIDE ? sHW[WIDE ? 3 * p + k : 0] : sC[WIDE ? 0 : CR::C_W0 + 2 * KC + 3 * p + k][lv];
                 }
             }
             if (KC > 0) {
@@ -487,10 +483,14 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                         // The comparison's result is already a 64-bit lane mask: its two halves are the words of
                         // this token (32-lane rows: in the wave's two segments), and lane i of 32 keeps token i's.  (Packed
                         // by five lane exchanges per token, the mask took 7 of a tile's 15 us: B4 L2048 J768 with
-                        // a mask 46.2 -> 35.4 us.)
-                        const unsigned long long bal = __ballot((int)g & (int)active);
-                        const uint32_t half = (tid & 32) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
-                        mword = lv % 32 == i ? half : mword;
+                        // a mask 46.2 -> 35.4 us; then a select of the half and of the lane, five instructions, now two.)
+                        [[maybe_unused]] const unsigned long long bal = __builtin_amdgcn_ballot_w64(g & active);
+#if defined(__HIP_DEVICE_COMPILE__)
+                        asm("s_nop 1\n"      // (wait states, should a vector instruction have written the mask)
+                            "v_writelane_b32 %0, %1, %3\n"
+                            "v_writelane_b32 %0, %2, %4"
+                            : "+v"(mword) : "s"((uint32_t)bal), "s"((uint32_t)(bal >> 32)), "i"(i), "i"(32 + i));
+#endif
                     }
                     float nr, ni;
                     if (RET) {
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         const uint32_t next_ticket = SINGLE ? NO_TICKET : (uint32_t)__builtin_amdgcn_readfirstlane((int)sTicket[(it + 1) & 1]);
         TileId Tn{};
         if (!SINGLE && next_ticket < qtiles) {
-            Tn = tile_of(next_ticket);
+            Tn = decode_tile(next_ticket, a.nLB, a.B, a.nT);
             stage_tile(Tn);
         }
 
@@ -719,42 +719,23 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             uint32_t off = ((uint32_t)(seg * NSTEP) * ost32 + (uint32_t)(lv * V)) * ES;   // bytes
             const bool full = (tt + 1) * TILE_T <= a.L && (T.lb + 1) * JB <= a.J;
             const bool plain = full && !(a.state_out && tt == a.nT - 1);   // no per-row checks at all
-            // HC: where my lane sits in its head; which neighbour comes from, or goes to, the next block
-            const int hq = HC ? (int)((uint32_t)T.lb % hcG) : 0;
-            const int hk = HC ? (a.F >= JB ? hq * JB + lv : j0 % a.F) : 0;
+            // HC: whether my lane is the first or the last of its head
+            const int hk = HC && !WIDE ? j0 % a.F : 0;
             const bool h_first = hk == 0, h_last = hk == a.F - 1;
-            // (h_dn: this group goes down the head; the roles of the block's first and last lane swap)
-            const bool h_dn = HC && ((ticket / hcG) & 1u);
-            const bool h_lo = HC && lv == 0 && hq > 0, h_hi = HC && lv == LPR - 1 && hq + 1 < (int)hcG;
-            const bool h_prev = h_dn ? h_hi : h_lo;     // my outer neighbour was left in LDS by the previous tile
-            const bool h_defer = h_dn ? h_lo : h_hi;    // my output waits for the next tile
-            const bool h_zl = h_first || (h_defer && h_dn), h_zr = h_last || (h_defer && !h_dn);
-            const float h_wr = h_dn ? hw[0][0] : hw[0][2], h_wi = h_dn ? hw[1][0] : hw[1][2];   // tap that completes it
-            const bool h_tl = h_prev && !h_dn, h_tr = h_prev && h_dn;        // which neighbour comes from LDS
-            // where the completed output is stored (0: this lane has none to complete)
-            const ptrdiff_t h_back = h_prev ? (h_dn ? (ptrdiff_t)ES : -(ptrdiff_t)ES) : 0;
-            auto replay = [&](auto plain_c, auto multi_c, auto ck_c) {
+            // WIDE: a lane beside a boundary between waves has one neighbour in another wave
+            const int blk = WIDE ? lv / 64 : 0;
+            const bool e_lo = WIDE && lane == 0 && blk > 0, e_hi = WIDE && lane == 63 && blk + 1 < WPS;
+            const int bnd = e_lo ? blk - 1 : (e_hi ? blk : 0);
+            auto replay = [&](auto plain_c, auto whole_c, auto ck_c) {
                 constexpr bool PLAIN = decltype(plain_c)::value;
                 constexpr bool CK = decltype(ck_c)::value;       // checkpoints wanted (uniform over the launch)
-                // heads of several lane blocks (1, 2); this tile completes outputs of the previous one (2); heads
-                // narrower than a block (0), of exactly a block (3)
-                constexpr bool MULTI = HC && (decltype(multi_c)::value == 1 || decltype(multi_c)::value == 2);
-                constexpr bool RECV = HC && decltype(multi_c)::value == 2, WHOLE = HC && decltype(multi_c)::value == 3;
+                constexpr bool WHOLE = decltype(whole_c)::value; // a wave's 64 lanes are one head, or a part of one
                 if constexpr (HC) {
                     // The harmonic convolution, four tokens at a time: the recurrence of the four, then all
-                    // their lane exchanges and LDS reads (one wait instead of one per token), then outputs.
-                    // No branch in here, so the steps stay one block of code.  MULTI (a head spans several
-                    // blocks): every lane reads the slot of its row (a broadcast) and selects; every lane
-                    // writes -- the deferring lane into the slot, the others into words of sE that nobody
-                    // reads before the next tile rewrites them; the deferring lane's global
-                    // stores are masked off and the receiving lane of the next tile stores the completed
-                    // element: a second store that only the receiving lane executes (streamed stores are not merged
-                    // in a cache: a second store from every lane, repeating its first, doubled the tile's writes).
+                    // their lane exchanges, then outputs.  No branch in here, so the steps stay one block of code.
                     constexpr int CH = 4;
                     static_assert(NSTEP % CH == 0, "whole chunks");
-#pragma unroll
-                    for (int c0 = 0; c0 < NSTEP; c0 += CH) {
-                        float z_r[CH], z_i[CH], lzr[CH], lzi[CH], rzr[CH], rzi[CH], dpr[CH], dpi[CH];
+                    auto states = [&](int c0, float (&z_r)[CH], float (&z_i)[CH]) {
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
                             const int i = c0 + k;
@@ -782,80 +763,80 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                                 a.state_out[((size_t)b * 2 + 1) * a.J + j0] = ni;
                             }
                         }
-                        float c_r[CH], c_i[CH];                    // the outputs
-                        if constexpr (WHOLE) {      // a row is one head: the shift itself brings the zeros beyond its ends
+                    };
+                    if constexpr (WIDE) {
+#pragma unroll
+                        for (int c0 = 0; c0 < NSTEP; c0 += CH) {
+                            float z_r[CH], z_i[CH];
+                            states(c0, z_r, z_i);
 #pragma unroll
                             for (int k = 0; k < CH; ++k) {
-                                dpr[k] = dpi[k] = 0.f;
+                                pr[c0 + k][0] = z_r[k];
+                                pi[c0 + k][0] = z_i[k];
+                            }
+                        }
+                        if (e_lo || e_hi) {
+                            const int side = e_hi ? 0 : 1;
+#pragma unroll
+                            for (int i = 0; i < NSTEP; ++i) {
+                                sEdge[0][bnd][side][seg * NSTEP + i] = pr[i][0];
+                                sEdge[1][bnd][side][seg * NSTEP + i] = pi[i][0];
+                            }
+                        }
+                        lds_barrier_raw();     // (the next tile's rows may be on their way)
+                    }
+#pragma unroll
+                    for (int c0 = 0; c0 < NSTEP; c0 += CH) {
+                        float z_r[CH], z_i[CH], c_r[CH], c_i[CH];
+                        if constexpr (WIDE) {
+#pragma unroll
+                            for (int k = 0; k < CH; ++k) {
+                                z_r[k] = pr[c0 + k][0];
+                                z_i[k] = pi[c0 + k][0];
+                            }
+                        } else {
+                            states(c0, z_r, z_i);
+                        }
+                        if constexpr (WHOLE) {      // the shift itself brings the zeros beyond the wave's ends
+#pragma unroll
+                            for (int k = 0; k < CH; ++k) {
                                 c_r[k] = __builtin_fmaf(hw[0][1], z_r[k], hb[0]);
                                 c_i[k] = __builtin_fmaf(hw[1][1], z_i[k], hb[1]);
                             }
 #pragma unroll
                             for (int k = 0; k < CH; k += 2)
                                 fma_neighbours(c_r[k], c_i[k], c_r[k + 1], c_i[k + 1], z_r[k], z_i[k], z_r[k + 1], z_i[k + 1], hw);
+                            if (WIDE && (e_lo || e_hi)) {
+                                const int side = e_hi ? 1 : 0;
+                                const float w_r = e_hi ? hw[0][2] : hw[0][0], w_i = e_hi ? hw[1][2] : hw[1][0];
+#pragma unroll
+                                for (int k = 0; k < CH; ++k) {
+                                    c_r[k] = __builtin_fmaf(w_r, sEdge[0][bnd][side][WIDE ? seg * NSTEP + c0 + k : 0], c_r[k]);
+                                    c_i[k] = __builtin_fmaf(w_i, sEdge[1][bnd][side][WIDE ? seg * NSTEP + c0 + k : 0], c_i[k]);
+                                }
+                            }
                         } else {
 #pragma unroll
-                        for (int k = 0; k < CH; ++k) {
-                            const int ix = seg * NSTEP + c0 + k;
-                            lzr[k] = wave_shift_up0(z_r[k]);       // (statements of their own: every lane executes them)
-                            lzi[k] = wave_shift_up0(z_i[k]);
-                            rzr[k] = wave_shift_down0(z_r[k]);
-                            rzi[k] = wave_shift_down0(z_i[k]);
-                            dpr[k] = dpi[k] = 0.f;     // the neighbouring block's unfinished output, completed
-                            if constexpr (RECV) {
-                                const float nzr = sHZ[0][ix], nzi = sHZ[1][ix];
-                                lzr[k] = h_tl ? nzr : lzr[k];
-                                lzi[k] = h_tl ? nzi : lzi[k];
-                                rzr[k] = h_tr ? nzr : rzr[k];
-                                rzi[k] = h_tr ? nzi : rzi[k];
-                                dpr[k] = __builtin_fmaf(h_wr, z_r[k], sHP[0][ix]);     // (same head: same taps)
-                                dpi[k] = __builtin_fmaf(h_wi, z_i[k], sHP[1][ix]);
+                            for (int k = 0; k < CH; ++k) {
+                                // (the shifts are statements of their own: every lane executes them)
+                                const float lzr = wave_shift_up0(z_r[k]), lzi = wave_shift_up0(z_i[k]);
+                                const float rzr = wave_shift_down0(z_r[k]), rzi = wave_shift_down0(z_i[k]);
+                                const float l_r = h_first ? 0.f : lzr, l_i = h_first ? 0.f : lzi;
+                                const float r_r = h_last ? 0.f : rzr, r_i = h_last ? 0.f : rzi;
+                                c_r[k] = __builtin_fmaf(hw[0][2], r_r, __builtin_fmaf(hw[0][1], z_r[k], __builtin_fmaf(hw[0][0], l_r, hb[0])));
+                                c_i[k] = __builtin_fmaf(hw[1][2], r_i, __builtin_fmaf(hw[1][1], z_i[k], __builtin_fmaf(hw[1][0], l_i, hb[1])));
                             }
                         }
 #pragma unroll
                         for (int k = 0; k < CH; ++k) {
-                            const float l_r = h_zl ? 0.f : lzr[k], l_i = h_zl ? 0.f : lzi[k];
-                            const float r_r = h_zr ? 0.f : rzr[k], r_i = h_zr ? 0.f : rzi[k];
-                            c_r[k] = __builtin_fmaf(hw[0][2], r_r, __builtin_fmaf(hw[0][1], z_r[k], __builtin_fmaf(hw[0][0], l_r, hb[0])));
-                            c_i[k] = __builtin_fmaf(hw[1][2], r_i, __builtin_fmaf(hw[1][1], z_i[k], __builtin_fmaf(hw[1][0], l_i, hb[1])));
-                        }
-                        }
-#pragma unroll
-                        for (int k = 0; k < CH; ++k) {
-                            const int ix = seg * NSTEP + c0 + k;
-                            const float cr_ = c_r[k], ci_ = c_i[k];
-                            if constexpr (MULTI) {      // (the reads of these slots, above, come first in this wave)
-                                float *wz = h_defer ? &sHZ[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][0][lv];
-                                float *wp = h_defer ? &sHP[0][ix] : &sE[seg < NSEG - 1 ? seg : 0][1][lv];
-                                constexpr int PL = TILE_T;      // from plane 0 to plane 1 of a slot
-                                wz[0] = z_r[k];
-                                wz[h_defer ? PL : 0] = z_i[k];
-                                wp[0] = cr_;
-                                wp[h_defer ? PL : 0] = ci_;
-                            }
-                            // (the deferring lane stores nothing: the receiving lane of the head's next block
-                            // stores the completed element, so exactly one store reaches that address)
-                            if ((PLAIN || (active && t0 + c0 + k < a.L)) && !(MULTI && h_defer)) {
+                            if (PLAIN || (active && t0 + c0 + k < a.L)) {
                                 char *pr_ = reinterpret_cast<char *>(zre) + off, *pi_ = reinterpret_cast<char *>(zim) + off;
-                                // A head that spans several blocks leaves one element of each row segment to another
-                                // tile's store: such rows take the default policy, which merges the two stores in the
-                                // cache (streamed, they reach memory as two partial writes of one line: 309 against
-                                // 232 us on the training-step shape).  Rows stored by one tile alone are streamed.
-                                auto put = [&](char *q, float v) {
-                                    if constexpr (BF) {     // (default policy, see the plain replay below)
-                                        *reinterpret_cast<uint16_t *>(q) = to_bf16(v);
-                                    } else {
-                                        if constexpr (MULTI) *reinterpret_cast<float *>(q) = v;
-                                        else st_stream(reinterpret_cast<float *>(q), v);
-                                    }
-                                };
-                                put(pr_, cr_);
-                                put(pi_, ci_);
-                                if constexpr (RECV) {
-                                    if (h_prev) {       // (one lane per segment: a store under its own EXEC mask)
-                                        put(pr_ + h_back, dpr[k]);
-                                        put(pi_ + h_back, dpi[k]);
-                                    }
+                                if constexpr (BF) {     // (default policy, see the plain replay below)
+                                    *reinterpret_cast<uint16_t *>(pr_) = to_bf16(c_r[k]);
+                                    *reinterpret_cast<uint16_t *>(pi_) = to_bf16(c_i[k]);
+                                } else {
+                                    st_stream(reinterpret_cast<float *>(pr_), c_r[k]);
+                                    st_stream(reinterpret_cast<float *>(pi_), c_i[k]);
                                 }
                             }
                             off += ost32 * ES;
@@ -912,31 +893,22 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             // What is still in flight ahead of this tile's output stores must be complete now: the next
             // tile's staged rows (needed after the next barrier).  The output stores themselves (the
             // 2 * NSTEP youngest operations when no row needed a check) are left in flight.
-            // (a tile that completes its predecessor's outputs issues twice the stores, more than the 63 a
-            // wave can leave in flight behind its wait: the wait below then covers half of the tile's own
-            // stores, about 4 us in a tile of 12; the first tile of a group does not)
-            const bool recv_tile = HC && (h_dn ? hq + 1 < (int)hcG : hq > 0);
-            using M0 = std::integral_constant<int, 0>;
-            using M1 = std::integral_constant<int, 1>;
-            using M2 = std::integral_constant<int, 2>;
-            using M3 = std::integral_constant<int, 3>;
             using T_ = std::true_type;
             using F_ = std::false_type;
-            auto replay_ck = [&](auto plain_c, auto multi_c) {
-                if (ckp) replay(plain_c, multi_c, T_{});
-                else replay(plain_c, multi_c, F_{});
+            auto replay_ck = [&](auto plain_c, auto whole_c) {
+                if (ckp) replay(plain_c, whole_c, T_{});
+                else replay(plain_c, whole_c, F_{});
+            };
+            auto replay_hc = [&](auto plain_c) {
+                if constexpr (WIDE) replay_ck(plain_c, T_{});
+                else if (HC && a.F == JB) replay_ck(plain_c, T_{});
+                else replay_ck(plain_c, F_{});
             };
             if (plain) {
-                if (recv_tile) replay_ck(T_{}, M2{});
-                else if (HC && hcG > 1) replay_ck(T_{}, M1{});
-                else if (HC && a.F == JB) replay_ck(T_{}, M3{});
-                else replay_ck(T_{}, M0{});
+                replay_hc(T_{});
                 wait_vm<(2 * NSTEP < 63 ? 2 * NSTEP : 63)>();
             } else {
-                if (recv_tile) replay_ck(F_{}, M2{});
-                else if (HC && hcG > 1) replay_ck(F_{}, M1{});
-                else if (HC && a.F == JB) replay_ck(F_{}, M3{});
-                else replay_ck(F_{}, M0{});
+                replay_hc(F_{});
                 wait_vm<0>();
             }
         }
@@ -1050,16 +1022,25 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long w
 //     convolution 513 - 560 tiles 0.96 - 1.11, mean 1.03, 575 tiles 1.05 (7 - 15), from 600 on 0.85 - 1.00; other kinds, and even chains, 0.85 - 1.00
 // bf16 without retentions needs fewer registers in MANY, of which 768 workgroups fit, than in ONE, of which 512 do: in
 // between every workgroup of MANY has one tile and ONE takes a second round, B1 L8192 J768 (768) 28.8 / 31.1.
-// Heads of several 64-lane blocks take their blocks one after the other in one workgroup: always MANY.
+// Heads of 128 and 256 harmonics behind the harmonic convolution (rows of their own width, 64 tokens a tile): a workgroup of
+// 128-lane rows is half a compute unit, and of 256-lane rows, which need twice the waves, a whole one, which has nothing else to do while
+// its rows are on their way.  Time ONE / time MANY, conv 3, the means of four kinds in fp32 and bf16:
+//   128 lanes: up to 2500 tiles 0.86 - 0.97 (2496 tiles of 24 chains 1.05 and 1.02), 2900 - 6000 tiles 0.86 - 0.90 (6 chains), 0.92 -
+//     1.00 (16), 1.02 - 1.15 (64; bf16 with retentions 0.97 - 1.00)
+//   256 lanes: up to 256 tiles 0.93 - 0.98, beyond 1.01 - 1.23 (where a few tiles more than 256 take a second round most)
+// MANY stages 16 bytes a load only: rows that start elsewhere go to ONE.  (Blocks of 64 lanes of such a head one after the other in one
+// workgroup, which handed the outermost lanes on in LDS, as it was: a call's blocks of one head in series, and where the
+// workgroup was one of few all of its tiles too: B1 L6532 H1 F256 bf16 with retentions 2104 us, now 28; B8 L465 H16 F256 84, now 66;
+// B2 L16025 H6 F128 122, now 119.)
 template <class G, int KC, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
 {
     // (the host divided the call by the tile it chose: the same one, or nothing is launched)
     if (a.nLB != (a.J + G::JB - 1) / G::JB || a.nT != (a.L + G::TILE_T - 1) / G::TILE_T) return hipErrorInvalidValue;
-    const uint32_t units = (uint32_t)(a.nLB / a.hcG) * a.B;           // (the blocks of a wide head go to one workgroup)
+    const uint32_t units = (uint32_t)a.nLB * a.B;
     const long long jobs = (long long)units * a.nT;
     if constexpr (!G::SHORT) {
-        constexpr bool W64 = G::JB == 64;
+        constexpr bool W64 = G::JB == 64, W128 = G::JB > 64;
         const long long one = fwd_resident<G, KC, VALVE, RET, BF, HC, false>(), many = fwd_resident<G, KC, VALVE, RET, BF, HC, true>(), cus = fwd_cus();
         if (one <= 0 || many <= 0) return hipErrorUnknown;
         const bool light = KC == 0 && !VALVE && (RET ? BF : HC) && units > 32;
@@ -1068,66 +1049,74 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
         const bool few_more = jobs > one && !dealt &&
                               (one >= 3 * cus ? !RET && (!W64 || HC) && 3 * jobs <= 4 * one
                                               : (RET ? !(BF && HC) : !BF) && units % 2 && jobs - one <= (units < 16 ? 64 : 48));
-        if (a.hcG > 1 || jobs > per_cu * cus || (jobs > one && jobs <= many) || few_more)
+        const bool wide_many = a.stage16 && (G::JB == 256 ? jobs > one : units > 32 && jobs > 9 * cus && !(RET && BF));
+        if (W128) return wide_many ? launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s)
+                                   : launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
+        if (jobs > per_cu * cus || (jobs > one && jobs <= many) || few_more)
             return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s);   // persistent: what fits on the chip
         return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
-    } else if constexpr (!HC) {
-        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
     } else {
-        const long long fit = fwd_resident<G, KC, VALVE, RET, BF, HC, false>();
-        if (fit <= 0) return hipErrorUnknown;
-        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs < fit ? jobs : fit, s);
+        return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
     }
 }
 
 // The tile shape of a call (the host computed nT and nLB from the same rule): 64-lane rows with the harmonic
-// convolution, 32-lane rows without.
-template <bool SHORT, int KC, bool VALVE, bool RET, bool BF>
+// convolution, 128 or 256 for heads of that width, 32-lane rows without.
+template <bool SHORT, int KC, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_fwd_k(const FwdArgs &a, hipStream_t s)
 {
     using std::conditional_t;
-#ifndef CAWN_DEV_PLAIN
-    if (a.hconv) return launch_fwd_tile<conditional_t<SHORT, FwdShortHead, FwdHead>, KC, VALVE, RET, BF, true>(a, s);
-#endif
-    return launch_fwd_tile<conditional_t<SHORT, FwdShort, conditional_t<BF, FwdHead, FwdGeom>>, KC, VALVE, RET, BF, false>(a, s);
+    if constexpr (HC) {
+        if constexpr (!SHORT) {
+            if (a.F == FwdWide128::JB) return launch_fwd_tile<FwdWide128, KC, VALVE, RET, BF, true>(a, s);
+            if (a.F == FwdWide256::JB) return launch_fwd_tile<FwdWide256, KC, VALVE, RET, BF, true>(a, s);
+        }
+        return launch_fwd_tile<conditional_t<SHORT, FwdShortHead, FwdHead>, KC, VALVE, RET, BF, true>(a, s);
+    } else {
+        return launch_fwd_tile<conditional_t<SHORT, FwdShort, conditional_t<BF, FwdHead, FwdGeom>>, KC, VALVE, RET, BF, false>(a, s);
+    }
 }
 
 // Tuning aid: -DCAWN_DEV_KC=<k> compiles only the conv_k = k kernels and -DCAWN_DEV_PLAIN only the
 // threshold-mode fp32 ones without the harmonic convolution (a build for timing one variant in
 // seconds; every other variant then fails to launch with hipErrorInvalidValue).  The library is
 // always built without them.
-template <bool SHORT, bool VALVE, bool RET, bool BF>
+template <bool SHORT, bool VALVE, bool RET, bool HC, bool BF>
 static hipError_t launch_fwd_act(const FwdArgs &a, int conv_k, hipStream_t s)
 {
 #ifdef CAWN_DEV_PLAIN
-    if constexpr (VALVE || RET || BF) return hipErrorInvalidValue; else
+    if constexpr (VALVE || RET || BF || HC) return hipErrorInvalidValue; else
 #endif
     switch (conv_k) {
 #ifdef CAWN_DEV_KC
-    case CAWN_DEV_KC: return launch_fwd_k<SHORT, CAWN_DEV_KC, VALVE, RET, BF>(a, s);
+    case CAWN_DEV_KC: return launch_fwd_k<SHORT, CAWN_DEV_KC, VALVE, RET, BF, HC>(a, s);
 #else
-    case 0: return launch_fwd_k<SHORT, 0, VALVE, RET, BF>(a, s);
-    case 1: return launch_fwd_k<SHORT, 1, VALVE, RET, BF>(a, s);
-    case 2: return launch_fwd_k<SHORT, 2, VALVE, RET, BF>(a, s);
-    case 3: return launch_fwd_k<SHORT, 3, VALVE, RET, BF>(a, s);
-    case 4: return launch_fwd_k<SHORT, 4, VALVE, RET, BF>(a, s);
+    case 0: return launch_fwd_k<SHORT, 0, VALVE, RET, BF, HC>(a, s);
+    case 1: return launch_fwd_k<SHORT, 1, VALVE, RET, BF, HC>(a, s);
+    case 2: return launch_fwd_k<SHORT, 2, VALVE, RET, BF, HC>(a, s);
+    case 3: return launch_fwd_k<SHORT, 3, VALVE, RET, BF, HC>(a, s);
+    case 4: return launch_fwd_k<SHORT, 4, VALVE, RET, BF, HC>(a, s);
 #endif
     default: return hipErrorInvalidValue;
     }
 }
 
-// One translation unit per family of forward kernels (tile length x gate mode x retention mode): they compile side by
-// side.
-template <bool SHORT, bool VALVE, bool RET>
+// One translation unit per family of forward kernels (tile length x gate mode x retention mode, long tiles x harmonic
+// convolution): they compile side by side.
+template <bool SHORT, bool VALVE, bool RET, bool HC>
 static hipError_t launch_fwd_family(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return a.bf16 ? launch_fwd_act<SHORT, VALVE, RET, true>(a, conv_k, s) : launch_fwd_act<SHORT, VALVE, RET, false>(a, conv_k, s);
+    return a.bf16 ? launch_fwd_act<SHORT, VALVE, RET, HC, true>(a, conv_k, s) : launch_fwd_act<SHORT, VALVE, RET, HC, false>(a, conv_k, s);
 }
 hipError_t launch_fwd_plain(const FwdArgs &a, int conv_k, hipStream_t s);        // threshold gate, constant retention
 hipError_t launch_fwd_valve(const FwdArgs &a, int conv_k, hipStream_t s);        // per-head valve, constant retention
 hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, hipStream_t s);          // threshold gate, data-dependent retention
 hipError_t launch_fwd_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);    // valve and data-dependent retention
-hipError_t launch_fwd_short_plain(const FwdArgs &a, int conv_k, hipStream_t s);  // the same four on short tiles
+hipError_t launch_fwd_hconv_plain(const FwdArgs &a, int conv_k, hipStream_t s);  // the same four with the harmonic convolution
+hipError_t launch_fwd_hconv_valve(const FwdArgs &a, int conv_k, hipStream_t s);
+hipError_t launch_fwd_hconv_ret(const FwdArgs &a, int conv_k, hipStream_t s);
+hipError_t launch_fwd_hconv_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);
+hipError_t launch_fwd_short_plain(const FwdArgs &a, int conv_k, hipStream_t s);  // and on short tiles, with and without it
 hipError_t launch_fwd_short_valve(const FwdArgs &a, int conv_k, hipStream_t s);
 hipError_t launch_fwd_short_ret(const FwdArgs &a, int conv_k, hipStream_t s);
 hipError_t launch_fwd_short_valve_ret(const FwdArgs &a, int conv_k, hipStream_t s);

@@ -5,7 +5,7 @@ namespace cawn {
 
 hipError_t launch_fwd_ret(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return launch_fwd_family<false, false, true>(a, conv_k, s);
+    return launch_fwd_family<false, false, true, false>(a, conv_k, s);
 }
 
 }  // namespace cawn

@@ -5,7 +5,7 @@ namespace cawn {
 
 hipError_t launch_fwd_short_ret(const FwdArgs &a, int conv_k, hipStream_t s)
 {
-    return launch_fwd_family<true, false, true>(a, conv_k, s);
+    return a.hconv ? launch_fwd_family<true, false, true, true>(a, conv_k, s) : launch_fwd_family<true, false, true, false>(a, conv_k, s);
 }
 
 }  // namespace cawn
