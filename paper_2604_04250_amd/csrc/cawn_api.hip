@@ -628,6 +628,11 @@ static bool gate_set_of(bool fused, int amp_mode, float conv_clamp, float tau, G
         last = k;
     }
     *out = set;
+    // The second of two intervals is the increasing end of |A(SiLU(x))| or of |x|: it has no upper end.  Without one, nothing
+    // is above a2.
+    const float inf = std::numeric_limits<float>::infinity();
+    if (!(set.a2 <= set.b2)) out->a2 = std::numeric_limits<float>::quiet_NaN();
+    else if (set.b2 != inf) return false;
     return true;
 }
 static float valve_threshold_of(float eps)

@@ -32,18 +32,6 @@ namespace cawn {
 #define BWD_STAMP(k) do { } while (0)
 #endif
 
-// x + (x moved across lanes by a DPP control): row_ror:n is 0x120 + n (rotate within a row of 16).
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x)
-{
-    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-// rows 1 and 3 of the wave add lane 15 of the row below them (row_bcast:15); rows 0 and 2 add zero
-__device__ __forceinline__ float dpp_add_bcast15(float x)
-{
-    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x142, 0xA, 0xF, false));
-}
-
 template <int V> struct BVec;
 template <> struct BVec<1> {
     static __device__ __forceinline__ void ld(float (&d)[1], const float *p) { d[0] = *p; }
@@ -74,28 +62,56 @@ __device__ __forceinline__ void stu(float *ubase, uint32_t boff, const float (&x
     BVec<V>::st(reinterpret_cast<float *>(reinterpret_cast<char *>(ubase) + boff), x);
 }
 
-// Sum of w over the lanes that share a head inside the 32-lane block (8, 16 or 32 lanes).  Rotations
-// within each row of 16 lanes leave the row's sum in all of its lanes (four full-rate adds); a 32-lane
-// group then takes the lower row's sum into its upper row.  The total is valid in the lanes for which
-// head_sum_lane() holds.
-__device__ __forceinline__ float head_sum(float w, int vwidth)
+// Sum of w over the 8 lanes that share a head; valid in its first lane.
+__device__ __forceinline__ float head_sum8(float w)
 {
-    if (vwidth >= 16) {
-        w = dpp_add<0x128>(w);
-        w = dpp_add<0x124>(w);
-        w = dpp_add<0x122>(w);
-        w = dpp_add<0x121>(w);
-        if (vwidth == 32) w = dpp_add_bcast15(w);
-    } else {
 #pragma unroll
-        for (int o = 4; o >= 1; o >>= 1)
-            if (o < vwidth) w += __shfl_xor(w, o, 64);
-    }
+    for (int o = 4; o >= 1; o >>= 1) w += __shfl_xor(w, o, 64);
     return w;
 }
-__device__ __forceinline__ bool head_sum_lane(int lv, int vwidth)
+// Sums over the rows of 16 lanes of two tokens' terms (a0, a1), or of two quantities' (a0, a1 and b0, b1), several at a time: a
+// step that folds a row in half leaves room for another sum in the other half (the lanes a masked add leaves alone keep the
+// sum that was written before).  Lane 0 of the row then holds a0's sum and lane 8 a1's; with b, lane 0 a0's, lane 4 a1's, lane 8
+// b0's, lane 12 b1's.  5 and 8 adds instead of 8 and 16 (and 2 and 4 more for the sum of two rows, which is taken once where the
+// sums leave the tile).  Two wait states stand between a vector write and a shifted read of it.
+__device__ __forceinline__ float row_sums(float a0, float a1)
 {
-    return vwidth >= 16 ? (lv == vwidth - 16 || (vwidth == 16 && lv == 16)) : (lv % vwidth == 0);
+    float t = 0.f;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n"
+                 "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+                 "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+                 : "=&v"(t) : "v"(a0), "v"(a1));
+#endif
+    return t;
+}
+__device__ __forceinline__ float row_sums(float a0, float a1, float b0, float b1)
+{
+    [[maybe_unused]] float t = 0.f;
+    float u = 0.f;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n"
+                 "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+                 "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n"
+                 "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+                 "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0x3\n"
+                 "s_nop 0\n"
+                 "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n"
+                 "s_nop 0\n"
+                 "v_add_f32_dpp %1, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %1, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n"
+                 "s_nop 1\n"
+                 "v_add_f32_dpp %1, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+                 : "=&v"(t), "=&v"(u) : "v"(a0), "v"(a1), "v"(b0), "v"(b1));
+#endif
+    return u;
 }
 
 // VALVE: gate_mode 1, the per-head input valve of Sec. 3.3 in place of the per-lane threshold.
@@ -185,12 +201,16 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     static_assert(!RED_OVER_ROWS || (size_t)NW * ROWS * JB <= (size_t)2 * NRTP * JBS, "the partial-sum staging fits over the input rows");
     float (*sRed)[ROWS][JB] = RED_OVER_ROWS ? reinterpret_cast<float (*)[ROWS][JB]>(&sU[0][0]) : sRedOwn;
     constexpr int GPB_MAX = HC ? 1 : (VALVE && RET ? 2 : 4);   // heads per lane block: F >= 8, with both 16, behind the harmonic convolution 32
-    __shared__ float sV[VALVE ? BwdGeom::TILE_T * GPB_MAX : 1];      // valve logits, [group][token]
-    __shared__ float sVp[VALVE ? BwdGeom::TILE_T * GPB_MAX : 1];     // valve gradient terms summed over a group's lanes
+    // (the terms of a 32-lane group are kept as the sums of its two rows of 16 lanes)
+    constexpr int SUMS = GPB_MAX > 2 ? GPB_MAX : 2;
+    __shared__ float sV[VALVE ? BwdGeom::TILE_T * SUMS : 1];         // valve logits, then the factors beta, [group][token]
+    float *sVp = &sV[0];                        // valve gradient terms summed over a group's, or a row's lanes (the factors are dead by then)
     __shared__ float sTaps[LEAN ? 2 * KC1 : 1][JB];                 // conv taps of the lane block (valve kernels)
-    __shared__ float sPb[RET ? NW : 1][JB];                        // product of each wave's retentions
+    constexpr int N_PB = NW * JB, N_RP = BwdGeom::TILE_T * SUMS;
+    __shared__ float sPool2[RET ? (N_PB > N_RP ? N_PB : N_RP) : 1];
+    float (*sPb)[JB] = reinterpret_cast<float (*)[JB]>(&sPool2[0]);    // product of each wave's retentions
     float (*sPt)[JB] = &sPb[0];                 // product of the tile's retentions (head group; the first wave's own is read by nobody)
-    __shared__ float sRp[RET ? BwdGeom::TILE_T * GPB_MAX : 1];       // retention-logit gradient terms per (group, token)
+    float *sRp = &sPool2[0];                    // retention-logit gradient terms like the valve's (the products are dead by then)
     __shared__ float sR[RET && !REGS ? BwdGeom::TILE_T * GPB_MAX : 1];  // retention logits, staged with the gradients
     __shared__ uint32_t sTicket[2], sLast, sEpoch;     // tickets of this tile and the next one
 
@@ -364,9 +384,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             // 31 | 32, exactly the lanes that take the staged edge instead.  Positions outside the head are NOT
             // zeroed here: the callers fold that into the taps, or into the finished sums, once per tile.)
             // The shifts are statements of their own, in front of every choice: written inside one arm of a `?:` a
-            // shift runs under that arm's narrowed EXEC mask, and a lane whose source lane is switched off keeps its
-            // own value.  (Cross-lane operations are convergent: the compiler does not move them under a condition.)
-            const float mr = wave_shift_up(c0r), mi = wave_shift_up(c0i), pr = wave_shift_down(c0r), pi = wave_shift_down(c0i);
+            // shift runs under that arm's narrowed EXEC mask, and a lane whose source lane is switched off gets
+            // nothing.  (Cross-lane operations are convergent: the compiler does not move them under a condition.)
+            const float mr = wave_shift_up0(c0r), mi = wave_shift_up0(c0i), pr = wave_shift_down0(c0r), pi = wave_shift_down0(c0i);
             cr[0] = k.use_lo ? er : mr;
             ci[0] = k.use_lo ? ei : mi;
             cr[2] = k.use_hi ? er : pr;
@@ -548,7 +568,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         stage_rows<TILE_T, JBS, HALO, 4>(&sU[0][0], a.mag, a.ang, BF ? nullptr : tail_in, b, tt * TILE_T, lb, BF ? a.J / 2 : a.J,
                                  a.L, BF ? a.isb / 2 : a.isb, BF ? (int)a.ist / 2 : (int)a.ist, wave, NW, lane);
 
-    if (VALVE && wave == 0) stage_valve<TILE_T, JB>(&sV[0], a.valve, b, tt * TILE_T, lb, a.L, a.H, a.F, a.gpb, lane);
+    if (VALVE && wave == NW - 1) stage_valve<TILE_T, JB>(&sV[0], a.valve, b, tt * TILE_T, lb, a.L, a.H, a.F, a.gpb, lane);
 
     // gradient of the carried state joins the last token
     if (a.dstate_out && active && a.L - 1 >= t0 && a.L - 1 < t0 + NSTEP) {
@@ -695,6 +715,10 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // operations, in flight: their round trip is nobody's business here)
     if (wave == 0 && chained && feeds) wait_vm<(RET ? 3 : 2) * V>();
     else wait_stores_done();
+    if (VALVE && wave == NW - 1) {      // logits to factors (0: closed): one element a lane instead of one a lane, token and head
+        for (int i = 0; i < TILE_T * a.gpb / 64; ++i)
+            sV[i * 64 + lane] = __builtin_fmaxf(valve_factor(sV[i * 64 + lane], a.valve_thr), 0.0f);
+    }
     if (AHEAD && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
     if (LEAN && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
 #pragma unroll
@@ -728,7 +752,11 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // ---- front-end recompute, rows from LDS as a sliding window
     float cs[NSTEP][V], sn[NSTEP][V], ag[NSTEP][V], dsm[NSTEP][V];   // ag: a*g*SiLU'(z_ang)
     float am[VALVE ? NSTEP : 1][V];                                  // the amplitude itself (valve gradient)
-    float Spr[PARAM ? NSTEP : 1][V], Spi[PARAM ? NSTEP : 1][V];      // forward state before each token
+    // Forward state before each token; ROT: rotated by e^{i theta} already, which with retentions both the recurrence and the
+    // parameter terms ask for (four instructions a token-lane less).  Not behind the harmonic convolution, whose tap terms
+    // need the state itself.  (With a constant retention two instructions less, and no faster: B2 L4096 J4096 bf16 270 / 270 us.)
+    constexpr bool ROT = RET && !HC;
+    float Spr[PARAM ? NSTEP : 1][V], Spi[PARAM ? NSTEP : 1][V];
     float Efr[V], Efi[V];
 
     const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;   // rows before a sequence start
@@ -800,9 +828,10 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                 }
                 float amp = xm;
                 if (AMP) {
-                    const float sp = softplus_fast(xm);
+                    float sg;
+                    const float sp = softplus_sigmoid_fast(xm, sg);
                     amp = __builtin_fminf(sp, 10.0f);
-                    km *= sp < 10.0f ? sigmoid_fast(xm) : 0.0f;
+                    km *= sp < 10.0f ? sg : 0.0f;
                 }
                 // (the valve kernels keep the reduced angle, not its sin and cos: one register per
                 // token-lane less, paid for with two hardware sin/cos in the reverse pass)
@@ -810,8 +839,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                 const float s = __builtin_amdgcn_sinf(rev), c = __builtin_amdgcn_cosf(rev);
                 float agv;
                 if (VALVE) {      // p = beta a e^{i phi}: beta multiplies both returned gradients
-                    const float vl = sV[vbase + i];
-                    const float beta = vl >= a.valve_thr ? sigmoid_fast(vl - 3.0f) : 0.0f;
+                    const float beta = sV[vbase + i];
                     agv = beta * amp;
                     km *= beta;
                     am[i][v] = amp;
@@ -823,16 +851,26 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                 dsm[i][v] = km;
                 ag[i][v] = agv * ka;
                 if (PARAM) {   // forward scan from the checkpoint; the state before token i is kept
-                    Spr[i][v] = Efr[v];
-                    Spi[i][v] = Efi[v];
                     const float pr = agv * c, pi = agv * s;
                     float nr, ni;
+                    if (ROT) {
+                        const float ct_ = lr[v], st_ = li[v], g_ = gm[i][v];
+                        const float rr = __builtin_fmaf(ct_, Efr[v], -st_ * Efi[v]);
+                        const float ri = __builtin_fmaf(st_, Efr[v], ct_ * Efi[v]);
+                        Spr[i][v] = rr;
+                        Spi[i][v] = ri;
+                        nr = __builtin_fmaf(g_, rr, pr);
+                        ni = __builtin_fmaf(g_, ri, pi);
+                    } else {
+                    Spr[i][v] = Efr[v];
+                    Spi[i][v] = Efi[v];
                     if (RET) {
                         nr = __builtin_fmaf(gm[i][v], __builtin_fmaf(lr[v], Efr[v], -li[v] * Efi[v]), pr);
                         ni = __builtin_fmaf(gm[i][v], __builtin_fmaf(li[v], Efr[v], lr[v] * Efi[v]), pi);
                     } else {
                         nr = __builtin_fmaf(lr[v], Efr[v], __builtin_fmaf(-li[v], Efi[v], pr));
                         ni = __builtin_fmaf(li[v], Efr[v], __builtin_fmaf(lr[v], Efi[v], pi));
+                    }
                     }
                     Efr[v] = nr;
                     Efi[v] = ni;
@@ -857,30 +895,32 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         // ---- the harmonic convolution's tap and bias terms, in a pass of its own (inside the front-end its
         //      temporaries came on top of the kernel's register peak): the state after token i is the state
         //      before token i+1; Z[t] = clamp(S[t]) meets the gradients at k+1, k, k-1 (taps 0, 1, 2)
+        //      Rows and lanes outside the tensor staged a valid address: their state counts as zero.
+        //      (With the neighbours' gradients taken by the multiply-add's own lane shift, as in the forward, and
+        //      the edges summed beside, four instructions a token-lane less, 15 more values were spilled.)
         __builtin_amdgcn_sched_barrier(0);
         const HcLane hk = hc_setup();
-        auto tap_pass = [&](auto full_c) {
 #pragma unroll
-            for (int i = 0; i < NSTEP; ++i) {
-                const float sr_ = i + 1 < NSTEP ? Spr[i + 1 < NSTEP ? i + 1 : 0][0] : Efr[0];
-                const float si_ = i + 1 < NSTEP ? Spi[i + 1 < NSTEP ? i + 1 : 0][0] : Efi[0];
-                const float zr_ = clampf(sr_, a.out_clamp), zi_ = clampf(si_, a.out_clamp);
-                float cr[3], ci[3];
-                hc_read(full_c, i, hk, cr, ci);
+        for (int i = 0; i < NSTEP; ++i) {
+            const float sr_ = i + 1 < NSTEP ? Spr[i + 1 < NSTEP ? i + 1 : 0][0] : Efr[0];
+            const float si_ = i + 1 < NSTEP ? Spi[i + 1 < NSTEP ? i + 1 : 0][0] : Efi[0];
+            const bool live = i < hk.nlive;
+            const float oc = live ? a.out_clamp : 0.0f, one = live ? 1.0f : 0.0f;
+            const float zr_ = clampf(sr_, oc), zi_ = clampf(si_, oc);
+            float cr[3], ci[3];
+            hc_read(std::true_type{}, i, hk, cr, ci);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    hacc[q] = __builtin_fmaf(zr_, cr[2 - q], hacc[q]);
-                    hacc[3 + q] = __builtin_fmaf(zi_, ci[2 - q], hacc[3 + q]);
-                }
-                hacc[6] += cr[1];
-                hacc[7] += ci[1];
-                // (the sums are used at the end of the tile only; left alone, the compiler moves the whole chain
-                // down there and keeps all 48 gradients alive until then)
-#pragma unroll
-                for (int q = 0; q < HC_PART_ROWS; ++q) asm volatile("" : "+v"(hacc[q]));
+            for (int q = 0; q < 3; ++q) {
+                hacc[q] = __builtin_fmaf(zr_, cr[2 - q], hacc[q]);
+                hacc[3 + q] = __builtin_fmaf(zi_, ci[2 - q], hacc[3 + q]);
             }
-        };
-        tap_pass(std::false_type{});      // (one copy of the pass: a second one for whole tiles costs more registers than its four selects per token)
+            hacc[6] = __builtin_fmaf(one, cr[1], hacc[6]);
+            hacc[7] = __builtin_fmaf(one, ci[1], hacc[7]);
+            // (the sums are used at the end of the tile only; left alone, the compiler moves the whole chain
+            // down there and keeps all 48 gradients alive until then)
+#pragma unroll
+            for (int q = 0; q < HC_PART_ROWS; ++q) asm volatile("" : "+v"(hacc[q]));
+        }
         // a neighbour outside my head contributes nothing: tap 0 met the gradient at k+1, tap 2 the one at k-1
         hacc[0] = hk.last ? 0.f : hacc[0];
         hacc[3] = hk.last ? 0.f : hacc[3];
@@ -989,6 +1029,14 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 #pragma unroll
     for (int v = 0; v < V; ++v) acc_g[v] = acc_t[v] = 0.f;
     const int vbase = (VALVE || RET) ? valve_base() : 0;
+    // where my lane's share of two tokens' row sums goes (row_sums): [row of 16 lanes][token], a later token one word on
+    float *sum_to = nullptr;
+    float wv = 0.f, wr = 0.f, wv1 = 0.f, wr1 = 0.f;
+    if constexpr (VALVE || RET) {
+        const int row_ = (lv >> 4) * TILE_T + seg * NSTEP;
+        if (VALVE && RET) sum_to = ((lv & 8) ? sRp : sVp) + row_ + (HC ? 0 : (lv >> 2) & 1);
+        else sum_to = (VALVE ? sVp : sRp) + row_ + ((lv >> 3) & 1);
+    }
 #pragma unroll
     for (int i = NSTEP - 1; i >= 0; --i) {
 #pragma unroll
@@ -1007,44 +1055,44 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             }
             if (PARAM) {
                 const float ct_ = RET ? lr[v] : cth[v], st_ = RET ? li[v] : sth[v];
-                const float rr = __builtin_fmaf(ct_, Spr[i][v], -st_ * Spi[i][v]);
-                const float ri = __builtin_fmaf(st_, Spr[i][v], ct_ * Spi[i][v]);
+                const float rr = ROT ? Spr[i][v] : __builtin_fmaf(ct_, Spr[i][v], -st_ * Spi[i][v]);
+                const float ri = ROT ? Spi[i][v] : __builtin_fmaf(st_, Spr[i][v], ct_ * Spi[i][v]);
                 const float tg = __builtin_fmaf(nr, rr, ni * ri);
                 const float tth = (RET ? gm[i][v] : gam[v]) * __builtin_fmaf(ni, rr, -nr * ri);
                 acc_g[v] += clampf(tg, a.grad_clamp);
                 acc_t[v] += clampf(tth, a.grad_clamp);
-                if (RET) {  // d gamma, clamped, through the sigmoid, summed over the lanes of the head
-                    float wr = active ? clampf(tg, a.grad_clamp) * gm[i][v] * (1.0f - gm[i][v]) : 0.0f;
-                    wr = head_sum(wr, vwidth);
-                    if (head_sum_lane(lv, vwidth)) sRp[vbase + i] = wr;
-                }
+                if (RET) wr = clampf(tg, a.grad_clamp) * gm[i][v] * (1.0f - gm[i][v]);   // d gamma, clamped, through the sigmoid
             }
             const float gr_ = clampf(nr, a.grad_clamp), gi_ = clampf(ni, a.grad_clamp);
             const float c_ = LEAN ? __builtin_amdgcn_cosf(cs[i][v]) : cs[i][v];
             const float s_ = LEAN ? __builtin_amdgcn_sinf(cs[i][v]) : sn[i][v];
             const float da = __builtin_fmaf(gr_, c_, gi_ * s_);
             const float dph = __builtin_fmaf(gi_, c_, -gr_ * s_);
-            if (VALVE) {      // d/d beta, summed over the lanes that share the valve
-                float wv = active ? am[i][v] * da : 0.0f;
-                if (vwidth >= 16) {
-                    // rotations within each row of 16 lanes leave the row's sum in all of its lanes
-                    // (four full-rate adds); a 32-lane group then takes the lower row's sum into its
-                    // upper row, whose lanes end up with the group's total
-                    wv = dpp_add<0x128>(wv);
-                    wv = dpp_add<0x124>(wv);
-                    wv = dpp_add<0x122>(wv);
-                    wv = dpp_add<0x121>(wv);
-                    if (vwidth == 32) wv = dpp_add_bcast15(wv);
-                    if (lv == vwidth - 16 || (vwidth == 16 && lv == 16)) sVp[vbase + i] = wv;
-                } else {
-#pragma unroll
-                    for (int o = 4; o >= 1; o >>= 1)
-                        if (o < vwidth) wv += __shfl_xor(wv, o, 64);
-                    if (lv % vwidth == 0) sVp[vbase + i] = wv;
-                }
-            }
+            if (VALVE) wv = am[i][v] * da;      // d/d beta
             dzr[i][v] = da * dsm[i][v];          // d/d(conv pre-activation), magnitude stream
             dzi[i][v] = dph * ag[i][v];          //                           angle stream
+        }
+        // both are summed over the lanes of the head (whole groups lie inside the tensor or outside of it, which are not stored)
+        if constexpr (VALVE || RET) {
+            if (vwidth >= 16) {
+                if constexpr (VALVE && RET && HC) {
+                    // (token by token: the two values carried to the next token are two more spilled ones)
+                    const float u = row_sums(wv, wr);
+                    if ((tid & 7) == 0) sum_to[i] = u;
+                } else if (i & 1) {
+                    wv1 = wv;
+                    wr1 = wr;
+                } else if constexpr (VALVE && RET) {
+                    const float u = row_sums(wv, wv1, wr, wr1);
+                    if ((tid & 3) == 0) sum_to[i] = u;
+                } else {
+                    const float u = VALVE ? row_sums(wv, wv1) : row_sums(wr, wr1);
+                    if ((tid & 7) == 0) sum_to[i] = u;
+                }
+            } else if (VALVE != RET) {
+                const float u = head_sum8(VALVE ? wv : wr);
+                if ((tid & 7) == 0) (VALVE ? sVp : sRp)[vbase + i] = u;
+            }
         }
         // (the valve kernels are at their register budget: keep the tokens' work from interleaving)
         if (VALVE || RET) __builtin_amdgcn_sched_barrier(0);
@@ -1136,7 +1184,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             for (int e = tid; e < a.gpb * TILE_T; e += NT) {
                 const int g = e / TILE_T, tok = e - g * TILE_T;
                 const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
-                if (t < a.L && grp < a.G) a.vpart[((size_t)b * a.G + grp) * a.L + t] = sVp[e];
+                if (t < a.L && grp < a.G) a.vpart[((size_t)b * a.G + grp) * a.L + t] = vwidth == 32 ? sVp[e] + sVp[TILE_T + e] : sVp[e];
             }
         }
         // ---- and the retention logits' in the same layout
@@ -1144,7 +1192,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             for (int e = tid; e < a.gpb * TILE_T; e += NT) {
                 const int g = e / TILE_T, tok = e - g * TILE_T;
                 const int t = tt * TILE_T + tok, grp = lb * a.gpb + g;
-                if (t < a.L && grp < a.G) a.rpart[((size_t)b * a.G + grp) * a.L + t] = sRp[e];
+                if (t < a.L && grp < a.G) a.rpart[((size_t)b * a.G + grp) * a.L + t] = vwidth == 32 ? sRp[e] + sRp[TILE_T + e] : sRp[e];
             }
         }
     };

@@ -323,22 +323,25 @@ __device__ __forceinline__ float softplus_fast(float m)
     return __builtin_fmaxf(m, 0.0f) + 0.6931471805599453f * __builtin_amdgcn_logf(1.0f + e);
 }
 
+// softplus(m) as above, and its derivative sigmoid(m) from the same exponential
+__device__ __forceinline__ float softplus_sigmoid_fast(float m, float &sig)
+{
+    const float e = __builtin_amdgcn_exp2f(-1.4426950408889634f * __builtin_fabsf(m)), t = 1.0f + e;
+    const float r = __builtin_amdgcn_rcpf(t);
+    sig = m >= 0.0f ? r : e * r;
+    return __builtin_fmaxf(m, 0.0f) + 0.6931471805599453f * __builtin_amdgcn_logf(t);
+}
+
+// (a second interval has no upper end, see gate_set_of: three comparisons)
 __device__ __forceinline__ bool in_gate(const GateSet &g, float x)
 {
     // bitwise on purpose: short-circuit forms compile to divergent branches
-    return (bool)(((int)(x >= g.a1) & (int)(x <= g.b1)) | ((int)(x >= g.a2) & (int)(x <= g.b2)));
+    return (bool)(((int)(x >= g.a1) & (int)(x <= g.b1)) | (int)(x >= g.a2));
 }
 
 // Whole-wave shifts by one lane (DPP wave_shr:1 / wave_shl:1): lane i takes lane i-1's (i+1's) value, the
-// first (last) lane keeps its own; the *0 forms give it zero.
-__device__ __forceinline__ float wave_shift_up(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_shift_down(float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), 0x130, 0xF, 0xF, false));
-}
+// first (last) lane zero.  (By the shift's own rule for lanes without a source: keeping the lane's own value, or writing into
+// a register cleared before, is a second instruction.)
 __device__ __forceinline__ float wave_shift_up0(float x)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, true));
