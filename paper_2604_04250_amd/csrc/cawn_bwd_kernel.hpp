@@ -222,7 +222,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     uint32_t ticket_ahead = NO_TICKET;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
     if (tid_ == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // all three round trips at once
-        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x, 1u);
+        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -639,7 +639,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // (the next tile must be known by the time its gradients are staged; asked for here, the answer
     // arrives with this wave's staged rows, which it waits for below anyway)
     if (AHEAD && tid == 0 && !a.tq.one_each)
-        ticket_ahead = next_ticket_of(a.hdr, 1u);
+        ticket_ahead = next_ticket_of(a.hdr);
     float Xr[V], Xi[V];     // adjoint entering my segment (from later segments), zero tile input
     float Cb[V];            // RET: product of the retentions of the segments after mine
     {
@@ -961,7 +961,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     };
     if (AHEAD && !HC && wave != 0) stage_next();
     // (a workgroup without a next tile: one of the waves that would only wait counts it)
-    const TileQueues tq_ = {a.tq.lq, a.tq.one_each, a.tq.group};
+    const TileQueues tq_ = {a.tq.units, a.tq.one_each, a.tq.group};
     if (counts_early(tq_, epoch) && tid == NT - 64 &&
         leave_last(a.hdr, tq_, blockIdx.x, gridDim.x, leave_ask(a.hdr, tq_, blockIdx.x, gridDim.x)))
         reset_header(a.hdr, epoch + 1u, 0u, 1u);
@@ -1112,7 +1112,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 
     ARGS_AGAIN();
     if (!AHEAD && tid == 0 && !a.tq.one_each)
-        ticket_ahead = next_ticket_of(a.hdr, 1u);
+        ticket_ahead = next_ticket_of(a.hdr);
     // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order (behind a barrier)
     auto param_terms = [&]() {
         if constexpr (PARAM) {

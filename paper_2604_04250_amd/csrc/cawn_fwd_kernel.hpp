@@ -191,7 +191,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
 
     if (tid == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // both round trips at once
-        const uint32_t t = EACH ? next_ticket_of(a.hdr, 1u) : first_ticket(a.hdr, a.tq, blockIdx.x, 1u);
+        const uint32_t t = EACH ? next_ticket_of(a.hdr) : first_ticket(a.hdr, a.tq, blockIdx.x);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                              // merge of values that would wait for the atomic right here)
         if (tid == 0) {
             if (SINGLE || (!EACH && a.tq.one_each)) ticket_ahead = NO_TICKET;
-            else ticket_ahead = next_ticket_of(a.hdr, 1u);
+            else ticket_ahead = next_ticket_of(a.hdr);
         }
 
         // ---- the staged rows have landed (each wave waited for its own loads: before the loop, or
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
 
         // (the last tile of a workgroup that is counted early: by a wave that waits for the owner's carry)
         if constexpr (COUNT_EARLY) {
-            const TileQueues tq_ = {a.tq.lq, a.tq.one_each, a.tq.group};
+            const TileQueues tq_ = {a.tq.units, a.tq.one_each, a.tq.group};
             if (next_ticket >= qtiles && counts_early(tq_, epoch) && tid == 0 &&
                 leave_last(a.hdr, tq_, blockIdx.x, gridDim.x, leave_ask(a.hdr, tq_, blockIdx.x, gridDim.x)))
                 reset_header(a.hdr, epoch + 1u, 0u, 1u);
@@ -1001,14 +1001,12 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long w
 // 32-lane rows a prefix per tile (see make_queues).  (Both schemes in one kernel: the first kind 1 - 2.5 % slower, B16 L1000 J768
 // 53.9 us against 52.4, the second 4 %.)
 // A call may have more tiles than fit as workgroups of ONE at a time: the others start as these end, and still draw in
-// the chains' order.  They start with nothing on its way, and where there are many of them MANY is ahead.  All first draws of
-// ONE come from one counter with an odd number of chains, from two, four or eight with more factors of two (make_queues),
-// 11 ns each: the fewer counters, the later its tiles start, unless the chains are so few that their own length bounds the
-// call.  Time ONE / time MANY, conv 3 if not said, 3100 calls (chains in brackets):
-//   32 lanes, constant retention (768 fit at a time): tau 770 - 830 tiles 0.56 (1), 0.87 (5), 0.95 (7), 1.05 (13 - 63 odd); 0.56 (2), 0.86 (10),
-//     0.89 (14), 0.93 (18 - 66); 0.87 (24).  840 - 1020 tiles 0.55 (1), 0.89 (5), 0.98 - 1.03 (7), 1.03 (9), 1.10 (13 - 63); 0.94 (10), 0.98 (14),
-//     1.01 (18 - 66); 0.95 (24).  1150 tiles 0.90 (22 - 128), 1400 tiles 0.96 - 1.01, 1536 and more 1.02 - 1.25.  Valve the same to 0.03,
-//     at 840 - 1020 tiles 1.03 (18 - 66), 1.12 (21 - 63): B7 L5035 J224 39.1 us MANY, 45.0 ONE
+// the chains' order.  They start with nothing on its way, and where there are many of them MANY is ahead.
+// Time ONE / time MANY, conv 3 if not said, 3100 calls (chains in brackets; with fewer than four counters for the first draws of ONE where the
+// chains are no multiple of four, which cost it up to a seventh where there are few more tiles than fit at a time -- with eight for any
+// number of chains 595 such calls, 513 - 620 and 770 - 1020 tiles, are 0.85 - 1.03 of what MANY took):
+//   32 lanes, constant retention (768 fit at a time): 770 - 1020 tiles 0.55 - 0.97 (1 - 66); 1150 tiles 0.90 (22 - 128), 1400 tiles 0.96 - 1.01,
+//     1536 and more 1.02 - 1.25
 //   32 lanes, retentions: 560 - 1020 tiles 0.79 - 0.95 (even), 0.94 - 1.00 (odd); 1150 tiles 0.92, 1400 tiles 0.96; 1536 1.04 with the valve
 //   64 lanes, no retentions: bf16 800 - 1750 tiles 0.68 - 0.97, 2000 0.87 - 1.01, 3000 0.92 - 1.18, with the valve at 1280 0.90, at 1500 0.89 -
 //     1.03; harmonic convolution 560 - 2300 tiles 0.77 - 1.00, 3000 0.86 - 1.04, 4500 0.83 - 1.14
@@ -1018,8 +1016,6 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long w
 //     1.05; the other kinds 0.80 - 1.12, mean 0.98 (0.97 with conv 1), with retentions at 2020 tiles 1.02: B4 L3741 J1088 fp32 with retentions and the
 //     harmonic convolution 67 us MANY, 72 - 75 ONE.  Up to 32 chains 0.81 - 1.07, mean 0.95.  Up to conv 2 768 of ONE fit behind the harmonic
 //     convolution without retentions, and 800 - 1010 tiles are 1.00 - 1.10 (15, 49)
-//   a few tiles more than the 512 that fit, an odd number of 7 chains and more: fp32, and bf16 with retentions but without the harmonic
-//     convolution 513 - 560 tiles 0.96 - 1.11, mean 1.03, 575 tiles 1.05 (7 - 15), from 600 on 0.85 - 1.00; other kinds, and even chains, 0.85 - 1.00
 // bf16 without retentions needs fewer registers in MANY, of which 768 workgroups fit, than in ONE, of which 512 do: in
 // between every workgroup of MANY has one tile and ONE takes a second round, B1 L8192 J768 (768) 28.8 / 31.1.
 // Heads of 128 and 256 harmonics behind the harmonic convolution (rows of their own width, 64 tokens a tile): a workgroup of
@@ -1045,14 +1041,10 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
         if (one <= 0 || many <= 0) return hipErrorUnknown;
         const bool light = KC == 0 && !VALVE && (RET ? BF : HC) && units > 32;
         const int per_cu = !W64 || (BF && VALVE && !RET && !HC) ? 4 : light ? 5 : RET && KC > 0 ? 8 : 7;      // (tiles a compute unit)
-        const bool dealt = units % 4 == 0 || units <= (units % 2 ? 5u : 14u);      // (four counters or more, or few chains)
-        const bool few_more = jobs > one && !dealt &&
-                              (one >= 3 * cus ? !RET && (!W64 || HC) && 3 * jobs <= 4 * one
-                                              : (RET ? !(BF && HC) : !BF) && units % 2 && jobs - one <= (units < 16 ? 64 : 48));
         const bool wide_many = a.stage16 && (G::JB == 256 ? jobs > one : units > 32 && jobs > 9 * cus && !(RET && BF));
         if (W128) return wide_many ? launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s)
                                    : launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
-        if (jobs > per_cu * cus || (jobs > one && jobs <= many) || few_more)
+        if (jobs > per_cu * cus || (jobs > one && jobs <= many))
             return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s);   // persistent: what fits on the chip
         return launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);
     } else {

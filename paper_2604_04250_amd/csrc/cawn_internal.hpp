@@ -122,16 +122,19 @@ inline __host__ __device__ uint32_t done_word(uint32_t q) { return ticket_word(q
 // addresses 128 bytes apart side by side): the 384 workgroups of a 4096-token call on 768 lanes had their first tickets
 // after 4.4 us, their second ones (which only tell them that there is nothing left) 4.4 us later, and their last
 // count took as long again.  So:
-//   * a call whose workgroups take one tile each (a head's G tiles) draws no second ticket, and its U chains (or
-//     groups of G) are dealt to 2^lq counters; 2^lq divides U, so tile numbers stay what they are,
-//         tile = (number drawn from counter q << lq) + q G,
-//     a chain belongs to one counter, and a tile still only waits for tiles with a lower ticket of its own counter, which
-//     a running workgroup holds.  A workgroup draws from counter (index mod 2^lq): as many draws as the counter has tiles.
+//   * a call whose workgroups take one tile each draws no second ticket, and its U chains are dealt to eight counters:
+//     chain c to counter c mod 8, whose n-th draw is tile n / C of its chain number n mod C (C chains of this counter); tile
+//     numbers stay what they are (tile in time x U + chain), a chain belongs to one counter, and a tile still only waits
+//     for tiles with a lower ticket of its own counter, which a running workgroup holds.  Workgroup w draws from the counter
+//     of chain w mod U: as many draws as the counter has tiles.  (Dealt to 2^k counters only where 2^k divides U, an odd number
+//     of chains had one counter: a draw then took 2.3 us on average and 4.3 at most in a grid of 384 workgroups, 3.1 and 6.0
+//     in one of 512; with eight 0.9 - 1.0 and 1.6.  Forward calls of 7 - 66 chains with a few tiles more than fit: 3 - 14 % of
+//     the call.)
 //   * a call with more tiles than workgroups keeps one counter: its draws are spread over the call and cost nothing
 //     (eight counters with a second choice where one ran dry were slower: training step 431 -> 454 us, bf16 B2 L4096
 //     J4096 284 -> 298; the first tickets' delay keeps the workgroups out of step, and loads beside arithmetic);
 //   * the many workgroups of such a one-tile-each call are counted in two levels, in the middle of their tile (counts_early).
-struct TileQueues { uint32_t lq, one_each, group; };     // group: tiles of a chain between two prefixes (see chain_carry)
+struct TileQueues { uint32_t units, one_each, group; };     // group: tiles of a chain between two prefixes (see chain_carry)
 // Tiles between two prefixes in the forward: 8; 16 where there are so few chains that passing prefixes on bounds the call.
 // us a call with 2 / 4 / 8 / 16: B1 L4096 J768 20.5 / 18.8 / 18.1 / 19.2; B1 L32768 J256 of the paper's layer in bf16 109 /
 // 71 / 52 / 49, with the harmonic convolution 111 / 73 / 58 / 56; B2 L4096 J4096 bf16 84.5 / 83.6 / 84.8 / 86.9.
@@ -143,9 +146,7 @@ struct TileQueues { uint32_t lq, one_each, group; };     // group: tiles of a ch
 // J256 74.4 against 77.4 (with bf16 or the harmonic convolution, on 64-lane rows, the fold is ahead there too).
 inline TileQueues make_queues(uint32_t U, uint32_t nT, long long workgroups)
 {
-    TileQueues t{0, workgroups >= (long long)U * nT ? 1u : 0u, U <= 8 ? 16u : 8u};
-    while (t.one_each && (2u << t.lq) <= (uint32_t)MAX_QUEUES && U % (2u << t.lq) == 0) ++t.lq;
-    return t;
+    return TileQueues{U, workgroups >= (long long)U * nT ? 1u : 0u, U <= 8 ? 16u : 8u};
 }
 
 struct WsLayout {
@@ -541,16 +542,22 @@ __device__ __forceinline__ float tagged_value(tagged_t w) { return __uint_as_flo
 
 __device__ __forceinline__ uint32_t *hdr_word(WsHeader *h, uint32_t w) { return reinterpret_cast<uint32_t *>(h) + w; }
 constexpr uint32_t NO_TICKET = 0x7fffffffu;     // beyond every call's tiles
-// the first tile (of G) of workgroup `wg`: see TileQueues
-__device__ __forceinline__ uint32_t first_ticket(WsHeader *h, const TileQueues &t, uint32_t wg, uint32_t G)
+// the first tile of workgroup `wg`: see TileQueues
+__device__ __forceinline__ uint32_t first_ticket(WsHeader *h, const TileQueues &t, uint32_t wg)
 {
-    const uint32_t q = wg & ((1u << t.lq) - 1u);
-    return (__hip_atomic_fetch_add(hdr_word(h, ticket_word(q)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) << t.lq) + q * G;
+    auto draw = [&](uint32_t q) { return __hip_atomic_fetch_add(hdr_word(h, ticket_word(q)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (!t.one_each) return draw(0);
+    constexpr uint32_t Q = MAX_QUEUES;
+    if (t.units % Q == 0) return draw(wg % Q) * Q + wg % Q;
+    const uint32_t q = wg % t.units % Q, C = (t.units - q + Q - 1) / Q, n = draw(q);
+    // n / C: n < 2^18, so that the reciprocal's error is below the distance of (n + 1/2) / C from a whole number
+    const uint32_t tt = (uint32_t)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)C));
+    return tt * t.units + (n - tt * C) * Q + q;
 }
 // ... and the next ones (calls with one counter)
-__device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h, uint32_t G)
+__device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h)
 {
-    return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_add(hdr_word(h, ticket_word(0)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // A workgroup leaves the call: the count is asked for (leave_ask), and its answer says whether it was the last one of the
 // grid (leave_last).  96 and more workgroups that take one tile each, and so are counted at about the same time, are counted
