@@ -653,20 +653,16 @@ static float valve_threshold_of(float eps)
 // Short tiles (64 tokens, 8 per thread) for calls whose 256-token tiles would leave much of the chip idle: as long as
 // every short tile has a workgroup of its own on the chip (4 per compute unit, 1 of twice the threads with the harmonic
 // convolution; beyond that a workgroup's second tile, and all draws on one counter, double a call's time), and while a tile's
-// way to its carry is not too long.  A short tile reads the aggregates of all tiles before it in its chain, which costs
-// with the chain's length (0.15 us a tile, 0.24 with the product of the retentions), and the tiles of a call cost 5 ns each
-// where they start and leave; long tiles cost nearly the same whatever the call.  So the line between them is where
+// way to its carry is not too long.  A short tile reads the aggregates of all tiles before it in its chain, and the tiles of a call
+// cost where they start and leave; long tiles cost nearly the same whatever the call.  So the line between them is where
 //     (tiles in a chain) x per + (tiles)  =  most,
-// set from 742 calls without the harmonic convolution (J = 64, 256 and 768, 5 - 64 tiles a chain, 32 - 1024 tiles) while long
-// tiles staged their rows; calls just below it are up to a fifth faster on long tiles since those read their rows themselves.
+// set from 394 calls of ten kinds (1 - 64 chains of 6 - 64 short tiles, conv 3).  us a call, long / short tiles, tiles a chain in front:
+//   fp32, 2 chains  10: 10.2 / 8.1  36: 11.3 / 10.5  50: 11.2 / 11.7;  12 chains  10: 10.7 / 8.6  24: 11.3 / 10.5  36: 11.9 / 12.4  64: 12.3 / 15.5;
+//     24 chains  16: 11.1 / 10.2  36: 12.4 / 15.1;  with valve and retentions, 2 chains  36: 13.2 / 12.2  50: 13.2 / 13.7;  24 chains  16: 13.1 / 12.0  36: 14.4 / 18.4
+//   bf16 (long tiles of 64 lanes), 8 chains  36: 12.5 / 12.2, with the valve 50: 13.5 / 13.4;  24 chains  16: 11.9 / 10.0  24: 12.7 / 11.9  36: 13.6 / 15.1
+//   harmonic convolution (up to 256 tiles)  4 chains  16: 11.5 / 9.7  50: 13.3 / 13.4  64: 13.6 / 14.8, of the paper's layer 64: 15.5 / 15.5;  16 chains  16: 11.7 / 10.8
 // With a constant retention a short tile's error is half as large (runs of 8 instead of 32 tokens between exact powers of
 // lambda: 1.8e-7 against 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
-// Long against short, us a call, conv 4 (3 with the valve or retentions; tiles in brackets): J64 4 x L512 11.1 / 8.7 (64), J256
-// L2048 11.8 / 12.4 (256), L3584 12.5 / 15.9 (448), 4 x L2048 12.7 / 15.9 (1024); J768 L1024 11.6 / 10.6 (384), L2048 12.2 / 14.7
-// (768, short), 3 x L768 12.1 / 12.6 (864, short); paper's layer, J256: L1024 14.5 / 11.6 (128), L1536 14.7 / 13.2 (192), 7 x L1024 15.5 /
-// 16.5 (896), L3072 16.1 / 18.9 (384), in bf16 L1536 15.7 / 13.4, 7 x L1024 15.6 / 16.6, L3072 17.6 / 19.1; J256 L2048 with the valve in bf16
-// 14.9 / 12.8 (256).  With the harmonic convolution, J256: L1024 12.4 / 11.1 (64), L2048 14.3 / 13.7 (128), L4096 15.1 / 18.2 (256,
-// short), paper's layer L2048 18.7 / 16.8 (128), L3700 19.1 / 21.3 (232, short).
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
@@ -676,11 +672,9 @@ static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, in
     const size_t nT = ((size_t)d->L + FwdShort::TILE_T - 1) / FwdShort::TILE_T;
     const size_t tiles = (size_t)d->B * nT * (((size_t)w.J + JB - 1) / JB);
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
-    if (nT > (hc && ret ? 60 : 64) || tiles > 256u * (hc ? 1 : 4)) return false;
-    if (!hc) {
-        const size_t per = ret ? (bf16 ? 16 : 40) : 24, most = ret ? (bf16 ? 1056 : 1480) : 1608;
-        if (nT * per + tiles > most) return false;
-    }
+    if (nT > (size_t)FwdShort::MAX_CHAIN || tiles > 256u * (hc ? 1 : 4)) return false;
+    const size_t per = hc ? 6 : bf16 ? 12 : 17, most = hc ? 510 : bf16 ? 960 : 880;
+    if (!(hc && ret) && nT * per + tiles > most) return false;
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
 

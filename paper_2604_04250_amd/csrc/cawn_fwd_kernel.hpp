@@ -81,7 +81,10 @@ template <class G> struct FwdConsts {
 };
 // 16 bytes per lane per load: JB / 4 lanes cover a row.  Called by one wave.  Table rows are 256-byte aligned and
 // padded, so every address is valid.
-template <class G, int NCR>
+// Rows NCM .. NCR - 1: lambda^TILE_T as a double-float (table rows PT, PT + 1, PTL, PTL + 1).
+template <class G, int NCM, int PT, int PTL>
+__device__ __forceinline__ int const_row(int r) { return r < NCM ? FwdConsts<G>::table_row(r) : r < NCM + 2 ? PT + (r - NCM) : PTL + (r - NCM - 2); }
+template <class G, int NCR, int NCM, int PT, int PTL>
 __device__ __forceinline__ void stage_consts(float *sC, const float *table, int Jp, int lb, int lane)
 {
     constexpr int JB = G::JB, LR = JB / 4, RPI = 64 / LR;      // lanes per row, rows per instruction
@@ -90,7 +93,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
     for (int i = 0; i < (NCR + RPI - 1) / RPI; ++i) {
         const int r = i * RPI + r_in;
         if (r < NCR) {
-            const float *src = table + ((size_t)FwdConsts<G>::table_row(r) * Jp + (size_t)lb * JB + c_in);
+            const float *src = table + ((size_t)const_row<G, NCM, PT, PTL>(r) * Jp + (size_t)lb * JB + c_in);
 #if defined(__HIP_DEVICE_COMPILE__)
             __builtin_amdgcn_global_load_lds(src, sC + (size_t)(i * RPI) * JB, 16, 0, 0);
 #else
@@ -149,8 +152,15 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     static_assert(JB <= 256 && 256 % JB == 0, "a staged row must fit a wave");
     static_assert(NW > WPS, "the last segment's waves own the chain, the others stage the next tile");
 
+    // One tile a workgroup: the aggregates of a group's tiles, read by all segments where one group of threads would need more
+    // than a round trip (NB tiles each); over the staged rows, which are dead by then
+    constexpr int NB = G::SHORT ? (RET ? (HC ? 6 : 4) : (HC ? 8 : 6)) : (HC && RET ? 2 : (BF && !RET && !HC ? 4 : 7));
+    // (not in the kernel of which three workgroups fit a compute unit: its registers are taken, 12 - 36 spilled)
+    constexpr bool ALL_READ = SINGLE && (G::SHORT || BF || VALVE || RET || HC);
+    constexpr int N_AGG = ALL_READ ? (G::SHORT ? FwdShort::MAX_CHAIN : 16) * (RET ? 3 : 2) * JB : 1, N_U = ONE ? 1 : 2 * NRTP * JBS;
+    __shared__ __attribute__((aligned(16))) float sPoolU[N_AGG > N_U ? N_AGG : N_U];
     // ONE: a thread reads its rows from memory itself (see the loads below)
-    __shared__ __attribute__((aligned(16))) float sU[ONE ? 1 : 2 * NRTP][JBS];  // [stream*NRTP + rr][lane]
+    float (*sU)[JBS] = reinterpret_cast<float (*)[JBS]>(&sPoolU[0]);  // [stream*NRTP + rr][lane]
     // element (row, lane) of the staged rows as fp32
     auto su = [&](int r, int l) -> float {
         if constexpr (BF) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(&sU[r][0])[l] << 16);
@@ -159,7 +169,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     __shared__ float sE[NSEG - 1][2][JB];          // (the last segment's is nobody's predecessor inside the tile)
     __shared__ float sCarry[2][JB];
     typedef FwdConsts<G> CR;
-    constexpr int NCR = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0);     // staged lane-constant rows
+    // staged lane-constant rows.  SINGLE: and lambda^TILE_T, which other kernels load where they need it -- a load on one of
+    // several paths there, which the compiler waits for where the paths meet, behind the stores of the aggregate
+    constexpr int NCM = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0), NCR = NCM + (SINGLE ? 4 : 0);
     __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
     // lambda^TILE_T as a double-float: leading part re, im, remainder re, im
     constexpr int PT = TILE_T == 64 ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
@@ -217,7 +229,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     const int ist32 = (int)a.ist;
     auto stage_tile = [&](const TileId &T) {
         if (owner_wave) return;
-        if (wave == 0) stage_consts<G, NCR>(&sC[0][0], a.table, a.Jp, T.lb, lane);
+        if (wave == 0) stage_consts<G, NCR, NCM, PT, PTL>(&sC[0][0], a.table, a.Jp, T.lb, lane);
 #if defined(__HIP_DEVICE_COMPILE__)
         if (WIDE && wave == 0 && lane < HC_ROWS)
             __builtin_amdgcn_global_load_lds(a.table + ((size_t)(R_W0 + 2 * KC + lane) * a.Jp + (size_t)T.lb * JB), &sHW[0], 4, 0, 0);
@@ -260,7 +272,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
 #pragma unroll
         for (int q = 0; q < NCQ; ++q) {
             const int w = q * NT + tid < NCR * JB / 4 ? q * NT + tid : 0;
-            cv[q] = *reinterpret_cast<const v4f *>(a.table + (size_t)CR::table_row(w / (JB / 4)) * a.Jp + (size_t)T.lb * JB + w % (JB / 4) * 4);
+            cv[q] = *reinterpret_cast<const v4f *>(a.table + (size_t)const_row<G, NCM, PT, PTL>(w / (JB / 4)) * a.Jp + (size_t)T.lb * JB + w % (JB / 4) * 4);
         }
         auto logit = [&](const float *p, int i) {       // (beyond the end: a valid address, never used)
             const int t = T.tt * TILE_T + i % TILE_T, g = i / TILE_T, h = (T.lb * JB) / a.F + (g < a.gpb ? g : 0);
@@ -586,9 +598,17 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         //      the look-back and publish the prefix, all within their own wave (stores are waited
         //      for with that wave's vmcnt, so no workgroup barrier sits on the publication path).
         const size_t slot = (size_t)id * 2 * JB + lv * V;
+        // (what this tile publishes: its aggregate, the chain's first tile its prefix instead; the last of a
+        // group also its prefix; the chain's last tile nothing)
+        // (EACH: a prefix per tile, the first tile's with the others)
+        const int group = EACH ? 1 : (int)a.tq.group;
+        const bool feeds = tt + 1 < a.nT, ends_group = EACH || (tt & (group - 1)) == group - 1;
+        const int before = tt & (group - 1);                     // tiles before this one in its group
+        const bool all_read = ALL_READ && before > NB;           // (uniform over the workgroup)
+        float Tr[V], Ti[V], hr[V], hi[V], qr[V], qi[V];
+        float Pt[V];      // RET: product of the whole tile's retentions
+        tagged_t w0 = 0, w1 = 0;
         if (is_tail_seg) {
-            float Tr[V], Ti[V], hr[V], hi[V], qr[V], qi[V];
-            float Pt[V];      // RET: product of the whole tile's retentions
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 if (RET) {
@@ -604,41 +624,58 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                 }
                 hr[v] = hi[v] = qr[v] = qi[v] = 0.f;
             }
-            if (active) {   // lambda^TILE_T as a double-float
+            if constexpr (SINGLE) {
+                hr[0] = sC[SINGLE ? NCM : 0][lv];
+                hi[0] = sC[SINGLE ? NCM + 1 : 0][lv];
+                qr[0] = sC[SINGLE ? NCM + 2 : 0][lv];
+                qi[0] = sC[SINGLE ? NCM + 3 : 0][lv];
+            } else if (active) {   // lambda^TILE_T as a double-float
                 const float *tb = a.table + j0;
                 Vec<V>::ld(hr, tb + (size_t)PT * a.Jp);
                 Vec<V>::ld(hi, tb + (size_t)(PT + 1) * a.Jp);
                 Vec<V>::ld(qr, tb + (size_t)PTL * a.Jp);
                 Vec<V>::ld(qi, tb + (size_t)(PTL + 1) * a.Jp);
             }
+            if (tt > 0 && feeds && (EACH || !ends_group)) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    tagged_store(a.agg + slot + v, Tr[v], tag);
+                    tagged_store(a.agg + slot + JB + v, Ti[v], tag);
+                    if (RET) tagged_store(a.aggp + (size_t)id * JB + lv * V + v, Pt[v], tag);
+                }
+            }
+            if (all_read && tt != before) {       // (the prefix is asked for ahead of the aggregates)
+                const tagged_t *src = a.pre + (size_t)(id - (uint32_t)(before + 1) * (uint32_t)a.B) * 2 * JB + lv;
+                w0 = tagged_load(src);
+                w1 = tagged_load(src + JB);
+            }
+        }
+        bool read_ok = true;
+        if constexpr (ALL_READ) {
+            if (all_read) {
+                read_ok = read_aggregates<JB, HC && RET ? 2 : 4, NSEG, RET>(&sPoolU[0], a.agg, a.aggp, id, (uint32_t)a.B, tt, before, seg, lv,
+                                                                           a.spin_limit, tag);
+                if (!read_ok && lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                lds_barrier();
+            }
+        }
+        if (is_tail_seg) {
             float cr[V], ci[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) cr[v] = ci[v] = 0.f;
-            // (what this tile publishes: its aggregate, the chain's first tile its prefix instead; the last of a
-            // group also its prefix; the chain's last tile nothing)
-            // (EACH: a prefix per tile, the first tile's with the others)
-            const int group = EACH ? 1 : (int)a.tq.group;
-            const bool feeds = tt + 1 < a.nT, ends_group = EACH || (tt & (group - 1)) == group - 1;
             if (tt == 0) {
                 if (a.state_in && active) {
                     Vec<V>::ld(cr, a.state_in + ((size_t)b * 2 + 0) * a.J + j0);
                     Vec<V>::ld(ci, a.state_in + ((size_t)b * 2 + 1) * a.J + j0);
                 }
             } else {
-                if (feeds && (EACH || !ends_group)) {
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        tagged_store(a.agg + slot + v, Tr[v], tag);
-                        tagged_store(a.agg + slot + JB + v, Ti[v], tag);
-                        if (RET) tagged_store(a.aggp + (size_t)id * JB + lv * V + v, Pt[v], tag);
-                    }
-                }
-                // aggregates read per round trip: what the register budget leaves
-                constexpr int NB = G::SHORT ? (RET ? (HC ? 6 : 4) : (HC ? 8 : 6)) : (HC && RET ? 2 : (BF && !RET && !HC ? 4 : 7));
                 bool got;
                 if constexpr (EACH)
                     got = look_back<V, false, LPR, 2, RET>(a.agg, a.pre, id - (uint32_t)a.B, (uint32_t)a.B, tt, JB, lv * V, lv, hr, hi,
                                                            qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
+                else if (all_read)
+                    got = fold_aggregates<JB, RET, false>(&sPoolU[0], a.pre, id, (uint32_t)a.B, tt, before, lv, w0, w1, hr[0], hi[0], qr[0], qi[0],
+                                                   a.spin_limit, tag, cr[0], ci[0]);
                 else
                     got = chain_carry<JB, NB, RET, !G::SHORT && !(HC && RET)>(a.agg, a.aggp, a.pre, id, (uint32_t)a.B, tt, group, lv, hr[0], hi[0], qr[0],
                                                      qi[0], a.spin_limit, tag, cr[0], ci[0]);

@@ -48,6 +48,7 @@ namespace cawn {
 template <int NSTEP_, int JB_, int NT_> struct FwdTile {
     static constexpr int NSTEP = NSTEP_, JB = JB_, NT = NT_, NSEG = NT / JB, TILE_T = NSEG * NSTEP;
     static constexpr bool SHORT = NSTEP < 32;
+    static constexpr int MAX_CHAIN = 64;       // most short tiles of a chain (one group)
 };
 using FwdGeom = FwdTile<32, 32, 256>;      // 256 tokens x 32 lanes
 using FwdHead = FwdTile<32, 64, 256>;      // 128 tokens x 64 lanes: harmonic convolution
@@ -658,6 +659,42 @@ __device__ __forceinline__ bool group_all(bool ok)
 // `id` is the tile's index, `stride` the distance to its predecessor's, tt >= 1 its position in the chain.  M is
 // lambda^TILE_T as a double-float; its power is formed in fp64.  Every wait is bounded: false if one gave up (the carry
 // is then meaningless).
+//
+// The fold of a group's aggregates, one at a time in order; LINK: and the power of M, for the link on the prefix before them.
+struct ChainFold {
+    float Er = 0.f, Ei = 0.f, P = 1.f;
+    double mr = 1.0, mi = 0.0;
+    template <bool RET, bool CONJ>
+    __device__ __forceinline__ void add(bool first, bool link, float tr, float ti, float p, float hr, float hi, float qr, float qi)
+    {
+        if constexpr (RET) {
+            Er *= p;
+            Ei *= p;
+            P *= p;
+        }
+        if (first) {
+            Er = tr;
+            Ei = ti;
+        } else {
+            float nr, ni;
+            chain_step<CONJ>(tr, ti, hr, hi, qr, qi, Er, Ei, nr, ni);
+            Er = nr;
+            Ei = ni;
+        }
+        if (link) {
+            const double Mr = (double)hr + (double)qr, Mi = (double)hi + (double)qi, t = mr * Mr - mi * Mi;
+            mi = mr * Mi + mi * Mr;
+            mr = t;
+        }
+    }
+    template <bool RET, bool CONJ>
+    __device__ __forceinline__ void link(float cr, float ci, float &Pr, float &Pi)      // E + P M^r c
+    {
+        const float ar = (float)mr, ai = (float)mi;
+        if constexpr (RET) { cr *= P; ci *= P; }
+        chain_step<CONJ>(Er, Ei, ar, ai, (float)(mr - (double)ar), (float)(mi - (double)ai), cr, ci, Pr, Pi);
+    }
+};
 template <int JB, int NB, bool RET, bool PRE>
 __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t *aggp, const tagged_t *pre, uint32_t id,
                                             uint32_t stride, int tt, int G, int lv, float hr, float hi, float qr, float qi,
@@ -667,9 +704,7 @@ __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t 
     const bool first_group = tt == r;
     const uint32_t first = id - (uint32_t)r * stride;
     uint32_t spins = 0;
-    float Er = 0.f, Ei = 0.f, P = 1.f;
-    const double Mr = (double)hr + (double)qr, Mi = (double)hi + (double)qi;
-    double mr = 1.0, mi = 0.0;
+    ChainFold f;
     // (PRE: the prefix is asked for with the first aggregates: where it is already there, one round trip brings both)
     const tagged_t *src = pre + (size_t)(first - stride) * 2 * JB + lv;
     tagged_t w0 = 0, w1 = 0;
@@ -699,34 +734,12 @@ __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t 
             __builtin_amdgcn_s_sleep(1);
         }
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            if (base + k < r) {
-                const float tr = tagged_value(wr[k]), ti = tagged_value(wi[k]);
-                if constexpr (RET) {
-                    const float p = tagged_value(wp[k]);
-                    Er *= p;
-                    Ei *= p;
-                    P *= p;
-                }
-                if (base + k == 0) {
-                    Er = tr;
-                    Ei = ti;
-                } else {
-                    float nr, ni;
-                    chain_step<false>(tr, ti, hr, hi, qr, qi, Er, Ei, nr, ni);
-                    Er = nr;
-                    Ei = ni;
-                }
-                if (!first_group) {
-                    const double t = mr * Mr - mi * Mi;
-                    mi = mr * Mi + mi * Mr;
-                    mr = t;
-                }
-            }
-        }
+        for (int k = 0; k < NB; ++k)
+            if (base + k < r)
+                f.add<RET, false>(base + k == 0, !first_group, tagged_value(wr[k]), tagged_value(wi[k]), RET ? tagged_value(wp[RET ? k : 0]) : 1.f, hr, hi, qr, qi);
     }
-    cr = Er;
-    ci = Ei;
+    cr = f.Er;
+    ci = f.Ei;
     if (first_group) return true;
     while (!group_all<JB>(tagged_ok(w0, tag) && tagged_ok(w1, tag))) {
         if (++spins > spin_limit) return false;
@@ -736,14 +749,78 @@ __device__ __forceinline__ bool chain_carry(const tagged_t *agg, const tagged_t 
     }
     cr = tagged_value(w0);
     ci = tagged_value(w1);
-    if (r > 0) {
-        const float ar = (float)mr, ai = (float)mi;
-        float nr, ni;
-        if constexpr (RET) { cr *= P; ci *= P; }
-        chain_step<false>(Er, Ei, ar, ai, (float)(mr - (double)ar), (float)(mi - (double)ai), cr, ci, nr, ni);
-        cr = nr;
-        ci = ni;
+    if (r > 0) f.link<RET, false>(cr, ci, cr, ci);
+    return true;
+}
+
+// The same with all of a workgroup's segments reading: segment `seg` of NSEG takes tiles seg, seg + NSEG, ... of the r before this
+// one in its group, NB per round trip, and leaves them in LDS (out [tile][2 or 3][JB]), where the fold finds them behind a barrier.
+// One or two round trips for the whole group, by waves that would only wait: a group of 16 or a short chain of up to 64 took
+// one per NB tiles.  False if a wait gave up (what it leaves is then meaningless).
+template <int JB, int NB, int NSEG, bool RET>
+__device__ __forceinline__ bool read_aggregates(float *out, const tagged_t *agg, const tagged_t *aggp, uint32_t id, uint32_t stride, int tt,
+                                                int r, int seg, int lv, uint32_t spin_limit, uint32_t tag)
+{
+    const uint32_t first = id - (uint32_t)r * stride;
+    uint32_t spins = 0;
+    for (int base = seg; base < r; base += NB * NSEG) {
+        tagged_t wr[NB], wi[NB], wp[RET ? NB : 1];
+        while (true) {
+            bool ok = true;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const size_t t = first + (uint32_t)(base + k * NSEG < r ? base + k * NSEG : base) * stride;     // (past the end: the first again)
+                wr[k] = tagged_load(agg + t * 2 * JB + lv);
+                wi[k] = tagged_load(agg + t * 2 * JB + JB + lv);
+                if constexpr (RET) wp[k] = tagged_load(aggp + t * JB + lv);
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                ok = ok && tagged_ok(wr[k], tag) && tagged_ok(wi[k], tag);
+                if constexpr (RET) ok = ok && (tagged_ok(wp[k], tag) || (tt == r && (base + k * NSEG < r ? base + k * NSEG : base) == 0));
+            }
+            if (group_all<JB>(ok)) break;
+            if (++spins > spin_limit) return false;
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const int t = base + k * NSEG;
+            if (t < r) {
+                float *o = out + (size_t)t * (RET ? 3 : 2) * JB + lv;
+                o[0] = tagged_value(wr[k]);
+                o[JB] = tagged_value(wi[k]);
+                if constexpr (RET) o[2 * JB] = tagged_value(wp[k]);
+            }
+        }
     }
+    return true;
+}
+template <int JB, bool RET, bool CONJ>
+__device__ __forceinline__ bool fold_aggregates(const float *in, const tagged_t *pre, uint32_t id, uint32_t stride, int tt, int r, int lv,
+                                                tagged_t w0, tagged_t w1, float hr, float hi, float qr, float qi, uint32_t spin_limit,
+                                                uint32_t tag, float &cr, float &ci)
+{
+    const bool first_group = tt == r;
+    ChainFold f;
+#pragma unroll 4
+    for (int t = 0; t < r; ++t) {
+        const float *o = in + (size_t)t * (RET ? 3 : 2) * JB + lv;
+        f.add<RET, CONJ>(t == 0, !first_group, o[0], o[JB], RET ? o[RET ? 2 * JB : 0] : 1.f, hr, hi, qr, qi);
+    }
+    cr = f.Er;
+    ci = f.Ei;
+    if (first_group) return true;
+    const tagged_t *src = pre + (size_t)(id - (uint32_t)(r + 1) * stride) * 2 * JB + lv;
+    for (uint32_t spins = 0; !group_all<JB>(tagged_ok(w0, tag) && tagged_ok(w1, tag));) {
+        if (++spins > spin_limit) return false;
+        __builtin_amdgcn_s_sleep(1);
+        w0 = tagged_load(src);
+        w1 = tagged_load(src + JB);
+    }
+    cr = tagged_value(w0);
+    ci = tagged_value(w1);
+    if (r > 0) f.link<RET, CONJ>(cr, ci, cr, ci);
     return true;
 }
 
