@@ -129,7 +129,10 @@ __device__ __forceinline__ float row_sums(float a0, float a1, float b0, float b1
 // the rows.  The tap gradients d w_i = sum dC[k] Z[k+i-1] = sum_k' Z[k'] dC[k'-i+1] pair a thread's own
 // clamped state Z (rebuilt in the front-end) with the same three gradients, read again from LDS there; they
 // leave the tile as 8 more rows of per-lane partial sums.
-template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
+// MODE: how a workgroup's tiles follow each other.  AHEAD, LATE: it takes several (see the comment on staging below).  ONE: a
+// workgroup for every tile, known at compile time: nothing is kept across a loop, and the carry comes by groups of tiles.
+enum BwdMode { AHEAD_ = 0, LATE_ = 1, ONE_ = 2 };
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, int MODE>
 __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_kernel(const BwdArgs a)
 {
     static_assert(!HC || (PARAM && V == 1), "harmonic convolution: with the state rebuild, one lane per thread");
@@ -139,7 +142,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // of its sin and cos between the front-end and the reverse pass, park the conv taps in LDS during
     // the reverse pass and fetch the reverse-pass constants after the front-end.
     constexpr bool LEAN = VALVE || RET;
-    static_assert(AHEAD || LEAN, "the other kernels stage a tile ahead in every call");
+    constexpr bool AHEAD = MODE == AHEAD_, ONE = MODE == ONE_;
+    static_assert(MODE != LATE_ || LEAN, "the other kernels stage a tile ahead in every call of several tiles a workgroup");
     constexpr int TILE_T = BwdGeom::TILE_T, NSTEP = BwdGeom::NSTEP, NSEG = BwdGeom::NSEG, LPR = BwdLPR;
     constexpr int JB = V * LPR;
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
@@ -177,7 +181,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // only because arrays with disjoint lifetimes share storage: the conv-gradient halo rows (written
     // after the reverse pass) lie over the segment aggregates (dead by then), and the partial-sum
     // staging lies over the input rows (dead after the last weight-gradient read, one more barrier).
-    constexpr bool REGS = !AHEAD && !HC;
+    // (ONE with both kinds of logits: staged too, at the top of its tile: a training step of B7 L1024 J256 of the paper's layer
+    // 36.5 us with registers, 9 values of them spilled, 34.9 staged)
+    constexpr bool REGS = !AHEAD && !HC && !(ONE && VALVE && RET);
     constexpr int RB_ROW = HC ? 4 + HC_ROWS : 4;
     constexpr int NRZ = staged_rows<TILE_T, JBS, 0>();                // staged rows per gradient stream
     __shared__ __attribute__((aligned(16))) float sDz[REGS ? 1 : 2 * NRZ][JBS];    // [stream*NRZ + token][lane]
@@ -189,8 +195,11 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     __shared__ float sLam[REGS ? 1 : RB_ROW + (RET ? 1 : 0)][JB];
     // HC: the gradients of the two lanes beside the lane block, [plane][side: lane -1, lane JB][token]
     __shared__ float sEdge[HC ? 4 * NRZ : 1];
-    constexpr int N_EB = NW * 2 * JB, N_HALO = NW * HALO1 * 2 * JB;
-    __shared__ float sPool[N_EB > N_HALO ? N_EB : N_HALO];
+    // (and, between the two, over both: the aggregates of a group of tiles, in calls with a workgroup for every tile)
+    constexpr int GROUP = 16;
+    constexpr int N_EB = NW * 2 * JB, N_HALO = NW * HALO1 * 2 * JB, N_FOLD = ONE ? (GROUP - 1) * (RET ? 3 : 2) * JB : 0;
+    constexpr int N_POOL = N_EB > N_HALO ? N_EB : N_HALO;
+    __shared__ float sPool[N_POOL > N_FOLD ? N_POOL : N_FOLD];
     float (*sEb)[2][JB] = reinterpret_cast<float (*)[2][JB]>(&sPool[0]);
     float (*sHalo)[HALO1][2][JB] = reinterpret_cast<float (*)[HALO1][2][JB]>(&sPool[0]);   // [NW]: first rows of each wave's earlier segment
     __shared__ float sCarry[2][JB];
@@ -222,7 +231,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     uint32_t ticket_ahead = NO_TICKET;   // thread 0: the ticket asked for in this tile, until it is parked in LDS
     if (tid_ == 0) {
         const uint32_t e = flag_load(&a.hdr->epoch);     // all three round trips at once
-        const uint32_t t = first_ticket(a.hdr, a.tq, blockIdx.x);
+        const uint32_t t = ONE ? first_ticket(a.hdr, a.tq, blockIdx.x) : next_ticket_of(a.hdr);
         sEpoch = e;
         sTicket[0] = t;
         sLast = 0;
@@ -274,6 +283,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     const bool head = seg == 0;                       // owns the tile's adjoint aggregate and the chain
     const bool chained = ttr > 0;                     // has a predecessor in the chain
     const bool feeds = tt > 0;                        // has a successor in the chain
+    const int before = ttr & (GROUP - 1);             // tiles before this one in its group
 
     // (the wave that owns the chain runs at raised priority until the tile's prefix is out: what it does in
     // that span -- aggregate, look-back, prefix -- is what other tiles wait for; 0.5 % on the whole kernel)
@@ -638,8 +648,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     BWD_STAMP(2);
     // (the next tile must be known by the time its gradients are staged; asked for here, the answer
     // arrives with this wave's staged rows, which it waits for below anyway)
-    if (AHEAD && tid == 0 && !a.tq.one_each)
-        ticket_ahead = next_ticket_of(a.hdr);
+    if (AHEAD && tid == 0) ticket_ahead = next_ticket_of(a.hdr);
     float Xr[V], Xi[V];     // adjoint entering my segment (from later segments), zero tile input
     float Cb[V];            // RET: product of the retentions of the segments after mine
     {
@@ -702,7 +711,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             sCarry[0][lv * V + v] = Tr[v];     // parked here until the look-back (frees registers)
             sCarry[1][lv * V + v] = Ti[v];
         }
-        if (chained && feeds) {
+        if ((chained || ONE) && feeds) {      // (the first tile's is its prefix: nothing enters it)
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 tagged_store(a.agg + slot + v, Tr[v], tag);
@@ -713,7 +722,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
     // the staged rows have landed (the head wave leaves the stores of its aggregate, its youngest
     // operations, in flight: their round trip is nobody's business here)
-    if (wave == 0 && chained && feeds) wait_vm<(RET ? 3 : 2) * V>();
+    if (wave == 0 && (chained || ONE) && feeds) wait_vm<(RET ? 3 : 2) * V>();
     else wait_stores_done();
     if (VALVE && wave == NW - 1) {      // logits to factors (0: closed): one element a lane instead of one a lane, token and head
         for (int i = 0; i < TILE_T * a.gpb / 64; ++i)
@@ -961,11 +970,28 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     };
     if (AHEAD && !HC && wave != 0) stage_next();
     // (a workgroup without a next tile: one of the waves that would only wait counts it)
-    const TileQueues tq_ = {a.tq.units, a.tq.one_each, a.tq.group};
-    if (counts_early(tq_, epoch) && tid == NT - 64 &&
+    const TileQueues tq_ = {a.tq.units, 1u, a.tq.group};
+    if (ONE && counts_early(tq_, epoch) && tid == NT - 64 &&
         leave_last(a.hdr, tq_, blockIdx.x, gridDim.x, leave_ask(a.hdr, tq_, blockIdx.x, gridDim.x)))
         reset_header(a.hdr, epoch + 1u, 0u, 1u);
     // ---- chain, second half: look-back (its round trips were hidden behind the recompute above)
+    // In calls with a workgroup for every tile all tiles publish their aggregates at about the same time, before their
+    // front-ends: each of the 16 segments reads one of the group's, in one round trip, and the head group folds them from LDS;
+    // prefixes are passed on once per group (the scheme of the forward's chain_carry).  With a prefix per tile, as the other kernels,
+    // the carry went from tile to tile, a round trip each: training steps B1 L14638 J96 bf16 of the paper's layer with the harmonic
+    // convolution (115 tiles a chain) 70.6 -> 55.9 us, B1 L5697 J64 bf16 with the valve (45) 37.1 -> 30.6, B7 L517 J160 with the
+    // valve (5) 31.1 -> 27.1.  (In the other kernels the words of a group do not fit the registers beside a tile's own.)
+    tagged_t w0 = 0, w1 = 0;
+    if (ONE && before > 0) {
+        if (head && ttr != before) {
+            const tagged_t *src = a.pre + (size_t)(ticket - (uint32_t)(before + 1) * chain_stride) * 2 * JB + lv;
+            w0 = tagged_load(src);
+            w1 = tagged_load(src + JB);
+        }
+        if (!read_aggregates<JB, 1, NSEG, RET>(&sPool[0], a.agg, a.aggp, ticket, chain_stride, ttr, before, seg, lv, a.spin_limit, tag) && lv == 0)
+            __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        lds_barrier_raw();
+    }
     if (head) {
         float cr[V], ci[V], Tr[V], Ti[V], hr[V], hi[V], qr[V], qi[V];
 #pragma unroll
@@ -979,10 +1005,14 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         ldu<V>(qr, row(R_PTB_LR), jb);
         ldu<V>(qi, row(R_PTB_LI), jb);
         if (chained) {
-            if (!look_back<V, true, LPR, 1, RET>(a.agg, a.pre, ticket - chain_stride, chain_stride, ttr, JB, lv * V, lv,
-                                                 hr, hi, qr, qi, a.spin_limit, tag, cr, ci, a.aggp)) {
-                if (lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            bool got;
+            if constexpr (ONE)
+                got = fold_aggregates<JB, RET, true>(&sPool[0], a.pre, ticket, chain_stride, ttr, before, lv, w0, w1, hr[0], hi[0],
+                                                     qr[0], qi[0], a.spin_limit, tag, cr[0], ci[0]);
+            else
+                got = look_back<V, true, LPR, 1, RET>(a.agg, a.pre, ticket - chain_stride, chain_stride, ttr, JB, lv * V, lv,
+                                                      hr, hi, qr, qi, a.spin_limit, tag, cr, ci, a.aggp);
+            if (!got && lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // every load of this block has arrived before its stores go out (see above)
 #pragma unroll
@@ -992,7 +1022,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             sCarry[0][lv * V + v] = cr[v];
             sCarry[1][lv * V + v] = ci[v];
         }
-        if (feeds) {    // P = T + conj(lambda^T) carry: the tile's inclusive prefix
+        if (feeds && (!ONE || before == GROUP - 1)) {    // P = T + conj(lambda^T) carry: the tile's inclusive prefix
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 float P_r, P_i;
@@ -1111,8 +1141,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     }
 
     ARGS_AGAIN();
-    if (!AHEAD && tid == 0 && !a.tq.one_each)
-        ticket_ahead = next_ticket_of(a.hdr);
+    if (MODE == LATE_ && tid == 0) ticket_ahead = next_ticket_of(a.hdr);
     // ---- parameter partials: my tokens, then the wave's two segments, then the waves in order (behind a barrier)
     auto param_terms = [&]() {
         if constexpr (PARAM) {
@@ -1450,6 +1479,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         param_sums();
     }
 
+    if (ONE) break;
     // ---- LDS is reused by the next tile
     if (!AHEAD && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
     lds_barrier_raw();
@@ -1461,7 +1491,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 
     // ---- the workgroup that leaves last resets the ticket and advances the epoch for the next call.
     //      Workgroups are counted, not tiles: every one of the grid has then drawn its last ticket.
-    if (counts_early(a.tq, epoch)) return;      // (counted in its tile)
+    if (ONE && counts_early(a.tq, epoch)) return;      // (counted in its tile)
     if (tid_ == 0)
         sLast = leave_last(a.hdr, a.tq, blockIdx.x, gridDim.x, leave_ask(a.hdr, a.tq, blockIdx.x, gridDim.x)) ? 1u : 0u;
     __syncthreads();
@@ -1475,7 +1505,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 }
 
 // Workgroups of a kernel that fit on the chip (asked once per kernel); 0: the runtime would not say
-template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, int MODE>
 static long long bwd_resident()
 {
     static std::atomic<long long> known{0};
@@ -1483,7 +1513,7 @@ static long long bwd_resident()
         int dev = 0, n = 0;
         hipDeviceProp_t prop;
         if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>, BwdGeom::NSEG * BwdLPR, 0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, MODE>, BwdGeom::NSEG * BwdLPR, 0) != hipSuccess)
             return 0;
         known.store((long long)(n > 0 ? n : 1) * prop.multiProcessorCount, std::memory_order_relaxed);
     }
@@ -1491,15 +1521,16 @@ static long long bwd_resident()
 }
 
 // Persistent grid: what fits on the chip at once, never more than tiles.
-template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, bool AHEAD>
+template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC, int MODE>
 static hipError_t launch_bwd_tiles(const BwdArgs &a, hipStream_t s)
 {
-    long long g = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>();
+    long long g = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, MODE>();
     if (g <= 0) return hipErrorUnknown;
     if (g > (long long)a.total_tiles) g = a.total_tiles;
     BwdArgs b = a;
     b.tq = make_queues((uint32_t)a.B * a.nLB, (uint32_t)a.nT, g);
-    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, b);
+    b.tq.one_each = MODE == ONE_ ? 1u : 0u;
+    hipLaunchKernelGGL((bwd_kernel<V, KC, PARAM, VALVE, RET, BF, HC, MODE>), dim3((unsigned)g), dim3(BwdGeom::NSEG * BwdLPR), 0, s, b);
     return hipGetLastError();
 }
 // Kernels with the valve or retentions: a tile's gradients staged ahead, or loaded at its top and the next tile drawn late
@@ -1518,16 +1549,17 @@ static hipError_t launch_bwd_tiles(const BwdArgs &a, hipStream_t s)
 template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
 {
+    const long long tiles = a.total_tiles, one = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, ONE_>();
+    if (one <= 0) return hipErrorUnknown;
+    if (tiles <= one) return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, ONE_>(a, s);
     if constexpr (VALVE || RET) {
-        const long long fit = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, true>(), tiles = a.total_tiles;
+        const long long fit = bwd_resident<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD_>();
         if (fit <= 0) return hipErrorUnknown;
         const int few = RET || (HC && !BF) ? 32 : 64;
         const int halves = HC ? 4 : VALVE && RET ? (BF ? 4 : 2) : BF ? 8 : RET ? 3 : 4;     // tiles for half the workgroups
-        const bool late = tiles > fit ? (long long)a.B * a.nLB <= few || 2 * tiles <= halves * fit
-                                      : VALVE != RET && !HC && 2 * tiles <= fit;
-        if (late) return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, false>(a, s);
+        if ((long long)a.B * a.nLB <= few || 2 * tiles <= halves * fit) return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, LATE_>(a, s);
     }
-    return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, true>(a, s);
+    return launch_bwd_tiles<V, KC, PARAM, VALVE, RET, BF, HC, AHEAD_>(a, s);
 }
 
 // The kernels of one family (gate mode x retention mode x harmonic convolution), one per conv_k.  Each family
