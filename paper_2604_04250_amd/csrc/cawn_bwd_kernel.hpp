@@ -143,6 +143,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     // the reverse pass and fetch the reverse-pass constants after the front-end.
     constexpr bool LEAN = VALVE || RET;
     constexpr bool AHEAD = MODE == AHEAD_, ONE = MODE == ONE_;
+    constexpr bool SPARE = LEAN || (ONE && HC);    // (as ONE behind the harmonic convolution do: 3 - 23 values spilled otherwise)
     static_assert(MODE != LATE_ || LEAN, "the other kernels stage a tile ahead in every call of several tiles a workgroup");
     constexpr int TILE_T = BwdGeom::TILE_T, NSTEP = BwdGeom::NSTEP, NSEG = BwdGeom::NSEG, LPR = BwdLPR;
     constexpr int JB = V * LPR;
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
     constexpr int SUMS = GPB_MAX > 2 ? GPB_MAX : 2;
     __shared__ float sV[VALVE ? BwdGeom::TILE_T * SUMS : 1];         // valve logits, then the factors beta, [group][token]
     float *sVp = &sV[0];                        // valve gradient terms summed over a group's, or a row's lanes (the factors are dead by then)
-    __shared__ float sTaps[LEAN ? 2 * KC1 : 1][JB];                 // conv taps of the lane block (valve kernels)
+    __shared__ float sTaps[SPARE ? 2 * KC1 : 1][JB];                 // conv taps of the lane block (valve kernels)
     constexpr int N_PB = NW * JB, N_RP = BwdGeom::TILE_T * SUMS;
     __shared__ float sPool2[RET ? (N_PB > N_RP ? N_PB : N_RP) : 1];
     float (*sPb)[JB] = reinterpret_cast<float (*)[JB]>(&sPool2[0]);    // product of each wave's retentions
@@ -729,7 +730,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
             sV[i * 64 + lane] = __builtin_fmaxf(valve_factor(sV[i * 64 + lane], a.valve_thr), 0.0f);
     }
     if (AHEAD && tid == 0) sTicket[(it + 1) & 1] = ticket_ahead;
-    if (LEAN && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
+    if (SPARE && KC > 0 && seg == 0) {      // (read back after the barrier before the transposed conv)
 #pragma unroll
         for (int k = 0; k < KC; ++k)
 #pragma unroll
@@ -749,7 +750,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
 #pragma unroll
     for (int v = 0; v < V; ++v) { sth[v] = gam[v] = 0.f; cth[v] = 1.f; }
     if (REGS) load_ckpt();
-    if (!LEAN) {
+    if (!SPARE) {
         ldu<V>(psr, row(R_PSEGB + 2 * (NSEG - 1 - seg)), jb);    // adjoint: segments after mine
         ldu<V>(psi, row(R_PSEGB + 2 * (NSEG - 1 - seg) + 1), jb);
         if (PARAM) {
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         hacc[5] = hk.first ? 0.f : hacc[5];
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (LEAN) {
+    if (SPARE) {
         ldu<V>(psr, row(R_PSEGB + 2 * (NSEG - 1 - seg)), jb);
         ldu<V>(psi, row(R_PSEGB + 2 * (NSEG - 1 - seg) + 1), jb);
         if (PARAM && !RET) {      // (retention kernels: the table's lambda is e^{i theta} itself, and gamma is per token)
@@ -1327,8 +1328,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         for (int k = 0; k < KC; ++k)
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                wm[k][v] = LEAN ? sTaps[k][lv * V + v] : wmf[k][v];
-                wa[k][v] = LEAN ? sTaps[KC + k][lv * V + v] : waf[k][v];
+                wm[k][v] = SPARE ? sTaps[k][lv * V + v] : wmf[k][v];
+                wa[k][v] = SPARE ? sTaps[KC + k][lv * V + v] : waf[k][v];
             }
         float hm[HALO1][V], ha[HALO1][V];       // dz of the HALO tokens after my segment
 #pragma unroll
