@@ -169,9 +169,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     __shared__ float sE[NSEG - 1][2][JB];          // (the last segment's is nobody's predecessor inside the tile)
     __shared__ float sCarry[2][JB];
     typedef FwdConsts<G> CR;
-    // staged lane-constant rows.  SINGLE: and lambda^TILE_T, which other kernels load where they need it -- a load on one of
-    // several paths there, which the compiler waits for where the paths meet, behind the stores of the aggregate
-    constexpr int NCM = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0), NCR = NCM + (SINGLE ? 4 : 0);
+    // staged lane-constant rows.  ALL_READ: and lambda^TILE_T, which other kernels load where they need it -- a load on one of
+    // several paths there, which the compiler waits for where the paths meet, behind the stores of the aggregate.  (The plain
+    // fp32 kernel, three workgroups a compute unit: staged 26.2 us, loaded 25.4 for B4 L2048 J768 with a mask, inputs not cached)
+    constexpr int NCM = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0), NCR = NCM + (ALL_READ ? 4 : 0);
     __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
     // lambda^TILE_T as a double-float: leading part re, im, remainder re, im
     constexpr int PT = TILE_T == 64 ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
@@ -624,11 +625,11 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                 }
                 hr[v] = hi[v] = qr[v] = qi[v] = 0.f;
             }
-            if constexpr (SINGLE) {
-                hr[0] = sC[SINGLE ? NCM : 0][lv];
-                hi[0] = sC[SINGLE ? NCM + 1 : 0][lv];
-                qr[0] = sC[SINGLE ? NCM + 2 : 0][lv];
-                qi[0] = sC[SINGLE ? NCM + 3 : 0][lv];
+            if constexpr (ALL_READ) {
+                hr[0] = sC[ALL_READ ? NCM : 0][lv];
+                hi[0] = sC[ALL_READ ? NCM + 1 : 0][lv];
+                qr[0] = sC[ALL_READ ? NCM + 2 : 0][lv];
+                qi[0] = sC[ALL_READ ? NCM + 3 : 0][lv];
             } else if (active) {   // lambda^TILE_T as a double-float
                 const float *tb = a.table + j0;
                 Vec<V>::ld(hr, tb + (size_t)PT * a.Jp);
