@@ -124,13 +124,15 @@ inline __host__ __device__ uint32_t done_word(uint32_t q) { return ticket_word(q
 // after 4.4 us, their second ones (which only tell them that there is nothing left) 4.4 us later, and their last
 // count took as long again.  So:
 //   * a call whose workgroups take one tile each draws no second ticket, and its U chains are dealt to eight counters:
-//     chain c to counter c mod 8, whose n-th draw is tile n / C of its chain number n mod C (C chains of this counter); tile
-//     numbers stay what they are (tile in time x U + chain), a chain belongs to one counter, and a tile still only waits
-//     for tiles with a lower ticket of its own counter, which a running workgroup holds.  Workgroup w draws from the counter
-//     of chain w mod U: as many draws as the counter has tiles.  (Dealt to 2^k counters only where 2^k divides U, an odd number
-//     of chains had one counter: a draw then took 2.3 us on average and 4.3 at most in a grid of 384 workgroups, 3.1 and 6.0
-//     in one of 512; with eight 0.9 - 1.0 and 1.6.  Forward calls of 7 - 66 chains with a few tiles more than fit: 3 - 14 % of
-//     the call.)
+//     U / 8 adjacent ones each (one more to the first U mod 8 counters), and a counter's n-th draw is tile n / C of its chain number
+//     n mod C (C chains of this counter); tile numbers stay what they are (tile in time x U + chain), a chain belongs to one counter,
+//     and a tile still only waits for tiles with a lower ticket of its own counter, which a running workgroup holds.  Workgroup w
+//     draws from counter (w mod U) mod 8: as many draws as the counter has tiles.  (Dealt to 2^k counters only where 2^k divides U, an
+//     odd number of chains had one counter: a draw then took 2.3 us on average and 4.3 at most in a grid of 384 workgroups, 3.1 and
+//     6.0 in one of 512; with eight 0.9 - 1.0 and 1.6.  Forward calls of 7 - 66 chains with a few tiles more than fit: 3 - 14 % of
+//     the call.)  Where eight divides U, workgroups of a counter are those of one XCD, whose L2 then sees adjacent lane blocks of a
+//     row: the words of the gate mask, four bytes a block, are joined there, and no XCD is bound to one class of addresses (with
+//     chain c at counter c mod 8, every eighth block of 128 bytes): B4 L2048 J768 with a mask 25.4 -> 24.2 us;
 //   * a call with more tiles than workgroups keeps one counter: its draws are spread over the call and cost nothing
 //     (eight counters with a second choice where one ran dry were slower: training step 431 -> 454 us, bf16 B2 L4096
 //     J4096 284 -> 298; the first tickets' delay keeps the workgroups out of step, and loads beside arithmetic);
@@ -549,11 +551,11 @@ __device__ __forceinline__ uint32_t first_ticket(WsHeader *h, const TileQueues &
     auto draw = [&](uint32_t q) { return __hip_atomic_fetch_add(hdr_word(h, ticket_word(q)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
     if (!t.one_each) return draw(0);
     constexpr uint32_t Q = MAX_QUEUES;
-    if (t.units % Q == 0) return draw(wg % Q) * Q + wg % Q;
-    const uint32_t q = wg % t.units % Q, C = (t.units - q + Q - 1) / Q, n = draw(q);
+    // (as many workgroups of a period of `units` draw at a counter as it has chains)
+    const uint32_t q = t.units % Q ? wg % t.units % Q : wg % Q, C = (t.units - q + Q - 1) / Q, n = draw(q);
     // n / C: n < 2^18, so that the reciprocal's error is below the distance of (n + 1/2) / C from a whole number
-    const uint32_t tt = (uint32_t)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)C));
-    return tt * t.units + (n - tt * C) * Q + q;
+    const uint32_t tt = (uint32_t)(((float)n + 0.5f) * __builtin_amdgcn_rcpf((float)C)), rest = t.units % Q;
+    return tt * t.units + q * (t.units / Q) + (q < rest ? q : rest) + (n - tt * C);
 }
 // ... and the next ones (calls with one counter)
 __device__ __forceinline__ uint32_t next_ticket_of(WsHeader *h)
