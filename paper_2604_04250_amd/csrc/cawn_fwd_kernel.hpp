@@ -764,8 +764,12 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             const int blk = WIDE ? lv / 64 : 0;
             const bool e_lo = WIDE && lane == 0 && blk > 0, e_hi = WIDE && lane == 63 && blk + 1 < WPS;
             const int bnd = e_lo ? blk - 1 : (e_hi ? blk : 0);
-            auto replay = [&](auto plain_c, auto whole_c, auto ck_c) {
+            // bf16 rows of 64 and more lanes are whole 128-byte lines, where strides and bases say so: st_row16 streams them then
+            const bool lines = BF && ((ost32 * 2 | (uint32_t)a.osb * 2 | (uint32_t)reinterpret_cast<uintptr_t>(a.z_re) |
+                                       (uint32_t)reinterpret_cast<uintptr_t>(a.z_im)) & 127) == 0;
+            auto replay = [&](auto plain_c, auto whole_c, auto ck_c, auto lines_c) {
                 constexpr bool PLAIN = decltype(plain_c)::value;
+                constexpr bool LINES = decltype(lines_c)::value;
                 constexpr bool CK = decltype(ck_c)::value;       // checkpoints wanted (uniform over the launch)
                 constexpr bool WHOLE = decltype(whole_c)::value; // a wave's 64 lanes are one head, or a part of one
                 if constexpr (HC) {
@@ -869,9 +873,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                         for (int k = 0; k < CH; ++k) {
                             if (PLAIN || (active && t0 + c0 + k < a.L)) {
                                 char *pr_ = reinterpret_cast<char *>(zre) + off, *pi_ = reinterpret_cast<char *>(zim) + off;
-                                if constexpr (BF) {     // (default policy, see the plain replay below)
-                                    *reinterpret_cast<uint16_t *>(pr_) = to_bf16(c_r[k]);
-                                    *reinterpret_cast<uint16_t *>(pi_) = to_bf16(c_i[k]);
+                                if constexpr (BF) {
+                                    st_row16<LINES>(pr_, to_bf16(c_r[k]));
+                                    st_row16<LINES>(pi_, to_bf16(c_i[k]));
                                 } else {
                                     st_stream(reinterpret_cast<float *>(pr_), c_r[k]);
                                     st_stream(reinterpret_cast<float *>(pi_), c_i[k]);
@@ -909,11 +913,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                     }
                     if (PLAIN || (active && t < a.L)) {
                         if constexpr (BF) {
-                            // (default policy.  A row segment of 32 bf16 lanes, on short tiles, is half a 128-byte line, which
-                            // the cache joins with its neighbour's half: streamed, a forward took 155 against 136 us.  The 64
-                            // lanes of long tiles are whole lines; streaming those has not been measured)
-                            *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(zre) + off) = to_bf16(zr[0]);
-                            *reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(zim) + off) = to_bf16(zi[0]);
+                            st_row16<LINES>(reinterpret_cast<char *>(zre) + off, to_bf16(zr[0]));
+                            st_row16<LINES>(reinterpret_cast<char *>(zim) + off, to_bf16(zi[0]));
                         } else {
                             static_assert(V == 1, "streamed output stores: one lane per thread");
                             st_stream(reinterpret_cast<float *>(reinterpret_cast<char *>(zre) + off), zr[0]);
@@ -934,8 +935,16 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             using T_ = std::true_type;
             using F_ = std::false_type;
             auto replay_ck = [&](auto plain_c, auto whole_c) {
-                if (ckp) replay(plain_c, whole_c, T_{});
-                else replay(plain_c, whole_c, F_{});
+                auto replay_to = [&](auto lines_c) {
+                    if (ckp) replay(plain_c, whole_c, T_{}, lines_c);
+                    else replay(plain_c, whole_c, F_{}, lines_c);
+                };
+                if constexpr (BF && JB >= 64 && decltype(plain_c)::value && (!HC || decltype(whole_c)::value)) {
+                    if (lines) replay_to(T_{});
+                    else replay_to(F_{});
+                } else {
+                    replay_to(F_{});
+                }
             };
             auto replay_hc = [&](auto plain_c) {
                 if constexpr (WIDE) replay_ck(plain_c, T_{});
