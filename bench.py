@@ -485,20 +485,18 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
     tiles = chains * -(-L // (128 if w64 else 256))
     light = Kc == 0 and not valve_on and (bf16 if ret_on else hconv) and chains > 32
     per_cu = 4 if not w64 or (bf16 and valve_on and not ret_on and not hconv) else 5 if light else 8 if ret_on and Kc > 0 else 7
-    dealt = chains % 4 == 0 or chains <= (5 if chains % 2 else 14)
-    one = 768 if not ret_on and (Kc <= 2 if hconv else not bf16 and not (valve_on and Kc == 4)) else 512      # (tiles of the kernel with one a workgroup that fit)
-    few_more = tiles > one and not dealt and (3 * tiles <= 4 * one if one == 768 else
-                                              (not (bf16 and hconv) if ret_on else not bf16) and chains % 2 and
-                                              tiles - one <= (64 if chains < 16 else 48))
-    many = bool(tiles > 256 * per_cu or (hconv and F > 64) or (bf16 and not hconv and not ret_on and 512 < tiles <= 768) or few_more)
+    many = bool(tiles > 256 * per_cu or (bf16 and not hconv and not ret_on and 512 < tiles <= 768))
+    if hconv and F > 64:      # (a row is a whole head, tiles of 64 tokens)
+        fwd_tile, tiles = f"FwdTile<32,{F},{max(256, 2 * F)}>", B * H * -(-L // 64)
+        many = tiles > 256 if F == 256 else B * H > 32 and tiles > 2304 and not (ret_on and bf16)
     fwd_label = f"fwd_kernel<{fwd_tile},{Kc},{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(many)}>"
-    # (whether a backward tile's gradients are staged a tile ahead: the line at launch_bwd_vkp, for 512 workgroups)
+    # (a backward workgroup's tiles: 2 one; of several, 0 gradients staged a tile ahead, 1 drawn late; the line at launch_bwd_vkp, for 512 workgroups)
     bchains = B * -(-J // 32)
     btiles = bchains * -(-L // 128)
     halves = 4 if hconv else (4 if bf16 else 2) if valve_on and ret_on else 8 if bf16 else 3 if ret_on else 4
-    late = ((bchains <= (32 if ret_on or (hconv and not bf16) else 64) or 2 * btiles <= halves * 512) if btiles > 512 else
-            valve_on != ret_on and not hconv and 2 * btiles <= 512) if valve_on or ret_on else False
-    bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bflag(not late)}>"
+    bmode = 2 if btiles <= 512 else int((valve_on or ret_on) and (bchains <= (32 if ret_on or (hconv and not bf16) else 64) or
+                                                                   2 * btiles <= halves * 512))
+    bwd_label = f"bwd_kernel<1,{Kc},true,{bflag(valve_on)},{bflag(ret_on)},{bflag(bf16)},{bflag(hconv)},{bmode}>"
     extra = valve_on or ret_on or bf16 or unfused or hconv
     if paper:
         out["config"]["layer"] = ("the paper's statement of the layer: H=4, K=64 (Sec. 4.3), conv kernel 3 (Sec. 3.2), "

@@ -269,7 +269,7 @@ __device__ __forceinline__ float clampf(float v, float c) { return __builtin_amd
 __device__ __forceinline__ void st_stream(float *p, float v) { __builtin_nontemporal_store(v, p); }
 constexpr int DMA_STREAM = 2;      // cache-policy operand of the direct-to-LDS loads of staged rows: nt
 
-// An element of a bf16 output row, LINES: of rows of whole 128-byte lines, which are streamed (B4 L2048 J768 42.5 -> 39.2 us, the paper's
+// An element of a bf16 output row, LINES: of rows of whole 128-byte lines, which are streamed (B8 L2048 J768 42.5 -> 39.2 us, the paper's
 // layer behind the harmonic convolution B1 L32768 J256 44.9 -> 43.4).  Of others the cache joins a line's parts, which neighbouring
 // tiles store (streamed: 32-lane tiles 155 against 136 us, B3 L11401 J1200 training step 391 against 381, B8 L2048 J96 12.7 against 12.1).
 template <bool LINES> __device__ __forceinline__ void st_row16(char *p, uint16_t v)
