@@ -484,7 +484,7 @@ def run_workload(args, name, np, torch, K, WL, dev, ceiling, steps, warmup, head
     chains = B * -(-J // (64 if w64 else 32))
     tiles = chains * -(-L // (128 if w64 else 256))
     light = Kc == 0 and not valve_on and (bf16 if ret_on else hconv) and chains > 32
-    per_cu = 4 if not w64 or (bf16 and valve_on and not ret_on and not hconv) else 5 if light else 8 if ret_on and Kc > 0 else 7
+    per_cu = 4 if not w64 or (bf16 and valve_on and not ret_on and not hconv) else 5 if light else (16 if bf16 else 12) if valve_on and ret_on and Kc > (0 if hconv else 1) else 8 if ret_on and Kc > 0 else 7
     many = bool(tiles > 256 * per_cu or (bf16 and not hconv and not ret_on and 512 < tiles <= 768))
     if hconv and F > 64:      # (a row is a whole head, tiles of 64 tokens)
         fwd_tile, tiles = f"FwdTile<32,{F},{max(256, 2 * F)}>", B * H * -(-L // 64)

@@ -1057,7 +1057,10 @@ static hipError_t launch_fwd_chain(const FwdArgs &a, uint32_t units, long long w
 //   32 lanes, retentions: 560 - 1020 tiles 0.79 - 0.95 (even), 0.94 - 1.00 (odd); 1150 tiles 0.92, 1400 tiles 0.96; 1536 1.04 with the valve
 //   64 lanes, no retentions: bf16 800 - 1750 tiles 0.68 - 0.97, 2000 0.87 - 1.01, 3000 0.92 - 1.18, with the valve at 1280 0.90, at 1500 0.89 -
 //     1.03; harmonic convolution 560 - 2300 tiles 0.77 - 1.00, 3000 0.86 - 1.04, 4500 0.83 - 1.14
-//   64 lanes, retentions: 800 - 2300 tiles 0.80 - 1.01, 3000 0.84 - 1.03, 4500 0.84 - 1.13; B8 L8192 J768 (6144) 187 / 192 us
+//   64 lanes, retentions: 800 - 2300 tiles 0.80 - 1.01, 3000 0.84 - 1.03, 4500 0.84 - 1.13; with the valve, since adjacent chains share an XCD,
+//     conv 3 (8 - 128 chains): harmonic convolution bf16 2300 tiles 0.88 - 0.91, 3072 0.93, 4096 0.85 - 0.96, 4608 1.00, fp32 2300 0.95 - 0.97,
+//     3072 0.98, 4096 0.90 - 1.01, 6144 1.03; bf16 alone, conv 4, 2300 0.91 - 0.92, 3072 0.94, 4096 0.93 - 0.98, 6144 1.01; 43 drawn calls of
+//     conv 1 - 4 with 2060 - 3072 (4096) tiles 0.81 - 1.01, mean 0.95; bf16 alone with conv 1 and many chains 1.06
 //   64 lanes, no conv (less arithmetic to hide the loads of MANY behind), more than 32 chains: at 1300 / 1400 - 1600 / 1700 - 1800 tiles, mean,
 //     bf16 with retentions 0.98 / 1.06 / 1.02, fp32 harmonic convolution 1.00 / 1.03 / 1.06, in bf16 0.92 / 1.01 / 1.05, with retentions 0.96 / 1.00 /
 //     1.05; the other kinds 0.80 - 1.12, mean 0.98 (0.97 with conv 1), with retentions at 2020 tiles 1.02: B4 L3741 J1088 fp32 with retentions and the
@@ -1087,7 +1090,7 @@ static hipError_t launch_fwd_tile(const FwdArgs &a, hipStream_t s)
         const long long one = fwd_resident<G, KC, VALVE, RET, BF, HC, false>(), many = fwd_resident<G, KC, VALVE, RET, BF, HC, true>(), cus = fwd_cus();
         if (one <= 0 || many <= 0) return hipErrorUnknown;
         const bool light = KC == 0 && !VALVE && (RET ? BF : HC) && units > 32;
-        const int per_cu = !W64 || (BF && VALVE && !RET && !HC) ? 4 : light ? 5 : RET && KC > 0 ? 8 : 7;      // (tiles a compute unit)
+        const int per_cu = !W64 || (BF && VALVE && !RET && !HC) ? 4 : light ? 5 : RET && KC > 0 ? (VALVE && (HC || KC > 1) ? (BF ? 16 : 12) : 8) : 7;      // (tiles a compute unit)
         const bool wide_many = a.stage16 && (G::JB == 256 ? jobs > one : units > 32 && jobs > 9 * cus && !(RET && BF));
         if (W128) return wide_many ? launch_fwd_chain<G, KC, VALVE, RET, BF, HC, true>(a, units, jobs < many ? jobs : many, s)
                                    : launch_fwd_chain<G, KC, VALVE, RET, BF, HC, false>(a, units, jobs, s);

@@ -110,6 +110,16 @@ def test_long_tiles_around_the_line_between_one_and_several_a_workgroup(B, F, va
     _check(B, 1, F, 3, valve=valve, ret=ret, hconv=hconv, bf16=bf16, seed=4)
 
 
+# ... and 64-lane rows with both logits: 3072 tiles in fp32 and 4096 in bf16 (33 tiles a chain)
+@pytest.mark.parametrize("B,hconv,bf16", [(93, True, False), (94, True, False), (124, True, True), (125, True, True), (124, False, True), (125, False, True)])
+def test_long_tiles_around_the_line_with_both_logits(B, hconv, bf16):
+    if hconv:
+        _check(B, 1, 64, 1, valve=True, ret=True, hconv=True, bf16=bf16, seed=6)
+    else:
+        import test_gpu_bf16 as T
+        T._check_fwd(B, L, 1, 64, 2, T._inputs(B, L, 1, 64, 2, 9600), amp_mode=1, valve=True, ret=True)
+
+
 # ... with few chains: 5 and 7 of 159 and 113 tiles (a workgroup for each of 795, several of 791 a workgroup), 14 and 18 of 57 and 44
 # (798, 792); an odd number of chains with a few tiles more than the chip holds workgroups (33 of 17; 17 of 32; 25 of 33 where
 # 768 fit) and a few more still (35; 19); rows of 64 lanes without a conv, chains of 33
