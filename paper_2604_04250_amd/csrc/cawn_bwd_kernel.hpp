@@ -435,6 +435,18 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                     dzi[i][0] = __builtin_fmaf(w_[1][0], ci[2], __builtin_fmaf(w_[1][1], ci[1], w_[1][2] * ci[0]));
                     if (i & 1) __builtin_amdgcn_sched_barrier(0);     // (two tokens' reads in flight, not all eight)
                 }
+                if constexpr (!FULL) {      // what lies outside the tensor is zero for the tap terms' pass too (my own words: no barrier)
+                    for (int i = hk.nlive; i < NSTEP; ++i) {
+                        if constexpr (BF) {
+                            reinterpret_cast<uint16_t *>(&sDz[0][0])[hk.own + i * 2 * JBS] = 0;
+                            reinterpret_cast<uint16_t *>(&sDz[NRZ][0])[hk.own + i * 2 * JBS] = 0;
+                        } else {
+                            (&sDz[0][0])[hk.own + i * JBS] = 0.f;
+                            (&sDz[NRZ][0])[hk.own + i * JBS] = 0.f;
+                        }
+                        if (active) sEdge[hk.edge + i] = sEdge[2 * NRZ + hk.edge + i] = 0.f;
+                    }
+                }
                 return;
             }
 #pragma unroll
@@ -905,7 +917,9 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         // ---- the harmonic convolution's tap and bias terms, in a pass of its own (inside the front-end its
         //      temporaries came on top of the kernel's register peak): the state after token i is the state
         //      before token i+1; Z[t] = clamp(S[t]) meets the gradients at k+1, k, k-1 (taps 0, 1, 2)
-        //      Rows and lanes outside the tensor staged a valid address: their state counts as zero.
+        //      Rows and lanes outside the tensor staged a valid address, the last row's or another lane's: their gradients
+        //      were set to zero in LDS behind the first pass.  (A zero factor instead made an infinite gradient of the last
+        //      row a NaN of the tap and bias sums.)
         //      (With the neighbours' gradients taken by the multiply-add's own lane shift, as in the forward, and
         //      the edges summed beside, four instructions a token-lane less, 15 more values were spilled.)
         __builtin_amdgcn_sched_barrier(0);
@@ -914,9 +928,7 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
         for (int i = 0; i < NSTEP; ++i) {
             const float sr_ = i + 1 < NSTEP ? Spr[i + 1 < NSTEP ? i + 1 : 0][0] : Efr[0];
             const float si_ = i + 1 < NSTEP ? Spi[i + 1 < NSTEP ? i + 1 : 0][0] : Efi[0];
-            const bool live = i < hk.nlive;
-            const float oc = live ? a.out_clamp : 0.0f, one = live ? 1.0f : 0.0f;
-            const float zr_ = clampf(sr_, oc), zi_ = clampf(si_, oc);
+            const float zr_ = clampf(sr_, a.out_clamp), zi_ = clampf(si_, a.out_clamp);
             float cr[3], ci[3];
             hc_read(std::true_type{}, i, hk, cr, ci);
 #pragma unroll
@@ -924,8 +936,8 @@ __global__ __launch_bounds__(BwdGeom::NSEG *BwdLPR, CAWN_BWD_WAVES) void bwd_ker
                 hacc[q] = __builtin_fmaf(zr_, cr[2 - q], hacc[q]);
                 hacc[3 + q] = __builtin_fmaf(zi_, ci[2 - q], hacc[3 + q]);
             }
-            hacc[6] = __builtin_fmaf(one, cr[1], hacc[6]);
-            hacc[7] = __builtin_fmaf(one, ci[1], hacc[7]);
+            hacc[6] += cr[1];
+            hacc[7] += ci[1];
             // (the sums are used at the end of the tile only; left alone, the compiler moves the whole chain
             // down there and keeps all 48 gradients alive until then)
 #pragma unroll

@@ -285,3 +285,30 @@ def test_hconv_bias_gradients_are_the_rounded_sum(H, F):
         want = d[k].astype(np.int64).reshape(B, L, H, F).sum((0, 1, 3))
         assert want.min() > 1 << 24
         assert np.array_equal(out["dhconv_b"].reshape(2, H)[p], want.astype(np.float32))
+
+
+# A workgroup for every tile (12 tiles), several a workgroup drawn late (1080 tiles; plain: staged ahead), staged ahead (2160)
+@pytest.mark.parametrize("B", [2, 90, 180])
+@pytest.mark.parametrize("valve,ret,bf16", [(False, False, False), (True, False, True), (False, True, False), (True, True, False)])
+def test_hconv_backward_infinite_gradient_in_the_last_row(B, valve, ret, bf16):
+    """The last tile is ragged, and the last row's gradients beside a lane block's edge infinite: the tap and bias gradients of their
+    head are the oracle's infinities (rows past the end repeat the last row and contribute nothing, not zero times it), those
+    of the other head are untouched."""
+    L, H, F, Kc = 300, 2, 64, 3
+    d = _inputs_modes(B, L, H, F, Kc, 7300)
+    if bf16:
+        for k in ("mag", "ang", "dc_re", "dc_im"):
+            d[k] = _gpu().bf16_exact(d[k])
+    d["dc_re"][0, L - 1, 31] = np.inf
+    d["dc_im"][1, L - 1, 32] = -np.inf
+    out = _gpu().run_hconv_fwd_bwd(d, B, L, H, F, conv_k=Kc, gate_tau=0.0 if valve else 0.1, bf16=bf16, valve=d["valve"] if valve else None,
+                                   ret=d["ret"] if ret else None, ret_bias=d["ret_bias"] if ret else None)
+    f = O.phase_fwd(O.Cfg(B, L, H, F, conv_k=Kc, gate_tau=0.0 if valve else 0.1, gate_mode=int(valve), ret_mode=int(ret)), d["mag"], d["ang"],
+                    None if ret else d["gamma"], d["theta"], conv_w=d["conv_w"], conv_b=d["conv_b"], valve=d["valve"] if valve else None,
+                    ret=d["ret"] if ret else None, ret_bias=d["ret_bias"] if ret else None)
+    g = O.harmonic_conv_bwd(f["z_re"], f["z_im"], H, F, d["hconv_w"], d["dc_re"], d["dc_im"])
+    for k in ("dw", "dbias"):
+        got, want = out["dhconv_" + k[1]].reshape(g[k].shape), g[k]
+        assert np.isinf(want[:, 0]).all()
+        assert np.array_equal(got[:, 0], want[:, 0].astype(np.float32)), (k, got)
+        assert _gpu().rel_err(got[:, 1], want[:, 1]) <= TOL
