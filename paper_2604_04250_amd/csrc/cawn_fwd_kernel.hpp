@@ -656,7 +656,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             if (all_read) {
                 read_ok = read_aggregates<JB, HC && RET ? 2 : 4, NSEG, RET>(&sPoolU[0], a.agg, a.aggp, id, (uint32_t)a.B, tt, before, seg, lv,
                                                                            a.spin_limit, tag);
-                if (!read_ok && lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!read_ok && lv % 64 == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 lds_barrier();
             }
         }
@@ -681,8 +681,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                     got = chain_carry<JB, NB, RET, !G::SHORT && !(HC && RET)>(a.agg, a.aggp, a.pre, id, (uint32_t)a.B, tt, group, lv, hr[0], hi[0], qr[0],
                                                      qi[0], a.spin_limit, tag, cr[0], ci[0]);
                 if (!got) {
-                    // gave up: flag the workspace, keep going so that every wave exits
-                    if (lv == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // gave up: flag the workspace, keep going so that every wave exits.  (Rows of 128 and 256 lanes: each
+                    // wave waits for its own lanes, and gives up by itself)
+                    if (lv % 64 == 0) __hip_atomic_store(&a.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             CAWN_STAMP(5);

@@ -214,6 +214,33 @@ def _training_calls(B, L, H, F, ret, hconv=False, seed=0):
     return ws, fwd, bwd
 
 
+# one tile a workgroup in both calls, on rows of 32, 64, 128 and 256 lanes in the forward; several tiles a workgroup (1071, 2079)
+@pytest.mark.parametrize("B,L,H,F,hconv", [(1, 4200, 4, 32, False), (1, 2000, 4, 64, True), (2, 700, 2, 128, True), (1, 900, 2, 256, True),
+                                           (21, 4200, 3, 32, False)])
+@pytest.mark.parametrize("ret", [False, True])
+def test_a_forward_or_backward_that_gave_up_says_so_or_is_right(B, L, H, F, hconv, ret):
+    """With a spin limit of zero, set from the host, a call either reports that a wait gave up or has the results of the
+    call that waits; it leaves the workspace ready in both cases."""
+    from paper_2604_04250_amd import binding as K
+    import torch
+    ws, fwd, bwd = _training_calls(B, L, H, F, ret, hconv, seed=11)
+    ref = {fwd: [t.clone() for t in fwd()], bwd: [t.clone() for t in bwd()]}
+    for call in (bwd, fwd):                             # (the backward reads the checkpoints of a forward that waited)
+        torch.cuda.synchronize()
+        K.cawn_set_spin_limit(0)
+        try:
+            out = call()
+            status = K.cawn_workspace_status(ws)
+        finally:
+            K.cawn_set_spin_limit(1 << 20)
+        assert status == K.CAWN_ETIMEOUT or (status == K.CAWN_OK and all(torch.equal(a, b) for a, b in zip(ref[call], out)))
+        assert int(ws[:64].abs().sum()) == 0, "tickets"    # counters of queues 0 and 1
+    for call in (fwd, bwd):
+        out = call()
+        K.check(K.cawn_workspace_status(ws))
+        assert all(torch.equal(a, b) for a, b in zip(ref[call], out))
+
+
 # A workgroup for every tile, more than the chip holds at a time even alone: 960 tiles of 32 lanes, 768 with the valve and
 # retentions, 1536 of 64 lanes with the harmonic convolution (256 compute units; 3, 2 and 2 of them a compute unit)
 @pytest.mark.parametrize("B,L,H,F,ret,hconv", [(4, 4096, 15, 32, False, False), (4, 4096, 6, 64, True, False), (4, 4096, 12, 64, True, True)])

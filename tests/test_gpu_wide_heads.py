@@ -75,3 +75,50 @@ def test_wide_heads_rows_off_sixteen_bytes():
     a, b = run(0), run(1)
     for u, v in zip(a, b):       # (one passes a prefix on per group of tiles as the other does: the same association)
         assert np.array_equal(u, v)
+
+
+@pytest.mark.parametrize("F,ret", [(128, False), (256, False), (128, True), (256, True)])
+def test_wide_heads_every_wave_reports_that_it_gave_up(F, ret):
+    """Each wave of a row waits for its own lanes.  A call's published words are left valid for the next call (the host sets the epoch
+    back) in the first wave's lanes alone, and with a spin limit of zero, set from the host, the other waves give up unless
+    their words arrive in time: the call says so, or is right."""
+    import torch
+
+    from paper_2604_04250_amd import binding as K
+    G = _gpu()
+    B, L, H, Kc = 2, 64 * 12, 2, 2                   # twelve tiles a chain: read a few at a time, and by all segments
+    J = H * F
+    d = _inputs(B, L, H, F, Kc, 8700 + F)
+    ds = K.make_desc(B, L, H, F, conv_k=Kc, gate_tau=0.25, hconv_k=3, ret_mode=int(ret))
+    ws = torch.empty((K.cawn_workspace_bytes(ds) + 3) // 4, dtype=torch.int32, device=G.DEV)
+    K.check(K.cawn_workspace_init(ws))
+    x = [G.dev(d[k]) for k in ("mag", "ang")]
+    par = [None if ret else G.dev(d["gamma"])] + [G.dev(d[k]) for k in ("theta", "conv_w", "conv_b", "hconv_w", "hconv_b")]
+    rl, rb = (G.dev(d["ret"]), G.dev(d["ret_bias"])) if ret else (None, None)
+
+    def call():
+        z = torch.full((2, B, L, J), float("nan"), device=G.DEV)
+        K.check(K.cawn_phase_accumulate_hconv_fwd(ds, x[0], x[1], None, rl, rb, *par, None, z[0], z[1], None, None, None, ws,
+                                                  activations_bf16=0))
+        return z, K.cawn_workspace_status(ws)
+
+    right, st = call()
+    assert st == K.CAWN_OK
+    EPOCH_WORD = 64 + 2                              # header: 64 ticket words, finished count, error flag, epoch
+    w = ws.cpu().numpy().view(np.uint32)
+    assert w[EPOCH_WORD] == 1
+    at = np.flatnonzero(w[1::2] == np.uint32(0xFF800001))       # {value, tag} of epoch 0; the first is lane 0 of the first tile's
+    assert at.size and w.size * 4 >= 8 * at[-1]
+    lane = (at - at[0]) % F
+    for k in at[lane >= 64]:
+        w[2 * k:2 * k + 2] = 0
+    w[EPOCH_WORD] = 0
+    ws.copy_(torch.from_numpy(w.view(np.int32)))
+    K.cawn_set_spin_limit(0)
+    try:
+        z, st = call()
+    finally:
+        K.cawn_set_spin_limit(1 << 20)
+    assert st == K.CAWN_ETIMEOUT or (st == K.CAWN_OK and torch.equal(z, right))
+    z, st = call()
+    assert st == K.CAWN_OK and torch.equal(z, right)
