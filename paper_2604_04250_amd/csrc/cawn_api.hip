@@ -662,7 +662,9 @@ static float valve_threshold_of(float eps)
 //   bf16 (long tiles of 64 lanes), 8 chains  36: 12.5 / 12.2, with the valve 50: 13.5 / 13.4;  24 chains  16: 11.9 / 10.0  24: 12.7 / 11.9  36: 13.6 / 15.1
 //   harmonic convolution (up to 256 tiles)  4 chains  16: 11.5 / 9.7  50: 13.3 / 13.4  64: 13.6 / 14.8, of the paper's layer 64: 15.5 / 15.5;  16 chains  16: 11.7 / 10.8
 // With a constant retention a short tile's error is half as large (runs of 8 instead of 32 tokens between exact powers of
-// lambda: 1.8e-7 against 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).
+// lambda: 1.8e-7 against 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).  Calls of a
+// constant retention therefore stay on short tiles to where these used to be ahead of long ones (32-lane rows: 24 and 1608; the harmonic
+// convolution: no line), although between the two lines long tiles are faster, by the figures above.
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
@@ -674,7 +676,8 @@ static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, in
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
     if (nT > (size_t)FwdShort::MAX_CHAIN || tiles > 256u * (hc ? 1 : 4)) return false;
     const size_t per = hc ? 6 : bf16 ? 12 : 17, most = hc ? 510 : bf16 ? 960 : 880;
-    if (!(hc && ret) && nT * per + tiles > most) return false;
+    const bool ahead = (hc && ret) || nT * per + tiles <= most, closer = !ret && (hc || nT * 24 + tiles <= 1608);
+    if (!ahead && !closer) return false;
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
 
