@@ -82,9 +82,17 @@ template <class G> struct FwdConsts {
 // 16 bytes per lane per load: JB / 4 lanes cover a row.  Called by one wave.  Table rows are 256-byte aligned and
 // padded, so every address is valid.
 // Rows NCM .. NCR - 1: lambda^TILE_T as a double-float (table rows PT, PT + 1, PTL, PTL + 1).
-template <class G, int NCM, int PT, int PTL>
-__device__ __forceinline__ int const_row(int r) { return r < NCM ? FwdConsts<G>::table_row(r) : r < NCM + 2 ? PT + (r - NCM) : PTL + (r - NCM - 2); }
-template <class G, int NCR, int NCM, int PT, int PTL>
+// RUNS: two rows more in front of those, lambda^RUN (the table's first step between backward segments).
+template <class G, int NCM, int PT, int PTL, bool RUNS>
+__device__ __forceinline__ int const_row(int r)
+{
+    if (r < NCM) return FwdConsts<G>::table_row(r);
+    r -= NCM;
+    if (RUNS && r < 2) return R_PSEGB + 2 + r;
+    r -= RUNS ? 2 : 0;
+    return r < 2 ? PT + r : PTL + (r - 2);
+}
+template <class G, int NCR, int NCM, int PT, int PTL, bool RUNS>
 __device__ __forceinline__ void stage_consts(float *sC, const float *table, int Jp, int lb, int lane)
 {
     constexpr int JB = G::JB, LR = JB / 4, RPI = 64 / LR;      // lanes per row, rows per instruction
@@ -93,7 +101,7 @@ __device__ __forceinline__ void stage_consts(float *sC, const float *table, int 
     for (int i = 0; i < (NCR + RPI - 1) / RPI; ++i) {
         const int r = i * RPI + r_in;
         if (r < NCR) {
-            const float *src = table + ((size_t)const_row<G, NCM, PT, PTL>(r) * Jp + (size_t)lb * JB + c_in);
+            const float *src = table + ((size_t)const_row<G, NCM, PT, PTL, RUNS>(r) * Jp + (size_t)lb * JB + c_in);
 #if defined(__HIP_DEVICE_COMPILE__)
             __builtin_amdgcn_global_load_lds(src, sC + (size_t)(i * RPI) * JB, 16, 0, 0);
 #else
@@ -143,6 +151,15 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     // (64-lane rows with retentions and several tiles a workgroup: at the register limit, the count in the middle spilled 6 more values; the paper's layer
     // in bf16, B1 L32768, 56.1 -> 57.3 us)
     constexpr bool COUNT_EARLY = !EACH && !(JB >= 64 && MANY && RET);
+    // RUNS: a segment of 32 tokens is four runs of RUN, joined by the exact power lambda^RUN as segments are by theirs.  Within a
+    // run the rounding of lambda to fp32 adds up, coherently over its tokens; short tiles hold it to 8 of them, and calls of
+    // heads of 128 and 256 that short tiles once took run here: their rows are as wide as a head.  (The state's error, of its rms, on
+    // lanes whose lambda rounds worst: 1.14e-6 in runs of 32, now 2.2e-7, short tiles 2.3e-7.)  An instruction a token-lane and 8 - 10
+    // registers, which these kernels have: B8 L8192 J768 F128 178.2 -> 178.6 us, bf16 155.2 -> 156.0, F256 188.0 -> 189.3, B1 L700 13.7 both.
+    // On rows of 32 and 64 lanes they cost the third workgroup of a compute unit, or spill 17: such calls keep their short tiles instead.
+    constexpr int RUN = BwdGeom::NSTEP;
+    constexpr bool RUNS = WIDE && !RET;
+    static_assert(!RUNS || NSTEP % RUN == 0, "whole runs");
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
     constexpr int NT = G::NT;                      // threads
@@ -172,7 +189,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     // staged lane-constant rows.  ALL_READ: and lambda^TILE_T, which other kernels load where they need it -- a load on one of
     // several paths there, which the compiler waits for where the paths meet, behind the stores of the aggregate.  (The plain
     // fp32 kernel, three workgroups a compute unit: staged 26.2 us, loaded 25.4 for B4 L2048 J768 with a mask, inputs not cached)
-    constexpr int NCM = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0), NCR = NCM + (ALL_READ ? 4 : 0);
+    constexpr int NCM = CR::C_W0 + 2 * KC + (HC && !WIDE ? HC_ROWS : 0), C_RUN = NCM, C_PT = NCM + (RUNS ? 2 : 0),
+                  NCR = C_PT + (ALL_READ ? 4 : 0);
     __shared__ __attribute__((aligned(16))) float sC[NCR][JB];
     // lambda^TILE_T as a double-float: leading part re, im, remainder re, im
     constexpr int PT = TILE_T == 64 ? R_PT64_HR : (TILE_T == FwdGeom::TILE_T ? R_PT_HR : R_PTB_HR);
@@ -230,7 +248,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     const int ist32 = (int)a.ist;
     auto stage_tile = [&](const TileId &T) {
         if (owner_wave) return;
-        if (wave == 0) stage_consts<G, NCR, NCM, PT, PTL>(&sC[0][0], a.table, a.Jp, T.lb, lane);
+        if (wave == 0) stage_consts<G, NCR, NCM, PT, PTL, RUNS>(&sC[0][0], a.table, a.Jp, T.lb, lane);
 #if defined(__HIP_DEVICE_COMPILE__)
         if (WIDE && wave == 0 && lane < HC_ROWS)
             __builtin_amdgcn_global_load_lds(a.table + ((size_t)(R_W0 + 2 * KC + lane) * a.Jp + (size_t)T.lb * JB), &sHW[0], 4, 0, 0);
@@ -273,7 +291,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
 #pragma unroll
         for (int q = 0; q < NCQ; ++q) {
             const int w = q * NT + tid < NCR * JB / 4 ? q * NT + tid : 0;
-            cv[q] = *reinterpret_cast<const v4f *>(a.table + (size_t)const_row<G, NCM, PT, PTL>(w / (JB / 4)) * a.Jp + (size_t)T.lb * JB + w % (JB / 4) * 4);
+            cv[q] = *reinterpret_cast<const v4f *>(a.table + (size_t)const_row<G, NCM, PT, PTL, RUNS>(w / (JB / 4)) * a.Jp + (size_t)T.lb * JB + w % (JB / 4) * 4);
         }
         auto logit = [&](const float *p, int i) {       // (beyond the end: a valid address, never used)
             const int t = T.tt * TILE_T + i % TILE_T, g = i / TILE_T, h = (T.lb * JB) / a.F + (g < a.gpb ? g : 0);
@@ -331,6 +349,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     }
 
     float lr[V], li[V], pfr[V], pfi[V], psr[V], psi[V];
+    float prr[V], pri[V];                          // RUNS: lambda^RUN
     float wm[KC1][V], wa[KC1][V], bm[V], ba[V];
     float rb[V];                                   // RET: static retention bias of my lanes
     float hw[2][3], hb[2];                         // HC: taps and bias of my lane's two channels
@@ -366,6 +385,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             };
             cst(lr, CR::C_LR);
             cst(li, CR::C_LI);
+            if (RUNS) {
+                cst(prr, RUNS ? C_RUN : 0);
+                cst(pri, RUNS ? C_RUN + 1 : 0);
+            }
             cst(pfr, CR::C_P);                    // lambda^NSTEP
             cst(pfi, CR::C_P + 1);
             cst(psr, CR::C_P + 2 * (seg > 0 ? seg - 1 : 0));           // lambda^(NSTEP*seg)
@@ -401,6 +424,8 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         // ---- front-end, phasors, local scan from zero.  Rows come from LDS as a sliding window.
         float pr[NSTEP][V], pi[NSTEP][V];
         float Er[V], Ei[V];
+        constexpr int NER = RUNS ? NSTEP / RUN - 1 : 1;
+        float er[NER][V], ei[NER][V];             // RUNS: what each run but the last adds, from zero
         float gm[RET ? NSTEP : 1][V], Pth[V];     // RET: retention of each token, product over my tokens
         uint32_t mword = 0;                       // gate mask: my 32 lanes' word of my segment's token lv % 32
         const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;   // rows before a sequence start
@@ -450,8 +475,21 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             }
 #pragma unroll
             for (int v = 0; v < V; ++v) { Er[v] = Ei[v] = 0.f; Pth[v] = 1.f; }
+            float Ar[V], Ai[V];                       // RUNS: the segment up to the last run's start
 #pragma unroll
             for (int i = 0; i < NSTEP; ++i) {
+                if (RUNS && i > 0 && i % RUN == 0) {
+                    const int k = RUNS ? i / RUN - 1 : 0;
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const float ar = k > 0 ? Ar[v] : 0.f, ai = k > 0 ? Ai[v] : 0.f;
+                        er[k][v] = Er[v];
+                        ei[k][v] = Ei[v];
+                        Ar[v] = k > 0 ? __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, Er[v])) : Er[v];
+                        Ai[v] = k > 0 ? __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, Ei[v])) : Ei[v];
+                        Er[v] = Ei[v] = 0.f;
+                    }
+                }
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     wnm[(i + HALO) % KC1][v] = row_m(i + HALO);
@@ -520,6 +558,14 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                     }
                     Er[v] = nr;
                     Ei[v] = ni;
+                }
+            }
+            if (RUNS) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const float ar = Ar[v], ai = Ai[v];
+                    Er[v] = __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, Er[v]));
+                    Ei[v] = __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, Ei[v]));
                 }
             }
         };
@@ -626,10 +672,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                 hr[v] = hi[v] = qr[v] = qi[v] = 0.f;
             }
             if constexpr (ALL_READ) {
-                hr[0] = sC[ALL_READ ? NCM : 0][lv];
-                hi[0] = sC[ALL_READ ? NCM + 1 : 0][lv];
-                qr[0] = sC[ALL_READ ? NCM + 2 : 0][lv];
-                qi[0] = sC[ALL_READ ? NCM + 3 : 0][lv];
+                hr[0] = sC[ALL_READ ? C_PT : 0][lv];
+                hi[0] = sC[ALL_READ ? C_PT + 1 : 0][lv];
+                qr[0] = sC[ALL_READ ? C_PT + 2 : 0][lv];
+                qi[0] = sC[ALL_READ ? C_PT + 3 : 0][lv];
             } else if (active) {   // lambda^TILE_T as a double-float
                 const float *tb = a.table + j0;
                 Vec<V>::ld(hr, tb + (size_t)PT * a.Jp);
@@ -731,6 +777,23 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             }
         }
 
+        // RUNS: the state at the next run's start, behind the run that ends with token i
+        float Rr[V], Ri[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) { Rr[v] = Sr[v]; Ri[v] = Si[v]; }
+        auto next_run = [&](int i) {
+            if constexpr (RUNS) {
+                if ((i + 1) % RUN != 0 || i + 1 >= NSTEP) return;
+                const int k = (i + 1) / RUN - 1;
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const float ar = Rr[v], ai = Ri[v];
+                    Sr[v] = Rr[v] = __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, er[k][v]));
+                    Si[v] = Ri[v] = __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, ei[k][v]));
+                }
+            }
+        };
+
         // ---- optional gate mask: bit j%32 of word j/32, one word per thread (behind the look-back, whose polls
         //      would queue behind these stores; ahead of the output stores, which may stay in flight)
         if (a.mask && lv % 32 < NSTEP && t0 + lv % 32 < a.L) {
@@ -794,10 +857,11 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                             }
                             Sr[0] = nr;
                             Si[0] = ni;
+                            next_run(i);
                             if (CK && (i + 1) % CKPT_T == 0 && i + 1 < NSTEP && (PLAIN || (active && t0 + i + 1 < a.L))) {
                                 float *cq = reinterpret_cast<float *>(reinterpret_cast<char *>(ckp) + (uint32_t)((i + 1) / CKPT_T) * ck_step);
-                                cq[0] = nr;       // (checkpoints are read back by the backward of the same step: cached stores)
-                                cq[a.J] = ni;
+                                cq[0] = Sr[0];       // (checkpoints are read back by the backward of the same step: cached stores)
+                                cq[a.J] = Si[0];
                             }
                             z_r[k] = clampf(nr, a.out_clamp);
                             z_i[k] = clampf(ni, a.out_clamp);
@@ -907,6 +971,11 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                         zr[v] = clampf(nr, a.out_clamp);
                         zi[v] = clampf(ni, a.out_clamp);
                     }
+                    if (!PLAIN && t == a.L - 1 && a.state_out && active) {
+                        Vec<V>::st(a.state_out + ((size_t)b * 2 + 0) * a.J + j0, Sr);
+                        Vec<V>::st(a.state_out + ((size_t)b * 2 + 1) * a.J + j0, Si);
+                    }
+                    next_run(i);
                     if (CK && (i + 1) % CKPT_T == 0 && i + 1 < NSTEP && (PLAIN || (active && t + 1 < a.L))) {
                         float *cq = reinterpret_cast<float *>(reinterpret_cast<char *>(ckp) + (uint32_t)((i + 1) / CKPT_T) * ck_step);
                         Vec<V>::st(cq, Sr);       // the state before token t + 1
@@ -921,10 +990,6 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                             st_stream(reinterpret_cast<float *>(reinterpret_cast<char *>(zre) + off), zr[0]);
                             st_stream(reinterpret_cast<float *>(reinterpret_cast<char *>(zim) + off), zi[0]);
                         }
-                    }
-                    if (!PLAIN && t == a.L - 1 && a.state_out && active) {
-                        Vec<V>::st(a.state_out + ((size_t)b * 2 + 0) * a.J + j0, Sr);
-                        Vec<V>::st(a.state_out + ((size_t)b * 2 + 1) * a.J + j0, Si);
                     }
                     off += ost32 * ES;
                 }

@@ -28,10 +28,12 @@ def _lanes(r, n):
 
 
 # B, L, H, F, harmonic convolution, valve, bf16: rows of 32 lanes with 1, 12 and 24 chains, bf16 with 24, the harmonic convolution
-# with 4
+# with 4 and heads of 128 and 256 (rows of their own width, whole calls and several tiles a workgroup)
 @pytest.mark.parametrize("B,L,H,F,hc,valve,bf16", [
     (1, 3584, 1, 32, False, False, False), (1, 2304, 12, 32, False, False, False), (2, 2048, 12, 32, False, True, False),
-    (1, 1920, 24, 32, False, False, True), (1, 4096, 4, 64, True, False, False), (1, 4096, 4, 64, True, True, True)])
+    (1, 1920, 24, 32, False, False, True), (1, 4096, 4, 64, True, False, False), (1, 4096, 4, 64, True, True, True),
+    (1, 700, 1, 128, True, False, False), (2, 700, 1, 256, True, True, False), (1, 700, 2, 128, True, False, True),
+    (3, 5600, 1, 256, True, False, False)])
 def test_state_error_of_runs_of_eight(B, L, H, F, hc, valve, bf16):
     import gpu_util as G
     r = np.random.Generator(np.random.PCG64(9100 + L + F))
