@@ -33,3 +33,22 @@ def test_lane_table_angles(scale):
     ora = O.phase_fwd(O.Cfg(B, L, H, F), d["mag"], d["ang"], d["gamma"], d["theta"])
     out = G.run_fwd(d, B, L, H, F)
     assert max(G.rel_err(out[k], ora[k]) for k in ("z_re", "z_im")) <= TOL
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_infinite_retention_keeps_its_infinity(sign):
+    """gamma = +-inf, cos and sin positive, a state (1, -1) and no input: the real part is inf + inf, the imaginary one inf - inf."""
+    B, L, H, F = 1, 1, 1, 32
+    G = _gpu()
+    J = H * F
+    d = dict(mag=np.zeros((B, L, J), np.float32), ang=np.zeros((B, L, J), np.float32), gamma=np.full(J, 0.5, np.float32),
+             theta=np.linspace(0.1, 1.4, J).astype(np.float32))
+    d["gamma"][::3] = sign * np.inf
+    state = np.stack([np.ones((B, J)), -np.ones((B, J))], 1).astype(np.float32)
+    out = G.run_fwd(d, B, L, H, F, state_in=G.pack_state(state, None))
+    scan, _ = G.unpack_state(out["state_out"], B, J, 0)
+    assert np.all(out["z_re"][0, 0, ::3] == sign * 100.0) and np.all(scan[0, 0, ::3] == sign * np.inf)
+    assert np.all(np.isnan(scan[0, 1, ::3]))
+    lam = 0.5 * np.exp(1j * d["theta"].astype(np.float64)) * (1 - 1j)
+    rest = np.arange(J) % 3 != 0
+    assert np.allclose(scan[0, 0, rest], lam.real[rest], rtol=1e-6) and np.allclose(scan[0, 1, rest], lam.imag[rest], rtol=1e-6)
