@@ -662,10 +662,14 @@ static float valve_threshold_of(float eps)
 //     24 chains  16: 11.1 / 10.2  36: 12.4 / 15.1;  with valve and retentions, 2 chains  36: 13.2 / 12.2  50: 13.2 / 13.7;  24 chains  16: 13.1 / 12.0  36: 14.4 / 18.4
 //   bf16 (long tiles of 64 lanes), 8 chains  36: 12.5 / 12.2, with the valve 50: 13.5 / 13.4;  24 chains  16: 11.9 / 10.0  24: 12.7 / 11.9  36: 13.6 / 15.1
 //   harmonic convolution (up to 256 tiles)  4 chains  16: 11.5 / 9.7  50: 13.3 / 13.4  64: 13.6 / 14.8, of the paper's layer 64: 15.5 / 15.5;  16 chains  16: 11.7 / 10.8
-// With a constant retention a short tile's error is half as large (runs of 8 instead of 32 tokens between exact powers of
-// lambda: 1.8e-7 against 4.1e-7 of the outputs at retentions up to 0.9999; with retentions from the data both have 1.4e-7).  Calls of a
-// constant retention therefore stay on short tiles to where these used to be ahead of long ones (32-lane rows: 24 and 1608; the harmonic
-// convolution: no line), although between the two lines long tiles are faster, by the figures above.
+// With the harmonic convolution and retentions only the chain's length and the tiles in all bound the choice.  Long / short there (conv 3;
+// fp32, fp32 with the valve, bf16 with the valve): 1 chain 64: 13.3 / 14.1, 13.1 / 14.3, 13.5 / 14.5;  2 chains 56: 13.4 / 14.0, 13.5 / 14.2, 13.7 / 14.4  64: 13.6 /
+//   14.7, 13.6 / 14.9, 13.7 / 15.0;  4 chains 48: 13.8 / 13.6, 13.9 / 13.8, 14.2 / 13.9  64: 14.1 / 15.4, 14.3 / 15.6, 14.5 / 15.8;  5 chains 51: 15.5 / 14.3, 15.4 / 14.5,
+//   15.6 / 14.7;  8 chains 32: 13.6 / 12.5, 13.5 / 12.6, 13.7 / 12.9;  16 chains 16: 12.6 / 11.4, 12.6 / 11.7, 12.8 / 11.5
+// A short tile is closer to the exact result where the state reaches far back: it steps 8 instead of 32 tokens by lambda rounded to fp32.  With a
+// constant retention up to 0.9999 its outputs' error is 1.8e-7 against 4.1e-7; with retentions from the data 1.2e-7 in both at 0.73, 2.8e-7
+// against 4.1e-7 at 0.95 on lanes whose lambda rounds worst.  Calls therefore stay on short tiles to where these used to be ahead of
+// long ones (`closer`), although between that line and the one above long tiles are faster, by the figures above.
 // The words short tiles publish (aggregates, no prefixes) must fit where the workspace's layout has the long tiles' and,
 // behind those, the backward's: always so at cawn_workspace_bytes(); where the array of the allocation-free call is too
 // small for them the long tiles stay.
@@ -677,7 +681,8 @@ static bool use_short_tiles(const cawn_desc *d, bool bf16, const WsLayout &w, in
     const bool ret = d->ret_mode == 1, hc = d->hconv_k != 0;
     if (nT > (size_t)FwdShort::MAX_CHAIN || tiles > 256u * (hc ? 1 : 4)) return false;
     const size_t per = hc ? 6 : bf16 ? 12 : 17, most = hc ? 510 : bf16 ? 960 : 880;
-    const bool ahead = (hc && ret) || nT * per + tiles <= most, closer = !ret && (hc || nT * 24 + tiles <= 1608);
+    const size_t per8 = !ret ? 24 : bf16 ? 16 : 40, most8 = !ret ? 1608 : bf16 ? 1056 : 1480;
+    const bool ahead = nT * per + tiles <= most, closer = hc || nT * per8 + tiles <= most8;
     if (!ahead && !closer) return false;
     return w.off_agg + tiles * JB * (ret ? 3 : 2) * sizeof(tagged_t) <= workspace_bytes;
 }
