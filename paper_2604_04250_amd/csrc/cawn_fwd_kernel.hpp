@@ -154,11 +154,13 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
     // RUNS: a segment of 32 tokens is four runs of RUN, joined by the exact power lambda^RUN as segments are by theirs.  Within a
     // run the rounding of lambda to fp32 adds up, coherently over its tokens; short tiles hold it to 8 of them, and calls of
     // heads of 128 and 256 that short tiles once took run here: their rows are as wide as a head.  (The state's error, of its rms, on
-    // lanes whose lambda rounds worst: 1.14e-6 in runs of 32, now 2.2e-7, short tiles 2.3e-7.)  An instruction a token-lane and 8 - 10
-    // registers, which these kernels have: B8 L8192 J768 F128 178.2 -> 178.6 us, bf16 155.2 -> 156.0, F256 188.0 -> 189.3, B1 L700 13.7 both.
-    // On rows of 32 and 64 lanes they cost the third workgroup of a compute unit, or spill 17: such calls keep their short tiles instead.
+    // lanes whose lambda rounds worst: 1.14e-6 in runs of 32, now 2.2e-7, short tiles 2.3e-7; with retentions of 0.95 from the data 4.0e-7 and
+    // less than 3.4e-7.)  An instruction a token-lane and 8 - 10 registers, which these kernels have: B8 L8192 J768 F128 178.2 -> 178.6 us, bf16
+    // 155.2 -> 156.0, F256 188.0 -> 189.3, B1 L700 13.7 both, with retentions 15.6 -> 15.5, F256 18.6 -> 18.4.  Not where retentions meet several tiles a
+    // workgroup, calls that were never short: 13 registers more, conv 4 on rows of 128 leaves one wave a SIMD.  On rows of 32 and 64
+    // lanes they cost the third workgroup of a compute unit, or spill 17: such calls keep their short tiles instead.
     constexpr int RUN = BwdGeom::NSTEP;
-    constexpr bool RUNS = WIDE && !RET;
+    constexpr bool RUNS = WIDE && (ONE || !RET);
     static_assert(!RUNS || NSTEP % RUN == 0, "whole runs");
     constexpr int HALO = KC > 0 ? KC - 1 : 0;
     constexpr int KC1 = KC > 0 ? KC : 1;
@@ -425,7 +427,20 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
         float pr[NSTEP][V], pi[NSTEP][V];
         float Er[V], Ei[V];
         constexpr int NER = RUNS ? NSTEP / RUN - 1 : 1;
-        float er[NER][V], ei[NER][V];             // RUNS: what each run but the last adds, from zero
+        float er[NER][V], ei[NER][V], rp[NER][V]; // RUNS: what each run but the last adds, from zero, and RET: its retentions' product
+        // (a run's step: R = (its retentions' product) lambda^RUN R + what it adds)
+        auto run_step = [&](float &Rr_, float &Ri_, float q, float x, float y, int v) {
+            const float ar = Rr_, ai = Ri_;
+            if (RET) {
+                const float rr = __builtin_fmaf(prr[v], ar, -pri[v] * ai);
+                const float ri = __builtin_fmaf(pri[v], ar, prr[v] * ai);
+                Rr_ = __builtin_fmaf(q, rr, x);
+                Ri_ = __builtin_fmaf(q, ri, y);
+            } else {
+                Rr_ = __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, x));
+                Ri_ = __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, y));
+            }
+        };
         float gm[RET ? NSTEP : 1][V], Pth[V];     // RET: retention of each token, product over my tokens
         uint32_t mword = 0;                       // gate mask: my 32 lanes' word of my segment's token lv % 32
         const bool zero_hist = HALO > 0 && !tail_in && tt == 0 && seg == 0;   // rows before a sequence start
@@ -475,18 +490,26 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             }
 #pragma unroll
             for (int v = 0; v < V; ++v) { Er[v] = Ei[v] = 0.f; Pth[v] = 1.f; }
-            float Ar[V], Ai[V];                       // RUNS: the segment up to the last run's start
+            float Ar[V], Ai[V], Qr[V];                // RUNS: the segment up to my run's start; RET: the product of my run's retentions
+#pragma unroll
+            for (int v = 0; v < V; ++v) Qr[v] = 1.f;
 #pragma unroll
             for (int i = 0; i < NSTEP; ++i) {
                 if (RUNS && i > 0 && i % RUN == 0) {
                     const int k = RUNS ? i / RUN - 1 : 0;
 #pragma unroll
                     for (int v = 0; v < V; ++v) {
-                        const float ar = k > 0 ? Ar[v] : 0.f, ai = k > 0 ? Ai[v] : 0.f;
                         er[k][v] = Er[v];
                         ei[k][v] = Ei[v];
-                        Ar[v] = k > 0 ? __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, Er[v])) : Er[v];
-                        Ai[v] = k > 0 ? __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, Ei[v])) : Ei[v];
+                        rp[k][v] = Qr[v];
+                        if (k > 0) {
+                            run_step(Ar[v], Ai[v], Qr[v], Er[v], Ei[v], v);
+                        } else {
+                            Ar[v] = Er[v];
+                            Ai[v] = Ei[v];
+                        }
+                        Pth[v] *= Qr[v];
+                        Qr[v] = 1.f;
                         Er[v] = Ei[v] = 0.f;
                     }
                 }
@@ -547,7 +570,7 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                     if (RET) {
                         const float gmv = sigmoid_fast(sR[vbase + i] + rb[v]);
                         gm[i][v] = gmv;
-                        Pth[v] *= gmv;
+                        (RUNS ? Qr[v] : Pth[v]) *= gmv;
                         const float rr = __builtin_fmaf(lr[v], Er[v], -li[v] * Ei[v]);
                         const float ri = __builtin_fmaf(li[v], Er[v], lr[v] * Ei[v]);
                         nr = __builtin_fmaf(gmv, rr, pr[i][v]);
@@ -563,9 +586,10 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
             if (RUNS) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const float ar = Ar[v], ai = Ai[v];
-                    Er[v] = __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, Er[v]));
-                    Ei[v] = __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, Ei[v]));
+                    run_step(Ar[v], Ai[v], Qr[v], Er[v], Ei[v], v);
+                    Er[v] = Ar[v];
+                    Ei[v] = Ai[v];
+                    Pth[v] *= Qr[v];
                 }
             }
         };
@@ -787,9 +811,9 @@ __global__ __launch_bounds__(G::NT, G::SHORT ? (HC ? 2 : 4) : ((MANY ? BF : !BF 
                 const int k = (i + 1) / RUN - 1;
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const float ar = Rr[v], ai = Ri[v];
-                    Sr[v] = Rr[v] = __builtin_fmaf(prr[v], ar, __builtin_fmaf(-pri[v], ai, er[k][v]));
-                    Si[v] = Ri[v] = __builtin_fmaf(pri[v], ar, __builtin_fmaf(prr[v], ai, ei[k][v]));
+                    run_step(Rr[v], Ri[v], rp[k][v], er[k][v], ei[k][v], v);
+                    Sr[v] = Rr[v];
+                    Si[v] = Ri[v];
                 }
             }
         };

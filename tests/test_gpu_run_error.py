@@ -46,9 +46,10 @@ def test_state_error_of_runs_of_eight(B, L, H, F, hc, valve, bf16):
 
 
 # Retentions from the data, about 0.95: the state reaches 20 tokens back, the retentions' own roundings (2^-24 each at most) add to the
-# sums', and the bar is the same.  Rows of 32 lanes with 24 chains, bf16 with 64.
+# sums', and the bar is the same.  Rows of 32 lanes with 24 chains, bf16 with 64, heads of 128 and 256.
 @pytest.mark.parametrize("B,L,H,F,hc,valve,bf16", [
-    (2, 1472, 12, 32, False, False, False), (2, 1472, 12, 32, False, True, False), (2, 832, 32, 32, False, False, True)])
+    (2, 1472, 12, 32, False, False, False), (2, 1472, 12, 32, False, True, False), (2, 832, 32, 32, False, False, True),
+    (1, 700, 2, 128, True, False, False), (2, 700, 1, 256, True, True, False), (1, 700, 1, 128, True, True, True)])
 def test_state_error_with_retentions_from_the_data(B, L, H, F, hc, valve, bf16):
     r = np.random.Generator(np.random.PCG64(9200 + L + F))
     J = H * F
