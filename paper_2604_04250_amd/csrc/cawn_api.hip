@@ -197,13 +197,16 @@ __global__ __launch_bounds__(128) void lane_table_kernel(const float *__restrict
     double m = 1.0, ml = 0.0;
     auto times = [&](double f, double fl) {
         const double p = m * f, e = __builtin_fma(m, f, -p) + __builtin_fma(m, fl, ml * f);
-        const bool whole = !(__builtin_fabs(p) < __builtin_inf());      // (infinite or NaN: the remainder would make a NaN of it)
-        m = whole ? p : p + e;
-        ml = whole ? 0.0 : e - (m - p);
+        m = p + e;
+        ml = e - (m - p);
     };
     for (int bit = 31 - __builtin_clz(n | 1); bit >= 0; --bit) {     // (n is the same for the whole block)
         times(m, ml);
         if (n >> bit & 1) times(g, 0.0);
+    }
+    if (!(__builtin_fabs(m) < __builtin_inf())) {       // (the remainder of an infinite product is a NaN: without it)
+        m = 1.0;
+        for (int bit = 31 - __builtin_clz(n | 1); bit >= 0; --bit) m *= n >> bit & 1 ? m * g : m;
     }
     const double re = m * c, im = m * s;
     if (slot == 0) {
