@@ -146,7 +146,7 @@ __device__ __forceinline__ void sincos_f64(double x, double &s, double &c)
 // lambda, or one of the values that are copied into the table.  A call's cost is its longest chain of dependent reads and
 // arithmetic, all cold behind the kernels of a training step: one thread copying a lane's taps, each read behind the last
 // one's store, and library pow, sin and cos took 4.2 - 4.7 us at 120 and 256 lanes and 5.8 - 6.6 us in large steps (an empty
-// kernel 1.6); a slot for every value, powers by squaring: 3.2 and 4.8 - 4.9.
+// kernel 1.6); a slot for every value, powers by squaring: 3.3 and 4.7 - 4.8.
 // (One thread per lane, working through all powers in turn, took 24 us.)
 // gamma == nullptr (data-dependent retention): the table is built with gamma = 1, i.e. its powers
 // are pure rotations, and row R_RBIAS receives the static retention bias b_k of the lane's harmonic.

@@ -1556,8 +1556,6 @@ static hipError_t launch_bwd_tiles(const BwdArgs &a, hipStream_t s)
 //       - 1024 tiles                                 a second one)  : 1.03 1.01 1.00 | 1.07 1.05 1.02 | 1.01 1.02 1.02 | 1.05 1.03 1.05
 //       - 2048 tiles                                                : 0.99 0.99 0.97 | 1.05 1.02 0.99 | 0.99 1.01 1.01 | 1.03 1.01 1.03
 //       more                                                        : 1.00 0.99 0.97 | 1.01 0.99 0.94 | 0.97 0.97 0.99 | 1.00 1.00 1.00
-//   a workgroup for every tile, up to 256                           : 1.05 1.05 1.01 | 1.03 1.04 1.00 | 1.00 1.01 1.00 | 1.01 1.00 1.00
-//     257 - 512                                                     : 1.01 1.02 0.98 | 1.01 1.01 0.97 | 1.00 1.00 1.00 | 1.00 1.00 1.00
 // (B1 L32768 H4 F64: valve 94 / 86 us, retentions 96 / 90, both with the convolution 122 / 111)
 template <int V, int KC, bool PARAM, bool VALVE, bool RET, bool BF, bool HC>
 static hipError_t launch_bwd_vkp(const BwdArgs &a, hipStream_t s)
